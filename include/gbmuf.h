@@ -32,8 +32,8 @@
  *                each other, so that what one workgroup streams is one short address range.
  *                This is the fast layout on MI355X (see gbmuf_recommend_layout).
  *     Component i is elements [comp_offsets[i], comp_offsets[i+1]) of every worker.  No
- *     alignment is required; 16-byte aligned bases with strides that are multiples of 4
- *     floats take the 16-byte path, and rows (blocks) that start on multiples of 4 KB let
+ *     alignment is required (every row is read and written with 16-byte accesses wherever it
+ *     starts); rows (blocks) that start on multiples of 4 KB let
  *     every tile of the kernel cover whole cache lines.
  *   - All parameter arithmetic is IEEE binary32, round to nearest even, every multiply and
  *     add rounded separately (no fused multiply-add).  Sampling is integer only.
@@ -118,8 +118,8 @@ typedef struct gbmuf_plan_desc {
     int32_t sweep;                  /* GBMUF_SWEEP_*                                              */
     int32_t cache_hints;            /* bit 0: non-temporal stores, bit 1: non-temporal loads      */
     int32_t workgroups_per_cu;      /* upper bound on the fused kernel's resident workgroups per
-                                       compute unit (enforced through its LDS request); 0 = by
-                                       layout: none for rows, a small number for blocked state    */
+                                       compute unit (enforced through its LDS request); 0 = a
+                                       small number by layout and K                               */
 } gbmuf_plan_desc_t;
 
 /* What a plan was made with (after defaults were resolved) and how it will run. */

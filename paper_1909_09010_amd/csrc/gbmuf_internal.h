@@ -9,8 +9,7 @@ namespace gbmuf {
 
 // One workgroup's share of a sync: elements [lo, lo + n) of component `comp`, for all K
 // workers.  The range never crosses a component boundary and lies inside one run of
-// tile_columns 16-byte columns (columns are aligned to multiples of 4 elements, so that a
-// worker row with a 16-byte aligned base is read with 16-byte loads).  q is the number of
+// tile_columns 16-byte columns (a column is 4 elements whose first index is a multiple of 4).  q is the number of
 // neighbours this component draws.
 struct TileDesc {
     int64_t lo;
@@ -49,6 +48,7 @@ struct SyncArgs {
     Placement at;
     int32_t K, q;            // q: neighbours per component (the largest q_i when they differ)
     int32_t logT;            // log2(columns per tile)
+    int32_t xcd_log;         // log2(consecutive tiles that one XCD takes)
     int32_t mode;            // GBMUF_MODE_*
     float eta, zeta, inv;    // inv = 1/(q+1), rounded once on the host (plans with one q)
     int32_t flags;           // bit 0: streaming stores, bit 1: streaming loads, bit 3: walk the
@@ -104,8 +104,8 @@ int launch_final_average(const float *theta, const Placement &at, int K, int64_t
 int launch_state_copy(float *dst, const Placement &dst_at, const float *src, const Placement &src_at, int K,
                       int64_t P, hipStream_t stream);
 int launch_copy_probe(float *dst, const float *src, int64_t n_floats, int flags, int blocks, hipStream_t stream);
-int launch_sync(const Variant &v, bool vec4, const SyncArgs &a, int64_t n_tiles, size_t lds_floor, hipStream_t stream);
-size_t sync_lds_bytes(const Variant &v, bool vec4, int K, int q, int C, bool in_kernel_sampling);
+int launch_sync(const Variant &v, const SyncArgs &a, int64_t n_tiles, size_t lds_floor, hipStream_t stream);
+size_t sync_lds_bytes(const Variant &v, int K, int q, int C, bool in_kernel_sampling);
 int prepare_kernels(const Variant &v, int K, int q, int C, bool mixed_q, bool *can_sample_in_kernel);
 const Variant *variant_table(int *count);
 

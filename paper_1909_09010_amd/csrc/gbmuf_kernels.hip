@@ -129,19 +129,27 @@ __device__ __forceinline__ void filter(float avg, float om, float de, float eta,
     th_out = tn; om_out = on; de_out = dn;
 }
 
-// Which tile this workgroup takes.  Normally its own index.  With the backwards flag (set on
-// odd rounds unless the plan asked for forward sweeps) the list is walked backwards, so that
-// what the previous sync wrote last is read first, while it may still be in the 256 MB
-// memory-side cache (it is for states of up to a few GB; larger states neither gain nor lose);
-// the reversal keeps the index modulo 8, i.e. the XCD (workgroups are dealt round-robin to the
-// 8 XCDs) and its L2.
-__device__ __forceinline__ unsigned tile_of_block(int flags)
+// Which tile this workgroup takes.  Workgroups are dealt round-robin to the 8 XCDs (blockIdx mod 8);
+// the list is cut into groups of 8 * 2^xcd_log consecutive tiles, and in every group XCD r takes the
+// r-th run of 2^xcd_log tiles (xcd_granule on the host says how long a run is and why).  With the
+// backwards flag (set on odd rounds unless the plan asked for forward sweeps) the list is walked
+// backwards, so that what the previous sync wrote last is read first, while it may still be in the
+// 256 MB memory-side cache (it is for states of up to a few GB; larger states neither gain nor
+// lose); the XCD of a tile stays the same.  Tiles beyond the last whole group are taken in order.
+__device__ __forceinline__ unsigned tile_of_block(const SyncArgs &a)
 {
-    const unsigned b = blockIdx.x;
-    if (!(flags & kFlagBackwards)) return b;
-    const unsigned r = b & 7u;
-    const unsigned in_class = (gridDim.x - r + 7u) >> 3;      // tiles with index == r (mod 8)
-    return ((in_class - 1u - (b >> 3)) << 3) | r;
+    const unsigned n = gridDim.x, lg = static_cast<unsigned>(a.xcd_log);
+    const unsigned whole = (n >> (3 + lg)) << (3 + lg);           // tiles in whole groups
+    unsigned b = blockIdx.x, i;
+    if (a.flags & kFlagBackwards) {
+        const unsigned rest = n - whole;                          // these come first
+        if (b < rest) return n - 1u - b;
+        i = (whole >> 3) - 1u - ((b - rest) >> 3);
+    } else {
+        if (b >= whole) return b;
+        i = b >> 3;
+    }
+    return ((((i >> lg) << 3) | (b & 7u)) << lg) | (i & ((1u << lg) - 1u));
 }
 
 // Neighbour rows of this tile's component -> LDS, merged with the worker itself and sorted
@@ -196,34 +204,40 @@ __device__ __forceinline__ size_t ids_words(int K, int q)      // uint16 entries
 }
 
 // ---------------------------------------------------------------------------------------
-// 16-byte path: worker rows are 16-byte aligned (bases and stride), a column is 4 floats.
+// The fused kernel.  A column is 4 consecutive floats, loaded and stored as one 16-byte access
+// wherever the row starts: global memory takes 16-byte accesses at any 4-byte address, and what a
+// misaligned row costs is only the cache lines that two tiles share (xcd_granule).
 // Q1 = q+1 when known at compile time (the sum is then fully unrolled), 0 = run-time q.
 // Slot s of the tile (s = tid + n*NT) is worker s >> logT, column s & (T-1).
+//
+// Bound by HBM.  Measured on 16 workers x 35.0 M parameters (6.7 GB) in plain [K, P] tensors with an
+// odd P: 2483 us (5406 GB/s); with 4-byte accesses, tiles dealt to the XCDs one by one: 3230 us.
 // ---------------------------------------------------------------------------------------
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
 
 __device__ __forceinline__ v4f load4(const float *p, bool streaming)
 {
-    const v4f *q = reinterpret_cast<const v4f *>(p);
+    const v4f_any *q = reinterpret_cast<const v4f_any *>(p);
     return streaming ? __builtin_nontemporal_load(q) : *q;
 }
 
 __device__ __forceinline__ void store4(float *p, v4f v, bool streaming)
 {
-    v4f *q = reinterpret_cast<v4f *>(p);
+    v4f_any *q = reinterpret_cast<v4f_any *>(p);
     if (streaming) __builtin_nontemporal_store(v, q);
     else *q = v;
 }
 
 template <int NT, int SLOTS, int Q1>
-__global__ __launch_bounds__(NT) void sync_vec4_kernel(SyncArgs a)
+__global__ __launch_bounds__(NT) void sync_kernel(SyncArgs a)
 {
     extern __shared__ float4 lds4[];
     v4f *tile = reinterpret_cast<v4f *>(lds4);
     uint16_t *ids = reinterpret_cast<uint16_t *>(lds4 + NT * SLOTS);
 
     const int tid = threadIdx.x;
-    const TileDesc td = a.tiles[tile_of_block(a.flags)];
+    const TileDesc td = a.tiles[tile_of_block(a)];
     if ((a.flags & kFlagCheckPeriods) && a.step % static_cast<uint64_t>(a.comp[td.comp].period) != 0)
         return;                                                   // not due: the whole workgroup leaves
     const int K = a.K, q1 = (Q1 > 0) ? Q1 : td.q + 1, q = q1 - 1;
@@ -406,70 +420,6 @@ __global__ __launch_bounds__(256) void copy_probe_kernel(v4f *dst, const v4f *sr
     }
 }
 
-// ---------------------------------------------------------------------------------------
-// 4-byte path for rows that are not 16-byte aligned: the same tile is walked in passes of
-// T single-float columns.
-// ---------------------------------------------------------------------------------------
-template <int NT, int SLOTS>
-__global__ __launch_bounds__(NT) void sync_vec1_kernel(SyncArgs a)
-{
-    extern __shared__ float4 lds4[];
-    float *tile = reinterpret_cast<float *>(lds4);
-    uint16_t *ids = reinterpret_cast<uint16_t *>(tile + NT * SLOTS);
-
-    const int tid = threadIdx.x;
-    const TileDesc td = a.tiles[tile_of_block(a.flags)];
-    if ((a.flags & kFlagCheckPeriods) && a.step % static_cast<uint64_t>(a.comp[td.comp].period) != 0)
-        return;                                                   // not due: the whole workgroup leaves
-    const int K = a.K, q1 = td.q + 1, q = td.q;
-    const float inv = (a.flags & kFlagMixedQ) ? a.comp[td.comp].inv : a.inv;
-    const int logT = a.logT, T = 1 << logT;
-    const int mode = a.mode;
-    const int64_t hi = td.lo + td.n;
-    const int64_t shift = (td.lo >> a.at.logB) * a.at.block_extra;
-
-    if (a.nbr != nullptr) stage_ids(ids, a.nbr, td.comp, K, q, a.q, tid, NT);
-    else draw_ids(ids, reinterpret_cast<int32_t *>(ids + ids_words(K, a.q)), a, td.comp, q, tid, NT);
-
-    for (int64_t first = td.lo; first < hi; first += T) {
-        const int ncols = static_cast<int>(hi - first < T ? hi - first : T);
-        float th[SLOTS], om[SLOTS], de[SLOTS];
-#pragma unroll
-        for (int n = 0; n < SLOTS; ++n) {
-            const int slot = tid + n * NT;
-            const int w = slot >> logT, col = slot & (T - 1);
-            th[n] = 0.f; om[n] = 0.f; de[n] = 0.f;
-            if (w < K && col < ncols) {
-                const int64_t at = static_cast<int64_t>(w) * a.at.stride + first + col + shift;
-                th[n] = a.theta[at];
-                if (mode != GBMUF_MODE_GOSSIP_MA) { om[n] = a.omega[at]; de[n] = a.delta[at]; }
-            }
-        }
-#pragma unroll
-        for (int n = 0; n < SLOTS; ++n) tile[tid + n * NT] = th[n];
-        __syncthreads();
-#pragma unroll
-        for (int n = 0; n < SLOTS; ++n) {
-            const int slot = tid + n * NT;
-            const int w = slot >> logT, col = slot & (T - 1);
-            if (!(w < K && col < ncols)) continue;
-            const uint16_t *row = ids + w * q1;
-            float s = tile[(static_cast<int>(row[0]) << logT) + col];
-            for (int j = 1; j < q1; ++j) s = s + tile[(static_cast<int>(row[j]) << logT) + col];
-            float tn = s * inv, on = 0.f, dn = 0.f;
-            const int64_t at = static_cast<int64_t>(w) * a.at.stride + first + col + shift;
-            if (mode != GBMUF_MODE_GOSSIP_MA) {
-                const float avg = tn;
-                filter(avg, om[n], de[n], a.eta, a.zeta, mode, tn, on, dn);
-                a.omega[at] = on;
-                a.delta[at] = dn;
-            }
-            a.theta[at] = tn;
-        }
-        __syncthreads();                                          // tile is reused by the next pass
-    }
-}
-
 constexpr Variant kVariants[] = {
     {256, 8}, {512, 8}, {512, 4}, {256, 16}, {1024, 4}, {256, 4},
     {256, 2}, {512, 2}, {1024, 2}, {1024, 1}, {512, 1}, {256, 1},
@@ -479,22 +429,22 @@ constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 using KernelFn = void (*)(SyncArgs);
 
 template <int NT, int SLOTS>
-KernelFn pick_vec4(int q1)
+KernelFn pick_q(int q1)
 {
     switch (q1) {
-        case 1: return sync_vec4_kernel<NT, SLOTS, 1>;
-        case 2: return sync_vec4_kernel<NT, SLOTS, 2>;
-        case 3: return sync_vec4_kernel<NT, SLOTS, 3>;
-        case 4: return sync_vec4_kernel<NT, SLOTS, 4>;
-        case 5: return sync_vec4_kernel<NT, SLOTS, 5>;
-        default: return sync_vec4_kernel<NT, SLOTS, 0>;
+        case 1: return sync_kernel<NT, SLOTS, 1>;
+        case 2: return sync_kernel<NT, SLOTS, 2>;
+        case 3: return sync_kernel<NT, SLOTS, 3>;
+        case 4: return sync_kernel<NT, SLOTS, 4>;
+        case 5: return sync_kernel<NT, SLOTS, 5>;
+        default: return sync_kernel<NT, SLOTS, 0>;
     }
 }
 
-KernelFn pick_kernel(const Variant &v, bool vec4, int q1)
+KernelFn pick_kernel(const Variant &v, int q1)
 {
 #define GBMUF_CASE(NT, SL) \
-    if (v.threads == NT && v.slots == SL) return vec4 ? pick_vec4<NT, SL>(q1) : sync_vec1_kernel<NT, SL>;
+    if (v.threads == NT && v.slots == SL) return pick_q<NT, SL>(q1);
     GBMUF_CASE(256, 8)
     GBMUF_CASE(512, 8)
     GBMUF_CASE(512, 4)
@@ -531,9 +481,9 @@ const Variant *variant_table(int *count)
 
 // Dynamic LDS one workgroup of the fused kernel needs: the theta tile, the merged neighbour
 // rows (q = the largest q_i) and, when it draws them itself, the candidate copies.
-size_t sync_lds_bytes(const Variant &v, bool vec4, int K, int q, int C, bool in_kernel_sampling)
+size_t sync_lds_bytes(const Variant &v, int K, int q, int C, bool in_kernel_sampling)
 {
-    return static_cast<size_t>(v.threads) * v.slots * (vec4 ? sizeof(float4) : sizeof(float)) + ids_bytes(K, q) +
+    return static_cast<size_t>(v.threads) * v.slots * sizeof(float4) + ids_bytes(K, q) +
            (in_kernel_sampling ? perm_bytes(K, C) : 0);
 }
 
@@ -544,33 +494,31 @@ int prepare_kernels(const Variant &v, int K, int q, int C, bool mixed_q, bool *c
 {
     const bool inl = can_sample_inline(K, C);
     *can_sample_in_kernel = inl;
-    const size_t lds4 = sync_lds_bytes(v, true, K, q, C, inl);
+    const size_t lds = sync_lds_bytes(v, K, q, C, inl);
     int dev = 0, max_lds = 0;
     hipError_t err = hipGetDevice(&dev);
     if (err != hipSuccess) return hip_failed("hipGetDevice", err, GBMUF_EDEVICE);
     err = hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
     if (err != hipSuccess) return hip_failed("hipDeviceGetAttribute(MaxSharedMemoryPerBlock)", err, GBMUF_EDEVICE);
-    if (lds4 > static_cast<size_t>(max_lds)) return GBMUF_EUNSUPPORTED;
-    KernelFn k4 = pick_kernel(v, true, mixed_q ? 0 : q + 1), k1 = pick_kernel(v, false, q + 1);
-    if (!k4 || !k1) return GBMUF_EINVAL;
-    err = hipFuncSetAttribute(reinterpret_cast<const void *>(k4), hipFuncAttributeMaxDynamicSharedMemorySize, max_lds);
-    if (err != hipSuccess) return hip_failed("hipFuncSetAttribute(16-byte kernel)", err, GBMUF_EDEVICE);
-    err = hipFuncSetAttribute(reinterpret_cast<const void *>(k1), hipFuncAttributeMaxDynamicSharedMemorySize, max_lds);
-    if (err != hipSuccess) return hip_failed("hipFuncSetAttribute(4-byte kernel)", err, GBMUF_EDEVICE);
+    if (lds > static_cast<size_t>(max_lds)) return GBMUF_EUNSUPPORTED;
+    KernelFn k = pick_kernel(v, mixed_q ? 0 : q + 1);
+    if (!k) return GBMUF_EINVAL;
+    err = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, max_lds);
+    if (err != hipSuccess) return hip_failed("hipFuncSetAttribute(fused kernel)", err, GBMUF_EDEVICE);
     return GBMUF_OK;
 }
 
 // lds_floor: the workgroup asks for at least this much dynamic LDS, which bounds how many
 // workgroups a compute unit holds at once (0 = only what it needs).
-int launch_sync(const Variant &v, bool vec4, const SyncArgs &a, int64_t n_tiles, size_t lds_floor, hipStream_t stream)
+int launch_sync(const Variant &v, const SyncArgs &a, int64_t n_tiles, size_t lds_floor, hipStream_t stream)
 {
     if (n_tiles <= 0) return GBMUF_OK;
     if (n_tiles > 0x7fffffffLL) return GBMUF_EUNSUPPORTED;
     const bool mixed = (a.flags & kFlagMixedQ) != 0;
-    KernelFn k = pick_kernel(v, vec4, mixed ? 0 : a.q + 1);
+    KernelFn k = pick_kernel(v, mixed ? 0 : a.q + 1);
     if (!k) return GBMUF_EINVAL;
     if (a.nbr == nullptr && (!can_sample_inline(a.K, a.C) || (a.cand == nullptr && a.C > 0))) return GBMUF_EINVAL;
-    size_t lds = sync_lds_bytes(v, vec4, a.K, a.q, a.C, a.nbr == nullptr);
+    size_t lds = sync_lds_bytes(v, a.K, a.q, a.C, a.nbr == nullptr);
     if (lds < lds_floor) lds = lds_floor;
     SyncArgs args = a;
     void *argv[] = {&args};

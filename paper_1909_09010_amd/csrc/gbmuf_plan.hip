@@ -183,11 +183,6 @@ void host_pick(const int32_t *cand, int32_t C, int32_t q, uint64_t seed, uint64_
 // ---------------------------------------------------------------------------------------
 // Tile shapes
 // ---------------------------------------------------------------------------------------
-// Measured on MI355X.  Rows (3K address streams): short tiles of about 32 columns (512 B per
-// worker row) with few 16-byte slots per thread, as many workgroups per CU as fit.  Blocked
-// state (one address stream): the same 32 columns in workgroups of 512 threads, and only one
-// or two workgroups per CU, so that what the whole chip has in flight is a short stretch of
-// memory.
 bool find_variant(int threads, int slots, Variant *out)
 {
     int count = 0;
@@ -200,35 +195,46 @@ bool find_variant(int threads, int slots, Variant *out)
     return false;
 }
 
+// Measured on MI355X.  What the chip has in flight at one time decides, not how much of it: a short
+// stretch of memory is fast, and a tile should cover whole kilobytes of a worker row.
+//   Blocked state (one address stream): 32 columns (512 B per worker row) in workgroups of 512
+//     threads; the gossip-MA branch (theta only) takes twice the columns.
+//   Rows (3K address streams): 64 columns.  16 workers x 35.0 M in plain tensors, on a fast and on a
+//     slow placement: 1024 x 1 slots, two per CU 2251 / 2634 us; 512 x 1 (32 columns), three per CU
+//     2365 / 2751; 256 x 2 (32), unbounded 2652 / 2957.  32 workers x 45.8 M: 1024 x 2 7065, 512 x 2
+//     7092.  64 workers x 26.9 M: 1024 x 4 9771, 512 x 4 (32) 10072.  Padded rows: within 3 %.
+//     Gossip-MA at 64 workers x 45.8 M: 1024 x 4 4730, 1024 x 2 4957.
 Variant default_variant(int K, int layout, int what)
 {
     Variant v{1024, 4};
-    if (layout == kRows) {
-        const int threads = K <= 32 ? 256 : 1024;
-        const int slots = K <= 8 ? 1 : K <= 16 ? 2 : 4;
-        find_variant(threads, slots, &v);
-    } else if (what == kBmuf) {
-        // 32 columns (512 B) per worker row in workgroups of 512 threads, K/16 slots per thread
+    if (what == kMa) {
+        if (K <= 16) find_variant(512, 2, &v);
+        else if (K <= (layout == kBlocked ? 64 : 32)) find_variant(1024, 2, &v);
+    } else if (layout == kBlocked) {
         if (K <= 4) find_variant(256, 1, &v);
         else if (K <= 16) find_variant(512, 1, &v);
         else if (K <= 32) find_variant(512, 2, &v);
         else if (K <= 64) find_variant(512, 4, &v);
         else if (K <= 128) find_variant(512, 8, &v);
     } else {
-        if (K <= 16) find_variant(512, 2, &v);             // theta only: twice the columns per workgroup
-        else if (K <= 64) find_variant(1024, 2, &v);
+        if (K <= 4) find_variant(256, 1, &v);
+        else if (K <= 8) find_variant(512, 1, &v);
+        else if (K <= 16) find_variant(1024, 1, &v);
+        else if (K <= 32) find_variant(1024, 2, &v);
     }
     return v;
 }
 
 // Blocked state: what the chip has in flight should stay near 12-24 MB (24-48 KB per workgroup
 // at two workgroups per CU, or 96 KB at one; the gossip-MA branch moves a third of that per
-// workgroup and takes twice as many); more resident workgroups lose 5-15 points.
+// workgroup and takes twice as many); more resident workgroups lose 5-15 points.  Rows: about 1200
+// columns per CU up to K = 8, two workgroups above (one at K = 32: 7065 us against 7143); beyond
+// that the tile's LDS is bound enough.
 int32_t default_workgroups_per_cu(int K, int layout, int what)
 {
-    if (layout != kBlocked) return 0;
-    if (what == kBmuf) return K <= 4 ? 4 : K <= 32 ? 2 : 1;
-    return K <= 16 ? 4 : 2;
+    if (what == kMa) return K <= 16 ? 4 : 2;
+    if (layout == kBlocked) return K <= 4 ? 4 : K <= 32 ? 2 : 1;
+    return K <= 4 ? 4 : K <= 8 ? 20 / K : K <= 24 ? 2 : K <= 32 ? 1 : 0;
 }
 
 // Split every component into runs of at most T 16-byte columns (the fused kernel's work list).
@@ -422,7 +428,23 @@ gbmuf_state_t rows_state(float *theta, float *omega, float *delta, int64_t strid
     return st;
 }
 
-bool placement_vec4(const Placement &at) { return at.stride % 4 == 0 && at.block_extra % 4 == 0; }
+// log2 of how many consecutive tiles one XCD takes (tile_of_block), from how many bytes of a worker
+// row one XCD should own.  Measured on MI355X with the fused kernel:
+//   Rows or blocks that do not start on 128-byte lines: neighbouring tiles share a line, and unless
+//     both are taken by one XCD its L2 cannot join the halves: every shared line is fetched twice and
+//     written in two pieces.  With 32 KB per XCD one line in 256 is shared.  16 workers x 35.0 M in
+//     plain tensors: 3944 GB/s at 512 B, 4984 at 4 KB, 5073 at 16 KB (aligned rows: 5161); 64 workers
+//     x 26.9 M: 3880 at 1 KB, 4405 at 4 KB, 5163 at 32 KB.
+//   Lines of one tile only: tile by tile (padded rows: 1 to 32 KB per XCD are within 2 %).
+int32_t xcd_granule(int32_t logT, const Placement &at, const gbmuf_state_t *st, int32_t mode)
+{
+    uintptr_t low = reinterpret_cast<uintptr_t>(st->theta) | (static_cast<uintptr_t>(at.stride | at.block_extra) << 2);
+    if (mode != GBMUF_MODE_GOSSIP_MA)
+        low |= reinterpret_cast<uintptr_t>(st->omega) | reinterpret_cast<uintptr_t>(st->delta);
+    constexpr int32_t log_columns = 11;                    // 2^11 columns of 16 bytes
+    return (low & 127u) && log_columns > logT ? log_columns - logT : 0;
+}
+
 
 // The dynamic LDS a workgroup asks for so that at most `workgroups_per_cu` of them fit a CU.
 size_t lds_floor(const gbmuf_plan_s *pl, const LayoutCfg &cfg)
@@ -459,9 +481,8 @@ int enqueue_sync(const gbmuf_plan_s *pl, const int32_t *nbr_dev, const gbmuf_sta
     a.key0 = static_cast<uint32_t>(pl->seed); a.key1 = static_cast<uint32_t>(pl->seed >> 32);
     a.round0 = static_cast<uint32_t>(round); a.round1 = static_cast<uint32_t>(round >> 32);
     a.step = round;
-    bool vec4 = aligned16(st->theta) && placement_vec4(at);
-    if (mode != GBMUF_MODE_GOSSIP_MA) vec4 = vec4 && aligned16(st->omega) && aligned16(st->delta);
-    return launch_sync(cfg.variant, vec4, a, n_tiles, lds_floor(pl, cfg), stream);
+    a.xcd_log = xcd_granule(cfg.logT, at, st, mode);
+    return launch_sync(cfg.variant, a, n_tiles, lds_floor(pl, cfg), stream);
 }
 
 SampleArgs sample_args(const gbmuf_plan_s *pl, uint64_t round, int32_t *out)

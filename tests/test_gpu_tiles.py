@@ -1,0 +1,61 @@
+"""The fused kernel's work list at its edges, against the CPU oracle (needs an MI355X): numbers of
+tiles around the groups in which consecutive tiles go to one XCD, forwards and backwards, on rows
+that start anywhere.  Both sides perform the same IEEE operations in the same order, so every float
+has to be equal, and floats outside the parameters keep their junk."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1909_09010_amd import binding as B
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def check_rows(K, q, off, stride, skew=(0, 0, 0), mode=B.MODE_PAPER, rounds=(0, 1), seed=3, **plan):
+    """Syncs on three [K, stride] tensors whose bases are `skew` floats into their allocations."""
+    off = np.asarray(off, dtype=np.int64)
+    P = int(off[-1])
+    pl = B.Plan(off, K, q, 0, seed=seed, **plan)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    flat = [torch.randn(K * stride + s + 3, generator=g, device=DEV) * 0.05 for s in skew]
+    dev = [f[s:s + K * stride].view(K, stride) for f, s in zip(flat, skew)]
+    before = [f.clone() for f in flat]
+    host = [d.cpu().numpy().copy() for d in dev]
+    assert [d.data_ptr() % 16 for d in dev] == [4 * s % 16 for s in skew]
+    for r in rounds:
+        if mode == B.MODE_GOSSIP_MA:
+            pl.sync(dev[0], None, None, stride, 0.9, 1.0, mode, r, None)
+        else:
+            pl.sync(*dev, stride, 0.9, 1.0, mode, r, None)
+        oracle.sync(off, K, pl.info.p, q, seed, r, *host, np.float32(0.9), np.float32(1.0), mode)
+    torch.cuda.synchronize()
+    for f, d, h, s, b in zip(flat, dev, host, skew, before):
+        assert np.array_equal(d.cpu().numpy(), h)                       # padding included: the oracle leaves it too
+        assert torch.equal(f[:s], b[:s]) and torch.equal(f[s + K * stride:], b[s + K * stride:])
+    info = pl.info
+    pl.destroy()
+    return info
+
+
+# groups are 8 * 32 tiles of 64 columns for rows that share lines (K = 4, 16, 64), and of 8 tiles for those that do not
+@pytest.mark.parametrize("K", [4, 7, 16, 33])
+@pytest.mark.parametrize("tiles", [1, 9, 255, 256, 257, 511, 515])
+@pytest.mark.parametrize("odd", [0, 1])
+def test_every_tile_is_taken_once_around_the_xcd_groups(K, tiles, odd):
+    _need_gpu()
+    pl = B.Plan([0, 1 << 20], K, 1, 0, seed=0)
+    width = 4 * pl.info.tile_columns
+    pl.destroy()
+    P = tiles * width - (5 if odd else 0)
+    stride = P + 3 if odd else -(-P // 1024) * 1024
+    info = check_rows(K, 1, [0, P // 3, P], stride, (1, 0, 3) if odd else (0, 0, 0),
+                      mode=B.MODE_GOSSIP_MA if tiles == 511 else B.MODE_PAPER)
+    assert info.n_tiles in (tiles, tiles + 1)                           # the component edge cuts one tile
