@@ -86,6 +86,16 @@ struct SampleArgs {
     uint64_t step;
 };
 
+// Arguments of the placement change: up to three arrays, all from placement `sa` to `da`.
+struct CopyArgs {
+    float *dst[3];
+    const float *src[3];
+    Placement da, sa;
+    int64_t P;
+    int32_t K;
+    int32_t run_log;         // log2 of the pieces of one worker that follow each other (set by the launch)
+};
+
 // One tile shape of the fused kernel: threads per workgroup and 16-byte slots per thread.
 // A tile holds threads*slots slots = K worker rows of tile_columns columns each.
 struct Variant {
@@ -101,8 +111,7 @@ int hip_failed(const char *what, hipError_t err, int status);
 int launch_sampler(const SampleArgs &a, hipStream_t stream);
 int launch_final_average(const float *theta, const Placement &at, int K, int64_t P, float inv, float *out,
                          int rows_in_flight, size_t lds_floor, hipStream_t stream);
-int launch_state_copy(float *dst, const Placement &dst_at, const float *src, const Placement &src_at, int K,
-                      int64_t P, hipStream_t stream);
+int launch_state_copy(const CopyArgs &c, int arrays, hipStream_t stream);
 int launch_copy_probe(float *dst, const float *src, int64_t n_floats, int flags, int blocks, hipStream_t stream);
 int launch_sync(const Variant &v, const SyncArgs &a, int64_t n_tiles, size_t lds_floor, hipStream_t stream);
 size_t sync_lds_bytes(const Variant &v, int K, int q, int C, bool in_kernel_sampling);

@@ -891,12 +891,16 @@ int gbmuf_state_copy(const gbmuf_plan_t *plan, const gbmuf_state_t *dst, const g
     if (rc != GBMUF_OK) return rc;
     if ((rc = check_state(plan, &sgeo, false, &sat, &sl)) != GBMUF_OK) return rc;
     if ((rc = check_device(plan)) != GBMUF_OK) return rc;
+    CopyArgs c{};
+    int n = 0;
     for (int a = 0; a < 3; ++a) {
         if (!(which & (1 << a))) continue;
-        rc = launch_state_copy(d[a], dat, s[a], sat, plan->K, plan->P, static_cast<hipStream_t>(stream));
-        if (rc != GBMUF_OK) return rc;
+        c.dst[n] = d[a];
+        c.src[n++] = s[a];
     }
-    return GBMUF_OK;
+    c.da = dat; c.sa = sat;
+    c.P = plan->P; c.K = plan->K;
+    return launch_state_copy(c, n, static_cast<hipStream_t>(stream));
 }
 
 int gbmuf_recommend_layout(const gbmuf_plan_t *plan, int64_t P, int32_t K, int32_t kind, gbmuf_layout_t *out)

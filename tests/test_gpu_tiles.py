@@ -59,3 +59,44 @@ def test_every_tile_is_taken_once_around_the_xcd_groups(K, tiles, odd):
     info = check_rows(K, 1, [0, P // 3, P], stride, (1, 0, 3) if odd else (0, 0, 0),
                       mode=B.MODE_GOSSIP_MA if tiles == 511 else B.MODE_PAPER)
     assert info.n_tiles in (tiles, tiles + 1)                           # the component edge cuts one tile
+
+
+# one piece is 256 columns of 4 floats; runs of 32 pieces when rows are written; the destination's first column
+# starts up to 31 floats before the row
+@pytest.mark.parametrize("K", [1, 3, 16])
+@pytest.mark.parametrize("P", [1, 3, 1023, 1024, 1057, 32 * 1024 - 1, 32 * 1024 + 5, 3 * 32 * 1024 + 1021])
+@pytest.mark.parametrize("which", [7, 2, 5])
+def test_state_copy_at_the_edges_of_its_pieces(K, P, which):
+    _need_gpu()
+    pl = B.Plan([0, P], K, 0, 0, seed=0)
+    Bf = pl.info.min_block_floats * (1 if P < 40000 else 4)
+    blocks = -(-P // Bf)
+    ws, gap = Bf + (5 if K == 3 else 0), 7                   # K = 3: odd strides, so that columns cross no alignment
+    bs = 3 * K * ws + gap
+    g = torch.Generator(device=DEV)
+    g.manual_seed(P)
+    stride = P + 1
+    rows = [torch.randn(K * stride + 9, generator=g, device=DEV) for _ in range(3)]
+    skew = (0, 1, 6)
+    arena = torch.full((blocks * bs + 64,), 7.0, device=DEV)
+    want = arena.clone()
+    blocked = B.make_state(*[arena.data_ptr() + 4 * (a * K * ws + 3) for a in range(3)], ws, Bf, bs)
+    idx = torch.arange(P, device=DEV)
+    at = (idx // Bf) * bs + idx % Bf
+    for a in range(3):
+        if which >> a & 1:
+            for w in range(K):
+                want[3 + a * K * ws + w * ws + at] = rows[a][skew[a] + w * stride:][:P]
+    pl.state_copy(blocked, B.make_state(*[r.data_ptr() + 4 * s for r, s in zip(rows, skew)], stride), which, None)
+    torch.cuda.synchronize()
+    assert torch.equal(arena, want)
+    back = [torch.full_like(r, 5.0) for r in rows]
+    pl.state_copy(B.make_state(*[b.data_ptr() + 4 * s for b, s in zip(back, skew[::-1])], stride), blocked, which, None)
+    torch.cuda.synchronize()
+    for a in range(3):
+        expect = torch.full_like(rows[a], 5.0)
+        if which >> a & 1:
+            for w in range(K):
+                expect[skew[2 - a] + w * stride:][:P] = rows[a][skew[a] + w * stride:][:P]
+        assert torch.equal(back[a], expect)
+    pl.destroy()
