@@ -97,11 +97,16 @@ struct CopyArgs {
 };
 
 // One tile shape of the fused kernel: threads per workgroup and 16-byte slots per thread.
-// A tile holds threads*slots slots = K worker rows of tile_columns columns each.
+// A tile holds threads*slots slots = K worker rows of tile_columns columns each.  depth > 0: the
+// kernel for many workers, which holds `depth` slots of omega and Delta at a time.
 struct Variant {
     int threads;
     int slots;
+    int depth;
 };
+constexpr Variant kMany = {1024, 4, 2};            // 64 < K <= 128
+constexpr Variant kVeryMany = {512, 16, 4};        // K > 128
+constexpr size_t kLdsPerWorkgroup = 160 * 1024;    // gfx950
 
 // Remembers the most recent failing HIP call of this thread (what gbmuf_last_error_detail
 // returns) and maps it to a status.
@@ -116,6 +121,7 @@ int launch_copy_probe(float *dst, const float *src, int64_t n_floats, int flags,
 int launch_sync(const Variant &v, const SyncArgs &a, int64_t n_tiles, size_t lds_floor, hipStream_t stream);
 size_t sync_lds_bytes(const Variant &v, int K, int q, int C, bool in_kernel_sampling);
 int prepare_kernels(const Variant &v, int K, int q, int C, bool mixed_q, bool *can_sample_in_kernel);
-const Variant *variant_table(int *count);
+bool can_sample_inline(int K, int C);
+const Variant *variant_table(int *count);          // the shapes a plan description can name
 
 }  // namespace gbmuf

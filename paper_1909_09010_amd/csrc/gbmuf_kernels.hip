@@ -229,6 +229,35 @@ __device__ __forceinline__ void store4(float *p, v4f v, bool streaming)
     else *q = v;
 }
 
+__device__ __forceinline__ int64_t placed(const Placement &at, int64_t e)
+{
+    return e + (e >> at.logB) * at.block_extra;
+}
+
+// A column of which only the floats in `mk` are this tile's (all four if WHOLE).
+template <bool WHOLE>
+__device__ __forceinline__ v4f load_col(const float *p, unsigned mk, bool streaming)
+{
+    if (WHOLE || mk == 0xFu) return load4(p, streaming);
+    v4f v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+        if (mk & (1u << c)) v[c] = p[c];
+    return v;
+}
+
+template <bool WHOLE>
+__device__ __forceinline__ void store_col(float *p, v4f v, unsigned mk, bool streaming)
+{
+    if (WHOLE || mk == 0xFu) {
+        store4(p, v, streaming);
+        return;
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+        if (mk & (1u << c)) p[c] = v[c];
+}
+
 template <int NT, int SLOTS, int Q1>
 __global__ __launch_bounds__(NT) void sync_kernel(SyncArgs a)
 {
@@ -339,14 +368,110 @@ __global__ __launch_bounds__(NT) void sync_kernel(SyncArgs a)
 }
 
 // ---------------------------------------------------------------------------------------
+// The fused kernel for many workers (K > 64).  A tile holds theta of all K workers, so its width is
+// what K leaves of the 160 KB LDS; narrow tiles touch each row in pieces of 256 bytes and less, which
+// HBM answers at two thirds of the rate of 512-byte pieces.  So the tile takes up to 128 KB, all of
+// theta is loaded and parked first, and omega and Delta, whose values no other worker needs, are not
+// held for the whole tile but streamed through DEPTH slots of registers.
+// NT is a multiple of T here, so a thread keeps one column and visits every (NT/T)-th worker.
+//
+// Bound by HBM.  256 workers x 6.2 M (19 GB, blocked), T = 32: 6290 us (6040 GB/s); the kernel above
+// with T = 16, all that its registers hold of three arrays: 7576 us.
+// ---------------------------------------------------------------------------------------
+template <int NT, int SLOTS, int DEPTH, int Q1, bool WHOLE>
+__device__ __forceinline__ void wide_tile(const SyncArgs &a, const TileDesc &td, v4f *tile, uint16_t *ids)
+{
+    const int tid = threadIdx.x;
+    const int K = a.K, q1 = (Q1 > 0) ? Q1 : td.q + 1, q = q1 - 1;
+    const float inv = (a.flags & kFlagMixedQ) ? a.comp[td.comp].inv : a.inv;
+    const int logT = a.logT, mode = a.mode;
+    const bool slots_too = mode != GBMUF_MODE_GOSSIP_MA;
+    const bool nt_load = (a.flags & kFlagStreamLoads) != 0, nt_store = (a.flags & kFlagStreamStores) != 0;
+    const int col = tid & ((1 << logT) - 1), w0 = tid >> logT, dw = NT >> logT;
+    const int64_t e = ((td.lo >> 2) + col) << 2;
+    unsigned mk = 0xFu;                                           // which of the 4 floats are ours
+    if (!WHOLE) {
+        mk = 0;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) mk |= (e + c >= td.lo && e + c < td.lo + td.n) ? (1u << c) : 0u;
+    }
+    const int mine = (mk != 0u && w0 < K) ? (K - w0 + dw - 1) / dw : 0;       // slots of this thread
+    const int64_t at0 = static_cast<int64_t>(w0) * a.at.stride + placed(a.at, e);
+    const int64_t step = static_cast<int64_t>(dw) * a.at.stride;
+
+    v4f th[SLOTS], om[DEPTH], de[DEPTH];
+#pragma unroll
+    for (int n = 0; n < SLOTS; ++n)
+        if (n < mine) th[n] = load_col<WHOLE>(a.theta + at0 + n * step, mk, nt_load);
+#pragma unroll
+    for (int n = 0; n < DEPTH; ++n)
+        if (n < mine && slots_too) {
+            om[n] = load_col<WHOLE>(a.omega + at0 + n * step, mk, nt_load);
+            de[n] = load_col<WHOLE>(a.delta + at0 + n * step, mk, nt_load);
+        }
+
+    if (a.nbr != nullptr) stage_ids(ids, a.nbr, td.comp, K, q, a.q, tid, NT);
+    else draw_ids(ids, reinterpret_cast<int32_t *>(ids + ids_words(K, a.q)), a, td.comp, q, tid, NT);
+
+#pragma unroll
+    for (int n = 0; n < SLOTS; ++n)
+        if (n < mine) tile[tid + n * NT] = th[n];
+    __syncthreads();
+
+#pragma unroll
+    for (int n = 0; n < SLOTS; ++n) {
+        if (n >= mine) continue;
+        const v4f o = om[n % DEPTH], d = de[n % DEPTH];
+        if (n + DEPTH < SLOTS && n + DEPTH < mine && slots_too) {
+            om[n % DEPTH] = load_col<WHOLE>(a.omega + at0 + (n + DEPTH) * step, mk, nt_load);
+            de[n % DEPTH] = load_col<WHOLE>(a.delta + at0 + (n + DEPTH) * step, mk, nt_load);
+        }
+        const uint16_t *row = ids + (w0 + n * dw) * q1;
+        v4f s = tile[(static_cast<int>(row[0]) << logT) + col];
+        if (Q1 > 0) {
+#pragma unroll
+            for (int j = 1; j < Q1; ++j) s = s + tile[(static_cast<int>(row[j]) << logT) + col];
+        } else {
+            for (int j = 1; j < q1; ++j) s = s + tile[(static_cast<int>(row[j]) << logT) + col];
+        }
+        v4f tn = s * inv;
+        const int64_t at = at0 + n * step;
+        if (slots_too) {
+            const v4f avg = tn;
+            v4f on, dn;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                float t1, o1, d1;
+                filter(avg[c], o[c], d[c], a.eta, a.zeta, mode, t1, o1, d1);
+                tn[c] = t1; on[c] = o1; dn[c] = d1;
+            }
+            store_col<WHOLE>(a.omega + at, on, mk, nt_store);
+            store_col<WHOLE>(a.delta + at, dn, mk, nt_store);
+        }
+        store_col<WHOLE>(a.theta + at, tn, mk, nt_store);
+    }
+}
+
+template <int NT, int SLOTS, int DEPTH, int Q1>
+__global__ __launch_bounds__(NT) void sync_wide_kernel(SyncArgs a)
+{
+    extern __shared__ float4 lds4[];
+    v4f *tile = reinterpret_cast<v4f *>(lds4);
+    uint16_t *ids = reinterpret_cast<uint16_t *>(lds4 + NT * SLOTS);
+    const TileDesc td = a.tiles[tile_of_block(a)];
+    if ((a.flags & kFlagCheckPeriods) && a.step % static_cast<uint64_t>(a.comp[td.comp].period) != 0)
+        return;                                                   // not due: the whole workgroup leaves
+    // a tile of whole columns, or one that a component edge cuts
+    if (((td.lo & 3) | (td.n & ~(4 << a.logT))) == 0)
+        wide_tile<NT, SLOTS, DEPTH, Q1, true>(a, td, tile, ids);
+    else
+        wide_tile<NT, SLOTS, DEPTH, Q1, false>(a, td, tile, ids);
+}
+
+// ---------------------------------------------------------------------------------------
 // Final model average (Algorithm 1, RETURN): out[e] = fl(1/K) * (theta[0][e] + theta[1][e] + ...),
 // summed in ascending worker id.  One thread per 16-byte column; 4(K+1) bytes per parameter.
 // ---------------------------------------------------------------------------------------
-__device__ __forceinline__ int64_t placed(const Placement &at, int64_t e)
-{
-    return e + (e >> at.logB) * at.block_extra;
-}
-
 template <int B>
 __global__ __launch_bounds__(256) void final_average_vec4_kernel(const float *theta, Placement at, int K,
                                                                  int64_t P, float inv, float *out)
@@ -431,8 +556,8 @@ __global__ __launch_bounds__(256) void copy_probe_kernel(v4f *dst, const v4f *sr
 }
 
 constexpr Variant kVariants[] = {
-    {256, 8}, {512, 8}, {512, 4}, {256, 16}, {1024, 4}, {256, 4},
-    {256, 2}, {512, 2}, {1024, 2}, {1024, 1}, {512, 1}, {256, 1},
+    {256, 8, 0}, {512, 8, 0}, {512, 4, 0}, {256, 16, 0}, {1024, 4, 0}, {256, 4, 0},
+    {256, 2, 0}, {512, 2, 0}, {1024, 2, 0}, {1024, 1, 0}, {512, 1, 0}, {256, 1, 0},
 };
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 
@@ -451,8 +576,24 @@ KernelFn pick_q(int q1)
     }
 }
 
+template <int NT, int SLOTS, int DEPTH>
+KernelFn pick_wide(int q1)
+{
+    switch (q1) {
+        case 1: return sync_wide_kernel<NT, SLOTS, DEPTH, 1>;
+        case 2: return sync_wide_kernel<NT, SLOTS, DEPTH, 2>;
+        case 3: return sync_wide_kernel<NT, SLOTS, DEPTH, 3>;
+        case 4: return sync_wide_kernel<NT, SLOTS, DEPTH, 4>;
+        case 5: return sync_wide_kernel<NT, SLOTS, DEPTH, 5>;
+        default: return sync_wide_kernel<NT, SLOTS, DEPTH, 0>;
+    }
+}
+
 KernelFn pick_kernel(const Variant &v, int q1)
 {
+    if (v.depth == 2 && v.threads == 1024 && v.slots == 4) return pick_wide<1024, 4, 2>(q1);
+    if (v.depth == 4 && v.threads == 512 && v.slots == 16) return pick_wide<512, 16, 4>(q1);
+    if (v.depth != 0) return nullptr;
 #define GBMUF_CASE(NT, SL) \
     if (v.threads == NT && v.slots == SL) return pick_q<NT, SL>(q1);
     GBMUF_CASE(256, 8)
@@ -478,10 +619,10 @@ size_t ids_bytes(int K, int q)
 
 size_t perm_bytes(int K, int C) { return static_cast<size_t>(K) * static_cast<size_t>(C) * sizeof(int32_t); }
 
+}  // namespace
+
 // Workgroups draw their own neighbour rows when the candidates of all workers fit 8 KB of LDS.
 bool can_sample_inline(int K, int C) { return perm_bytes(K, C) <= 8192; }
-
-}  // namespace
 
 const Variant *variant_table(int *count)
 {

@@ -27,7 +27,7 @@ struct TileSet {
 
 // How the fused kernel runs on one kind of state placement.
 struct LayoutCfg {
-    Variant variant{256, 8};
+    Variant variant{256, 8, 0};
     int32_t logT = 0;
     int32_t set = 0;                   // which TileSet
     int32_t workgroups_per_cu = 0;     // 0 = no bound
@@ -50,6 +50,7 @@ struct gbmuf_plan_s {
     std::vector<int32_t> cand;       // [K][C] ring candidates, order of Definition 1
     std::vector<CompDesc> comp;      // m: per-component constants of the kernels
     LayoutCfg cfg[2][2];             // [kRows, kBlocked][kBmuf, kMa]
+    int32_t min_block_logT = 0;      // blocks hold at least 4 << min_block_logT floats
     TileSet sets[kMaxTileSets];      // one per distinct tile width among the four configurations
     int32_t n_sets = 0;
     float inv = 1.0f;                // 1/(q+1), rounded once (plans with one q)
@@ -206,7 +207,7 @@ bool find_variant(int threads, int slots, Variant *out)
 //     Gossip-MA at 64 workers x 45.8 M: 1024 x 4 4730, 1024 x 2 4957.
 Variant default_variant(int K, int layout, int what)
 {
-    Variant v{1024, 4};
+    Variant v{1024, 4, 0};
     if (what == kMa) {
         if (K <= 16) find_variant(512, 2, &v);
         else if (K <= (layout == kBlocked ? 64 : 32)) find_variant(1024, 2, &v);
@@ -235,6 +236,26 @@ int32_t default_workgroups_per_cu(int K, int layout, int what)
     if (what == kMa) return K <= 16 ? 4 : 2;
     if (layout == kBlocked) return K <= 4 ? 4 : K <= 32 ? 2 : 1;
     return K <= 4 ? 4 : K <= 8 ? 20 / K : K <= 24 ? 2 : K <= 32 ? 1 : 0;
+}
+
+// Whether the kernel for many workers takes over (where its tile fits).  Measured, old shape against
+// new, us: blocked 72 workers x 6.2 M 2083 / 1724, 128: 3416 / 3114, 256: 7576 / 6310, 1024 x 3.6 M
+// 36480 / 19785; plain rows 128: 3881 / 3775, 200 x 3.6 M 3560 / 3561, 1024: 25489 / 21464.  Gossip-MA has
+// no omega and Delta to stream and gains where its old tile was narrow or half empty: blocked 128:
+// 1233 / 1329 (so not there), 200 x 3.1 M 1112 / 1034, 300: 2017 / 1780, 1024: 9179 / 6423, but 256 x 6.2 M,
+// where two full 64 KB tiles of 16 columns share a CU, 2621 / 2720.
+bool takes_many(int K, int layout, int what)
+{
+    if (what == kBmuf) return K > 64;
+    return K > 128 && !(layout == kBlocked && K > 224 && K <= 256);
+}
+
+// log2 of the largest power of two T with K * T <= the shape's slots.
+int32_t widest_tile(const Variant &v, int K)
+{
+    int32_t lg = 0;
+    while ((static_cast<int64_t>(K) << (lg + 1)) <= static_cast<int64_t>(v.threads) * v.slots) ++lg;
+    return lg;
 }
 
 // Split every component into runs of at most T 16-byte columns (the fused kernel's work list).
@@ -386,11 +407,6 @@ bool arrays_overlap(const float *x, const float *y, int64_t K, int64_t stride, i
     return false;
 }
 
-int32_t max_blocked_logT(const gbmuf_plan_s *pl)
-{
-    return std::max(pl->cfg[kBlocked][kBmuf].logT, pl->cfg[kBlocked][kMa].logT);
-}
-
 // Validates a state description for this plan and turns it into the kernels' placement.
 int check_state(const gbmuf_plan_s *pl, const gbmuf_state_t *st, bool need_slots, Placement *at, int *layout)
 {
@@ -404,7 +420,7 @@ int check_state(const gbmuf_plan_s *pl, const gbmuf_state_t *st, bool need_slots
     } else {
         const int64_t B = st->block_floats;
         if (B < 0 || (B & (B - 1)) != 0 || B > (static_cast<int64_t>(1) << 30)) return GBMUF_EINVAL;
-        if (B < (static_cast<int64_t>(4) << max_blocked_logT(pl))) return GBMUF_EINVAL;      // a tile must fit a block
+        if (B < (static_cast<int64_t>(4) << pl->min_block_logT)) return GBMUF_EINVAL;
         if (st->worker_stride < B) return GBMUF_EINVAL;
         if (st->block_stride < static_cast<int64_t>(pl->K - 1) * st->worker_stride + B) return GBMUF_EINVAL;
         int32_t lg = 0;
@@ -435,14 +451,16 @@ gbmuf_state_t rows_state(float *theta, float *omega, float *delta, int64_t strid
 //     written in two pieces.  With 32 KB per XCD one line in 256 is shared.  16 workers x 35.0 M in
 //     plain tensors: 3944 GB/s at 512 B, 4984 at 4 KB, 5073 at 16 KB (aligned rows: 5161); 64 workers
 //     x 26.9 M: 3880 at 1 KB, 4405 at 4 KB, 5163 at 32 KB.
-//   Lines of one tile only: tile by tile (padded rows: 1 to 32 KB per XCD are within 2 %).
-int32_t xcd_granule(int32_t logT, const Placement &at, const gbmuf_state_t *st, int32_t mode)
+//   Lines of one tile only: tile by tile (padded rows: 1 to 32 KB per XCD are within 2 %), but 1 KB for
+//     more than 128 workers (blocked, 256 x 5.2 M: 512 B 5279 us, 1 KB 5224, 2 KB 5907; 512 workers, whose
+//     tiles have 256 B: 13112, 512 B 12924, 1 KB 12278).
+int32_t xcd_granule(const LayoutCfg &cfg, const Placement &at, const gbmuf_state_t *st, int32_t mode)
 {
     uintptr_t low = reinterpret_cast<uintptr_t>(st->theta) | (static_cast<uintptr_t>(at.stride | at.block_extra) << 2);
     if (mode != GBMUF_MODE_GOSSIP_MA)
         low |= reinterpret_cast<uintptr_t>(st->omega) | reinterpret_cast<uintptr_t>(st->delta);
-    constexpr int32_t log_columns = 11;                    // 2^11 columns of 16 bytes
-    return (low & 127u) && log_columns > logT ? log_columns - logT : 0;
+    const int32_t log_columns = (low & 127u) ? 11 : cfg.variant.depth == kVeryMany.depth ? 6 : 0;   // of 16 bytes
+    return log_columns > cfg.logT ? log_columns - cfg.logT : 0;
 }
 
 
@@ -481,7 +499,7 @@ int enqueue_sync(const gbmuf_plan_s *pl, const int32_t *nbr_dev, const gbmuf_sta
     a.key0 = static_cast<uint32_t>(pl->seed); a.key1 = static_cast<uint32_t>(pl->seed >> 32);
     a.round0 = static_cast<uint32_t>(round); a.round1 = static_cast<uint32_t>(round >> 32);
     a.step = round;
-    a.xcd_log = xcd_granule(cfg.logT, at, st, mode);
+    a.xcd_log = xcd_granule(cfg, at, st, mode);
     return launch_sync(cfg.variant, a, n_tiles, lds_floor(pl, cfg), stream);
 }
 
@@ -592,11 +610,19 @@ int gbmuf_plan_create(gbmuf_plan_t **out, const gbmuf_plan_desc_t *desc)
                     cfg.variant = default_variant(K, l / 2, l % 2);
                 }
                 if (rc != GBMUF_OK) break;
-                const int slots = cfg.variant.threads * cfg.variant.slots;
-                if (K > slots) { rc = desc->tile_threads != 0 ? GBMUF_EINVAL : GBMUF_EUNSUPPORTED; break; }
-                int lg = 0;
-                while ((static_cast<int64_t>(K) << (lg + 1)) <= slots) ++lg;
-                cfg.logT = lg;                             // T = largest power of two with K*T <= slots
+                if (K > cfg.variant.threads * cfg.variant.slots) { rc = desc->tile_threads != 0 ? GBMUF_EINVAL : GBMUF_EUNSUPPORTED; break; }
+                cfg.logT = widest_tile(cfg.variant, K);
+                if (l / 2 == kBlocked) pl->min_block_logT = std::max(pl->min_block_logT, cfg.logT);
+                // Many workers: the wider shapes, where the neighbour rows fit beside their tile.  They
+                // look an element's block up column by column, so a block may be narrower than a tile
+                // and min_block_logT does not grow.
+                if (desc->tile_threads == 0 && takes_many(K, l / 2, l % 2)) {
+                    const Variant &v = K <= 128 ? kMany : kVeryMany;
+                    if (sync_lds_bytes(v, K, pl->q, pl->C, can_sample_inline(K, pl->C)) <= kLdsPerWorkgroup) {
+                        cfg.variant = v;
+                        cfg.logT = widest_tile(v, K);
+                    }
+                }
                 cfg.workgroups_per_cu = desc->workgroups_per_cu != 0 ? desc->workgroups_per_cu
                                                                      : default_workgroups_per_cu(K, l / 2, l % 2);
             }
@@ -670,7 +696,7 @@ int gbmuf_plan_info(const gbmuf_plan_t *plan, gbmuf_info_t *info)
     info->threads_blocked = plan->cfg[kBlocked][kBmuf].variant.threads;
     info->workgroups_per_cu_blocked = plan->cfg[kBlocked][kBmuf].workgroups_per_cu;
     info->tile_columns_blocked_ma = 1 << plan->cfg[kBlocked][kMa].logT;
-    info->min_block_floats = 4 << max_blocked_logT(plan);
+    info->min_block_floats = 4 << plan->min_block_logT;
     return GBMUF_OK;
 }
 
@@ -920,7 +946,7 @@ int gbmuf_recommend_layout(const gbmuf_plan_t *plan, int64_t P, int32_t K, int32
     // blocks lose 7-10 points for both.  A plan with very wide tiles needs more.
     int64_t B = 8192;
     if (plan)
-        while (B < (static_cast<int64_t>(4) << max_blocked_logT(plan))) B <<= 1;
+        while (B < (static_cast<int64_t>(4) << plan->min_block_logT)) B <<= 1;
     const int64_t blocks = (P + B - 1) / B;
     out->worker_stride = B;
     out->block_floats = B;

@@ -100,3 +100,37 @@ def test_state_copy_at_the_edges_of_its_pieces(K, P, which):
                 expect[skew[2 - a] + w * stride:][:P] = rows[a][skew[a] + w * stride:][:P]
         assert torch.equal(back[a], expect)
     pl.destroy()
+
+
+# The kernel for many workers: 64 < K <= 128 with 4096 slots, above with 8192; component edges inside and at the
+# ends of a tile, blocks as narrow as they may be (narrower than its tile), caller's tables, all modes.
+@pytest.mark.parametrize("K,q", [(65, 2), (90, 5), (128, 7), (129, 4), (200, 1), (256, 3), (257, 0), (600, 9), (1024, 2)])
+@pytest.mark.parametrize("mode", [0, 1, 2, 3])
+def test_many_workers(K, q, mode):
+    _need_gpu()
+    off = [0, 1, 130, 130, 1029, 1030, 2048, 2300]
+    P = off[-1]
+    check_rows(K, q, off, P + 1, (1, 2, 0), mode=mode, seed=K)
+    check_rows(K, q, off, 2304, mode=mode, seed=K)
+    pl = B.Plan(off, K, q, 0, seed=K)
+    assert mode != 1 or K <= 64 or pl.info.min_block_floats <= 4 * pl.info.tile_columns_blocked
+    Bf = pl.info.min_block_floats
+    blocks = -(-P // Bf)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(K)
+    arena = torch.randn(blocks * 3 * K * Bf, generator=g, device=DEV) * 0.05
+    view = arena.view(blocks, 3, K, Bf)
+    host = [view[:, a].permute(1, 0, 2).reshape(K, -1).cpu().numpy().copy() for a in range(3)]
+    state = B.make_state(*[None if a and mode == 3 else arena.data_ptr() + 4 * a * K * Bf for a in range(3)], Bf, Bf, 3 * K * Bf)
+    table = torch.zeros((len(off) - 1, K, max(q, 1)), dtype=torch.int32, device=DEV)
+    for r in (0, 1):
+        if r and q:
+            pl.neighbours_device(r, table, None)
+            pl.sync_table_state(table.flip(-1).contiguous(), state, 0.9, 1.0, mode, None)
+        else:
+            pl.sync_state(state, 0.9, 1.0, mode, r, None)
+        oracle.sync(np.asarray(off, dtype=np.int64), K, pl.info.p, q, K, r, *host, np.float32(0.9), np.float32(1.0), mode)
+    torch.cuda.synchronize()
+    for a in range(3):
+        assert np.array_equal(view[:, a].permute(1, 0, 2).reshape(K, -1).cpu().numpy(), host[a])
+    pl.destroy()
