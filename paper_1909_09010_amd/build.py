@@ -4,11 +4,13 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "libgbmuf.so")
-SOURCES = ["gbmuf_plan.hip", "gbmuf_kernels.hip"]
+# (source, defines): the fused kernel's shapes are compiled in five parts
+UNITS = [("gbmuf_sync.hip", [f"-DGBMUF_PART={i}"]) for i in range(5)] + [("gbmuf_plan.hip", []), ("gbmuf_kernels.hip", [])]
 
 # -ffp-contract=off: the method's fp32 arithmetic rounds every multiply and add separately.
 # The packed-fp32 feature is switched off on purpose (scalar fp32 VALU ops only).
@@ -27,11 +29,23 @@ def hipcc() -> str:
 
 
 def build_library(verbose: bool = True, extra_flags=()) -> str:
-    """Compiles every HIP source into paper_1909_09010_amd/libgbmuf.so (always recompiles)."""
-    cmd = [hipcc(), *HIPCC_FLAGS, *extra_flags, "-o", LIB_PATH] + [os.path.join(CSRC, s) for s in SOURCES]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.run(cmd, check=True, cwd=CSRC)
+    """Compiles every HIP source into paper_1909_09010_amd/libgbmuf.so (always recompiles), the
+    objects side by side."""
+    flags = [f for f in HIPCC_FLAGS if f != "-shared"] + list(extra_flags)
+    with tempfile.TemporaryDirectory(prefix="gbmuf_build_") as tmp:
+        objects, commands = [], []
+        for src, define in UNITS:
+            obj = os.path.join(tmp, f"{len(objects)}.o")
+            objects.append(obj)
+            commands.append([hipcc(), *flags, *define, "-c", "-o", obj, os.path.join(CSRC, src)])
+        if verbose:
+            for cmd in commands:
+                print(" ".join(cmd), flush=True)
+        running = [subprocess.Popen(cmd, cwd=CSRC) for cmd in commands]
+        for cmd, status in [(cmd, p.wait()) for cmd, p in zip(commands, running)]:
+            if status != 0:
+                raise subprocess.CalledProcessError(status, cmd)
+        subprocess.run([hipcc(), "--offload-arch=gfx950", "-fPIC", "-shared", "-o", LIB_PATH, *objects], check=True, cwd=CSRC)
     return LIB_PATH
 
 

@@ -3,6 +3,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 namespace gbmuf {
@@ -54,11 +55,9 @@ struct SyncArgs {
     int32_t flags;           // bit 0: streaming stores, bit 1: streaming loads, bit 3: walk the
                              // tile list backwards, bit 4: components draw different q (read the
                              // tile's q and the component's inv), bit 5: skip components whose
-                             // period does not divide `step`
-    // in-kernel sampling (nbr == nullptr): same bits as the sampler kernel, drawn from the
-    // candidates and the key below; C ints per worker go to LDS
-    const int32_t *cand;     // [K][C], device
-    int32_t C;
+                             // period does not divide `step`, bit 6: rotate the XCDs (tile_of_block)
+    // in-kernel sampling (nbr == nullptr): same bits as the sampler kernel, drawn from the key below
+    int32_t p, C;            // ring degree, candidates per worker
     uint32_t key0, key1, round0, round1;
     uint64_t step;           // with flag bit 5: component i syncs iff step % H_i == 0
 };
@@ -69,16 +68,17 @@ enum : int32_t {
     kFlagBackwards = 8,
     kFlagMixedQ = 16,
     kFlagCheckPeriods = 32,
+    kFlagRotate = 64,
 };
 
 // Arguments of the neighbour-sampling kernel: pairs [first_pair, first_pair + pairs) of the
 // (component, worker) grid, pair = component * K + worker.
 struct SampleArgs {
-    const int32_t *cand;     // [K][C] ring candidates in the order of Definition 1, device
     const CompDesc *comp;    // [m]
     int32_t *out;            // [m][K][width]; entries beyond a component's q are set to -1
     int64_t first_pair, pairs;
-    int32_t K, C, q, width;  // q is used unless `mixed`
+    int32_t K, p, C;         // ring degree, candidates per worker
+    int32_t q, width;        // q is every component's unless `mixed`, the largest otherwise
     int32_t mixed;           // components draw different q: take comp[i].q
     int32_t check_periods;   // skip components whose period does not divide `step`
     uint32_t key0, key1;     // seed low / high
@@ -97,16 +97,36 @@ struct CopyArgs {
 };
 
 // One tile shape of the fused kernel: threads per workgroup and 16-byte slots per thread.
-// A tile holds threads*slots slots = K worker rows of tile_columns columns each.  depth > 0: the
-// kernel for many workers, which holds `depth` slots of omega and Delta at a time.
+// A tile holds threads*slots slots = K worker rows of tile_columns columns each.  depth: how many
+// slots of omega and Delta a thread holds at a time (depth < slots: for many workers).
 struct Variant {
     int threads;
     int slots;
     int depth;
 };
+constexpr Variant kSixtyFour = {1024, 2, 1};       // blocked, 33 to 44 and 57 to 64 workers
 constexpr Variant kMany = {1024, 4, 2};            // 64 < K <= 128
 constexpr Variant kVeryMany = {512, 16, 4};        // K > 128
 constexpr size_t kLdsPerWorkgroup = 160 * 1024;    // gfx950
+
+// Which instance of the fused kernel a component's neighbour count takes (gbmuf_sync.hip), and the
+// layout of its neighbour rows in LDS.
+constexpr int kFewDraws = 7;                       // up to so many neighbours are drawn in registers
+constexpr int kUpTo8 = 8, kMixed = 9, kAnyQ = 0;
+constexpr int kernel_q1(int q, bool mixed) { return q > kFewDraws ? kAnyQ : mixed ? kMixed : q > 4 ? kUpTo8 : q + 1; }
+// uint16 per row, and in all rows (padded to 16 bytes)
+__host__ __device__ constexpr int ids_pitch(int Q1, int q) { return Q1 == kAnyQ ? q + 1 : Q1 <= 4 ? 4 : 8; }
+__host__ __device__ constexpr size_t ids_words(int K, int pitch)
+{
+    return (static_cast<size_t>(K) * static_cast<size_t>(pitch) + 7) & ~static_cast<size_t>(7);
+}
+
+using KernelFn = void (*)(SyncArgs);
+KernelFn pick_kernel_0(const Variant &v, int q, bool mixed);
+KernelFn pick_kernel_1(const Variant &v, int q, bool mixed);
+KernelFn pick_kernel_2(const Variant &v, int q, bool mixed);
+KernelFn pick_kernel_3(const Variant &v, int q, bool mixed);
+KernelFn pick_kernel_4(const Variant &v, int q, bool mixed);
 
 // Remembers the most recent failing HIP call of this thread (what gbmuf_last_error_detail
 // returns) and maps it to a status.
@@ -119,9 +139,10 @@ int launch_final_average(const float *theta, const Placement &at, int K, int64_t
 int launch_state_copy(const CopyArgs &c, int arrays, hipStream_t stream);
 int launch_copy_probe(float *dst, const float *src, int64_t n_floats, int flags, int blocks, hipStream_t stream);
 int launch_sync(const Variant &v, const SyncArgs &a, int64_t n_tiles, size_t lds_floor, hipStream_t stream);
-size_t sync_lds_bytes(const Variant &v, int K, int q, int C, bool in_kernel_sampling);
-int prepare_kernels(const Variant &v, int K, int q, int C, bool mixed_q, bool *can_sample_in_kernel);
+size_t sync_lds_bytes(const Variant &v, int K, int q, bool mixed, int C, bool in_kernel_sampling);
+int prepare_kernels(const Variant &v, int K, int q, bool mixed, int C, bool *can_sample_in_kernel);
 bool can_sample_inline(int K, int C);
+bool draws_in_registers(int q);
 const Variant *variant_table(int *count);          // the shapes a plan description can name
 
 }  // namespace gbmuf

@@ -27,10 +27,12 @@ struct TileSet {
 
 // How the fused kernel runs on one kind of state placement.
 struct LayoutCfg {
-    Variant variant{256, 8, 0};
+    Variant variant{256, 8, 8};
     int32_t logT = 0;
     int32_t set = 0;                   // which TileSet
     int32_t workgroups_per_cu = 0;     // 0 = no bound
+    int32_t xcd_columns_log = 0;       // log2 of the columns of a row that one XCD takes in one run (if more than a tile)
+    bool rotate = false;               // see tile_of_block
 };
 
 enum { kRows = 0, kBlocked = 1 };
@@ -56,12 +58,12 @@ struct gbmuf_plan_s {
     float inv = 1.0f;                // 1/(q+1), rounded once (plans with one q)
     int32_t flags = 0;               // load/store cache hints of the fused kernel
     bool in_kernel_sampling = false; // workgroups draw their own neighbour rows (no sampler launch)
+    bool in_kernel_sampling_ma = false;   // the same for the gossip-MA branch
     bool alternate = true;           // odd rounds walk the tile list backwards (see tile_of_block)
 
     bool has_device = false;
     int device = -1;
     int32_t lds_per_cu = 0;
-    int32_t *d_cand = nullptr;
     CompDesc *d_comp = nullptr;
     int32_t *d_nbr = nullptr;        // neighbour scratch of gbmuf_sync, [m][K][q]
 };
@@ -196,46 +198,73 @@ bool find_variant(int threads, int slots, Variant *out)
     return false;
 }
 
-// Measured on MI355X.  What the chip has in flight at one time decides, not how much of it: a short
-// stretch of memory is fast, and a tile should cover whole kilobytes of a worker row.
-//   Blocked state (one address stream): 32 columns (512 B per worker row) in workgroups of 512
-//     threads; the gossip-MA branch (theta only) takes twice the columns.
-//   Rows (3K address streams): 64 columns.  16 workers x 35.0 M in plain tensors, on a fast and on a
-//     slow placement: 1024 x 1 slots, two per CU 2251 / 2634 us; 512 x 1 (32 columns), three per CU
-//     2365 / 2751; 256 x 2 (32), unbounded 2652 / 2957.  32 workers x 45.8 M: 1024 x 2 7065, 512 x 2
-//     7092.  64 workers x 26.9 M: 1024 x 4 9771, 512 x 4 (32) 10072.  Padded rows: within 3 %.
-//     Gossip-MA at 64 workers x 45.8 M: 1024 x 4 4730, 1024 x 2 4957.
-Variant default_variant(int K, int layout, int what)
+// How the fused kernel runs, by K, layout and branch, unless the plan description names a shape.
+// All figures: MI355X, us per sync, parameters as stated, the shape taken against what it replaced
+// or its nearest rival.  What decides is how the accesses that the chip has in flight at one time lie in
+// memory, less how many they are: a short stretch of memory is fast, and so are tiles that cover 512
+// bytes to 1 KB of a worker row.
+Variant default_variant(int K, int layout, int what, bool large)
 {
-    Variant v{1024, 4, 0};
+    Variant v{1024, 4, 4};
     if (what == kMa) {
+        // theta only: more columns than the three-array update.  Blocked 32 workers x 45.8 M: 512 x 2
+        // (four per CU) 1793, 1024 x 2 (two) 2054; 64 x 32.8 M: 512 x 4 2611, 1024 x 2 3033.  Rows 24 x 58.9 M:
+        // 512 x 4 2071, 1024 x 2 2357; 64 x 45.8 M: 1024 x 4 4730, 1024 x 2 4957.
         if (K <= 16) find_variant(512, 2, &v);
-        else if (K <= (layout == kBlocked ? 64 : 32)) find_variant(1024, 2, &v);
+        else if (K <= 32) find_variant(512, layout == kBlocked ? 2 : 4, &v);
+        else if (K <= 64 && layout == kBlocked) find_variant(512, 4, &v);
     } else if (layout == kBlocked) {
+        // one address stream: T = 32 (64 for few workers).  256 x 2 / 512 x 1: 16 workers x 278.6 M 16290 /
+        // 17100, 8 x 84.8 M 2517 / 2577, but below `large` 16 x 2.6 M 166 / 161, 12 x 2.6 M 122 / 118.
+        // 1024 x 1 / 512 x 2: 24 x 45.8 M 4073 / 4253, 32: 5390 / 5477, 20: 3690 / 3550, 28: 4920 / 4813.
+        // kSixtyFour (two per CU) / 512 x 4 (one): 42 x 34.9 M 5414 / 5820, 48 x 32.8 M 6030 / 5944, 56: 7291 /
+        // 6997, 64 x 57.8 M 14150 / 14410.
         if (K <= 4) find_variant(256, 1, &v);
+        else if (K <= 16 && large) find_variant(256, 2, &v);
         else if (K <= 16) find_variant(512, 1, &v);
+        else if ((K > 21 && K <= 24) || (K > 29 && K <= 32)) find_variant(1024, 1, &v);
         else if (K <= 32) find_variant(512, 2, &v);
+        else if (K <= 44 || (K > 56 && K <= 64)) v = kSixtyFour;
         else if (K <= 64) find_variant(512, 4, &v);
-        else if (K <= 128) find_variant(512, 8, &v);
     } else {
-        if (K <= 4) find_variant(256, 1, &v);
-        else if (K <= 8) find_variant(512, 1, &v);
-        else if (K <= 16) find_variant(1024, 1, &v);
+        // 3K address streams: T = 64 and more.  8 x 58.9 M padded / plain: 1024 x 1 1939 / 2118, 512 x 1
+        // 2031 / 2172; 16 x 35.0 M plain, on a fast and on a slow placement: 1024 x 1 2251 / 2634, 512 x 1
+        // 2365 / 2751, 256 x 2 2652 / 2957; 64 x 32.8 M: kMany 10088 / 10256, 1024 x 4 10282 / 10577.
+        if (K <= 16) find_variant(1024, 1, &v);
         else if (K <= 32) find_variant(1024, 2, &v);
+        else if (K <= 64) v = kMany;
     }
     return v;
 }
 
-// Blocked state: what the chip has in flight should stay near 12-24 MB (24-48 KB per workgroup
-// at two workgroups per CU, or 96 KB at one; the gossip-MA branch moves a third of that per
-// workgroup and takes twice as many); more resident workgroups lose 5-15 points.  Rows: about 1200
-// columns per CU up to K = 8, two workgroups above (one at K = 32: 7065 us against 7143); beyond
-// that the tile's LDS is bound enough.
-int32_t default_workgroups_per_cu(int K, int layout, int what)
+// Resident workgroups per CU (0: what the LDS holds).  Blocked: about 1200 columns, but two workgroups
+// at least, and one of the large tiles from 45 to 56: 5 workers 1584 at four, 1876 at two; 10 workers 2219 at
+// four, 2648 at two; 14 workers 3122 at three, 3237 at two; 16 workers x 278.6 M 16290 at two, 17200 at three.
+// A state that fits the caches has nothing to gain from the bound and loses latency: 4 workers x 0.45 M
+// 10.9 at eight, 12.1 at four.  Rows: two, but one from 25 to 64 workers (32 workers 7065 against 7143).
+int32_t default_workgroups_per_cu(int K, int layout, int what, int logT, int64_t values)
 {
-    if (what == kMa) return K <= 16 ? 4 : 2;
-    if (layout == kBlocked) return K <= 4 ? 4 : K <= 32 ? 2 : 1;
-    return K <= 4 ? 4 : K <= 8 ? 20 / K : K <= 24 ? 2 : K <= 32 ? 1 : 0;
+    if (values <= 8000000) return 8;                       // 96 MB of theta, omega and Delta
+    if (what == kMa) return layout == kBlocked ? (K <= 64 ? 4 : 2) : (K <= 16 ? 4 : K <= 32 ? 3 : 0);
+    if (layout == kBlocked) {
+        const int columns = K << logT, aim = K <= 4 ? 1024 : 1200;
+        return K <= 24 ? std::max(2, (aim + columns / 2) / columns) : K > 44 && K <= 56 ? 1 : 2;
+    }
+    return K <= 24 ? 2 : K <= 64 ? 1 : 0;
+}
+
+// Above so many values per sync a plan draws its rows in a kernel of its own.
+constexpr int64_t kLargeValues = 500000000;
+
+// What one of the plan's syncs moves as a rule: with periods, the components that sync most often.
+int64_t values_per_sync(const gbmuf_plan_s &pl)
+{
+    const int32_t often = pl.periods.empty() ? 1 : *std::min_element(pl.periods.begin(), pl.periods.end());
+    int64_t n = 0;
+    for (int32_t i = 0; i < pl.m; ++i)
+        if (pl.periods[static_cast<size_t>(i)] == often)
+            n += pl.off[static_cast<size_t>(i) + 1] - pl.off[static_cast<size_t>(i)];
+    return pl.K * n;
 }
 
 // Whether the kernel for many workers takes over (where its tile fits).  Measured, old shape against
@@ -248,6 +277,18 @@ bool takes_many(int K, int layout, int what)
 {
     if (what == kBmuf) return K > 64;
     return K > 128 && !(layout == kBlocked && K > 224 && K <= 256);
+}
+
+// Which XCD takes which tiles of a blocked state (tile_of_block).  512 bytes of a row (one tile of 32
+// columns) or 1 KB in one run: 28 workers 4955 / 4813 (gossip-MA 32: 1816 / 1793), 512 workers 13112 / 12278,
+// but 16 workers x 278.6 M 16295 / 16630; 2 KB is the worst (256 workers 5224 / 5907).
+// Rotated: blocks of a row lie 32 KB apart, which is 64 tiles of 32 columns, so without it one XCD sees
+// the same addresses modulo 4 KB in every block; 64 workers 14783 / 14225 (gossip-MA 2660 / 2611).
+void blocked_xcds(int K, int what, LayoutCfg &cfg)
+{
+    const bool one_kb = what == kBmuf ? (K > 24 && K <= 29) || K > 128 : K > 16 && K <= 32;
+    cfg.xcd_columns_log = one_kb ? 6 : 0;
+    cfg.rotate = K > 32 && K <= 64;
 }
 
 // log2 of the largest power of two T with K * T <= the shape's slots.
@@ -290,14 +331,13 @@ void build_tiles(const gbmuf_plan_s &pl, TileSet &ts)
 
 void free_device(gbmuf_plan_s &pl)
 {
-    if (pl.d_cand) (void)hipFree(pl.d_cand);
     if (pl.d_comp) (void)hipFree(pl.d_comp);
     if (pl.d_nbr) (void)hipFree(pl.d_nbr);
     for (TileSet &ts : pl.sets) {
         if (ts.d_tiles) (void)hipFree(ts.d_tiles);
         ts.d_tiles = nullptr;
     }
-    pl.d_cand = nullptr; pl.d_comp = nullptr; pl.d_nbr = nullptr;
+    pl.d_comp = nullptr; pl.d_nbr = nullptr;
 }
 
 template <class T>
@@ -336,22 +376,30 @@ int make_device_state(gbmuf_plan_s &pl, int32_t sampling)
     int rc = GBMUF_OK;
     for (int l = 0; l < 4 && rc == GBMUF_OK; ++l) {
         bool c = false;
-        rc = prepare_kernels(pl.cfg[l / 2][l % 2].variant, pl.K, pl.q, pl.C, pl.mixed_q, &c);
+        rc = prepare_kernels(pl.cfg[l / 2][l % 2].variant, pl.K, pl.q, pl.mixed_q, pl.C, &c);
         can = l == 0 ? c : (can && c);
     }
     if (rc != GBMUF_OK) return rc;
-    // Drawing the rows inside every workgroup saves the sampler launch (about 2 us of a 8 us
-    // sync on a 200k-parameter model) but costs about 2 % once there are millions of tiles:
-    // by default only launch-bound plans do it.
+    // Drawing the rows inside every workgroup saves the sampler launch, about 5 us of a sync, and costs
+    // about 1 % of it where the rows are drawn in registers.  Measured, in the kernel / separate, us:
+    // 16 workers x 6.2 M 395 / 402, 20.6 M 1365 / 1373, 35.0 M 2045 / 2032, 278.6 M 16715 / 16295; 8 x 20.6 M
+    // 639 / 643; 64 x 5.4 M 1311 / 1315, 9.3 M 2274 / 2277.  Gossip-MA moves a third of the bytes: 4 x 84.8 M
+    // 422 / 409, 18 x 4.3 M 157 / 164.  Rows of more than 7 neighbours are drawn through LDS, which only
+    // launch-bound plans do.
     if (sampling == GBMUF_SAMPLING_IN_KERNEL) {
         if (!can) return GBMUF_EUNSUPPORTED;
-        pl.in_kernel_sampling = true;
+        pl.in_kernel_sampling = pl.in_kernel_sampling_ma = true;
     } else if (sampling == GBMUF_SAMPLING_SEPARATE) {
-        pl.in_kernel_sampling = false;
+        pl.in_kernel_sampling = pl.in_kernel_sampling_ma = false;
     } else {
-        pl.in_kernel_sampling = can && pl.sets[pl.cfg[kRows][kBmuf].set].tiles.size() <= 8192;
+        const int64_t values = values_per_sync(pl);
+        if (draws_in_registers(pl.q)) {
+            pl.in_kernel_sampling = values <= kLargeValues;
+            pl.in_kernel_sampling_ma = values <= 130000000;
+        } else {
+            pl.in_kernel_sampling = pl.in_kernel_sampling_ma = can && pl.sets[pl.cfg[kRows][kBmuf].set].tiles.size() <= 8192;
+        }
     }
-    if ((rc = upload(&pl.d_cand, pl.cand)) != GBMUF_OK) return rc;
     if ((rc = upload(&pl.d_comp, pl.comp)) != GBMUF_OK) return rc;
     for (int s = 0; s < pl.n_sets; ++s)
         if ((rc = upload(&pl.sets[s].d_tiles, pl.sets[s].tiles)) != GBMUF_OK) return rc;
@@ -444,25 +492,19 @@ gbmuf_state_t rows_state(float *theta, float *omega, float *delta, int64_t strid
     return st;
 }
 
-// log2 of how many consecutive tiles one XCD takes (tile_of_block), from how many bytes of a worker
-// row one XCD should own.  Measured on MI355X with the fused kernel:
-//   Rows or blocks that do not start on 128-byte lines: neighbouring tiles share a line, and unless
-//     both are taken by one XCD its L2 cannot join the halves: every shared line is fetched twice and
-//     written in two pieces.  With 32 KB per XCD one line in 256 is shared.  16 workers x 35.0 M in
-//     plain tensors: 3944 GB/s at 512 B, 4984 at 4 KB, 5073 at 16 KB (aligned rows: 5161); 64 workers
-//     x 26.9 M: 3880 at 1 KB, 4405 at 4 KB, 5163 at 32 KB.
-//   Lines of one tile only: tile by tile (padded rows: 1 to 32 KB per XCD are within 2 %), but 1 KB for
-//     more than 128 workers (blocked, 256 x 5.2 M: 512 B 5279 us, 1 KB 5224, 2 KB 5907; 512 workers, whose
-//     tiles have 256 B: 13112, 512 B 12924, 1 KB 12278).
-int32_t xcd_granule(const LayoutCfg &cfg, const Placement &at, const gbmuf_state_t *st, int32_t mode)
+// log2 of how many consecutive tiles one XCD takes (tile_of_block).  In rows or blocks that do not start
+// on 128-byte lines neighbouring tiles share a line, and unless both are taken by one XCD its L2 cannot
+// join the halves: every shared line is fetched twice and written in two pieces.  With 32 KB per XCD one
+// line in 256 is shared.  16 workers x 35.0 M in plain tensors: 3944 GB/s at 512 B, 4984 at 4 KB, 5073 at
+// 16 KB (aligned rows: 5161); 64 workers x 26.9 M: 3880 at 1 KB, 4405 at 4 KB, 5163 at 32 KB.
+int32_t xcd_run(const LayoutCfg &cfg, const Placement &at, const gbmuf_state_t *st, int32_t mode)
 {
     uintptr_t low = reinterpret_cast<uintptr_t>(st->theta) | (static_cast<uintptr_t>(at.stride | at.block_extra) << 2);
     if (mode != GBMUF_MODE_GOSSIP_MA)
         low |= reinterpret_cast<uintptr_t>(st->omega) | reinterpret_cast<uintptr_t>(st->delta);
-    const int32_t log_columns = (low & 127u) ? 11 : cfg.variant.depth == kVeryMany.depth ? 6 : 0;   // of 16 bytes
-    return log_columns > cfg.logT ? log_columns - cfg.logT : 0;
+    const int32_t columns_log = (low & 127u) ? 11 : cfg.xcd_columns_log;
+    return std::max(0, columns_log - cfg.logT);
 }
-
 
 // The dynamic LDS a workgroup asks for so that at most `workgroups_per_cu` of them fit a CU.
 size_t lds_floor(const gbmuf_plan_s *pl, const LayoutCfg &cfg)
@@ -493,25 +535,28 @@ int enqueue_sync(const gbmuf_plan_s *pl, const int32_t *nbr_dev, const gbmuf_sta
     a.K = pl->K; a.q = pl->q; a.logT = cfg.logT; a.mode = mode;
     a.eta = eta; a.zeta = zeta; a.inv = pl->inv;
     a.flags = pl->flags | ((pl->alternate && (round & 1)) ? kFlagBackwards : 0) | (pl->mixed_q ? kFlagMixedQ : 0) |
-              (check_periods ? kFlagCheckPeriods : 0);
-    a.cand = pl->d_cand;                                    // used only when nbr_dev == nullptr
-    a.C = pl->C;
+              (check_periods ? kFlagCheckPeriods : 0) | (cfg.rotate ? kFlagRotate : 0);
+    a.p = pl->p; a.C = pl->C;                               // used only when nbr_dev == nullptr
     a.key0 = static_cast<uint32_t>(pl->seed); a.key1 = static_cast<uint32_t>(pl->seed >> 32);
     a.round0 = static_cast<uint32_t>(round); a.round1 = static_cast<uint32_t>(round >> 32);
     a.step = round;
-    a.xcd_log = xcd_granule(cfg, at, st, mode);
+    a.xcd_log = xcd_run(cfg, at, st, mode);
     return launch_sync(cfg.variant, a, n_tiles, lds_floor(pl, cfg), stream);
+}
+
+bool draws_itself(const gbmuf_plan_s *pl, int32_t mode)
+{
+    return mode == GBMUF_MODE_GOSSIP_MA ? pl->in_kernel_sampling_ma : pl->in_kernel_sampling;
 }
 
 SampleArgs sample_args(const gbmuf_plan_s *pl, uint64_t round, int32_t *out)
 {
     SampleArgs s{};
-    s.cand = pl->d_cand;
     s.comp = pl->d_comp;
     s.out = out;
     s.first_pair = 0;
     s.pairs = static_cast<int64_t>(pl->m) * pl->K;
-    s.K = pl->K; s.C = pl->C; s.q = pl->q; s.width = pl->q;
+    s.K = pl->K; s.p = pl->p; s.C = pl->C; s.q = pl->q; s.width = pl->q;
     s.mixed = pl->mixed_q ? 1 : 0;
     s.check_periods = 0;
     s.key0 = static_cast<uint32_t>(pl->seed); s.key1 = static_cast<uint32_t>(pl->seed >> 32);
@@ -602,29 +647,32 @@ int gbmuf_plan_create(gbmuf_plan_t **out, const gbmuf_plan_desc_t *desc)
             }
             pl->flags = desc->cache_hints;
             pl->alternate = desc->sweep == GBMUF_SWEEP_AUTO;
+            const int64_t values = values_per_sync(*pl);
             for (int l = 0; l < 4 && rc == GBMUF_OK; ++l) {
                 LayoutCfg &cfg = pl->cfg[l / 2][l % 2];
                 if (desc->tile_threads != 0) {
                     if (!find_variant(desc->tile_threads, desc->tile_slots, &cfg.variant)) rc = GBMUF_EINVAL;
                 } else {
-                    cfg.variant = default_variant(K, l / 2, l % 2);
+                    cfg.variant = default_variant(K, l / 2, l % 2, values > kLargeValues);
                 }
                 if (rc != GBMUF_OK) break;
                 if (K > cfg.variant.threads * cfg.variant.slots) { rc = desc->tile_threads != 0 ? GBMUF_EINVAL : GBMUF_EUNSUPPORTED; break; }
-                cfg.logT = widest_tile(cfg.variant, K);
-                if (l / 2 == kBlocked) pl->min_block_logT = std::max(pl->min_block_logT, cfg.logT);
-                // Many workers: the wider shapes, where the neighbour rows fit beside their tile.  They
-                // look an element's block up column by column, so a block may be narrower than a tile
-                // and min_block_logT does not grow.
-                if (desc->tile_threads == 0 && takes_many(K, l / 2, l % 2)) {
+                // Blocks may be as narrow as min_block_logT says, narrower than a tile too: the kernel
+                // looks an element's block up column by column (where a thread keeps its column, T <= threads).
+                if (desc->tile_threads != 0) {
+                    pl->min_block_logT = widest_tile(cfg.variant, K);
+                } else {
+                    pl->min_block_logT = widest_tile(Variant{K <= 16 ? 1024 : K <= 64 ? 2048 : 4096, 1, 1}, K);
                     const Variant &v = K <= 128 ? kMany : kVeryMany;
-                    if (sync_lds_bytes(v, K, pl->q, pl->C, can_sample_inline(K, pl->C)) <= kLdsPerWorkgroup) {
+                    // the wider shapes for many workers, where the neighbour rows fit beside their tile
+                    if (takes_many(K, l / 2, l % 2) &&
+                        sync_lds_bytes(v, K, pl->q, pl->mixed_q, pl->C, can_sample_inline(K, pl->C)) <= kLdsPerWorkgroup)
                         cfg.variant = v;
-                        cfg.logT = widest_tile(v, K);
-                    }
+                    if (l / 2 == kBlocked) blocked_xcds(K, l % 2, cfg);
                 }
+                cfg.logT = widest_tile(cfg.variant, K);
                 cfg.workgroups_per_cu = desc->workgroups_per_cu != 0 ? desc->workgroups_per_cu
-                                                                     : default_workgroups_per_cu(K, l / 2, l % 2);
+                                                                     : default_workgroups_per_cu(K, l / 2, l % 2, cfg.logT, values);
             }
             if (rc == GBMUF_OK) {
                 // one tile list per distinct tile width
@@ -751,7 +799,7 @@ int gbmuf_sync_state(const gbmuf_plan_t *plan, const gbmuf_state_t *state, float
     int rc = check_sync(plan, state, nesterov, &at, &layout);
     if (rc != GBMUF_OK) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (plan->in_kernel_sampling) return enqueue_sync(plan, nullptr, state, at, layout, eta, zeta, nesterov, s, round);
+    if (draws_itself(plan, nesterov)) return enqueue_sync(plan, nullptr, state, at, layout, eta, zeta, nesterov, s, round);
     rc = launch_sampler(sample_args(plan, round, plan->d_nbr), s);
     if (rc != GBMUF_OK) return rc;
     return enqueue_sync(plan, plan->d_nbr, state, at, layout, eta, zeta, nesterov, s, round);
@@ -817,7 +865,7 @@ int gbmuf_sync_step_state(const gbmuf_plan_t *plan, const gbmuf_state_t *state, 
     if (runs == 0) return GBMUF_OK;
     const bool one_run = runs == 1;
     const int32_t *nbr = nullptr;                           // nullptr: workgroups draw their own rows
-    if (!plan->in_kernel_sampling) {
+    if (!draws_itself(plan, nesterov)) {
         // only the components that are due are sampled: the launch spans first..last of them and
         // the threads of components in between that are not due leave without drawing
         SampleArgs sa = sample_args(plan, step, plan->d_nbr);

@@ -1,0 +1,427 @@
+// gbmuf_sync.hip -- the fused gather-average-momentum kernel of libgbmuf (Algorithm 1, sync branch, of
+// arXiv 1909.09010) in all its shapes.  Compiled once per GBMUF_PART, each with a part of the shapes
+// (they take minutes one after the other).
+//
+// Fused kernel, in one sentence: a workgroup owns a tile of T 16-byte columns of one
+// component for ALL K workers, parks the K x T block of theta in LDS (so every worker's
+// average reads its neighbours from LDS, and all reads of theta happen before any write:
+// the in-place update keeps snapshot semantics), and streams omega and Delta through
+// registers; every state byte is read once and written once.  Where an element lives is a
+// Placement: plain rows, or blocks of 2^logB floats whose same-index blocks of all workers lie
+// together (one offset per tile, since a tile never crosses a block).
+#include "gbmuf_device.h"
+
+#include "../../include/gbmuf.h"
+
+#pragma clang fp contract(off)
+
+namespace gbmuf {
+
+namespace {
+
+// ---------------------------------------------------------------------------------------
+// The block-momentum filter and the restart for one element (Algorithm 1, gossip-BMUF
+// statements): G = avg - theta_{t-H};  Delta' = eta*Delta + zeta*G;  omega' = omega +
+// Delta';  theta' = omega' + eta*Delta'.  theta_{t-H} is omega + eta*Delta in the paper's
+// mode (what the previous restart wrote), omega otherwise.
+// ---------------------------------------------------------------------------------------
+__device__ __forceinline__ void filter(float avg, float om, float de, float eta, float zeta, int mode,
+                                       float &th_out, float &om_out, float &de_out)
+{
+    const float t = eta * de;
+    const float start = (mode == GBMUF_MODE_PAPER) ? om + t : om;
+    const float G = avg - start;
+    const float zg = zeta * G;
+    const float dn = t + zg;
+    const float on = om + dn;
+    float tn = on;
+    if (mode != GBMUF_MODE_NO_RESTART) {
+        const float r = eta * dn;
+        tn = on + r;
+    }
+    th_out = tn; om_out = on; de_out = dn;
+}
+
+// Which tile this workgroup takes.  Workgroups are dealt round-robin to the 8 XCDs (blockIdx mod 8);
+// the list is cut into groups of 8 * 2^xcd_log consecutive tiles, and in every group XCD r takes the
+// r-th run of 2^xcd_log tiles; with the rotate flag the runs move on by one XCD every 8 groups
+// (blocked_xcds and xcd_run on the host say when and why).  With the backwards flag (set on odd rounds unless the plan asked for forward sweeps) the list is walked
+// backwards, so that what the previous sync wrote last is read first, while it may still be in the
+// 256 MB memory-side cache (it is for states of up to a few GB; larger states neither gain nor
+// lose); the XCD of a tile stays the same.  Tiles beyond the last whole group are taken in order.
+__device__ __forceinline__ unsigned tile_of_block(const SyncArgs &a)
+{
+    const unsigned n = gridDim.x, lg = static_cast<unsigned>(a.xcd_log);
+    const unsigned whole = (n >> (3 + lg)) << (3 + lg);           // tiles in whole groups
+    unsigned b = blockIdx.x, i;
+    if (a.flags & kFlagBackwards) {
+        const unsigned rest = n - whole;                          // these come first
+        if (b < rest) return n - 1u - b;
+        i = (whole >> 3) - 1u - ((b - rest) >> 3);
+    } else {
+        if (b >= whole) return b;
+        i = b >> 3;
+    }
+    const unsigned group = i >> lg;
+    const unsigned r = (b + ((a.flags & kFlagRotate) ? group >> 3 : 0u)) & 7u;
+    return (((group << 3) | r) << lg) | (i & ((1u << lg) - 1u));
+}
+
+// ---------------------------------------------------------------------------------------
+// The neighbour rows of a tile's component in LDS: worker w's row holds the q+1 ids whose values it
+// averages, its own among them, ascending.  Kernels are built for these Q1:
+//   1..5         every component draws Q1 - 1 neighbours: sums fully unrolled
+//   kUpTo8       5 to 7 neighbours
+//   kMixed       up to 7 neighbours, a different number per component: a workgroup takes the path of
+//                its component's number at the start (a run-time count costs 2 % on 16 workers)
+//   kAnyQ        any number
+// All but the last keep rows of 4 or 8 uint16, which a thread gets in one read.
+// ---------------------------------------------------------------------------------------
+// Sorts worker w into its q neighbours (v[0..q)) and stores the row.
+template <int Q1>
+__device__ __forceinline__ void put_row(uint16_t *dst, int32_t (&v)[Q1], int w, int q)
+{
+#pragma unroll
+    for (int j = 0; j < Q1 - 1; ++j) v[j] = j < q ? v[j] : 0xFFFF;
+    v[Q1 - 1] = w;
+    sort_few(v);
+    uint32_t word[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int j = 0; j < Q1; ++j) word[j / 2] |= static_cast<uint32_t>(v[j]) << (16 * (j % 2));
+    if (Q1 <= 2) *reinterpret_cast<uint32_t *>(dst) = word[0];
+    else if (Q1 <= 4) *reinterpret_cast<uint2 *>(dst) = make_uint2(word[0], word[1]);
+    else *reinterpret_cast<uint4 *>(dst) = make_uint4(word[0], word[1], word[2], word[3]);
+}
+
+// Worker w's row of the table in memory.  Ids are clamped into [0, K) so that a bad caller table
+// cannot index outside the tile.
+template <int Q1>
+__device__ __forceinline__ void load_row(int32_t (&v)[Q1], const SyncArgs &a, int comp, int w, int q)
+{
+    const int32_t *row = a.nbr + (static_cast<int64_t>(comp) * a.K + w) * a.q;
+#pragma unroll
+    for (int j = 0; j < Q1 - 1; ++j)
+        if (j < q) v[j] = row[j];
+}
+
+template <int Q1>
+__device__ __forceinline__ void clamp_row(int32_t (&v)[Q1], int K)
+{
+#pragma unroll
+    for (int j = 0; j < Q1 - 1; ++j) v[j] = min(max(v[j], 0), K - 1);
+}
+
+struct LdsRow {
+    int32_t *base;
+    __device__ int32_t &operator()(int32_t x) const { return base[x]; }
+};
+
+// The rows of one tile.  begin() is called before the tile's loads are issued, so that the table's
+// loads, which return in order, are not queued behind them; finish() while they are in flight.
+// a.nbr == nullptr: thread w draws for worker w.
+template <int NT, int Q1>
+struct Rows {
+    int32_t v[Q1];
+    __device__ __forceinline__ void begin(const SyncArgs &a, const TileDesc &td)
+    {
+        const int tid = threadIdx.x, q = Q1 == kUpTo8 ? td.q : Q1 - 1;
+        if (a.nbr != nullptr && tid < a.K) load_row<Q1>(v, a, td.comp, tid, q);
+    }
+    __device__ __forceinline__ void finish(const SyncArgs &a, const TileDesc &td, uint16_t *ids)
+    {
+        const int K = a.K, q = Q1 == kUpTo8 ? td.q : Q1 - 1;
+        for (int w = threadIdx.x; w < K; w += NT) {
+            if (a.nbr != nullptr) {
+                if (w >= NT) load_row<Q1>(v, a, td.comp, w, q);
+                clamp_row<Q1>(v, K);
+            } else if constexpr (Q1 > 1) {
+                int32_t picked[Q1 - 1];
+                draw_few<Q1 - 1>(picked, K, a.p, a.C, q, DrawKey{a.key0, a.key1, a.round0, a.round1},
+                                 static_cast<uint32_t>(td.comp), w);
+#pragma unroll
+                for (int j = 0; j < Q1 - 1; ++j) v[j] = picked[j];
+            }
+            put_row<Q1>(ids + w * ids_pitch(Q1, 0), v, w, q);
+        }
+    }
+};
+
+template <int NT>
+struct Rows<NT, kAnyQ> {
+    __device__ __forceinline__ void begin(const SyncArgs &, const TileDesc &) {}
+    __device__ __forceinline__ void finish(const SyncArgs &a, const TileDesc &td, uint16_t *ids)
+    {
+        const int K = a.K, q = td.q, pitch = ids_pitch(kAnyQ, a.q);
+        int32_t *perm = reinterpret_cast<int32_t *>(ids + ids_words(K, pitch));
+        for (int w = threadIdx.x; w < K; w += NT) {
+            uint16_t *dst = ids + w * pitch;
+            if (a.nbr != nullptr) {
+                const int32_t *row = a.nbr + (static_cast<int64_t>(td.comp) * K + w) * a.q;
+                dst[0] = static_cast<uint16_t>(w);
+                for (int j = 0; j < q; ++j) {
+                    const int v = min(max(row[j], 0), K - 1);
+                    int b = j;
+                    while (b >= 0 && dst[b] > v) { dst[b + 1] = dst[b]; --b; }
+                    dst[b + 1] = static_cast<uint16_t>(v);
+                }
+            } else {
+                int32_t *mine = perm + w * a.C;
+                draw_many(LdsRow{mine}, K, a.p, a.C, q, DrawKey{a.key0, a.key1, a.round0, a.round1},
+                          static_cast<uint32_t>(td.comp), w);
+                int j = 0, o = 0;                           // mine[0..q) ascending; insert w
+                while (j < q && mine[j] < w) dst[o++] = static_cast<uint16_t>(mine[j++]);
+                dst[o++] = static_cast<uint16_t>(w);
+                while (j < q) dst[o++] = static_cast<uint16_t>(mine[j++]);
+            }
+        }
+    }
+};
+
+// ---------------------------------------------------------------------------------------
+// The fused kernel.  A column is 4 consecutive floats, loaded and stored as one 16-byte access
+// wherever the row starts: global memory takes 16-byte accesses at any 4-byte address, and what a
+// misaligned row costs is only the cache lines that two tiles share (xcd_run on the host).
+// Slot s of the tile (s = tid + n*NT) is worker s >> logT, column s & (T-1).
+//
+// Bound by HBM.  Measured on 16 workers x 35.0 M parameters (6.7 GB) in plain [K, P] tensors with an
+// odd P: 2483 us (5406 GB/s); with 4-byte accesses, tiles dealt to the XCDs one by one: 3230 us.
+// ---------------------------------------------------------------------------------------
+// A column of which only the floats in `mk` are this tile's (all four if WHOLE).
+template <bool WHOLE>
+__device__ __forceinline__ v4f load_col(const float *p, unsigned mk, bool streaming)
+{
+    if (WHOLE || mk == 0xFu) return load4(p, streaming);
+    v4f v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+        if (mk & (1u << c)) v[c] = p[c];
+    return v;
+}
+
+template <bool WHOLE>
+__device__ __forceinline__ void store_col(float *p, v4f v, unsigned mk, bool streaming)
+{
+    if (WHOLE || mk == 0xFu) {
+        store4(p, v, streaming);
+        return;
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+        if (mk & (1u << c)) p[c] = v[c];
+}
+
+// The average of one column: sum over the worker and its neighbours, ascending worker id, then * 1/(q+1).
+template <int Q1>
+__device__ __forceinline__ v4f average(const v4f *tile, const uint16_t *row, int q1, int logT, int col, float inv)
+{
+    v4f s;
+    if constexpr (Q1 != kAnyQ) {
+        uint32_t word[4];
+        if (Q1 <= 2) {
+            word[0] = *reinterpret_cast<const uint32_t *>(row);
+        } else if (Q1 <= 4) {
+            const uint2 v = *reinterpret_cast<const uint2 *>(row);
+            word[0] = v.x; word[1] = v.y;
+        } else {
+            const uint4 v = *reinterpret_cast<const uint4 *>(row);
+            word[0] = v.x; word[1] = v.y; word[2] = v.z; word[3] = v.w;
+        }
+#pragma unroll
+        for (int j = 0; j < Q1; ++j) {
+            if (Q1 == kUpTo8 && j >= q1) break;
+            const uint32_t id = (j & 1) ? word[j / 2] >> 16 : word[j / 2] & 0xFFFFu;
+            const v4f x = tile[(id << logT) + col];
+            s = j == 0 ? x : s + x;
+        }
+    } else {
+        s = tile[(static_cast<int>(row[0]) << logT) + col];
+        for (int j = 1; j < q1; ++j) s = s + tile[(static_cast<int>(row[j]) << logT) + col];
+    }
+    return s * inv;
+}
+
+// One tile.  Slot n of a thread is worker w0 + wn(n), column col0 + cn(n) with the same wn, cn for all
+// threads: with T <= NT a thread keeps its column and visits every (NT/T)-th worker, with T > NT (few
+// workers in a wide shape) slot n is one stretch of one worker's row.
+// WHOLE: all T columns belong to the tile entirely; else a component edge cuts it.
+// DEPTH == SLOTS: omega and Delta are loaded together with theta; DEPTH < SLOTS (T <= NT then): see
+// sync_kernel below.
+template <int NT, int SLOTS, int DEPTH, int Q1, bool WHOLE>
+__device__ __forceinline__ void do_tile(const SyncArgs &a, const TileDesc &td, v4f *tile, uint16_t *ids)
+{
+    const int tid = threadIdx.x, K = a.K, logT = a.logT, T = 1 << logT, mode = a.mode;
+    const float inv = (a.flags & kFlagMixedQ) ? a.comp[td.comp].inv : a.inv;
+    const bool slots_too = mode != GBMUF_MODE_GOSSIP_MA;
+    const bool nt_load = (a.flags & kFlagStreamLoads) != 0, nt_store = (a.flags & kFlagStreamStores) != 0;
+    const int col0 = tid & (T - 1), w0 = tid >> logT;
+    auto wn = [&](int n) { return (n * NT) >> logT; };
+    auto cn = [&](int n) { return (n * NT) & (T - 1); };
+    const int64_t e0 = ((td.lo >> 2) + col0) << 2;
+    const int64_t at0 = static_cast<int64_t>(w0) * a.at.stride + placed(a.at, e0);
+    auto at = [&](int n) { return at0 + static_cast<int64_t>(wn(n)) * a.at.stride + 4 * cn(n); };
+    // which of the 4 floats of slot n are this tile's (0: none, or no such worker)
+    auto mask = [&](int n) {
+        unsigned mk = 0;
+        if (w0 + wn(n) < K) {
+            if (WHOLE) return 0xFu;
+            const int64_t e = e0 + 4 * cn(n);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) mk |= (e + c >= td.lo && e + c < td.lo + td.n) ? (1u << c) : 0u;
+        }
+        return mk;
+    };
+
+    Rows<NT, Q1> rows;
+    rows.begin(a, td);
+    v4f th[SLOTS], om[DEPTH], de[DEPTH];
+    if constexpr (DEPTH < SLOTS) {
+#pragma unroll
+        for (int n = 0; n < SLOTS; ++n)
+            if (const unsigned mk = mask(n)) th[n] = load_col<WHOLE>(a.theta + at(n), mk, nt_load);
+    }
+#pragma unroll
+    for (int n = 0; n < DEPTH; ++n) {
+        const unsigned mk = mask(n);
+        if (mk == 0u) continue;
+        if (DEPTH == SLOTS) th[n] = load_col<WHOLE>(a.theta + at(n), mk, nt_load);
+        if (slots_too) {
+            om[n] = load_col<WHOLE>(a.omega + at(n), mk, nt_load);
+            de[n] = load_col<WHOLE>(a.delta + at(n), mk, nt_load);
+        }
+    }
+    rows.finish(a, td, ids);
+#pragma unroll
+    for (int n = 0; n < SLOTS; ++n)
+        if (mask(n)) tile[tid + n * NT] = th[n];
+    __syncthreads();
+
+    const int pitch = ids_pitch(Q1, a.q);
+#pragma unroll
+    for (int n = 0; n < SLOTS; ++n) {
+        const unsigned mk = mask(n);
+        if (mk == 0u) continue;
+        const v4f o = om[n % DEPTH], d = de[n % DEPTH];
+        if (n + DEPTH < SLOTS && slots_too) {
+            if (const unsigned next = mask(n + DEPTH)) {
+                om[n % DEPTH] = load_col<WHOLE>(a.omega + at(n + DEPTH), next, nt_load);
+                de[n % DEPTH] = load_col<WHOLE>(a.delta + at(n + DEPTH), next, nt_load);
+            }
+        }
+        v4f tn = average<Q1>(tile, ids + (w0 + wn(n)) * pitch, td.q + 1, logT, col0 + cn(n), inv);
+        if (slots_too) {
+            const v4f avg = tn;
+            v4f on, dn;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                float t1, o1, d1;
+                filter(avg[c], o[c], d[c], a.eta, a.zeta, mode, t1, o1, d1);
+                tn[c] = t1; on[c] = o1; dn[c] = d1;
+            }
+            store_col<WHOLE>(a.omega + at(n), on, mk, nt_store);
+            store_col<WHOLE>(a.delta + at(n), dn, mk, nt_store);
+        }
+        store_col<WHOLE>(a.theta + at(n), tn, mk, nt_store);
+    }
+}
+
+template <int NT, int SLOTS, int DEPTH, int Q1>
+__device__ __forceinline__ void any_tile(const SyncArgs &a, const TileDesc &td, v4f *tile, uint16_t *ids)
+{
+    if (((td.lo & 3) | (td.n & ~(4 << a.logT))) == 0)             // n is T columns exactly
+        do_tile<NT, SLOTS, DEPTH, Q1, true>(a, td, tile, ids);
+    else
+        do_tile<NT, SLOTS, DEPTH, Q1, false>(a, td, tile, ids);
+}
+
+// DEPTH < SLOTS is for many workers.  A tile holds theta of all K workers, so its width is what K
+// leaves of the 160 KB LDS; narrow tiles touch each row in pieces of 256 bytes and less, which HBM
+// answers at two thirds of the rate of 512-byte pieces.  So the tile takes up to 128 KB, all of theta is
+// loaded and parked first, and omega and Delta, whose values no other worker needs, are not held for
+// the whole tile but streamed through DEPTH slots of registers.  256 workers x 6.2 M (19 GB, blocked),
+// T = 32: 6290 us (6040 GB/s); T = 16, all that the registers hold of three arrays: 7576 us.
+template <int NT, int SLOTS, int DEPTH, int Q1>
+__global__ __launch_bounds__(NT) void sync_kernel(SyncArgs a)
+{
+    extern __shared__ float4 lds4[];
+    v4f *tile = reinterpret_cast<v4f *>(lds4);
+    uint16_t *ids = reinterpret_cast<uint16_t *>(lds4 + NT * SLOTS);
+    const TileDesc td = a.tiles[tile_of_block(a)];
+    if ((a.flags & kFlagCheckPeriods) && a.step % static_cast<uint64_t>(a.comp[td.comp].period) != 0)
+        return;                                                   // not due: the whole workgroup leaves
+    if constexpr (Q1 == kMixed) {
+        switch (td.q) {
+            case 0: return any_tile<NT, SLOTS, DEPTH, 1>(a, td, tile, ids);
+            case 1: return any_tile<NT, SLOTS, DEPTH, 2>(a, td, tile, ids);
+            case 2: return any_tile<NT, SLOTS, DEPTH, 3>(a, td, tile, ids);
+            case 3: return any_tile<NT, SLOTS, DEPTH, 4>(a, td, tile, ids);
+            case 4: return any_tile<NT, SLOTS, DEPTH, 5>(a, td, tile, ids);
+            default: return any_tile<NT, SLOTS, DEPTH, kUpTo8>(a, td, tile, ids);
+        }
+    } else {
+        any_tile<NT, SLOTS, DEPTH, Q1>(a, td, tile, ids);
+    }
+}
+
+template <int NT, int SLOTS, int DEPTH>
+KernelFn pick_q(int Q1)
+{
+    switch (Q1) {
+        case 1: return sync_kernel<NT, SLOTS, DEPTH, 1>;
+        case 2: return sync_kernel<NT, SLOTS, DEPTH, 2>;
+        case 3: return sync_kernel<NT, SLOTS, DEPTH, 3>;
+        case 4: return sync_kernel<NT, SLOTS, DEPTH, 4>;
+        case 5: return sync_kernel<NT, SLOTS, DEPTH, 5>;
+        case kUpTo8: return sync_kernel<NT, SLOTS, DEPTH, kUpTo8>;
+        case kMixed: return sync_kernel<NT, SLOTS, DEPTH, kMixed>;
+        default: return sync_kernel<NT, SLOTS, DEPTH, kAnyQ>;
+    }
+}
+
+}  // namespace
+
+#define GBMUF_CASE(NT, SL, D) \
+    if (v.threads == NT && v.slots == SL && v.depth == D) return pick_q<NT, SL, D>(kernel_q1(q, mixed));
+
+#if GBMUF_PART == 0
+KernelFn pick_kernel_0(const Variant &v, int q, bool mixed)
+{
+    GBMUF_CASE(256, 16, 16)
+    GBMUF_CASE(256, 2, 2)
+    GBMUF_CASE(256, 1, 1)
+    return nullptr;
+}
+#elif GBMUF_PART == 1
+KernelFn pick_kernel_1(const Variant &v, int q, bool mixed)
+{
+    GBMUF_CASE(512, 16, 4)
+    GBMUF_CASE(512, 1, 1)
+    GBMUF_CASE(512, 2, 2)
+    return nullptr;
+}
+#elif GBMUF_PART == 2
+KernelFn pick_kernel_2(const Variant &v, int q, bool mixed)
+{
+    GBMUF_CASE(256, 8, 8)
+    GBMUF_CASE(256, 4, 4)
+    GBMUF_CASE(1024, 1, 1)
+    GBMUF_CASE(1024, 2, 1)
+    return nullptr;
+}
+#elif GBMUF_PART == 3
+KernelFn pick_kernel_3(const Variant &v, int q, bool mixed)
+{
+    GBMUF_CASE(512, 8, 8)
+    GBMUF_CASE(1024, 2, 2)
+    GBMUF_CASE(512, 4, 4)
+    return nullptr;
+}
+#elif GBMUF_PART == 4
+KernelFn pick_kernel_4(const Variant &v, int q, bool mixed)
+{
+    GBMUF_CASE(1024, 4, 4)
+    GBMUF_CASE(1024, 4, 2)
+    return nullptr;
+}
+#endif
+
+}  // namespace gbmuf
