@@ -134,8 +134,14 @@ int hip_failed(const char *what, hipError_t err, int status);
 
 // gbmuf_kernels.hip
 int launch_sampler(const SampleArgs &a, hipStream_t stream);
+struct AverageShape {
+    int rows_in_flight;      // 16-byte loads a thread keeps in flight: 4, 8 or 16
+    size_t lds_floor;        // bounds the resident one-wave workgroups per compute unit like in launch_sync
+    int xcd_log;             // log2 of the consecutive workgroups that one XCD takes
+    bool rotate;
+};
 int launch_final_average(const float *theta, const Placement &at, int K, int64_t P, float inv, float *out,
-                         int rows_in_flight, size_t lds_floor, hipStream_t stream);
+                         const AverageShape &shape, hipStream_t stream);
 int launch_state_copy(const CopyArgs &c, int arrays, hipStream_t stream);
 int launch_copy_probe(float *dst, const float *src, int64_t n_floats, int flags, int blocks, hipStream_t stream);
 int launch_sync(const Variant &v, const SyncArgs &a, int64_t n_tiles, size_t lds_floor, hipStream_t stream);

@@ -54,27 +54,41 @@ __global__ void sample_kernel(SampleArgs a)
 
 // ---------------------------------------------------------------------------------------
 // Final model average (Algorithm 1, RETURN): out[e] = fl(1/K) * (theta[0][e] + theta[1][e] + ...),
-// summed in ascending worker id.  One thread per 16-byte column; 4(K+1) bytes per parameter.
+// summed in ascending worker id.  One thread per 16-byte column, one wave per workgroup; rows may start
+// at any 4-byte address; 4(K+1) bytes per parameter.
+//
+// Bound by HBM reads: what counts is that 32-48 KB per CU are in flight and no more (`bound` on the
+// host), and which XCD reads what.  64 workers x 57.8 M, blocked: 8 rows a time, four waves per CU, XCDs
+// rotated 2357 us (6373 GB/s); 4 rows, eight waves 2454; 8 rows, no bound 2597.  8 x 100 M, blocked: 8 rows, six
+// waves 560, four waves 653, no bound 641.  16 x 35.0 M in plain tensors (odd P): 408, one float per thread
+// FA_PLAIN_BEFORE.
 // ---------------------------------------------------------------------------------------
 template <int B>
-__global__ __launch_bounds__(256) void final_average_vec4_kernel(const float *theta, Placement at, int K,
-                                                                 int64_t P, float inv, float *out)
+__global__ __launch_bounds__(64) void final_average_kernel(const float *theta, Placement at, int K, int64_t P,
+                                                           float inv, float *out, int xcd_log, int rotate)
 {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+    // as in the fused kernel, XCD r takes the r-th run of 2^xcd_log workgroups in every group of 8 runs
+    const unsigned lg = static_cast<unsigned>(xcd_log), whole = (gridDim.x >> (3 + lg)) << (3 + lg);
+    unsigned b = blockIdx.x;
+    if (b < whole) {
+        const unsigned i = b >> 3, group = i >> lg, r = (b + (rotate ? group >> 3 : 0u)) & 7u;
+        b = (((group << 3) | r) << lg) | (i & ((1u << lg) - 1u));
+    }
+    const int64_t i = static_cast<int64_t>(b) * 64 + threadIdx.x;
     const int64_t n4 = P >> 2;
     if (i < n4) {
         const float *col = theta + placed(at, i << 2);
-        v4f s = *reinterpret_cast<const v4f *>(col);
+        v4f s = load4(col, false);
         for (int k0 = 1; k0 < K; k0 += B) {                // B rows in flight, then added in ascending order
             v4f v[B];
 #pragma unroll
             for (int j = 0; j < B; ++j)
-                if (k0 + j < K) v[j] = *reinterpret_cast<const v4f *>(col + static_cast<int64_t>(k0 + j) * at.stride);
+                if (k0 + j < K) v[j] = load4(col + static_cast<int64_t>(k0 + j) * at.stride, false);
 #pragma unroll
             for (int j = 0; j < B; ++j)
                 if (k0 + j < K) s = s + v[j];
         }
-        *reinterpret_cast<v4f *>(out + (i << 2)) = s * inv;
+        store4(out + (i << 2), s * inv, false);
     } else if (i == n4) {                                  // the last P % 4 elements
         for (int64_t e = n4 << 2; e < P; ++e) {
             const float *col = theta + placed(at, e);
@@ -83,18 +97,6 @@ __global__ __launch_bounds__(256) void final_average_vec4_kernel(const float *th
             out[e] = s * inv;
         }
     }
-}
-
-__global__ __launch_bounds__(256) void final_average_vec1_kernel(const float *theta, Placement at, int K,
-                                                                 int64_t P, float inv, float *out)
-{
-    const int64_t e = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (e >= P) return;
-    const float *col = theta + placed(at, e);
-    float s = col[0];
-#pragma unroll 4
-    for (int k = 1; k < K; ++k) s = s + col[static_cast<int64_t>(k) * at.stride];
-    out[e] = s * inv;
 }
 
 // ---------------------------------------------------------------------------------------
@@ -141,34 +143,20 @@ __global__ __launch_bounds__(256) void copy_probe_kernel(v4f *dst, const v4f *sr
 
 }  // namespace
 
-namespace {
-bool placement_vec4(const Placement &at)
-{
-    return at.stride % 4 == 0 && at.block_extra % 4 == 0 && at.logB >= 2;
-}
-}  // namespace
-
-// rows_in_flight: 16-byte loads a thread keeps in flight (4, 8 or 16); lds_floor bounds the
-// resident one-wave workgroups per compute unit like in launch_sync.
 int launch_final_average(const float *theta, const Placement &at, int K, int64_t P, float inv, float *out,
-                         int rows_in_flight, size_t lds_floor, hipStream_t stream)
+                         const AverageShape &shape, hipStream_t stream)
 {
     if (P <= 0) return GBMUF_OK;
-    if (lds_floor > 60 * 1024) lds_floor = 60 * 1024;      // stays below what needs a raised limit
-    const bool vec4 = ((reinterpret_cast<uintptr_t>(theta) | reinterpret_cast<uintptr_t>(out)) & 15u) == 0 &&
-                      placement_vec4(at);
-    const int64_t threads = vec4 ? (P >> 2) + 1 : P;
-    const int bs = vec4 ? 64 : 256;                        // one wave per workgroup measured fastest (16-byte path)
-    const int64_t blocks = (threads + bs - 1) / bs;
+    size_t lds_floor = shape.lds_floor < 60 * 1024 ? shape.lds_floor : 60 * 1024;   // stays below what needs a raised limit
+    const int64_t blocks = ((P >> 2) + 1 + 63) / 64;
     if (blocks > 0x7fffffffLL) return GBMUF_EUNSUPPORTED;
     Placement pl = at;
-    void *argv[] = {&theta, &pl, &K, &P, &inv, &out};
-    const void *fn = !vec4 ? reinterpret_cast<const void *>(final_average_vec1_kernel)
-                     : rows_in_flight <= 4 ? reinterpret_cast<const void *>(final_average_vec4_kernel<4>)
-                     : rows_in_flight <= 8 ? reinterpret_cast<const void *>(final_average_vec4_kernel<8>)
-                                           : reinterpret_cast<const void *>(final_average_vec4_kernel<16>);
-    const hipError_t err = hipLaunchKernel(fn, dim3(static_cast<unsigned>(blocks)), dim3(bs), argv,
-                                           vec4 ? lds_floor : 0, stream);
+    int xcd_log = shape.xcd_log, rotate = shape.rotate ? 1 : 0;
+    void *argv[] = {&theta, &pl, &K, &P, &inv, &out, &xcd_log, &rotate};
+    const void *fn = shape.rows_in_flight <= 4   ? reinterpret_cast<const void *>(final_average_kernel<4>)
+                     : shape.rows_in_flight <= 8 ? reinterpret_cast<const void *>(final_average_kernel<8>)
+                                                 : reinterpret_cast<const void *>(final_average_kernel<16>);
+    const hipError_t err = hipLaunchKernel(fn, dim3(static_cast<unsigned>(blocks)), dim3(64), argv, lds_floor, stream);
     return err == hipSuccess ? GBMUF_OK : hip_failed("hipLaunchKernel(final average)", err, GBMUF_EDEVICE);
 }
 

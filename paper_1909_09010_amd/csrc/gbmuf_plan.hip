@@ -916,18 +916,25 @@ int gbmuf_final_average_state(const gbmuf_plan_t *plan, const gbmuf_state_t *sta
     int rc = check_state(plan, state, false, &at, &layout);
     if (rc != GBMUF_OK) return rc;
     if ((rc = check_device(plan)) != GBMUF_OK) return rc;
-    // Measured on MI355X: rows: 8 loads per thread, as many one-wave workgroups as fit.  Blocked:
-    // the read stream is one address range, and 32-64 KB in flight per CU is the optimum
-    // (K <= 32: 16 loads x 4 waves; larger K: 4 loads x 8 waves), worth 3-8 points.
-    int rows_in_flight = 8;
-    size_t floor_bytes = 0;
-    if (layout == kBlocked && plan->lds_per_cu > 0) {
-        const int waves = plan->K <= 32 ? 4 : 8;
-        rows_in_flight = plan->K <= 32 ? 16 : 4;
-        floor_bytes = static_cast<size_t>(plan->lds_per_cu / waves - 2048);
+    // Measured on MI355X, us (waves: resident one-wave workgroups per CU):
+    //   blocked, 48 KB in flight per CU up to 32 workers: 8 x 100 M, 16 loads (8 used) x 6 waves 560, x 4 653;
+    //     16 x 119.2 M, 16 x 3, 4 KB of a row per XCD 1284, x 4 tile by tile 1316; 32 KB above: see the kernel.
+    //   rows: 16 x 35.0 M plain, 4 x 8 waves 408, 8 x unbounded 440; 64 x 35.0 M padded, 8 x 4 waves, 4 KB per
+    //     XCD 1565, 8 x unbounded 1688.
+    // Sums of a few MB, which take no longer than their first loads, run unbounded.
+    const int K = plan->K;
+    AverageShape shape{8, 0, 2, false};
+    int waves = 4;
+    if (layout == kBlocked) {
+        if (K <= 32) { shape.rows_in_flight = 16; waves = std::max(3, 48 / K); }
+        else { shape.xcd_log = 0; shape.rotate = true; }
+    } else if (K <= 32) {
+        shape.rows_in_flight = 4; shape.xcd_log = 1; waves = 8;
     }
-    return launch_final_average(state->theta, at, plan->K, plan->P, 1.0f / static_cast<float>(plan->K), out_dev,
-                                rows_in_flight, floor_bytes, static_cast<hipStream_t>(stream));
+    if (plan->lds_per_cu > 0 && waves < 32 && K * plan->P > 4000000)
+        shape.lds_floor = static_cast<size_t>(std::max(0, plan->lds_per_cu / waves - 2048));
+    return launch_final_average(state->theta, at, K, plan->P, 1.0f / static_cast<float>(K), out_dev, shape,
+                                static_cast<hipStream_t>(stream));
 }
 
 int gbmuf_final_average(const gbmuf_plan_t *plan, const float *replicas, int64_t worker_stride, float *out_dev,

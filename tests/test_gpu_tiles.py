@@ -134,3 +134,57 @@ def test_many_workers(K, q, mode):
     for a in range(3):
         assert np.array_equal(view[:, a].permute(1, 0, 2).reshape(K, -1).cpu().numpy(), host[a])
     pl.destroy()
+
+
+# one workgroup is 64 columns of 4 floats; groups of 8, 16 or 32 workgroups are dealt to the XCDs, the last P % 4 floats
+# go to one thread; more than 4 M values are bounded differently
+@pytest.mark.parametrize("K", [1, 2, 5, 16, 17, 32, 33, 64, 130])
+@pytest.mark.parametrize("P", [1, 4, 255, 256, 2048 * 4 + 3, 4 * 64 * 33 - 1, 262146])
+def test_final_average_at_its_edges(K, P):
+    _need_gpu()
+    pl = B.Plan([0, P], K, 0, 0, seed=0)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(P)
+    stride = P + (1 if P % 2 == 0 else 2)
+    flat = torch.randn(K * stride + 3, generator=g, device=DEV)
+    rows = flat[3:].view(K, stride)
+    want = oracle.final_average(rows.cpu().numpy(), P)
+    out = torch.full((P + 8,), 7.0, device=DEV)
+    pl.final_average(rows, stride, out[1:], None)
+    Bf = 2 * pl.info.min_block_floats
+    blocks = -(-P // Bf)
+    arena = torch.full((blocks, K, Bf), float("nan"), device=DEV)
+    arena.permute(1, 0, 2).copy_(torch.nn.functional.pad(rows[:, :P], (0, blocks * Bf - P)).view(K, blocks, Bf))
+    out2 = torch.full((P + 8,), 7.0, device=DEV)
+    pl.final_average_state(B.make_state(arena, None, None, Bf, Bf, K * Bf), out2[4:], None)
+    torch.cuda.synchronize()
+    assert np.array_equal(out[1:1 + P].cpu().numpy(), want) and np.array_equal(out2[4:4 + P].cpu().numpy(), want)
+    assert bool((out[1 + P:] == 7).all()) and bool((out2[4 + P:] == 7).all()) and float(out[0]) == 7
+    pl.destroy()
+
+
+# Rows drawn in registers (up to 7 neighbours, at the largest degree the ring wraps) and from a table, one number of
+# neighbours for all components and one each: the same bits as the host's and the oracle's draws.
+@pytest.mark.parametrize("K,p,q", [(2, 0, 1), (4, -1, 3), (5, 2, 4), (8, -1, 7), (9, -1, 8), (16, 0, [0, 1, 2, 3, 4, 5, 6]), (12, 5, [4, 2]),
+                                   (40, 6, [7, 0, 7]), (300, -1, 7), (300, 4, [8, 1])])
+@pytest.mark.parametrize("sampling", [B.SAMPLING_AUTO, B.SAMPLING_SEPARATE])
+def test_draws_in_registers(K, p, q, sampling):
+    _need_gpu()
+    m = 7 if np.ndim(q) == 0 else len(q)
+    off = np.concatenate([[0], np.cumsum([1000 + 37 * i for i in range(m)])]).astype(np.int64)
+    P, seed = int(off[-1]), 2**63 + 11
+    pl = B.Plan(off, K, q, p, seed=seed, sampling=sampling)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(K)
+    dev = [torch.randn((K, P), generator=g, device=DEV) * 0.05 for _ in range(3)]
+    host = [d.cpu().numpy().copy() for d in dev]
+    out = torch.zeros((m, K, pl.info.q), dtype=torch.int32, device=DEV)
+    for rnd in (0, 1, 2**33 + 7):
+        pl.sync(*dev, P, 0.9, 1.0, 1, rnd, None)
+        oracle.sync(off, K, pl.info.p, q, seed, rnd, *host, np.float32(0.9), np.float32(1.0), 1)
+        pl.neighbours_device(rnd, out, None)
+        torch.cuda.synchronize()
+        assert np.array_equal(out.cpu().numpy(), pl.neighbours_host(rnd))
+    for d, h in zip(dev, host):
+        assert np.array_equal(d.cpu().numpy(), h)
+    pl.destroy()
