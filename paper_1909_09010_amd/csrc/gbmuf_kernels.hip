@@ -57,11 +57,11 @@ __global__ void sample_kernel(SampleArgs a)
 // summed in ascending worker id.  One thread per 16-byte column, one wave per workgroup; rows may start
 // at any 4-byte address; 4(K+1) bytes per parameter.
 //
-// Bound by HBM reads: what counts is that 32-48 KB per CU are in flight and no more (`bound` on the
-// host), and which XCD reads what.  64 workers x 57.8 M, blocked: 8 rows a time, four waves per CU, XCDs
+// Bound by HBM reads: what counts is that 32-48 KB per CU are in flight and no more (the host
+// sets the bound), and which XCD reads what.  64 workers x 57.8 M, blocked: 8 rows a time, four waves per CU, XCDs
 // rotated 2357 us (6373 GB/s); 4 rows, eight waves 2454; 8 rows, no bound 2597.  8 x 100 M, blocked: 8 rows, six
-// waves 560, four waves 653, no bound 641.  16 x 35.0 M in plain tensors (odd P): 408, one float per thread
-// FA_PLAIN_BEFORE.
+// waves 560, four waves 653, no bound 641.  16 x 35.0 M in plain tensors (odd P): 420, one float per thread 431;
+// 8 x 35.0 M: 219, 243.
 // ---------------------------------------------------------------------------------------
 template <int B>
 __global__ __launch_bounds__(64) void final_average_kernel(const float *theta, Placement at, int K, int64_t P,

@@ -305,6 +305,12 @@ void build_tiles(const gbmuf_plan_s &pl, TileSet &ts)
     const int64_t T = static_cast<int64_t>(1) << ts.logT;
     ts.tiles.clear();
     ts.tile_start.assign(static_cast<size_t>(pl.m) + 1, 0);
+    int64_t count = 0;                                     // a list of millions is not grown step by step
+    for (int32_t i = 0; i < pl.m; ++i) {
+        const int64_t a = pl.off[static_cast<size_t>(i)], b = pl.off[static_cast<size_t>(i) + 1];
+        if (a < b) count += (((b + 3) >> 2) + T - 1) / T - (a >> 2) / T;
+    }
+    ts.tiles.reserve(static_cast<size_t>(count));
     for (int32_t i = 0; i < pl.m; ++i) {
         const int64_t a = pl.off[static_cast<size_t>(i)], b = pl.off[static_cast<size_t>(i) + 1];
         ts.tile_start[static_cast<size_t>(i)] = static_cast<int64_t>(ts.tiles.size());
