@@ -261,7 +261,7 @@ def main() -> int:
         "finite": g["finite"],
         "roofline": {"bound": "hbm", "achieved": head["kernel_GBps"], "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                      "frac": head["kernel_frac"], "traffic": traffic, "traffic_source": traffic_src,
-                     "kernel": "sync_vec4_kernel", "kernel_ms": head["kernel_ms"], "algorithmic_bytes": algo_bytes,
+                     "kernel": "sync_kernel", "kernel_ms": head["kernel_ms"], "algorithmic_bytes": algo_bytes,
                      "timing": "mean over the timed syncs, from events on the launch stream at the boundaries "
                                "between them (the few-microsecond sampler launch of a sync is inside)"},
     }

@@ -104,11 +104,13 @@ __global__ __launch_bounds__(64) void final_average_kernel(const float *theta, P
 // per thread, one load and one store in flight each: more of either per thread is slower here (5.6
 // against 6.2 TB/s on a plain copy).  The rows are cut into pieces of 256 columns (4 KB); the pieces
 // are walked in runs of 2^run_log pieces of one worker, then the same run of the next worker, so that
-// the blocked side is one moving stretch of memory.  Columns are counted from the destination row's
+// each side is a few moving stretches of memory.  Columns are counted from the destination row's
 // 128-byte line, so that stores cover whole lines; the loads take any 4-byte address.
-// Bound by HBM.  16 workers x 35.0 M, per array: plain rows (odd stride) to blocked 798 us at
-// run_log 0 (817 worker by worker, 1332 with one float per thread); blocked to plain rows 787 us at
-// run_log 5 (854 worker by worker, 790 with columns counted from the row start).
+// Bound by HBM.  16 workers x 35.0 M, per array: plain rows (odd stride) to blocked 800 us, worker by
+// worker 817, with one float per thread 1332; blocked to plain rows 787, worker by worker 854, with
+// columns counted from the row start 790.  Three arrays, runs of 128 KB / 32 KB / 4 KB: to blocked, 4 workers x
+// 79.3 M 1318 / 1311 / 1375, 64 x 10.1 M 2831 / 3023 / 2993; to plain rows 4 x 79.3 M 1365 / 1411 / 1435, 64 x 10.1 M
+// 3012 / 2910 / 2940 (padded 2750 / 2586 / 2710).
 // ---------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void state_copy_kernel(CopyArgs a)
 {
@@ -164,9 +166,8 @@ int launch_state_copy(const CopyArgs &c, int arrays, hipStream_t stream)
 {
     if (c.P <= 0 || c.K <= 0 || arrays <= 0) return GBMUF_OK;
     CopyArgs args = c;
-    // one moving stretch on the blocked side: runs of one piece when it is written, 32 (128 KB of a
-    // row) when rows are written
-    args.run_log = c.da.logB < 62 ? 0 : 5;
+    // runs of 128 KB of a row, 32 KB when many workers' rows are written
+    args.run_log = c.da.logB == 62 && c.K > 32 ? 3 : 5;
     const int64_t pieces = (c.P + 31 + 1023) / 1024;       // 31: the largest head
     const int64_t runs = (pieces + (static_cast<int64_t>(1) << args.run_log) - 1) >> args.run_log;
     const int64_t blocks = (runs * c.K) << args.run_log;
