@@ -75,7 +75,8 @@ enum {
 
 /* Where the neighbour rows of a sync are drawn (gbmuf_plan_desc_t.sampling). */
 enum {
-    GBMUF_SAMPLING_AUTO = 0,      /* in the fused kernel for small, launch-bound plans, else separate */
+    GBMUF_SAMPLING_AUTO = 0,      /* in the fused kernel up to some 10^8 values per sync (less for
+                                     gossip-MA) and 7 neighbours, and for launch-bound plans; else separate */
     GBMUF_SAMPLING_IN_KERNEL = 1, /* every workgroup draws its component's rows itself (one launch)  */
     GBMUF_SAMPLING_SEPARATE = 2   /* a sampler kernel fills a table first (two launches)            */
 };
@@ -136,7 +137,8 @@ typedef struct gbmuf_info {
     uint64_t seed;
     int32_t mixed_q;        /* 1 if components draw different numbers of neighbours          */
     int32_t has_periods;    /* 1 if sync periods were given                                  */
-    int32_t in_kernel_sampling; /* 1 if gbmuf_sync draws the rows inside the fused kernel    */
+    int32_t in_kernel_sampling; /* 1 if gbmuf_sync draws the rows inside the fused kernel in
+                                   every mode (no neighbour scratch is used then)            */
     int32_t tile_columns_blocked, threads_blocked;   /* the same for blocked state           */
     int32_t workgroups_per_cu_blocked;               /* resident workgroups per CU, blocked  */
     int32_t tile_columns_blocked_ma;  /* tile width of the gossip-MA branch on blocked state  */
@@ -150,7 +152,7 @@ typedef struct gbmuf_info {
  * > C, p < -1, H_i < 1, unknown enum or tile shape), EUNSUPPORTED (K > GBMUF_MAX_K, or the
  * neighbour rows of all workers do not fit on chip beside a tile), ENOMEM, EDEVICE (a GPU is
  * present but a HIP call failed).
- * If a GPU is present the plan allocates its small device tables (candidates, tile lists,
+ * If a GPU is present the plan allocates its small device tables (tile lists,
  * per-component table, neighbour scratch) on the current device; sync calls allocate nothing.
  */
 int gbmuf_plan_create(gbmuf_plan_t **out, const gbmuf_plan_desc_t *desc);

@@ -399,12 +399,9 @@ int make_device_state(gbmuf_plan_s &pl, int32_t sampling)
         pl.in_kernel_sampling = pl.in_kernel_sampling_ma = false;
     } else {
         const int64_t values = values_per_sync(pl);
-        if (draws_in_registers(pl.q)) {
-            pl.in_kernel_sampling = values <= kLargeValues;
-            pl.in_kernel_sampling_ma = values <= 130000000;
-        } else {
-            pl.in_kernel_sampling = pl.in_kernel_sampling_ma = can && pl.sets[pl.cfg[kRows][kBmuf].set].tiles.size() <= 8192;
-        }
+        const bool launch_bound = can && pl.sets[pl.cfg[kRows][kBmuf].set].tiles.size() <= 8192, few = draws_in_registers(pl.q);
+        pl.in_kernel_sampling = launch_bound || (few && values <= kLargeValues);
+        pl.in_kernel_sampling_ma = launch_bound || (few && values <= 130000000);
     }
     if ((rc = upload(&pl.d_comp, pl.comp)) != GBMUF_OK) return rc;
     for (int s = 0; s < pl.n_sets; ++s)
@@ -745,7 +742,7 @@ int gbmuf_plan_info(const gbmuf_plan_t *plan, gbmuf_info_t *info)
     info->seed = plan->seed;
     info->mixed_q = plan->mixed_q ? 1 : 0;
     info->has_periods = plan->has_periods ? 1 : 0;
-    info->in_kernel_sampling = plan->in_kernel_sampling ? 1 : 0;
+    info->in_kernel_sampling = plan->in_kernel_sampling && plan->in_kernel_sampling_ma ? 1 : 0;
     info->tile_columns_blocked = 1 << plan->cfg[kBlocked][kBmuf].logT;
     info->threads_blocked = plan->cfg[kBlocked][kBmuf].variant.threads;
     info->workgroups_per_cu_blocked = plan->cfg[kBlocked][kBmuf].workgroups_per_cu;
