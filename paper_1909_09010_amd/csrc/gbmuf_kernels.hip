@@ -1,6 +1,6 @@
-// gbmuf_kernels.hip -- gfx950 kernels of libgbmuf: the neighbour sampler and the fused
-// gather-average-momentum kernel (Algorithm 1, sync branch, of arXiv 1909.09010).
-//
+// gbmuf_kernels.hip -- gfx950 kernels of libgbmuf besides the fused one (gbmuf_sync.hip): the neighbour
+// sampler, the final model average and the placement change of Algorithm 1 (arXiv 1909.09010); and the
+// launches of all of them.
 #include "gbmuf_device.h"
 
 #include "../../include/gbmuf.h"

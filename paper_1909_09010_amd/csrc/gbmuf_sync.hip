@@ -8,7 +8,7 @@
 // the in-place update keeps snapshot semantics), and streams omega and Delta through
 // registers; every state byte is read once and written once.  Where an element lives is a
 // Placement: plain rows, or blocks of 2^logB floats whose same-index blocks of all workers lie
-// together (one offset per tile, since a tile never crosses a block).
+// together (a thread looks the block of its column up once).
 #include "gbmuf_device.h"
 
 #include "../../include/gbmuf.h"
@@ -45,10 +45,11 @@ __device__ __forceinline__ void filter(float avg, float om, float de, float eta,
 // Which tile this workgroup takes.  Workgroups are dealt round-robin to the 8 XCDs (blockIdx mod 8);
 // the list is cut into groups of 8 * 2^xcd_log consecutive tiles, and in every group XCD r takes the
 // r-th run of 2^xcd_log tiles; with the rotate flag the runs move on by one XCD every 8 groups
-// (blocked_xcds and xcd_run on the host say when and why).  With the backwards flag (set on odd rounds unless the plan asked for forward sweeps) the list is walked
-// backwards, so that what the previous sync wrote last is read first, while it may still be in the
-// 256 MB memory-side cache (it is for states of up to a few GB; larger states neither gain nor
-// lose); the XCD of a tile stays the same.  Tiles beyond the last whole group are taken in order.
+// (blocked_xcds and xcd_run on the host say when and why).  With the backwards flag (set on odd
+// rounds unless the plan asked for forward sweeps) the list is walked backwards, so that what the
+// previous sync wrote last is read first, while it may still be in the 256 MB memory-side cache (it
+// is for states of up to a few GB; larger states neither gain nor lose); the XCD of a tile stays the
+// same up to the rotation.  Tiles beyond the last whole group are taken in order.
 __device__ __forceinline__ unsigned tile_of_block(const SyncArgs &a)
 {
     const unsigned n = gridDim.x, lg = static_cast<unsigned>(a.xcd_log);
