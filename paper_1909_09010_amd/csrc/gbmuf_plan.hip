@@ -37,7 +37,10 @@ struct LayoutCfg {
 
 enum { kRows = 0, kBlocked = 1 };
 enum { kBmuf = 0, kMa = 1 };          // the three-array update, or the gossip-MA branch (theta only)
-constexpr int kMaxTileSets = 4;
+// How much one launch updates.  With sync periods that differs from call to call by orders of magnitude, so
+// everything that depends on it is chosen per launch, from the components that are due.
+enum { kCached = 0, kMiddle = 1, kLarge = 2, kSizes = 3 };
+constexpr int kMaxTileSets = 2 * 2 * kSizes;
 
 }  // namespace
 
@@ -51,14 +54,14 @@ struct gbmuf_plan_s {
     std::vector<int32_t> periods;    // m: sync period H_i (all 1 without periods)
     std::vector<int32_t> cand;       // [K][C] ring candidates, order of Definition 1
     std::vector<CompDesc> comp;      // m: per-component constants of the kernels
-    LayoutCfg cfg[2][2];             // [kRows, kBlocked][kBmuf, kMa]
+    LayoutCfg cfg[2][2][kSizes];     // [kRows, kBlocked][kBmuf, kMa][size of the launch]
     int32_t min_block_logT = 0;      // blocks hold at least 4 << min_block_logT floats
-    TileSet sets[kMaxTileSets];      // one per distinct tile width among the four configurations
+    TileSet sets[kMaxTileSets];      // one per distinct tile width among the configurations that calls can take
     int32_t n_sets = 0;
     float inv = 1.0f;                // 1/(q+1), rounded once (plans with one q)
     int32_t flags = 0;               // load/store cache hints of the fused kernel
-    bool in_kernel_sampling = false; // workgroups draw their own neighbour rows (no sampler launch)
-    bool in_kernel_sampling_ma = false;   // the same for the gossip-MA branch
+    int32_t sampling = GBMUF_SAMPLING_AUTO;   // as asked for
+    bool launch_bound = false;       // with AUTO: workgroups always draw their own neighbour rows
     bool alternate = true;           // odd rounds walk the tile list backwards (see tile_of_block)
 
     bool has_device = false;
@@ -203,7 +206,7 @@ bool find_variant(int threads, int slots, Variant *out)
 // or its nearest rival.  What decides is how the accesses that the chip has in flight at one time lie in
 // memory, less how many they are: a short stretch of memory is fast, and so are tiles that cover 512
 // bytes to 1 KB of a worker row.
-Variant default_variant(int K, int layout, int what, bool large)
+Variant default_variant(int K, int layout, int what, int size)
 {
     Variant v{1024, 4, 4};
     if (what == kMa) {
@@ -215,12 +218,12 @@ Variant default_variant(int K, int layout, int what, bool large)
         else if (K <= 64 && layout == kBlocked) find_variant(512, 4, &v);
     } else if (layout == kBlocked) {
         // one address stream: T = 32 (64 for few workers).  256 x 2 / 512 x 1: 16 workers x 278.6 M 16290 /
-        // 17100, 8 x 84.8 M 2517 / 2577, but below `large` 16 x 2.6 M 166 / 161, 12 x 2.6 M 122 / 118.
+        // 17100, 8 x 84.8 M 2517 / 2577, but below kLarge 16 x 2.6 M 166 / 161, 12 x 2.6 M 122 / 118.
         // 1024 x 1 / 512 x 2: 24 x 45.8 M 4073 / 4253, 32: 5390 / 5477, 20: 3690 / 3550, 28: 4920 / 4813.
         // kSixtyFour (two per CU) / 512 x 4 (one): 42 x 34.9 M 5414 / 5820, 48 x 32.8 M 6030 / 5944, 56: 7291 /
         // 6997, 64 x 57.8 M 14150 / 14410.
         if (K <= 4) find_variant(256, 1, &v);
-        else if (K <= 16 && large) find_variant(256, 2, &v);
+        else if (K <= 16 && size == kLarge) find_variant(256, 2, &v);
         else if (K <= 16) find_variant(512, 1, &v);
         else if ((K > 21 && K <= 24) || (K > 29 && K <= 32)) find_variant(1024, 1, &v);
         else if (K <= 32) find_variant(512, 2, &v);
@@ -242,9 +245,9 @@ Variant default_variant(int K, int layout, int what, bool large)
 // four, 2648 at two; 14 workers 3122 at three, 3237 at two; 16 workers x 278.6 M 16290 at two, 17200 at three.
 // A state that fits the caches has nothing to gain from the bound and loses latency: 4 workers x 0.45 M
 // 10.9 at eight, 12.1 at four.  Rows: two, but one from 25 to 64 workers (32 workers 7065 against 7143).
-int32_t default_workgroups_per_cu(int K, int layout, int what, int logT, int64_t values)
+int32_t default_workgroups_per_cu(int K, int layout, int what, int logT, int size)
 {
-    if (values <= 8000000) return 8;                       // 96 MB of theta, omega and Delta
+    if (size == kCached) return 8;
     if (what == kMa) return layout == kBlocked ? (K <= 64 ? 4 : 2) : (K <= 16 ? 4 : K <= 32 ? 3 : 0);
     if (layout == kBlocked) {
         const int columns = K << logT, aim = K <= 4 ? 1024 : 1200;
@@ -253,18 +256,22 @@ int32_t default_workgroups_per_cu(int K, int layout, int what, int logT, int64_t
     return K <= 24 ? 2 : K <= 64 ? 1 : 0;
 }
 
-// Above so many values per sync a plan draws its rows in a kernel of its own.
-constexpr int64_t kLargeValues = 500000000;
+// Above so many values a launch's rows are drawn in a kernel of its own (draws_itself).
+constexpr int64_t kLargeValues = 500000000, kLargeValuesMa = 130000000;
 
-// What one of the plan's syncs moves as a rule: with periods, the components that sync most often.
-int64_t values_per_sync(const gbmuf_plan_s &pl)
+// Up to so many values the three arrays (96 MB) stay in the memory-side cache from one sync to the next.
+constexpr int64_t kCachedValues = 8000000;
+
+int size_of_launch(int64_t values)
 {
-    const int32_t often = pl.periods.empty() ? 1 : *std::min_element(pl.periods.begin(), pl.periods.end());
-    int64_t n = 0;
-    for (int32_t i = 0; i < pl.m; ++i)
-        if (pl.periods[static_cast<size_t>(i)] == often)
-            n += pl.off[static_cast<size_t>(i) + 1] - pl.off[static_cast<size_t>(i)];
-    return pl.K * n;
+    return values <= kCachedValues ? kCached : values <= kLargeValues ? kMiddle : kLarge;
+}
+
+// Which sizes a call of this plan can have: without periods a call updates everything.
+bool size_occurs(const gbmuf_plan_s &pl, int size)
+{
+    const int all = size_of_launch(pl.K * pl.P);
+    return size == all || (pl.has_periods && size < all);
 }
 
 // Whether the kernel for many workers takes over (where its tile fits).  Measured, old shape against
@@ -359,6 +366,13 @@ int upload(T **dst, const std::vector<T> &src)
     return GBMUF_OK;
 }
 
+const LayoutCfg &cfg_of_all(const gbmuf_plan_s &pl, int layout, int what)
+{
+    return pl.cfg[layout][what][size_of_launch(pl.K * pl.P)];
+}
+
+const TileSet &set_of_all(const gbmuf_plan_s &pl) { return pl.sets[cfg_of_all(pl, kRows, kBmuf).set]; }
+
 int make_device_state(gbmuf_plan_s &pl, int32_t sampling)
 {
     int ndev = 0;
@@ -380,29 +394,13 @@ int make_device_state(gbmuf_plan_s &pl, int32_t sampling)
     }
     bool can = false;
     int rc = GBMUF_OK;
-    for (int l = 0; l < 4 && rc == GBMUF_OK; ++l) {
-        bool c = false;
-        rc = prepare_kernels(pl.cfg[l / 2][l % 2].variant, pl.K, pl.q, pl.mixed_q, pl.C, &c);
-        can = l == 0 ? c : (can && c);
-    }
+    for (int l = 0; l < 4 * kSizes && rc == GBMUF_OK; ++l)
+        if (size_occurs(pl, l % kSizes))
+            rc = prepare_kernels(pl.cfg[l / kSizes / 2][l / kSizes % 2][l % kSizes].variant, pl.K, pl.q, pl.mixed_q, pl.C, &can);
     if (rc != GBMUF_OK) return rc;
-    // Drawing the rows inside every workgroup saves the sampler launch, about 5 us of a sync, and costs
-    // about 1 % of it where the rows are drawn in registers.  Measured, in the kernel / separate, us:
-    // 16 workers x 6.2 M 395 / 402, 20.6 M 1365 / 1373, 35.0 M 2045 / 2032, 278.6 M 16715 / 16295; 8 x 20.6 M
-    // 639 / 643; 64 x 5.4 M 1311 / 1315, 9.3 M 2274 / 2277.  Gossip-MA moves a third of the bytes: 4 x 84.8 M
-    // 422 / 409, 18 x 4.3 M 157 / 164.  Rows of more than 7 neighbours are drawn through LDS, which only
-    // launch-bound plans do.
-    if (sampling == GBMUF_SAMPLING_IN_KERNEL) {
-        if (!can) return GBMUF_EUNSUPPORTED;
-        pl.in_kernel_sampling = pl.in_kernel_sampling_ma = true;
-    } else if (sampling == GBMUF_SAMPLING_SEPARATE) {
-        pl.in_kernel_sampling = pl.in_kernel_sampling_ma = false;
-    } else {
-        const int64_t values = values_per_sync(pl);
-        const bool launch_bound = can && pl.sets[pl.cfg[kRows][kBmuf].set].tiles.size() <= 8192, few = draws_in_registers(pl.q);
-        pl.in_kernel_sampling = launch_bound || (few && values <= kLargeValues);
-        pl.in_kernel_sampling_ma = launch_bound || (few && values <= 130000000);
-    }
+    if (sampling == GBMUF_SAMPLING_IN_KERNEL && !can) return GBMUF_EUNSUPPORTED;
+    pl.sampling = sampling;
+    pl.launch_bound = can && set_of_all(pl).tiles.size() <= 8192;
     if ((rc = upload(&pl.d_comp, pl.comp)) != GBMUF_OK) return rc;
     for (int s = 0; s < pl.n_sets; ++s)
         if ((rc = upload(&pl.sets[s].d_tiles, pl.sets[s].tiles)) != GBMUF_OK) return rc;
@@ -518,19 +516,57 @@ size_t lds_floor(const gbmuf_plan_s *pl, const LayoutCfg &cfg)
     return share > 0 ? static_cast<size_t>(share) : 0;
 }
 
-struct TileRange {
-    int64_t first = 0, count = -1;                            // count < 0: the whole list
+// What one call updates.
+struct Due {
+    int64_t values = 0;                                       // K times the elements of the components that are due
+    int32_t first = 0, last = -1;                             // the first and the last component with elements among them
+    bool one_run = true;                                      // they lie side by side, with none in between that is not due
 };
 
-int enqueue_sync(const gbmuf_plan_s *pl, const int32_t *nbr_dev, const gbmuf_state_t *st, const Placement &at,
-                 int layout, float eta, float zeta, int32_t mode, hipStream_t stream, uint64_t round,
-                 TileRange range = TileRange{}, bool check_periods = false)
+Due due_all(const gbmuf_plan_s *pl) { return Due{pl->K * pl->P, 0, pl->m - 1, true}; }
+
+// The components that are due at this step, on the host: empty ones do not matter.
+Due due_at(const gbmuf_plan_s *pl, uint64_t step)
 {
-    const LayoutCfg &cfg = pl->cfg[layout][mode == GBMUF_MODE_GOSSIP_MA ? kMa : kBmuf];
+    Due d;
+    int64_t end = 0;
+    for (int32_t i = 0; i < pl->m; ++i) {
+        const int64_t a = pl->off[static_cast<size_t>(i)], b = pl->off[static_cast<size_t>(i) + 1];
+        if (a == b || step % static_cast<uint64_t>(pl->periods[static_cast<size_t>(i)]) != 0) continue;
+        if (d.last < 0) d.first = i;
+        else if (a != end) d.one_run = false;
+        d.last = i;
+        end = b;
+        d.values += pl->K * (b - a);
+    }
+    return d;
+}
+
+// Whether a launch's workgroups draw its neighbour rows themselves.  That saves the sampler launch, about
+// 5 us of a sync, and costs about 1 % of it where the rows are drawn in registers.  Measured, in the kernel /
+// separate, us: 16 workers x 6.2 M 395 / 402, 20.6 M 1365 / 1373, 35.0 M 2045 / 2032, 166.1 M 10050 / 9880,
+// 278.6 M 16715 / 16295; 8 x 20.6 M 639 / 643; 64 x 5.4 M 1311 / 1315, 9.3 M 2274 / 2277.  Gossip-MA moves a third
+// of the bytes: 4 x 84.8 M 422 / 409, 18 x 4.3 M 157 / 164.  Rows of more than 7 neighbours are drawn through
+// LDS, which only launch-bound plans do.
+bool draws_itself(const gbmuf_plan_s *pl, int32_t mode, int64_t values)
+{
+    if (pl->sampling != GBMUF_SAMPLING_AUTO) return pl->sampling == GBMUF_SAMPLING_IN_KERNEL;
+    return pl->launch_bound ||
+           (draws_in_registers(pl->q) && values <= (mode == GBMUF_MODE_GOSSIP_MA ? kLargeValuesMa : kLargeValues));
+}
+
+int enqueue_sync(const gbmuf_plan_s *pl, const int32_t *nbr_dev, const gbmuf_state_t *st, const Placement &at,
+                 int layout, float eta, float zeta, int32_t mode, hipStream_t stream, uint64_t round, const Due &due)
+{
+    const LayoutCfg &cfg = pl->cfg[layout][mode == GBMUF_MODE_GOSSIP_MA ? kMa : kBmuf][size_of_launch(due.values)];
     const TileSet &ts = pl->sets[cfg.set];
-    const int64_t n_tiles = range.count < 0 ? static_cast<int64_t>(ts.tiles.size()) : range.count;
+    // One run of components is launched as exactly its tiles (the list is in component order); for several
+    // runs one launch covers all tiles, and the workgroups of components that are not due return at once.
+    const int64_t first = due.one_run && due.last >= 0 ? ts.tile_start[static_cast<size_t>(due.first)] : 0;
+    const int64_t end = due.one_run && due.last >= 0 ? ts.tile_start[static_cast<size_t>(due.last) + 1]
+                                                     : static_cast<int64_t>(ts.tiles.size());
     SyncArgs a{};
-    a.tiles = ts.d_tiles + range.first;
+    a.tiles = ts.d_tiles + first;
     a.nbr = nbr_dev;
     a.comp = pl->d_comp;
     a.theta = st->theta; a.omega = st->omega; a.delta = st->delta;
@@ -538,18 +574,13 @@ int enqueue_sync(const gbmuf_plan_s *pl, const int32_t *nbr_dev, const gbmuf_sta
     a.K = pl->K; a.q = pl->q; a.logT = cfg.logT; a.mode = mode;
     a.eta = eta; a.zeta = zeta; a.inv = pl->inv;
     a.flags = pl->flags | ((pl->alternate && (round & 1)) ? kFlagBackwards : 0) | (pl->mixed_q ? kFlagMixedQ : 0) |
-              (check_periods ? kFlagCheckPeriods : 0) | (cfg.rotate ? kFlagRotate : 0);
+              (due.one_run ? 0 : kFlagCheckPeriods) | (cfg.rotate ? kFlagRotate : 0);
     a.p = pl->p; a.C = pl->C;                               // used only when nbr_dev == nullptr
     a.key0 = static_cast<uint32_t>(pl->seed); a.key1 = static_cast<uint32_t>(pl->seed >> 32);
     a.round0 = static_cast<uint32_t>(round); a.round1 = static_cast<uint32_t>(round >> 32);
     a.step = round;
     a.xcd_log = xcd_run(cfg, at, st, mode);
-    return launch_sync(cfg.variant, a, n_tiles, lds_floor(pl, cfg), stream);
-}
-
-bool draws_itself(const gbmuf_plan_s *pl, int32_t mode)
-{
-    return mode == GBMUF_MODE_GOSSIP_MA ? pl->in_kernel_sampling_ma : pl->in_kernel_sampling;
+    return launch_sync(cfg.variant, a, end - first, lds_floor(pl, cfg), stream);
 }
 
 SampleArgs sample_args(const gbmuf_plan_s *pl, uint64_t round, int32_t *out)
@@ -650,13 +681,13 @@ int gbmuf_plan_create(gbmuf_plan_t **out, const gbmuf_plan_desc_t *desc)
             }
             pl->flags = desc->cache_hints;
             pl->alternate = desc->sweep == GBMUF_SWEEP_AUTO;
-            const int64_t values = values_per_sync(*pl);
-            for (int l = 0; l < 4 && rc == GBMUF_OK; ++l) {
-                LayoutCfg &cfg = pl->cfg[l / 2][l % 2];
+            for (int l = 0; l < 4 * kSizes && rc == GBMUF_OK; ++l) {
+                const int layout = l / kSizes / 2, what = l / kSizes % 2, size = l % kSizes;
+                LayoutCfg &cfg = pl->cfg[layout][what][size];
                 if (desc->tile_threads != 0) {
                     if (!find_variant(desc->tile_threads, desc->tile_slots, &cfg.variant)) rc = GBMUF_EINVAL;
                 } else {
-                    cfg.variant = default_variant(K, l / 2, l % 2, values > kLargeValues);
+                    cfg.variant = default_variant(K, layout, what, size);
                 }
                 if (rc != GBMUF_OK) break;
                 if (K > cfg.variant.threads * cfg.variant.slots) { rc = desc->tile_threads != 0 ? GBMUF_EINVAL : GBMUF_EUNSUPPORTED; break; }
@@ -668,19 +699,20 @@ int gbmuf_plan_create(gbmuf_plan_t **out, const gbmuf_plan_desc_t *desc)
                     pl->min_block_logT = widest_tile(Variant{K <= 16 ? 1024 : K <= 64 ? 2048 : 4096, 1, 1}, K);
                     const Variant &v = K <= 128 ? kMany : kVeryMany;
                     // the wider shapes for many workers, where the neighbour rows fit beside their tile
-                    if (takes_many(K, l / 2, l % 2) &&
+                    if (takes_many(K, layout, what) &&
                         sync_lds_bytes(v, K, pl->q, pl->mixed_q, pl->C, can_sample_inline(K, pl->C)) <= kLdsPerWorkgroup)
                         cfg.variant = v;
-                    if (l / 2 == kBlocked) blocked_xcds(K, l % 2, cfg);
+                    if (layout == kBlocked) blocked_xcds(K, what, cfg);
                 }
                 cfg.logT = widest_tile(cfg.variant, K);
                 cfg.workgroups_per_cu = desc->workgroups_per_cu != 0 ? desc->workgroups_per_cu
-                                                                     : default_workgroups_per_cu(K, l / 2, l % 2, cfg.logT, values);
+                                                                     : default_workgroups_per_cu(K, layout, what, cfg.logT, size);
             }
             if (rc == GBMUF_OK) {
                 // one tile list per distinct tile width
-                for (int l = 0; l < 4; ++l) {
-                    LayoutCfg &cfg = pl->cfg[l / 2][l % 2];
+                for (int l = 0; l < 4 * kSizes; ++l) {
+                    if (!size_occurs(*pl, l % kSizes)) continue;
+                    LayoutCfg &cfg = pl->cfg[l / kSizes / 2][l / kSizes % 2][l % kSizes];
                     int found = -1;
                     for (int s2 = 0; s2 < pl->n_sets; ++s2)
                         if (pl->sets[s2].logT == cfg.logT) found = s2;
@@ -736,17 +768,20 @@ int gbmuf_plan_info(const gbmuf_plan_t *plan, gbmuf_info_t *info)
     info->m = plan->m; info->K = plan->K; info->q = plan->q; info->p = plan->p; info->C = plan->C;
     info->has_device = plan->has_device ? 1 : 0;
     info->P = plan->P;
-    info->n_tiles = static_cast<int64_t>(plan->sets[plan->cfg[kRows][kBmuf].set].tiles.size());
-    info->tile_columns = 1 << plan->cfg[kRows][kBmuf].logT;
-    info->threads = plan->cfg[kRows][kBmuf].variant.threads;
+    const LayoutCfg &rows = cfg_of_all(*plan, kRows, kBmuf), &blocked = cfg_of_all(*plan, kBlocked, kBmuf);
+    info->n_tiles = static_cast<int64_t>(plan->sets[rows.set].tiles.size());
+    info->tile_columns = 1 << rows.logT;
+    info->threads = rows.variant.threads;
     info->seed = plan->seed;
     info->mixed_q = plan->mixed_q ? 1 : 0;
     info->has_periods = plan->has_periods ? 1 : 0;
-    info->in_kernel_sampling = plan->in_kernel_sampling && plan->in_kernel_sampling_ma ? 1 : 0;
-    info->tile_columns_blocked = 1 << plan->cfg[kBlocked][kBmuf].logT;
-    info->threads_blocked = plan->cfg[kBlocked][kBmuf].variant.threads;
-    info->workgroups_per_cu_blocked = plan->cfg[kBlocked][kBmuf].workgroups_per_cu;
-    info->tile_columns_blocked_ma = 1 << plan->cfg[kBlocked][kMa].logT;
+    const int64_t all = plan->K * plan->P;                  // what is drawn in the kernel for all is so for any part
+    info->in_kernel_sampling = plan->has_device && draws_itself(plan, GBMUF_MODE_PAPER, all) &&
+                                       draws_itself(plan, GBMUF_MODE_GOSSIP_MA, all) ? 1 : 0;
+    info->tile_columns_blocked = 1 << blocked.logT;
+    info->threads_blocked = blocked.variant.threads;
+    info->workgroups_per_cu_blocked = blocked.workgroups_per_cu;
+    info->tile_columns_blocked_ma = 1 << cfg_of_all(*plan, kBlocked, kMa).logT;
     info->min_block_floats = 4 << plan->min_block_logT;
     return GBMUF_OK;
 }
@@ -802,10 +837,12 @@ int gbmuf_sync_state(const gbmuf_plan_t *plan, const gbmuf_state_t *state, float
     int rc = check_sync(plan, state, nesterov, &at, &layout);
     if (rc != GBMUF_OK) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (draws_itself(plan, nesterov)) return enqueue_sync(plan, nullptr, state, at, layout, eta, zeta, nesterov, s, round);
+    const Due due = due_all(plan);
+    if (draws_itself(plan, nesterov, due.values))
+        return enqueue_sync(plan, nullptr, state, at, layout, eta, zeta, nesterov, s, round, due);
     rc = launch_sampler(sample_args(plan, round, plan->d_nbr), s);
     if (rc != GBMUF_OK) return rc;
-    return enqueue_sync(plan, plan->d_nbr, state, at, layout, eta, zeta, nesterov, s, round);
+    return enqueue_sync(plan, plan->d_nbr, state, at, layout, eta, zeta, nesterov, s, round, due);
 }
 
 int gbmuf_sync_static(const gbmuf_plan_t *plan, const gbmuf_state_t *state, float eta, float zeta, int32_t nesterov,
@@ -828,7 +865,7 @@ int gbmuf_sync_static(const gbmuf_plan_t *plan, const gbmuf_state_t *state, floa
     // the sampler fills every row the fused kernel reads, so nothing of an earlier call is seen
     rc = launch_sampler(sample_args(plan, round, table), s);
     if (rc != GBMUF_OK) return rc;
-    return enqueue_sync(plan, table, state, at, layout, eta, zeta, nesterov, s, round);
+    return enqueue_sync(plan, table, state, at, layout, eta, zeta, nesterov, s, round, due_all(plan));
 }
 
 int gbmuf_sync(const gbmuf_plan_t *plan, float *replicas, float *global, float *delta, int64_t worker_stride,
@@ -847,42 +884,21 @@ int gbmuf_sync_step_state(const gbmuf_plan_t *plan, const gbmuf_state_t *state, 
     if (rc != GBMUF_OK) return rc;
     if (!plan->has_periods) return gbmuf_sync_state(plan, state, eta, zeta, nesterov, step, stream);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // The tile list is in component order: the components that are due at this step cover one
-    // or more runs of it.  One run is launched as exactly that range; several runs take one
-    // launch over everything in which the workgroups of the other components return at once.
-    const TileSet &ts = plan->sets[plan->cfg[layout][nesterov == GBMUF_MODE_GOSSIP_MA ? kMa : kBmuf].set];
-    int64_t run_first = 0, run_end = 0;
-    int32_t comp_first = -1, comp_last = -1, runs = 0;
-    for (int32_t i = 0; i < plan->m; ++i) {
-        if (step % static_cast<uint64_t>(plan->periods[static_cast<size_t>(i)]) != 0) continue;
-        const int64_t t0 = ts.tile_start[static_cast<size_t>(i)], t1 = ts.tile_start[static_cast<size_t>(i) + 1];
-        if (t1 == t0) continue;
-        if (runs == 0 || t0 != run_end) {
-            ++runs;
-            if (runs == 1) run_first = t0;
-        }
-        run_end = t1;
-        if (comp_first < 0) comp_first = i;
-        comp_last = i;
-    }
-    if (runs == 0) return GBMUF_OK;
-    const bool one_run = runs == 1;
+    const Due due = due_at(plan, step);
+    if (due.last < 0) return GBMUF_OK;
     const int32_t *nbr = nullptr;                           // nullptr: workgroups draw their own rows
-    if (!draws_itself(plan, nesterov)) {
+    if (!draws_itself(plan, nesterov, due.values)) {
         // only the components that are due are sampled: the launch spans first..last of them and
         // the threads of components in between that are not due leave without drawing
         SampleArgs sa = sample_args(plan, step, plan->d_nbr);
-        sa.first_pair = static_cast<int64_t>(comp_first) * plan->K;
-        sa.pairs = static_cast<int64_t>(comp_last - comp_first + 1) * plan->K;
+        sa.first_pair = static_cast<int64_t>(due.first) * plan->K;
+        sa.pairs = static_cast<int64_t>(due.last - due.first + 1) * plan->K;
         sa.check_periods = 1;
         rc = launch_sampler(sa, s);
         if (rc != GBMUF_OK) return rc;
         nbr = plan->d_nbr;
     }
-    if (one_run)
-        return enqueue_sync(plan, nbr, state, at, layout, eta, zeta, nesterov, s, step,
-                            TileRange{run_first, run_end - run_first}, false);
-    return enqueue_sync(plan, nbr, state, at, layout, eta, zeta, nesterov, s, step, TileRange{}, true);
+    return enqueue_sync(plan, nbr, state, at, layout, eta, zeta, nesterov, s, step, due);
 }
 
 int gbmuf_sync_step(const gbmuf_plan_t *plan, float *replicas, float *global, float *delta, int64_t worker_stride,
@@ -901,7 +917,7 @@ int gbmuf_sync_table_state(const gbmuf_plan_t *plan, const int32_t *nbr_dev, con
     const int rc = check_sync(plan, state, nesterov, &at, &layout);
     if (rc != GBMUF_OK) return rc;
     return enqueue_sync(plan, nbr_dev ? nbr_dev : plan->d_nbr, state, at, layout, eta, zeta, nesterov,
-                        static_cast<hipStream_t>(stream), 0);
+                        static_cast<hipStream_t>(stream), 0, due_all(plan));
 }
 
 int gbmuf_sync_table(const gbmuf_plan_t *plan, const int32_t *nbr_dev, float *replicas, float *global,

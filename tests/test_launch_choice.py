@@ -1,0 +1,111 @@
+"""What a call launches, on what sizes: shapes, occupancy bounds and where the neighbour rows are drawn.
+The GPU tests record calls into a HIP graph, read the launches back and never run the graph, so that plans
+of any size are looked at without their memory."""
+import ctypes
+
+import numpy as np
+import pytest
+
+from paper_1909_09010_amd import binding as B
+
+SAMPLER_THREADS = 64                       # the sampler's launches have so many threads, the fused kernel's more
+
+
+class _Dim3(ctypes.Structure):
+    _fields_ = [("x", ctypes.c_uint32), ("y", ctypes.c_uint32), ("z", ctypes.c_uint32)]
+
+
+class _KernelNodeParams(ctypes.Structure):
+    _fields_ = [("block", _Dim3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p), ("grid", _Dim3),
+                ("params", ctypes.c_void_p), ("shared", ctypes.c_uint32)]
+
+
+def launches(call):
+    """[(blocks, threads, LDS bytes)] of what ``call(stream)`` enqueues; nothing runs."""
+    import torch
+    hip = ctypes.CDLL(B.LIB_PATH)          # the HIP runtime that the library itself is bound to
+    stream = torch.cuda.Stream()
+    graph, count = ctypes.c_void_p(), ctypes.c_size_t()
+    assert hip.hipStreamBeginCapture(ctypes.c_void_p(stream.cuda_stream), 1) == 0        # thread-local mode
+    try:
+        call(stream.cuda_stream)
+    finally:
+        assert hip.hipStreamEndCapture(ctypes.c_void_p(stream.cuda_stream), ctypes.byref(graph)) == 0
+    assert hip.hipGraphGetNodes(graph, None, ctypes.byref(count)) == 0
+    nodes = (ctypes.c_void_p * max(1, count.value))()
+    assert hip.hipGraphGetNodes(graph, nodes, ctypes.byref(count)) == 0
+    out = []
+    for node in nodes[:count.value]:
+        kind, p = ctypes.c_int(-1), _KernelNodeParams()
+        assert hip.hipGraphNodeGetType(ctypes.c_void_p(node), ctypes.byref(kind)) == 0 and kind.value == 0   # a kernel
+        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)) == 0
+        out.append((p.grid.x * p.grid.y * p.grid.z, p.block.x, p.shared))
+    assert hip.hipGraphDestroy(graph) == 0
+    return out
+
+
+def fake_state(plan, place="blocked", aligned=True):
+    """A state of the plan's size at addresses that nothing may touch."""
+    K, P, base = plan.info.K, plan.info.P, 1 << 40
+    if place == "blocked":
+        lay = B.recommend_layout(P, K, plan=plan)
+        at = [base, base + 4 * lay.omega_offset, base + 4 * lay.delta_offset]
+        return B.make_state(*at, lay.worker_stride, lay.block_floats, lay.block_stride)
+    stride = -(-P // 1024) * 1024 if aligned else P | 1
+    return B.make_state(*[base + 4 * a * (-(-K * stride // 1024) * 1024) for a in range(3)], stride)
+
+
+def need_gpu():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+# The component that syncs most often is a bias, or empty; all the others sync every 16th time.  A sync of everything
+# has to run like that of a plan without periods.
+RARE = [83_070_000 // 8] * 8
+
+
+@pytest.mark.parametrize("often", [0, 512])
+@pytest.mark.parametrize("K", [8, 16, 32, 64])
+def test_the_rate_of_syncs_does_not_change_how_all_components_are_synced(K, often):
+    off = np.concatenate([[0], np.cumsum([often] + RARE)])
+    with_periods, without = B.Plan(off, K, 2, 0, periods=[1] + [16] * 8).info, B.Plan(off, K, 2, 0).info
+    for name in ("n_tiles", "tile_columns", "threads", "tile_columns_blocked", "threads_blocked", "workgroups_per_cu_blocked",
+                 "tile_columns_blocked_ma", "min_block_floats", "in_kernel_sampling"):
+        assert getattr(with_periods, name) == getattr(without, name), name
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("place", ["blocked", "rows"])
+@pytest.mark.parametrize("mode", [B.MODE_PAPER, B.MODE_GOSSIP_MA])
+def test_a_step_runs_like_a_sync_of_what_is_due(place, mode):
+    need_gpu()
+    K, often = 16, 30_000_000
+    off = np.concatenate([[0], np.cumsum([often] + RARE)])
+    pl = B.Plan(off, K, 2, 0, periods=[1] + [16] * 8)
+    whole, part = B.Plan(off, K, 2, 0), B.Plan([0, often], K, 2, 0)
+    run = lambda p, call: launches(lambda s: call(fake_state(p, place), 0.9, 1.0, mode, 16, s))
+    everything, frequent = run(whole, whole.sync_state), run(part, part.sync_state)
+    # 1.8 G values: the rows are drawn by a kernel of their own; 480 M: in the fused kernel (gossip-MA moves a third)
+    assert len(everything) == 2 and len(frequent) == (2 if mode == B.MODE_GOSSIP_MA else 1)
+    assert run(pl, pl.sync_state) == everything and run(pl, pl.sync_step_state) == everything
+    got = launches(lambda s: pl.sync_step_state(fake_state(pl, place), 0.9, 1.0, mode, 17, s))
+    assert got[-1] == frequent[-1] and len(got) == len(frequent)
+    assert pl.info.in_kernel_sampling == 0                              # not all of its calls draw that way
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("often", [[0], [512]])
+def test_a_tiny_frequent_component_does_not_unbound_the_rest(often):
+    need_gpu()
+    off = np.concatenate([[0], np.cumsum(often + RARE)])
+    pl, without = B.Plan(off, 16, 2, 0, periods=[1] + [16] * 8), B.Plan(off, 16, 2, 0)
+    for place in ("blocked", "rows"):
+        st = fake_state(pl, place)
+        everything = launches(lambda s: without.sync_state(st, 0.9, 1.0, 1, 0, s))
+        assert launches(lambda s: pl.sync_state(st, 0.9, 1.0, 1, 0, s)) == everything
+        step = launches(lambda s: pl.sync_step_state(st, 0.9, 1.0, 1, 0, s))
+        assert len(step) == len(everything) == 2 and step[-1] == everything[-1]        # an empty component is not sampled
+        rare = launches(lambda s: pl.sync_step_state(st, 0.9, 1.0, 1, 1, s))
+        assert rare == [] if often == [0] else len(rare) == 1 and rare[0][0] <= 8
