@@ -1,0 +1,51 @@
+"""Calls that differ in what should cost nothing, timed against each other on one MI355X: within a call
+family the time may not depend on odd sizes.  Passes are replayed from a HIP graph, so that the host's
+launch time is not in them; the bounds are far from the noise (a few per cent) and from what a fault cost."""
+import pytest
+
+from paper_1909_09010_amd import binding as B
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def us(call, calls=20, replays=7):
+    """Microseconds of one ``call(round)`` among others, the best of several replays."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    call(0, None)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for r in range(calls):
+            call(r, torch.cuda.current_stream())
+    best = float("inf")
+    for _ in range(replays):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        graph.replay()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3 / calls)
+    return best
+
+
+def rows(K, stride):
+    return [torch.randn(K * stride, device=DEV) * 0.05 for _ in range(3)]
+
+
+def sync_us(off, K, q, stride, p=0, mode=B.MODE_PAPER, **plan):
+    pl = B.Plan(off, K, q, p, seed=1, **plan)
+    st = rows(K, stride)
+    return us(lambda r, s: pl.sync(*(st if mode != B.MODE_GOSSIP_MA else [st[0], None, None]), stride, 0.9, 1.0, mode, r, s))
+
+
+# The same tiles, with the component edges between 16-byte columns or inside one: a column that is cut issues all its
+# loads at once like a whole one.  Measured 1.19 to 1.31; 1.5 to 1.7 where each waits for the one before.
+@pytest.mark.parametrize("K", [16, 100, 200])
+def test_columns_cut_by_a_component_edge_wait_for_nothing(K):
+    T = 4 * 16
+    edges = lambda shift: sync_us([0] + [T * i - shift for i in range(1, 48)] + [48 * T], K, 2, 48 * T, tile=(1024, 4))
+    between, inside = edges(4), edges(2)
+    assert inside < 1.45 * between, (inside, between)
