@@ -62,6 +62,7 @@ struct gbmuf_plan_s {
     int32_t flags = 0;               // load/store cache hints of the fused kernel
     int32_t sampling = GBMUF_SAMPLING_AUTO;   // as asked for
     bool launch_bound = false;       // with AUTO: workgroups always draw their own neighbour rows
+    bool named_shape = false;        // the plan description names the tile shape
     bool alternate = true;           // odd rounds walk the tile list backwards (see tile_of_block)
 
     bool has_device = false;
@@ -306,18 +307,24 @@ int32_t widest_tile(const Variant &v, int K)
     return lg;
 }
 
+int64_t count_tiles(const gbmuf_plan_s &pl, int32_t logT)
+{
+    const int64_t T = static_cast<int64_t>(1) << logT;
+    int64_t count = 0;
+    for (int32_t i = 0; i < pl.m; ++i) {
+        const int64_t a = pl.off[static_cast<size_t>(i)], b = pl.off[static_cast<size_t>(i) + 1];
+        if (a < b) count += (((b + 3) >> 2) + T - 1) / T - (a >> 2) / T;
+    }
+    return count;
+}
+
 // Split every component into runs of at most T 16-byte columns (the fused kernel's work list).
 void build_tiles(const gbmuf_plan_s &pl, TileSet &ts)
 {
     const int64_t T = static_cast<int64_t>(1) << ts.logT;
     ts.tiles.clear();
     ts.tile_start.assign(static_cast<size_t>(pl.m) + 1, 0);
-    int64_t count = 0;                                     // a list of millions is not grown step by step
-    for (int32_t i = 0; i < pl.m; ++i) {
-        const int64_t a = pl.off[static_cast<size_t>(i)], b = pl.off[static_cast<size_t>(i) + 1];
-        if (a < b) count += (((b + 3) >> 2) + T - 1) / T - (a >> 2) / T;
-    }
-    ts.tiles.reserve(static_cast<size_t>(count));
+    ts.tiles.reserve(static_cast<size_t>(count_tiles(pl, ts.logT)));     // a list of millions is not grown step by step
     for (int32_t i = 0; i < pl.m; ++i) {
         const int64_t a = pl.off[static_cast<size_t>(i)], b = pl.off[static_cast<size_t>(i) + 1];
         ts.tile_start[static_cast<size_t>(i)] = static_cast<int64_t>(ts.tiles.size());
@@ -371,8 +378,6 @@ const LayoutCfg &cfg_of_all(const gbmuf_plan_s &pl, int layout, int what)
     return pl.cfg[layout][what][size_of_launch(pl.K * pl.P)];
 }
 
-const TileSet &set_of_all(const gbmuf_plan_s &pl) { return pl.sets[cfg_of_all(pl, kRows, kBmuf).set]; }
-
 int make_device_state(gbmuf_plan_s &pl, int32_t sampling)
 {
     int ndev = 0;
@@ -400,7 +405,13 @@ int make_device_state(gbmuf_plan_s &pl, int32_t sampling)
     if (rc != GBMUF_OK) return rc;
     if (sampling == GBMUF_SAMPLING_IN_KERNEL && !can) return GBMUF_EUNSUPPORTED;
     pl.sampling = sampling;
-    pl.launch_bound = can && set_of_all(pl).tiles.size() <= 8192;
+    // Small plans draw in the kernel whatever q is, so that their syncs may run on several streams at once
+    // (gbmuf_info_t.in_kernel_sampling).  Small is 8192 tiles of about 32 columns, not of whatever width the rows
+    // shape has: rows of more than 7 neighbours are drawn through LDS, and that is slow.  In the kernel / separate,
+    // 16 workers, 8 neighbours, us: 1.0 M parameters (drawn in the kernel) 116 / 78, 2.1 M (separate) 229 / 154.
+    const LayoutCfg &rows = cfg_of_all(pl, kRows, kBmuf);
+    const int slots = pl.K <= 8 ? 256 : pl.K <= 16 ? 512 : pl.K <= 32 ? 1024 : 4096;
+    pl.launch_bound = can && count_tiles(pl, pl.named_shape ? rows.logT : widest_tile(Variant{slots, 1, 1}, pl.K)) <= 8192;
     if ((rc = upload(&pl.d_comp, pl.comp)) != GBMUF_OK) return rc;
     for (int s = 0; s < pl.n_sets; ++s)
         if ((rc = upload(&pl.sets[s].d_tiles, pl.sets[s].tiles)) != GBMUF_OK) return rc;
@@ -680,20 +691,21 @@ int gbmuf_plan_create(gbmuf_plan_t **out, const gbmuf_plan_desc_t *desc)
                                 sizeof(int32_t) * static_cast<size_t>(pl->C));
             }
             pl->flags = desc->cache_hints;
+            pl->named_shape = desc->tile_threads != 0;
             pl->alternate = desc->sweep == GBMUF_SWEEP_AUTO;
             for (int l = 0; l < 4 * kSizes && rc == GBMUF_OK; ++l) {
                 const int layout = l / kSizes / 2, what = l / kSizes % 2, size = l % kSizes;
                 LayoutCfg &cfg = pl->cfg[layout][what][size];
-                if (desc->tile_threads != 0) {
+                if (pl->named_shape) {
                     if (!find_variant(desc->tile_threads, desc->tile_slots, &cfg.variant)) rc = GBMUF_EINVAL;
                 } else {
                     cfg.variant = default_variant(K, layout, what, size);
                 }
                 if (rc != GBMUF_OK) break;
-                if (K > cfg.variant.threads * cfg.variant.slots) { rc = desc->tile_threads != 0 ? GBMUF_EINVAL : GBMUF_EUNSUPPORTED; break; }
+                if (K > cfg.variant.threads * cfg.variant.slots) { rc = pl->named_shape ? GBMUF_EINVAL : GBMUF_EUNSUPPORTED; break; }
                 // Blocks may be as narrow as min_block_logT says, narrower than a tile too: the kernel
                 // looks an element's block up column by column (where a thread keeps its column, T <= threads).
-                if (desc->tile_threads != 0) {
+                if (pl->named_shape) {
                     pl->min_block_logT = widest_tile(cfg.variant, K);
                 } else {
                     pl->min_block_logT = widest_tile(Variant{K <= 16 ? 1024 : K <= 64 ? 2048 : 4096, 1, 1}, K);

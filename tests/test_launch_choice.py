@@ -109,3 +109,17 @@ def test_a_tiny_frequent_component_does_not_unbound_the_rest(often):
         assert len(step) == len(everything) == 2 and step[-1] == everything[-1]        # an empty component is not sampled
         rare = launches(lambda s: pl.sync_step_state(st, 0.9, 1.0, 1, 1, s))
         assert rare == [] if often == [0] else len(rare) == 1 and rare[0][0] <= 8
+
+
+# More than 7 neighbours are drawn through LDS, which only plans of up to 8192 tiles of about 32 columns do.
+@pytest.mark.gpu
+@pytest.mark.parametrize("K,p,q,most", [(8, -1, 7, None), (9, -1, 8, 8192 * 128), (16, -1, 8, 8192 * 128), (32, -1, 20, 8192 * 128),
+                                        (64, 16, 8, 8192 * 256), (200, 5, 9, 8192 * 64)])
+def test_only_small_plans_draw_through_lds(K, p, q, most):
+    need_gpu()
+    for P, expect in ((most, 1), (most + 1, 2)) if most else ((1 << 22, 1),):
+        pl = B.Plan([0, P], K, q, p)
+        assert pl.info.in_kernel_sampling == 2 - expect
+        for place in ("blocked", "rows"):
+            assert len(launches(lambda s: pl.sync_state(fake_state(pl, place), 0.9, 1.0, B.MODE_PAPER, 0, s))) == expect
+        pl.destroy()
