@@ -55,7 +55,8 @@ struct SyncArgs {
     int32_t flags;           // bit 0: streaming stores, bit 1: streaming loads, bit 3: walk the
                              // tile list backwards, bit 4: components draw different q (read the
                              // tile's q and the component's inv), bit 5: skip components whose
-                             // period does not divide `step`, bit 6: rotate the XCDs (tile_of_block)
+                             // period does not divide `step`, bit 6: rotate the XCDs (tile_of_block),
+                             // bit 7: the library's sampler wrote nbr (not a caller)
     // in-kernel sampling (nbr == nullptr): same bits as the sampler kernel, drawn from the key below
     int32_t p, C;            // ring degree, candidates per worker
     uint32_t key0, key1, round0, round1;
@@ -69,6 +70,7 @@ enum : int32_t {
     kFlagMixedQ = 16,
     kFlagCheckPeriods = 32,
     kFlagRotate = 64,
+    kFlagSampledTable = 128,
 };
 
 // Arguments of the neighbour-sampling kernel: pairs [first_pair, first_pair + pairs) of the

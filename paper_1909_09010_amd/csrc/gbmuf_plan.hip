@@ -567,7 +567,8 @@ bool draws_itself(const gbmuf_plan_s *pl, int32_t mode, int64_t values)
 }
 
 int enqueue_sync(const gbmuf_plan_s *pl, const int32_t *nbr_dev, const gbmuf_state_t *st, const Placement &at,
-                 int layout, float eta, float zeta, int32_t mode, hipStream_t stream, uint64_t round, const Due &due)
+                 int layout, float eta, float zeta, int32_t mode, hipStream_t stream, uint64_t round, const Due &due,
+                 bool callers_table = false)
 {
     const LayoutCfg &cfg = pl->cfg[layout][mode == GBMUF_MODE_GOSSIP_MA ? kMa : kBmuf][size_of_launch(due.values)];
     const TileSet &ts = pl->sets[cfg.set];
@@ -585,7 +586,8 @@ int enqueue_sync(const gbmuf_plan_s *pl, const int32_t *nbr_dev, const gbmuf_sta
     a.K = pl->K; a.q = pl->q; a.logT = cfg.logT; a.mode = mode;
     a.eta = eta; a.zeta = zeta; a.inv = pl->inv;
     a.flags = pl->flags | ((pl->alternate && (round & 1)) ? kFlagBackwards : 0) | (pl->mixed_q ? kFlagMixedQ : 0) |
-              (due.one_run ? 0 : kFlagCheckPeriods) | (cfg.rotate ? kFlagRotate : 0);
+              (due.one_run ? 0 : kFlagCheckPeriods) | (cfg.rotate ? kFlagRotate : 0) |
+              (nbr_dev != nullptr && !callers_table ? kFlagSampledTable : 0);
     a.p = pl->p; a.C = pl->C;                               // used only when nbr_dev == nullptr
     a.key0 = static_cast<uint32_t>(pl->seed); a.key1 = static_cast<uint32_t>(pl->seed >> 32);
     a.round0 = static_cast<uint32_t>(round); a.round1 = static_cast<uint32_t>(round >> 32);
@@ -929,7 +931,7 @@ int gbmuf_sync_table_state(const gbmuf_plan_t *plan, const int32_t *nbr_dev, con
     const int rc = check_sync(plan, state, nesterov, &at, &layout);
     if (rc != GBMUF_OK) return rc;
     return enqueue_sync(plan, nbr_dev ? nbr_dev : plan->d_nbr, state, at, layout, eta, zeta, nesterov,
-                        static_cast<hipStream_t>(stream), 0, due_all(plan));
+                        static_cast<hipStream_t>(stream), 0, due_all(plan), nbr_dev != nullptr);
 }
 
 int gbmuf_sync_table(const gbmuf_plan_t *plan, const int32_t *nbr_dev, float *replicas, float *global,

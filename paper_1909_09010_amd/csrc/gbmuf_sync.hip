@@ -147,17 +147,36 @@ struct Rows {
     }
 };
 
+// Any number of neighbours.  Rows that the library's sampler wrote are ascending, distinct and without the
+// worker: an entry's place follows from itself and its successor, and all threads place entries side by side.  A
+// caller's row may hold anything; a thread sorts it by insertion, a chain of LDS accesses for which the
+// whole workgroup waits.  9 neighbours, placed / sorted, us: 16 workers x 3.75 M 239 / 320 (7 neighbours, in
+// registers: 232), gossip-MA 10 x 6 M 110 / 182 (91); 20 neighbours, 24 x 2.5 M 287 / 412.
 template <int NT>
 struct Rows<NT, kAnyQ> {
     __device__ __forceinline__ void begin(const SyncArgs &, const TileDesc &) {}
     __device__ __forceinline__ void finish(const SyncArgs &a, const TileDesc &td, uint16_t *ids)
     {
         const int K = a.K, q = td.q, pitch = ids_pitch(kAnyQ, a.q);
+        const int32_t *table = a.nbr + static_cast<int64_t>(td.comp) * K * a.q;
+        if (a.flags & kFlagSampledTable) {
+            const int places = max(q, 1);                   // a component without neighbours: the worker itself
+            for (int i = threadIdx.x; i < K * places; i += NT) {
+                const int w = i / places, j = i - w * places;
+                const int32_t *row = table + static_cast<int64_t>(w) * a.q;
+                uint16_t *dst = ids + w * pitch;
+                const int v = q > 0 ? min(max(row[j], 0), K - 1) : K, next = j + 1 < q ? row[j + 1] : K;
+                if (q > 0) dst[v < w ? j : j + 1] = static_cast<uint16_t>(v);
+                if (v < w && w < next) dst[j + 1] = static_cast<uint16_t>(w);
+                if (j == 0 && w < v) dst[0] = static_cast<uint16_t>(w);
+            }
+            return;
+        }
         int32_t *perm = reinterpret_cast<int32_t *>(ids + ids_words(K, pitch));
         for (int w = threadIdx.x; w < K; w += NT) {
             uint16_t *dst = ids + w * pitch;
             if (a.nbr != nullptr) {
-                const int32_t *row = a.nbr + (static_cast<int64_t>(td.comp) * K + w) * a.q;
+                const int32_t *row = table + static_cast<int64_t>(w) * a.q;
                 dst[0] = static_cast<uint16_t>(w);
                 for (int j = 0; j < q; ++j) {
                     const int v = min(max(row[j], 0), K - 1);

@@ -49,3 +49,12 @@ def test_columns_cut_by_a_component_edge_wait_for_nothing(K):
     edges = lambda shift: sync_us([0] + [T * i - shift for i in range(1, 48)] + [48 * T], K, 2, 48 * T, tile=(1024, 4))
     between, inside = edges(4), edges(2)
     assert inside < 1.45 * between, (inside, between)
+
+
+# Averaging 9 neighbours instead of 7 may cost a little, preparing their rows may not: measured 0.98 to 1.21, and 1.36 to
+# 1.99 where a thread sorts each row.
+@pytest.mark.parametrize("K,mode", [(10, B.MODE_PAPER), (16, B.MODE_PAPER), (10, B.MODE_GOSSIP_MA), (24, B.MODE_GOSSIP_MA)])
+def test_more_neighbours_than_fit_registers(K, mode):
+    P = 60_000_000 // K // 1024 * 1024
+    seven, nine = (sync_us([0, P], K, q, P, p=5, mode=mode, sampling=B.SAMPLING_SEPARATE) for q in (7, 9))
+    assert nine < 1.32 * seven, (nine, seven)
