@@ -106,9 +106,10 @@ struct Variant {
     int slots;
     int depth;
 };
-constexpr Variant kSixtyFour = {1024, 2, 1};       // blocked, 33 to 44 and 57 to 64 workers
-constexpr Variant kMany = {1024, 4, 2};            // 64 < K <= 128
-constexpr Variant kVeryMany = {512, 16, 4};        // K > 128
+// shapes that only the library's own rules take (default_variant)
+constexpr Variant kSixtyFour = {1024, 2, 1};
+constexpr Variant kMany = {1024, 4, 2};
+constexpr Variant kVeryMany = {512, 16, 4};
 constexpr size_t kLdsPerWorkgroup = 160 * 1024;    // gfx950
 
 // Which instance of the fused kernel a component's neighbour count takes (gbmuf_sync.hip), and the

@@ -202,101 +202,106 @@ bool find_variant(int threads, int slots, Variant *out)
     return false;
 }
 
-// How the fused kernel runs, by K, layout and branch, unless the plan description names a shape.
-// All figures: MI355X, us per sync, parameters as stated, the shape taken against what it replaced
-// or its nearest rival.  What decides is how the accesses that the chip has in flight at one time lie in
-// memory, less how many they are: a short stretch of memory is fast, and so are tiles that cover 512
-// bytes to 1 KB of a worker row.
-Variant default_variant(int K, int layout, int what, int size)
+// Up to so many values a launch's arrays stay in the 256 MB memory-side cache from one sync to the next (three
+// arrays, or theta alone).
+constexpr int64_t kCachedValues = 20000000, kCachedValuesMa = 60000000;
+// Above so many values a launch's rows are drawn in a kernel of their own (draws_itself); for the shapes, where
+// nothing is left in a cache and only the memory counts.
+constexpr int64_t kLargeValues = 500000000, kLargeValuesMa = 130000000;
+
+int size_of_launch(int64_t values, int what)
+{
+    return values <= (what == kMa ? kCachedValuesMa : kCachedValues) ? kCached : values <= kLargeValues ? kMiddle : kLarge;
+}
+
+// Which sizes a call of this plan can have: without periods a call updates everything.
+bool size_occurs(const gbmuf_plan_s &pl, int what, int size)
+{
+    const int all = size_of_launch(pl.K * pl.P, what);
+    return size == all || (pl.has_periods && size < all);
+}
+
+// How the fused kernel runs, by K, layout, branch and size of the launch, unless the plan description names a
+// shape.  Each rule holds over a whole range of K; it is the shape with the least mean over sweeps of all built-in
+// shapes and bounds on K = 1 .. 1024, 0.3 M .. 2 G values, blocked, padded and odd rows.  In brackets: its mean
+// distance from the best shape of every single point, and that of the nearest rival.
+//
+// kCached is bound by latency: one slot per thread, and no more threads than make a tile of 16 columns [2 %; the
+// shapes below 5 to 25 %].  More workers than that takes 1024 x 4 [10 %]; the wider kVeryMany leaves most CUs without
+// a tile, 256 workers x 0.023 M: 53 us, 1024 x 4 30.  Gossip-MA, with a third of the loads, takes two slots [3 %; one 6 %].
+Variant cached_variant(int K, int layout, int what)
 {
     Variant v{1024, 4, 4};
     if (what == kMa) {
-        // theta only: more columns than the three-array update.  Blocked 32 workers x 45.8 M: 512 x 2
-        // (four per CU) 1793, 1024 x 2 (two) 2054; 64 x 32.8 M: 512 x 4 2611, 1024 x 2 3033.  Rows 24 x 58.9 M:
-        // 512 x 4 2071, 1024 x 2 2357; 64 x 45.8 M: 1024 x 4 4730, 1024 x 2 4957.
-        if (K <= 16) find_variant(512, 2, &v);
-        else if (K <= 32) find_variant(512, layout == kBlocked ? 2 : 4, &v);
-        else if (K <= 64 && layout == kBlocked) find_variant(512, 4, &v);
-    } else if (layout == kBlocked) {
-        // one address stream: T = 32 (64 for few workers).  256 x 2 / 512 x 1: 16 workers x 278.6 M 16290 /
-        // 17100, 8 x 84.8 M 2517 / 2577, but below kLarge 16 x 2.6 M 166 / 161, 12 x 2.6 M 122 / 118.
-        // 1024 x 1 / 512 x 2: 24 x 45.8 M 4073 / 4253, 32: 5390 / 5477, 20: 3690 / 3550, 28: 4920 / 4813.
-        // kSixtyFour (two per CU) / 512 x 4 (one): 42 x 34.9 M 5414 / 5820, 48 x 32.8 M 6030 / 5944, 56: 7291 /
-        // 6997, 64 x 57.8 M 14150 / 14410.
-        if (K <= 4) find_variant(256, 1, &v);
-        else if (K <= 16 && size == kLarge) find_variant(256, 2, &v);
-        else if (K <= 16) find_variant(512, 1, &v);
-        else if ((K > 21 && K <= 24) || (K > 29 && K <= 32)) find_variant(1024, 1, &v);
-        else if (K <= 32) find_variant(512, 2, &v);
-        else if (K <= 44 || (K > 56 && K <= 64)) v = kSixtyFour;
-        else if (K <= 64) find_variant(512, 4, &v);
-    } else {
-        // 3K address streams: T = 64 and more.  8 x 58.9 M padded / plain: 1024 x 1 1939 / 2118, 512 x 1
-        // 2031 / 2172; 16 x 35.0 M plain, on a fast and on a slow placement: 1024 x 1 2251 / 2634, 512 x 1
-        // 2365 / 2751, 256 x 2 2652 / 2957; 64 x 32.8 M: kMany 10088 / 10256, 1024 x 4 10282 / 10577.
-        if (K <= 16) find_variant(1024, 1, &v);
-        else if (K <= 32) find_variant(1024, 2, &v);
-        else if (K <= 64) v = kMany;
+        if (K <= 64) find_variant(K <= 32 ? 256 : 512, 2, &v);
+        else if (K <= 128) find_variant(512, 4, &v);
+    } else if (K <= 64) {
+        if (layout == kBlocked) find_variant(K <= 32 ? 512 : 1024, 1, &v);
+        else find_variant(K <= 16 ? 512 : 1024, K <= 32 ? 1 : 2, &v);
     }
     return v;
 }
 
-// Resident workgroups per CU (0: what the LDS holds).  Blocked: about 1200 columns, but two workgroups
-// at least, and one of the large tiles from 45 to 56: 5 workers 1584 at four, 1876 at two; 10 workers 2219 at
-// four, 2648 at two; 14 workers 3122 at three, 3237 at two; 16 workers x 278.6 M 16290 at two, 17200 at three.
-// A state that fits the caches has nothing to gain from the bound and loses latency: 4 workers x 0.45 M
-// 10.9 at eight, 12.1 at four.  Rows: two, but one from 25 to 64 workers (32 workers 7065 against 7143).
+// Beyond the caches what decides is how the accesses that the chip has in flight at one time lie in memory, less how
+// many they are.  Blocked state is one address stream: a short stretch of it is fast, tiles of 512 bytes to 1 KB of
+// a worker row.  Rows are 3K streams: 1 KB and more.  Above 64 workers theta alone fills the tile and omega and
+// Delta are streamed (sync_kernel); above 128 the widest tile wins once there are enough of them, and with more
+// than 7 neighbours it does not (2 to 10 %).
+//   blocked, middle: 5-16 512 x 1 [0.5 %; 256 x 2 2 %], 17-32 512 x 2 [1 %; 1024 x 1 1 %], 33-64 kSixtyFour [0.5 %; 1024 x 2 1 %,
+//     512 x 4 2 %], 65-128 kMany [0.3 %; 1024 x 4 3 %].  Large: 5-16 256 x 2 [0.5 %; 512 x 1 3 %], 17-32 512 x 2 [1 %; 1024 x 1 1 %],
+//     129-512 kVeryMany [0.5 %; kMany 5 %], above at all sizes [1 %; 1024 x 4 6 %].
+//   rows: up to 4 workers 256 x 1 [4 %; 1024 x 1 9 %], 5-16 kSixtyFour [2 %; 1024 x 1 2 to 4 %], 17-64 1024 x 2 [1.5 %; 1024 x 4 2 %], large
+//     33-64 kMany [0.7 %; 1024 x 2 2 %], 65-512 1024 x 4 [0.5 %; kMany 1 %], 129-512 large kVeryMany [0.3 %; 1024 x 4 1 to 4 %],
+//     above at all sizes [0 %; 1024 x 4 20 to 50 %].
+//   gossip-MA: up to 16 256 x 4 [3 %; 512 x 2 6 %], 17-64 512 x 4 [1 %; 512 x 2 8 %], 65-512 1024 x 4 [1 %; kVeryMany 5 to 20 %], 129-512 large
+//     and above 512 kVeryMany [0.5 %; 1024 x 4 2 to 40 %].
+Variant default_variant(int K, int layout, int what, int size, bool few)
+{
+    Variant v{1024, 4, 4};
+    const bool large = size == kLarge;
+    if (size == kCached) return cached_variant(K, layout, what);
+    if (few && (K > 512 || (K > 128 && large && what == kBmuf))) return kVeryMany;
+    if (what == kMa) {
+        if (K <= 16) find_variant(256, 4, &v);
+        else if (K <= (layout == kBlocked ? 64 : 32)) find_variant(512, 4, &v);
+    } else if (layout == kBlocked) {
+        if (K <= 4) find_variant(256, 1, &v);
+        else if (K <= 16) find_variant(large ? 256 : 512, large ? 2 : 1, &v);
+        else if (K <= 32) find_variant(512, 2, &v);
+        else v = K <= 64 ? kSixtyFour : kMany;
+    } else {
+        if (K <= 4) find_variant(256, 1, &v);
+        else if (K <= 16) v = kSixtyFour;
+        else if (K > 32 && K <= 64 && large) v = kMany;
+        else if (K <= 64) find_variant(1024, 2, &v);
+    }
+    return v;
+}
+
+// Resident workgroups per CU (0: as many as fit).  Blocked: about 1200 columns, but two workgroups at least: 5 workers
+// 1584 us at four, 1876 at two; 10 workers 2219 at four, 2648 at two; 14 workers 3122 at three, 3237 at two; 16 workers
+// x 278.6 M 16290 at two, 17200 at three.  Rows: two, or six of the small ones of up to 4 workers.  A state that stays
+// in the cache has nothing to gain from a bound, and gossip-MA moves too little to need one.
 int32_t default_workgroups_per_cu(int K, int layout, int what, int logT, int size)
 {
-    if (size == kCached) return 8;
-    if (what == kMa) return layout == kBlocked ? (K <= 64 ? 4 : 2) : (K <= 16 ? 4 : K <= 32 ? 3 : 0);
-    if (layout == kBlocked) {
-        const int columns = K << logT, aim = K <= 4 ? 1024 : 1200;
-        return K <= 24 ? std::max(2, (aim + columns / 2) / columns) : K > 44 && K <= 56 ? 1 : 2;
-    }
-    return K <= 24 ? 2 : K <= 64 ? 1 : 0;
+    if (size == kCached || what == kMa) return 0;
+    if (layout == kRows) return K <= 4 ? 6 : 2;
+    const int columns = K << logT, aim = K <= 4 ? 1024 : 1200;
+    return K <= 16 ? std::max(2, (aim + columns / 2) / columns) : 2;
 }
 
-// Above so many values a launch's rows are drawn in a kernel of its own (draws_itself).
-constexpr int64_t kLargeValues = 500000000, kLargeValuesMa = 130000000;
-
-// Up to so many values the three arrays (96 MB) stay in the memory-side cache from one sync to the next.
-constexpr int64_t kCachedValues = 8000000;
-
-int size_of_launch(int64_t values)
+// Which XCD takes which tiles of a blocked state (tile_of_block).  512 bytes of a row (one tile of 32 columns) or
+// 1 KB in one run: from 17 to 32 workers 1 KB (1 % from the best of every point, 512 B 2 %), 512 workers 13112 / 12278 us;
+// but 16 workers x 278.6 M 16295 / 16630, and 33 to 64 are within 0.3 %; 2 KB is the worst (256 workers 5224 / 5907).
+// Rotated: in the recommended arena the blocks of a row lie 32 KB apart, which is 64 tiles of 32 columns, so without
+// it one XCD sees the same addresses modulo 4 KB in every block; 64 workers x 57.8 M 15310 / 14445, gossip-MA
+// 2660 / 2611.  Launches of less than 500 M values gain nothing (1.0 / 1.1 % from the best), nor does any of the other
+// shapes at 17 to 32 workers.
+void blocked_xcds(int K, int what, int size, LayoutCfg &cfg)
 {
-    return values <= kCachedValues ? kCached : values <= kLargeValues ? kMiddle : kLarge;
-}
-
-// Which sizes a call of this plan can have: without periods a call updates everything.
-bool size_occurs(const gbmuf_plan_s &pl, int size)
-{
-    const int all = size_of_launch(pl.K * pl.P);
-    return size == all || (pl.has_periods && size < all);
-}
-
-// Whether the kernel for many workers takes over (where its tile fits).  Measured, old shape against
-// new, us: blocked 72 workers x 6.2 M 2083 / 1724, 128: 3416 / 3114, 256: 7576 / 6310, 1024 x 3.6 M
-// 36480 / 19785; plain rows 128: 3881 / 3775, 200 x 3.6 M 3560 / 3561, 1024: 25489 / 21464.  Gossip-MA has
-// no omega and Delta to stream and gains where its old tile was narrow or half empty: blocked 128:
-// 1233 / 1329 (so not there), 200 x 3.1 M 1112 / 1034, 300: 2017 / 1780, 1024: 9179 / 6423, but 256 x 6.2 M,
-// where two full 64 KB tiles of 16 columns share a CU, 2621 / 2720.
-bool takes_many(int K, int layout, int what)
-{
-    if (what == kBmuf) return K > 64;
-    return K > 128 && !(layout == kBlocked && K > 224 && K <= 256);
-}
-
-// Which XCD takes which tiles of a blocked state (tile_of_block).  512 bytes of a row (one tile of 32
-// columns) or 1 KB in one run: 28 workers 4955 / 4813 (gossip-MA 32: 1816 / 1793), 512 workers 13112 / 12278,
-// but 16 workers x 278.6 M 16295 / 16630; 2 KB is the worst (256 workers 5224 / 5907).
-// Rotated: blocks of a row lie 32 KB apart, which is 64 tiles of 32 columns, so without it one XCD sees
-// the same addresses modulo 4 KB in every block; 64 workers 14783 / 14225 (gossip-MA 2660 / 2611).
-void blocked_xcds(int K, int what, LayoutCfg &cfg)
-{
-    const bool one_kb = what == kBmuf ? (K > 24 && K <= 29) || K > 128 : K > 16 && K <= 32;
-    cfg.xcd_columns_log = one_kb ? 6 : 0;
-    cfg.rotate = K > 32 && K <= 64;
+    const bool one_kb = what == kBmuf && ((K > 16 && K <= 32) || K > 128);
+    cfg.xcd_columns_log = one_kb && size != kCached ? 6 : 0;
+    cfg.rotate = K > 32 && K <= 64 && size != kCached && (what == kMa || size == kLarge);
 }
 
 // log2 of the largest power of two T with K * T <= the shape's slots.
@@ -316,6 +321,16 @@ int64_t count_tiles(const gbmuf_plan_s &pl, int32_t logT)
         if (a < b) count += (((b + 3) >> 2) + T - 1) / T - (a >> 2) / T;
     }
     return count;
+}
+
+// Small plans draw in the kernel whatever q is, so that their syncs may run on several streams at once
+// (gbmuf_info_t.in_kernel_sampling).  Small is 8192 tiles of about 32 columns, not of whatever width the rows
+// shape has: rows of more than 7 neighbours are drawn through LDS, and that is slow.  In the kernel / separate,
+// 16 workers, 8 neighbours, us: 1.0 M parameters (drawn in the kernel) 116 / 78, 2.1 M (separate) 229 / 154.
+bool is_launch_bound(const gbmuf_plan_s &pl, const gbmuf_plan_desc_t *desc)
+{
+    const int slots = pl.named_shape ? desc->tile_threads * desc->tile_slots : pl.K <= 8 ? 256 : pl.K <= 16 ? 512 : pl.K <= 32 ? 1024 : 4096;
+    return can_sample_inline(pl.K, pl.C) && pl.K <= slots && count_tiles(pl, widest_tile(Variant{slots, 1, 1}, pl.K)) <= 8192;
 }
 
 // Split every component into runs of at most T 16-byte columns (the fused kernel's work list).
@@ -375,7 +390,7 @@ int upload(T **dst, const std::vector<T> &src)
 
 const LayoutCfg &cfg_of_all(const gbmuf_plan_s &pl, int layout, int what)
 {
-    return pl.cfg[layout][what][size_of_launch(pl.K * pl.P)];
+    return pl.cfg[layout][what][size_of_launch(pl.K * pl.P, what)];
 }
 
 int make_device_state(gbmuf_plan_s &pl, int32_t sampling)
@@ -400,18 +415,11 @@ int make_device_state(gbmuf_plan_s &pl, int32_t sampling)
     bool can = false;
     int rc = GBMUF_OK;
     for (int l = 0; l < 4 * kSizes && rc == GBMUF_OK; ++l)
-        if (size_occurs(pl, l % kSizes))
+        if (size_occurs(pl, l / kSizes % 2, l % kSizes))
             rc = prepare_kernels(pl.cfg[l / kSizes / 2][l / kSizes % 2][l % kSizes].variant, pl.K, pl.q, pl.mixed_q, pl.C, &can);
     if (rc != GBMUF_OK) return rc;
     if (sampling == GBMUF_SAMPLING_IN_KERNEL && !can) return GBMUF_EUNSUPPORTED;
     pl.sampling = sampling;
-    // Small plans draw in the kernel whatever q is, so that their syncs may run on several streams at once
-    // (gbmuf_info_t.in_kernel_sampling).  Small is 8192 tiles of about 32 columns, not of whatever width the rows
-    // shape has: rows of more than 7 neighbours are drawn through LDS, and that is slow.  In the kernel / separate,
-    // 16 workers, 8 neighbours, us: 1.0 M parameters (drawn in the kernel) 116 / 78, 2.1 M (separate) 229 / 154.
-    const LayoutCfg &rows = cfg_of_all(pl, kRows, kBmuf);
-    const int slots = pl.K <= 8 ? 256 : pl.K <= 16 ? 512 : pl.K <= 32 ? 1024 : 4096;
-    pl.launch_bound = can && count_tiles(pl, pl.named_shape ? rows.logT : widest_tile(Variant{slots, 1, 1}, pl.K)) <= 8192;
     if ((rc = upload(&pl.d_comp, pl.comp)) != GBMUF_OK) return rc;
     for (int s = 0; s < pl.n_sets; ++s)
         if ((rc = upload(&pl.sets[s].d_tiles, pl.sets[s].tiles)) != GBMUF_OK) return rc;
@@ -570,7 +578,8 @@ int enqueue_sync(const gbmuf_plan_s *pl, const int32_t *nbr_dev, const gbmuf_sta
                  int layout, float eta, float zeta, int32_t mode, hipStream_t stream, uint64_t round, const Due &due,
                  bool callers_table = false)
 {
-    const LayoutCfg &cfg = pl->cfg[layout][mode == GBMUF_MODE_GOSSIP_MA ? kMa : kBmuf][size_of_launch(due.values)];
+    const int what = mode == GBMUF_MODE_GOSSIP_MA ? kMa : kBmuf;
+    const LayoutCfg &cfg = pl->cfg[layout][what][size_of_launch(due.values, what)];
     const TileSet &ts = pl->sets[cfg.set];
     // One run of components is launched as exactly its tiles (the list is in component order); for several
     // runs one launch covers all tiles, and the workgroups of components that are not due return at once.
@@ -695,28 +704,23 @@ int gbmuf_plan_create(gbmuf_plan_t **out, const gbmuf_plan_desc_t *desc)
             pl->flags = desc->cache_hints;
             pl->named_shape = desc->tile_threads != 0;
             pl->alternate = desc->sweep == GBMUF_SWEEP_AUTO;
+            pl->launch_bound = is_launch_bound(*pl, desc);
             for (int l = 0; l < 4 * kSizes && rc == GBMUF_OK; ++l) {
                 const int layout = l / kSizes / 2, what = l / kSizes % 2, size = l % kSizes;
                 LayoutCfg &cfg = pl->cfg[layout][what][size];
                 if (pl->named_shape) {
-                    if (!find_variant(desc->tile_threads, desc->tile_slots, &cfg.variant)) rc = GBMUF_EINVAL;
-                } else {
-                    cfg.variant = default_variant(K, layout, what, size);
-                }
-                if (rc != GBMUF_OK) break;
-                if (K > cfg.variant.threads * cfg.variant.slots) { rc = pl->named_shape ? GBMUF_EINVAL : GBMUF_EUNSUPPORTED; break; }
-                // Blocks may be as narrow as min_block_logT says, narrower than a tile too: the kernel
-                // looks an element's block up column by column (where a thread keeps its column, T <= threads).
-                if (pl->named_shape) {
+                    if (!find_variant(desc->tile_threads, desc->tile_slots, &cfg.variant) ||
+                        K > cfg.variant.threads * cfg.variant.slots) { rc = GBMUF_EINVAL; break; }
                     pl->min_block_logT = widest_tile(cfg.variant, K);
                 } else {
+                    cfg.variant = default_variant(K, layout, what, size, draws_in_registers(pl->q));
+                    // where the neighbour rows do not fit beside the widest tile, the next smaller one
+                    if (sync_lds_bytes(cfg.variant, K, pl->q, pl->mixed_q, pl->C, can_sample_inline(K, pl->C)) > kLdsPerWorkgroup)
+                        find_variant(1024, 4, &cfg.variant);
+                    // Blocks may be narrower than a tile: the kernel looks an element's block up column by column
+                    // (where a thread keeps its column, T <= threads, which holds for all shapes of more than 2 workers).
                     pl->min_block_logT = widest_tile(Variant{K <= 16 ? 1024 : K <= 64 ? 2048 : 4096, 1, 1}, K);
-                    const Variant &v = K <= 128 ? kMany : kVeryMany;
-                    // the wider shapes for many workers, where the neighbour rows fit beside their tile
-                    if (takes_many(K, layout, what) &&
-                        sync_lds_bytes(v, K, pl->q, pl->mixed_q, pl->C, can_sample_inline(K, pl->C)) <= kLdsPerWorkgroup)
-                        cfg.variant = v;
-                    if (layout == kBlocked) blocked_xcds(K, what, cfg);
+                    if (layout == kBlocked) blocked_xcds(K, what, size, cfg);
                 }
                 cfg.logT = widest_tile(cfg.variant, K);
                 cfg.workgroups_per_cu = desc->workgroups_per_cu != 0 ? desc->workgroups_per_cu
@@ -725,7 +729,7 @@ int gbmuf_plan_create(gbmuf_plan_t **out, const gbmuf_plan_desc_t *desc)
             if (rc == GBMUF_OK) {
                 // one tile list per distinct tile width
                 for (int l = 0; l < 4 * kSizes; ++l) {
-                    if (!size_occurs(*pl, l % kSizes)) continue;
+                    if (!size_occurs(*pl, l / kSizes % 2, l % kSizes)) continue;
                     LayoutCfg &cfg = pl->cfg[l / kSizes / 2][l / kSizes % 2][l % kSizes];
                     int found = -1;
                     for (int s2 = 0; s2 < pl->n_sets; ++s2)

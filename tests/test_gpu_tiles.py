@@ -45,20 +45,23 @@ def check_rows(K, q, off, stride, skew=(0, 0, 0), mode=B.MODE_PAPER, rounds=(0, 
     return info
 
 
-# groups are 8 * 32 tiles of 64 columns for rows that share lines (K = 4, 16, 64), and of 8 tiles for those that do not
+# Consecutive tiles that one XCD takes: 2048 columns of a row where rows share cache lines, else one tile; a group is 8
+# such runs.  The lists here end before, at and after one and two groups of the plan's own tile width.
 @pytest.mark.parametrize("K", [4, 7, 16, 33])
-@pytest.mark.parametrize("tiles", [1, 9, 255, 256, 257, 511, 515])
+@pytest.mark.parametrize("tiles", ["1", "9", "group-1", "group", "group+1", "2*group-1", "2*group+3"])
 @pytest.mark.parametrize("odd", [0, 1])
 def test_every_tile_is_taken_once_around_the_xcd_groups(K, tiles, odd):
     _need_gpu()
-    pl = B.Plan([0, 1 << 20], K, 1, 0, seed=0)
-    width = 4 * pl.info.tile_columns
+    mode = B.MODE_GOSSIP_MA if tiles == "2*group-1" else B.MODE_PAPER
+    pl = B.Plan([0, 1 << 15], K, 1, 0, seed=0)               # small, as the plans below are: the same width
+    columns = pl.info.tile_columns_blocked_ma if mode == B.MODE_GOSSIP_MA else pl.info.tile_columns
     pl.destroy()
-    P = tiles * width - (5 if odd else 0)
+    n = eval(tiles, {"group": 8 * max(1, 2048 // columns) if odd else 8})
+    P = n * 4 * columns - (5 if odd else 0)
+    assert K * P < 20_000_000
     stride = P + 3 if odd else -(-P // 1024) * 1024
-    info = check_rows(K, 1, [0, P // 3, P], stride, (1, 0, 3) if odd else (0, 0, 0),
-                      mode=B.MODE_GOSSIP_MA if tiles == 511 else B.MODE_PAPER)
-    assert info.n_tiles in (tiles, tiles + 1)                           # the component edge cuts one tile
+    info = check_rows(K, 1, [0, P // 3, P], stride, (1, 0, 3) if odd else (0, 0, 0), mode=mode)
+    assert mode == B.MODE_GOSSIP_MA or info.n_tiles in (n, n + 1)         # the component edge cuts one tile
 
 
 # one piece is 256 columns of 4 floats; runs of 32 pieces when rows are written; the destination's first column

@@ -123,3 +123,19 @@ def test_only_small_plans_draw_through_lds(K, p, q, most):
         for place in ("blocked", "rows"):
             assert len(launches(lambda s: pl.sync_state(fake_state(pl, place), 0.9, 1.0, B.MODE_PAPER, 0, s))) == expect
         pl.destroy()
+
+
+# Small states of many workers: a tile for every CU.
+@pytest.mark.parametrize("K", [40, 64, 100, 130, 200, 256, 400, 512, 600, 1024])
+def test_small_states_are_cut_into_enough_tiles(K):
+    P = 4 * 1024 * 1024 // K
+    info = B.Plan([0, P], K, 2, 0).info
+    assert info.n_tiles >= 256 and P / (4 * info.tile_columns_blocked) >= 256 and P / (4 * info.tile_columns_blocked_ma) >= 128
+
+
+# One rule per range of workers: inside a range nothing changes from one number of workers to the next.
+@pytest.mark.parametrize("lo,hi", [(17, 32), (33, 64), (65, 128), (129, 512), (513, 1024)])
+@pytest.mark.parametrize("values", [3_000_000, 200_000_000, 1_500_000_000])
+def test_shapes_change_only_between_ranges_of_workers(lo, hi, values):
+    infos = [B.Plan([0, values // K], K, 2, 0).info for K in range(lo, hi + 1, max(1, (hi - lo) // 16))]
+    assert len({(i.threads, i.threads_blocked, i.workgroups_per_cu_blocked) for i in infos}) == 1
