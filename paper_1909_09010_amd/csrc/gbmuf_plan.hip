@@ -290,6 +290,14 @@ int32_t default_workgroups_per_cu(int K, int layout, int what, int logT, int siz
     return K <= 16 ? std::max(2, (aim + columns / 2) / columns) : 2;
 }
 
+// What a plan that names its shape gets if it does not name a bound: no bound on rows, few on blocked state.
+int32_t named_workgroups_per_cu(int K, int layout, int what)
+{
+    if (layout == kRows) return 0;
+    if (what == kMa) return K <= 16 ? 4 : 2;
+    return K <= 4 ? 4 : K <= 32 ? 2 : 1;
+}
+
 // Which XCD takes which tiles of a blocked state (tile_of_block).  512 bytes of a row (one tile of 32 columns) or
 // 1 KB in one run: from 17 to 32 workers 1 KB (1 % from the best of every point, 512 B 2 %), 512 workers 13112 / 12278 us;
 // but 16 workers x 278.6 M 16295 / 16630, and 33 to 64 are within 0.3 %; 2 KB is the worst (256 workers 5224 / 5907).
@@ -724,7 +732,8 @@ int gbmuf_plan_create(gbmuf_plan_t **out, const gbmuf_plan_desc_t *desc)
                 }
                 cfg.logT = widest_tile(cfg.variant, K);
                 cfg.workgroups_per_cu = desc->workgroups_per_cu != 0 ? desc->workgroups_per_cu
-                                                                     : default_workgroups_per_cu(K, layout, what, cfg.logT, size);
+                                        : pl->named_shape ? named_workgroups_per_cu(K, layout, what)
+                                                          : default_workgroups_per_cu(K, layout, what, cfg.logT, size);
             }
             if (rc == GBMUF_OK) {
                 // one tile list per distinct tile width

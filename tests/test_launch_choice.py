@@ -139,3 +139,17 @@ def test_small_states_are_cut_into_enough_tiles(K):
 def test_shapes_change_only_between_ranges_of_workers(lo, hi, values):
     infos = [B.Plan([0, values // K], K, 2, 0).info for K in range(lo, hi + 1, max(1, (hi - lo) // 16))]
     assert len({(i.threads, i.threads_blocked, i.workgroups_per_cu_blocked) for i in infos}) == 1
+
+
+# A plan that names its shape but no bound: none on rows, a few workgroups per CU on blocked state.
+@pytest.mark.gpu
+@pytest.mark.parametrize("K,tile,blocked", [(4, (256, 1), 4), (8, (256, 1), 2), (16, (256, 4), 2), (32, (1024, 1), 2), (48, (512, 4), 1), (64, (1024, 1), 1)])
+@pytest.mark.parametrize("P", [4096, 20_000_000])
+def test_named_shapes_are_bound_by_layout_alone(K, tile, blocked, P):
+    need_gpu()
+    pl = B.Plan([0, P], K, 2, 0, tile=tile)
+    needed = 16 * tile[0] * tile[1] + 16 * K                             # the tile and the neighbour rows, 4 ids each at most 8
+    assert launches(lambda s: pl.sync_state(fake_state(pl, "rows"), 0.9, 1.0, B.MODE_PAPER, 0, s))[-1][2] <= needed
+    lds = launches(lambda s: pl.sync_state(fake_state(pl), 0.9, 1.0, B.MODE_PAPER, 0, s))[-1][2]
+    assert pl.info.workgroups_per_cu_blocked == blocked and lds >= 160 * 1024 // blocked - 4096
+    pl.destroy()
