@@ -278,6 +278,20 @@ Variant default_variant(int K, int layout, int what, int size, bool few)
     return v;
 }
 
+// Small plans with rows of more than 7 neighbours draw them through LDS in every workgroup (launch_bound), a thread a
+// row: a chain that is hidden by many workgroups, not by large ones, and paid per tile.  9 neighbours, us, these
+// shapes / the default ones: 36 workers x 0.33 M blocked 112 / 167, rows 85 / 166; 17 x 0.71 M blocked 107 / 135.
+Variant lds_drawing_variant(int K, int layout)
+{
+    Variant v{1024, 4, 4};
+    if (layout == kBlocked && K > 4) {
+        if (K <= 64) find_variant(512, K <= 16 ? 1 : K <= 32 ? 2 : 4, &v);
+    } else if (K <= 32) {
+        find_variant(256, K <= 8 ? 1 : K <= 16 ? 2 : 4, &v);
+    }
+    return v;
+}
+
 // Resident workgroups per CU (0: as many as fit).  Blocked: about 1200 columns, but two workgroups at least: 5 workers
 // 1584 us at four, 1876 at two; 10 workers 2219 at four, 2648 at two; 14 workers 3122 at three, 3237 at two; 16 workers
 // x 278.6 M 16290 at two, 17200 at three.  Rows: two, or six of the small ones of up to 4 workers.  A state that stays
@@ -713,6 +727,8 @@ int gbmuf_plan_create(gbmuf_plan_t **out, const gbmuf_plan_desc_t *desc)
             pl->named_shape = desc->tile_threads != 0;
             pl->alternate = desc->sweep == GBMUF_SWEEP_AUTO;
             pl->launch_bound = is_launch_bound(*pl, desc);
+            const bool through_lds = !draws_in_registers(pl->q) && !pl->named_shape &&
+                                     (desc->sampling == GBMUF_SAMPLING_IN_KERNEL || (desc->sampling == GBMUF_SAMPLING_AUTO && pl->launch_bound));
             for (int l = 0; l < 4 * kSizes && rc == GBMUF_OK; ++l) {
                 const int layout = l / kSizes / 2, what = l / kSizes % 2, size = l % kSizes;
                 LayoutCfg &cfg = pl->cfg[layout][what][size];
@@ -721,7 +737,8 @@ int gbmuf_plan_create(gbmuf_plan_t **out, const gbmuf_plan_desc_t *desc)
                         K > cfg.variant.threads * cfg.variant.slots) { rc = GBMUF_EINVAL; break; }
                     pl->min_block_logT = widest_tile(cfg.variant, K);
                 } else {
-                    cfg.variant = default_variant(K, layout, what, size, draws_in_registers(pl->q));
+                    cfg.variant = through_lds ? lds_drawing_variant(K, layout)
+                                              : default_variant(K, layout, what, size, draws_in_registers(pl->q));
                     // where the neighbour rows do not fit beside the widest tile, the next smaller one
                     if (sync_lds_bytes(cfg.variant, K, pl->q, pl->mixed_q, pl->C, can_sample_inline(K, pl->C)) > kLdsPerWorkgroup)
                         find_variant(1024, 4, &cfg.variant);
@@ -732,6 +749,7 @@ int gbmuf_plan_create(gbmuf_plan_t **out, const gbmuf_plan_desc_t *desc)
                 }
                 cfg.logT = widest_tile(cfg.variant, K);
                 cfg.workgroups_per_cu = desc->workgroups_per_cu != 0 ? desc->workgroups_per_cu
+                                        : through_lds     ? 0
                                         : pl->named_shape ? named_workgroups_per_cu(K, layout, what)
                                                           : default_workgroups_per_cu(K, layout, what, cfg.logT, size);
             }

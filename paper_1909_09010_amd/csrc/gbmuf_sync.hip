@@ -159,7 +159,7 @@ struct Rows<NT, kAnyQ> {
     {
         const int K = a.K, q = td.q, pitch = ids_pitch(kAnyQ, a.q);
         const int32_t *table = a.nbr + static_cast<int64_t>(td.comp) * K * a.q;
-        if (a.flags & kFlagSampledTable) {
+        if ((a.flags & kFlagSampledTable) && 4 * K <= NT) { // with more workers every thread has a row to sort
             const int places = max(q, 1);                   // a component without neighbours: the worker itself
             for (int i = threadIdx.x; i < K * places; i += NT) {
                 const int w = i / places, j = i - w * places;

@@ -153,3 +153,10 @@ def test_named_shapes_are_bound_by_layout_alone(K, tile, blocked, P):
     lds = launches(lambda s: pl.sync_state(fake_state(pl), 0.9, 1.0, B.MODE_PAPER, 0, s))[-1][2]
     assert pl.info.workgroups_per_cu_blocked == blocked and lds >= 160 * 1024 // blocked - 4096
     pl.destroy()
+
+
+# Plans that draw rows of more than 7 neighbours through LDS keep tiles of 32 columns: the draws are paid per tile.
+@pytest.mark.parametrize("K,P", [(10, 100_000), (17, 700_000), (24, 500_000), (36, 330_000), (64, 60_000)])
+def test_drawing_through_lds_takes_wide_tiles(K, P):
+    info = B.Plan([0, P], K, 9, 5).info
+    assert info.tile_columns >= 32 and info.tile_columns_blocked >= 32
