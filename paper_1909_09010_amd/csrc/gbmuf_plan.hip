@@ -538,10 +538,11 @@ gbmuf_state_t rows_state(float *theta, float *omega, float *delta, int64_t strid
 // on 128-byte lines neighbouring tiles share a line, and unless both are taken by one XCD its L2 cannot
 // join the halves: every shared line is fetched twice and written in two pieces.  With 32 KB per XCD one
 // line in 256 is shared.  16 workers x 35.0 M in plain tensors: 3944 GB/s at 512 B, 4984 at 4 KB, 5073 at
-// 16 KB (aligned rows: 5161); 64 workers x 26.9 M: 3880 at 1 KB, 4405 at 4 KB, 5163 at 32 KB.
-int32_t xcd_run(const LayoutCfg &cfg, const Placement &at, const gbmuf_state_t *st, int32_t mode)
+// 16 KB (aligned rows: 5161); 64 workers x 26.9 M: 3880 at 1 KB, 4405 at 4 KB, 5163 at 32 KB.  (The stride of a single
+// worker is no distance between rows: 1 x 600 M, odd stride, 2497 us; by 32 KB 2694.)
+int32_t xcd_run(const LayoutCfg &cfg, const Placement &at, const gbmuf_state_t *st, int32_t mode, int K)
 {
-    uintptr_t low = reinterpret_cast<uintptr_t>(st->theta) | (static_cast<uintptr_t>(at.stride | at.block_extra) << 2);
+    uintptr_t low = reinterpret_cast<uintptr_t>(st->theta) | (static_cast<uintptr_t>((K > 1 ? at.stride : 0) | at.block_extra) << 2);
     if (mode != GBMUF_MODE_GOSSIP_MA)
         low |= reinterpret_cast<uintptr_t>(st->omega) | reinterpret_cast<uintptr_t>(st->delta);
     const int32_t columns_log = (low & 127u) ? 11 : cfg.xcd_columns_log;
@@ -623,7 +624,7 @@ int enqueue_sync(const gbmuf_plan_s *pl, const int32_t *nbr_dev, const gbmuf_sta
     a.key0 = static_cast<uint32_t>(pl->seed); a.key1 = static_cast<uint32_t>(pl->seed >> 32);
     a.round0 = static_cast<uint32_t>(round); a.round1 = static_cast<uint32_t>(round >> 32);
     a.step = round;
-    a.xcd_log = xcd_run(cfg, at, st, mode);
+    a.xcd_log = xcd_run(cfg, at, st, mode, pl->K);
     return launch_sync(cfg.variant, a, end - first, lds_floor(pl, cfg), stream);
 }
 

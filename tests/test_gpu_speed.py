@@ -58,3 +58,10 @@ def test_more_neighbours_than_fit_registers(K, mode):
     P = 60_000_000 // K // 1024 * 1024
     seven, nine = (sync_us([0, P], K, q, P, p=5, mode=mode, sampling=B.SAMPLING_SEPARATE) for q in (7, 9))
     assert nine < 1.32 * seven, (nine, seven)
+
+
+# A single worker's stride is no distance between rows: odd or padded, the same tiles go to the same XCDs.
+def test_the_stride_of_a_single_worker_does_not_matter():
+    P = 150_000_000
+    padded, odd = (sync_us([0, P], 1, 0, stride) for stride in (P + 1024 - P % 1024, P + 3))
+    assert abs(odd / padded - 1) < 0.03, (odd, padded)
