@@ -60,8 +60,11 @@ def test_more_neighbours_than_fit_registers(K, mode):
     assert nine < 1.32 * seven, (nine, seven)
 
 
-# A single worker's stride is no distance between rows: odd or padded, the same tiles go to the same XCDs.
+# A single worker's stride is no distance between rows: odd or padded, the same tiles go to the same XCDs.  Both run on the
+# same buffers, in turn; where an odd stride counted as rows that share cache lines it took 8 % longer.
 def test_the_stride_of_a_single_worker_does_not_matter():
     P = 150_000_000
-    padded, odd = (sync_us([0, P], 1, 0, stride) for stride in (P + 1024 - P % 1024, P + 3))
-    assert abs(odd / padded - 1) < 0.03, (odd, padded)
+    pl, st = B.Plan([0, P], 1, 0, 0, seed=1), rows(1, P + 1024)
+    padded, odd = (min(us(lambda r, s: pl.sync(*st, stride, 0.9, 1.0, B.MODE_PAPER, r, s)) for _ in range(2))
+                   for stride in (P + 1024 - P % 1024, P + 3))
+    assert odd < 1.05 * padded, (odd, padded)
