@@ -60,9 +60,42 @@ __global__ void sample_kernel(SampleArgs a)
 // Bound by HBM reads: what counts is that 32-48 KB per CU are in flight and no more (the host
 // sets the bound), and which XCD reads what.  64 workers x 57.8 M, blocked: 8 rows a time, four waves per CU, XCDs
 // rotated 2357 us (6373 GB/s); 4 rows, eight waves 2454; 8 rows, no bound 2597.  8 x 100 M, blocked: 8 rows, six
-// waves 560, four waves 653, no bound 641.  16 x 35.0 M in plain tensors (odd P): 420, one float per thread 431;
+// waves 560, four waves 653, no bound 641.  16 x 35.0 M in plain tensors (odd P): 408, one float per thread 431;
 // 8 x 35.0 M: 219, 243.
 // ---------------------------------------------------------------------------------------
+// s plus the last n <= B rows, all their loads in flight; a row that is not there is read as the last one.  No load of
+// an average is behind a branch: a guard on each cost a wait for those before it.  1024 workers x 36.5 K plain:
+// 93 us guarded, 70 now, the last P % 4 elements by one thread 333.
+template <int B, class V, class Load>
+__device__ __forceinline__ V add_last(V s, const float *col, int n, int64_t stride, Load load)
+{
+    if constexpr (B > 1)
+        if (n <= B / 2) return add_last<B / 2>(s, col, n, stride, load);
+    V v[B];
+#pragma unroll
+    for (int j = 0; j < B; ++j) v[j] = load(col + static_cast<int64_t>(min(j, n - 1)) * stride);
+#pragma unroll
+    for (int j = 0; j < B; ++j)
+        if (j < n) s = s + v[j];
+    return s;
+}
+
+template <int B, class V, class Load>
+__device__ __forceinline__ V worker_mean(const float *col, int K, int64_t stride, float inv, Load load)
+{
+    V s = load(col);
+    int k = 1;
+    for (; k + B <= K; k += B) {                           // B rows in flight, then added in ascending order
+        V v[B];
+#pragma unroll
+        for (int j = 0; j < B; ++j) v[j] = load(col + static_cast<int64_t>(k + j) * stride);
+#pragma unroll
+        for (int j = 0; j < B; ++j) s = s + v[j];
+    }
+    if (k < K) s = add_last<B>(s, col + static_cast<int64_t>(k) * stride, K - k, stride, load);
+    return s * inv;
+}
+
 template <int B>
 __global__ __launch_bounds__(64) void final_average_kernel(const float *theta, Placement at, int K, int64_t P,
                                                            float inv, float *out, int xcd_log, int rotate)
@@ -78,24 +111,11 @@ __global__ __launch_bounds__(64) void final_average_kernel(const float *theta, P
     const int64_t n4 = P >> 2;
     if (i < n4) {
         const float *col = theta + placed(at, i << 2);
-        v4f s = load4(col, false);
-        for (int k0 = 1; k0 < K; k0 += B) {                // B rows in flight, then added in ascending order
-            v4f v[B];
-#pragma unroll
-            for (int j = 0; j < B; ++j)
-                if (k0 + j < K) v[j] = load4(col + static_cast<int64_t>(k0 + j) * at.stride, false);
-#pragma unroll
-            for (int j = 0; j < B; ++j)
-                if (k0 + j < K) s = s + v[j];
-        }
-        store4(out + (i << 2), s * inv, false);
-    } else if (i == n4) {                                  // the last P % 4 elements
-        for (int64_t e = n4 << 2; e < P; ++e) {
-            const float *col = theta + placed(at, e);
-            float s = col[0];
-            for (int k = 1; k < K; ++k) s = s + col[static_cast<int64_t>(k) * at.stride];
-            out[e] = s * inv;
-        }
+        store4(out + (i << 2), worker_mean<B, v4f>(col, K, at.stride, inv, [](const float *p) { return load4(p, false); }), false);
+    } else if (static_cast<int64_t>(b) * 64 >= n4 && threadIdx.x < (P & 3)) {
+        // the last P % 4 elements, one thread each of a wave that holds no columns, for which they would wait
+        const int64_t e = (n4 << 2) + threadIdx.x;
+        out[e] = worker_mean<B, float>(theta + placed(at, e), K, at.stride, inv, [](const float *p) { return *p; });
     }
 }
 
@@ -150,7 +170,7 @@ int launch_final_average(const float *theta, const Placement &at, int K, int64_t
 {
     if (P <= 0) return GBMUF_OK;
     size_t lds_floor = shape.lds_floor < 60 * 1024 ? shape.lds_floor : 60 * 1024;   // stays below what needs a raised limit
-    const int64_t blocks = ((P >> 2) + 1 + 63) / 64;
+    const int64_t blocks = ((P >> 2) + 63) / 64 + ((P & 3) != 0);
     if (blocks > 0x7fffffffLL) return GBMUF_EUNSUPPORTED;
     Placement pl = at;
     int xcd_log = shape.xcd_log, rotate = shape.rotate ? 1 : 0;

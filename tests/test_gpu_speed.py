@@ -60,6 +60,17 @@ def test_more_neighbours_than_fit_registers(K, mode):
     assert nine < 1.32 * seven, (nine, seven)
 
 
+# The last P % 4 elements of a final average are read by threads of their own, with as many rows in flight as a column of
+# 4: measured 1.0 to 1.1, and 9 where one thread reads them one after the other.
+@pytest.mark.parametrize("rest", [1, 3])
+def test_the_last_elements_of_an_average_wait_for_nothing(rest):
+    K, P = 1024, 4000
+    st, out = torch.randn(K * (P + 4), device=DEV), torch.empty(P + 4, device=DEV)
+    plans = {n: B.Plan([0, P + n], K, 0, 0, seed=0) for n in (0, rest)}
+    whole, cut = (us(lambda r, s: plans[n].final_average(st, P + 4, out, s)) for n in (0, rest))
+    assert cut < 1.6 * whole, (cut, whole)
+
+
 # A single worker's stride is no distance between rows: odd or padded, the same tiles go to the same XCDs.  Both run on the
 # same buffers, in turn; where an odd stride counted as rows that share cache lines it took 8 % longer.
 def test_the_stride_of_a_single_worker_does_not_matter():

@@ -139,9 +139,9 @@ def test_many_workers(K, q, mode):
     pl.destroy()
 
 
-# one workgroup is 64 columns of 4 floats; groups of 8, 16 or 32 workgroups are dealt to the XCDs, the last P % 4 floats
-# go to one thread; more than 4 M values are bounded differently
-@pytest.mark.parametrize("K", [1, 2, 5, 16, 17, 32, 33, 64, 130])
+# one workgroup is 64 columns of 4 floats; groups of 8 or 32 workgroups are dealt to the XCDs, the last P % 4 floats go to
+# one thread each; rows are read 4, 8 or 16 at a time, the last ones in halves of that
+@pytest.mark.parametrize("K", [1, 2, 3, 4, 5, 6, 8, 9, 11, 14, 16, 17, 18, 21, 25, 32, 33, 35, 41, 64, 130])
 @pytest.mark.parametrize("P", [1, 4, 255, 256, 2048 * 4 + 3, 4 * 64 * 33 - 1, 262146])
 def test_final_average_at_its_edges(K, P):
     _need_gpu()
