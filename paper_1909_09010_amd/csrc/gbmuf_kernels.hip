@@ -57,11 +57,9 @@ __global__ void sample_kernel(SampleArgs a)
 // summed in ascending worker id.  One thread per 16-byte column, one wave per workgroup; rows may start
 // at any 4-byte address; 4(K+1) bytes per parameter.
 //
-// Bound by HBM reads: what counts is that 32-48 KB per CU are in flight and no more (the host
-// sets the bound), and which XCD reads what.  64 workers x 57.8 M, blocked: 8 rows a time, four waves per CU, XCDs
-// rotated 2357 us (6373 GB/s); 4 rows, eight waves 2454; 8 rows, no bound 2597.  8 x 100 M, blocked: 8 rows, six
-// waves 560, four waves 653, no bound 641.  16 x 35.0 M in plain tensors (odd P): 408, one float per thread 431;
-// 8 x 35.0 M: 219, 243.
+// Bound by HBM reads, and by the latency of the caches where they hold the rows: what counts is how many loads a CU has
+// in flight, and beyond the caches that there are no more than HBM takes; the host chooses both by the size of the sum
+// and says with which figures.
 // ---------------------------------------------------------------------------------------
 // s plus the last n <= B rows, all their loads in flight; a row that is not there is read as the last one.  No load of
 // an average is behind a branch: a guard on each cost a wait for those before it.  1024 workers x 36.5 K plain:

@@ -558,6 +558,39 @@ size_t lds_floor(const gbmuf_plan_s *pl, const LayoutCfg &cfg)
     return share > 0 ? static_cast<size_t>(share) : 0;
 }
 
+// Rows in flight per thread, resident one-wave workgroups per CU (32: as many as fit) and who reads what, for a final
+// average.  us on MI355X, in the order of the rules:
+//   sums of up to 60 M values come from the caches, whose latency more waves hide, with enough rows per thread that few
+//     workers take one pass: 8 x 4.2 M padded 25 (16 rows x 3 waves 33), 64 x 0.6 M 26 (4 x 8: 30), 1024 x 36 K 66 (8
+//     rows 87).
+//   one worker is a copy: 590 M 746, 16 waves 770, 8 waves 1303.
+//   blocked: as many loads as HBM takes best, fewer waves the more rows each has in flight: 8 x 16.1 M 97 (8 rows x 8; x
+//     32 107), 16 x 31.8 M 355 (16 x 6; x 32 383), 32 x 16.2 M 340 (16 x 4; x 32 376), 64 x 9.4 M 385 (8 x 4, XCDs
+//     rotated; x 8 399), 128 x 3.9 M 317 (16 x 3; x 32 336).
+//   rows: 2 x 61.6 M 123 (4 x 16; x 8 156), 4 x 134 M 433 (4 x 12; x 8 449), 8 x 16.1 M 100 (4 x 8; x 32 108), 16 x 31.8 M 362 (x
+//     32 400), 64 x 9.4 M 395 (x 32 424), 512 x 1 M 339 (16 x 6; 4 x 8 366).  Rows that share cache lines (xcd_run): 4 KB
+//     per XCD, 4 x 134 M 442, workgroup by workgroup 447.
+AverageShape average_shape(const gbmuf_plan_s *pl, int layout, bool shared_lines)
+{
+    const int K = pl->K;
+    AverageShape s{};
+    int waves = 32;
+    if (static_cast<int64_t>(K) * pl->P <= 60000000) {
+        s.rows_in_flight = K <= 4 ? 4 : K <= 16 ? 8 : 16;
+        s.xcd_log = K > 1 ? 2 : 0;
+    } else if (layout == kBlocked) {
+        s.rows_in_flight = K <= 3 ? 4 : K <= 8 || (K > 32 && K <= 64) ? 8 : 16;
+        waves = K <= 3 ? 32 : K <= 8 ? 8 : K <= 16 ? 6 : K <= 64 ? 4 : 3;
+        s.rotate = K > 32 && K <= 64;
+    } else {
+        s.rows_in_flight = K <= 64 ? 4 : 16;
+        waves = K == 1 ? 32 : K <= 3 ? 16 : K <= 7 ? 12 : K <= 64 ? 8 : 6;
+        s.xcd_log = K > 1 && shared_lines ? 2 : 0;
+    }
+    if (waves < 32 && pl->lds_per_cu > 0) s.lds_floor = static_cast<size_t>(std::max(0, pl->lds_per_cu / waves - 2048));
+    return s;
+}
+
 // What one call updates.
 struct Due {
     int64_t values = 0;                                       // K times the elements of the components that are due
@@ -981,23 +1014,8 @@ int gbmuf_final_average_state(const gbmuf_plan_t *plan, const gbmuf_state_t *sta
     int rc = check_state(plan, state, false, &at, &layout);
     if (rc != GBMUF_OK) return rc;
     if ((rc = check_device(plan)) != GBMUF_OK) return rc;
-    // Measured on MI355X, us (waves: resident one-wave workgroups per CU):
-    //   blocked, 48 KB in flight per CU up to 32 workers: 8 x 100 M, 16 loads (8 used) x 6 waves 560, x 4 653;
-    //     16 x 119.2 M, 16 x 3, 4 KB of a row per XCD 1284, x 4 tile by tile 1316; 32 KB above: see the kernel.
-    //   rows: 16 x 35.0 M plain, 4 x 8 waves 408, 8 x unbounded 440; 64 x 35.0 M padded, 8 x 4 waves, 4 KB per
-    //     XCD 1565, 8 x unbounded 1688.
-    // Sums of a few MB, which take no longer than their first loads, run unbounded.
     const int K = plan->K;
-    AverageShape shape{8, 0, 2, false};
-    int waves = 4;
-    if (layout == kBlocked) {
-        if (K <= 32) { shape.rows_in_flight = 16; waves = std::max(3, 48 / K); }
-        else { shape.xcd_log = 0; shape.rotate = true; }
-    } else if (K <= 32) {
-        shape.rows_in_flight = 4; shape.xcd_log = 1; waves = 8;
-    }
-    if (plan->lds_per_cu > 0 && waves < 32 && K * plan->P > 4000000)
-        shape.lds_floor = static_cast<size_t>(std::max(0, plan->lds_per_cu / waves - 2048));
+    const AverageShape shape = average_shape(plan, layout, at.stride % 32 != 0 || reinterpret_cast<uintptr_t>(state->theta) % 128 != 0);
     return launch_final_average(state->theta, at, K, plan->P, 1.0f / static_cast<float>(K), out_dev, shape,
                                 static_cast<hipStream_t>(stream));
 }

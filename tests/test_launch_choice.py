@@ -160,3 +160,19 @@ def test_named_shapes_are_bound_by_layout_alone(K, tile, blocked, P):
 def test_drawing_through_lds_takes_wide_tiles(K, P):
     info = B.Plan([0, P], K, 9, 5).info
     assert info.tile_columns >= 32 and info.tile_columns_blocked >= 32
+
+
+# A final average asks for LDS that bounds the resident workgroups per CU, except where the more the faster: sums that
+# the caches hold, and a single worker, which is a copy (1 x 590 M: 1303 us with 8 workgroups per CU, 746 without bound).
+@pytest.mark.gpu
+@pytest.mark.parametrize("place,aligned", [("blocked", True), ("rows", True), ("rows", False)])
+@pytest.mark.parametrize("K,values,bounded", [(1, 600_000_000, False), (1, 9_000_000, False), (8, 40_000_000, False),
+                                              (2, 150_000_000, True), (16, 150_000_000, True), (64, 59_000_000, False),
+                                              (1024, 40_000_000, False), (1024, 600_000_000, True)])
+def test_what_bounds_a_final_average(K, values, bounded, place, aligned):
+    need_gpu()
+    pl = B.Plan([0, values // K], K, 0, 0, seed=0)
+    (blocks, threads, lds), = launches(lambda s: pl.final_average_state(fake_state(pl, place, aligned), 1 << 36, s))
+    P = values // K
+    assert threads == 64 and blocks == -(-(P // 4) // 64) + (P % 4 > 0)
+    assert (lds > 0) == (bounded and not (K <= 3 and place == "blocked"))
