@@ -95,7 +95,7 @@ struct CopyArgs {
     Placement da, sa;
     int64_t P;
     int32_t K;
-    int32_t run_log;         // log2 of the pieces of one worker that follow each other (set by the launch)
+    uint32_t run_len;        // pieces of one worker that follow each other (set by the launch)
 };
 
 // One tile shape of the fused kernel: threads per workgroup and 16-byte slots per thread.

@@ -5,6 +5,8 @@
 
 #include "../../include/gbmuf.h"
 
+#include <algorithm>
+
 #pragma clang fp contract(off)
 
 namespace gbmuf {
@@ -121,20 +123,23 @@ __global__ __launch_bounds__(64) void final_average_kernel(const float *theta, P
 // Copy of up to three state arrays between two placements (blockIdx.z = array), one 16-byte column
 // per thread, one load and one store in flight each: more of either per thread is slower here (5.6
 // against 6.2 TB/s on a plain copy).  The rows are cut into pieces of 256 columns (4 KB); the pieces
-// are walked in runs of 2^run_log pieces of one worker, then the same run of the next worker, so that
-// each side is a few moving stretches of memory.  Columns are counted from the destination row's
-// 128-byte line, so that stores cover whole lines; the loads take any 4-byte address.
-// Bound by HBM.  16 workers x 35.0 M, per array: plain rows (odd stride) to blocked 800 us, worker by
-// worker 817, with one float per thread 1332; blocked to plain rows 787, worker by worker 854, with
-// columns counted from the row start 790.  Three arrays, runs of 128 KB / 32 KB / 4 KB: to blocked, 4 workers x
-// 79.3 M 1318 / 1311 / 1375, 64 x 10.1 M 2831 / 3023 / 2993; to plain rows 4 x 79.3 M 1365 / 1411 / 1435, 64 x 10.1 M
-// 3012 / 2910 / 2940 (padded 2750 / 2586 / 2710).
+// are walked in runs of run_len pieces of one worker, then the same run of the next worker.  Columns are counted from
+// the destination row's 128-byte line, so that stores cover whole lines; the loads take any 4-byte address.
+// Bound by HBM, which takes two long streams best: rows are copied whole, worker by worker, and so are arrays that the
+// caches hold (10 x 1.2 M to blocked 18 us, in pieces 22).  In a blocked source every
+// 32 KB of a row is followed by 32 KB of the next worker, and runs of a few blocks walk it nearly in its own order; into
+// a blocked destination a piece at a time does the same for few workers.  us for three arrays, runs of 4 KB / 16 KB /
+// 128 KB / whole rows:
+//   padded rows: 4 workers x 128 M 1985 / 2045 / 2072 / 1987, 64 x 7.9 M 2278 / 2343 / 2378 / 1966.
+//   blocked to blocked: 16 x 31.5 M 2288 / 2093 / 2025 / 2390, 64 x 7.9 M 2275 / 2052 / 2173 / 2378.
+//   blocked to plain rows: 16 x 31.5 M 2201 / 2205 / 2198 / 2295, 200 x 2.4 M 2183 / 2153 / 2201 / 2292.
+//   plain rows to blocked: 16 x 31.5 M 2132 / 2197 / 2178 / 2218, 64 x 7.9 M 2336 / 2307 / 2179 / 2239.
 // ---------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void state_copy_kernel(CopyArgs a)
 {
     const uint32_t i = blockIdx.y * gridDim.x + blockIdx.x, K = static_cast<uint32_t>(a.K);
-    const uint32_t run = i >> a.run_log, group = run / K, w = run - group * K;
-    const int64_t piece = (static_cast<int64_t>(group) << a.run_log) + (i & ((1u << a.run_log) - 1u));
+    const uint32_t run = i / a.run_len, group = run / K, w = run - group * K;
+    const int64_t piece = static_cast<int64_t>(group) * a.run_len + (i - run * a.run_len);
     const float *src = a.src[blockIdx.z] + w * a.sa.stride;
     float *dst = a.dst[blockIdx.z] + w * a.da.stride;
     const int64_t head = static_cast<int64_t>((reinterpret_cast<uintptr_t>(dst) >> 2) & 31u);
@@ -184,11 +189,15 @@ int launch_state_copy(const CopyArgs &c, int arrays, hipStream_t stream)
 {
     if (c.P <= 0 || c.K <= 0 || arrays <= 0) return GBMUF_OK;
     CopyArgs args = c;
-    // runs of 128 KB of a row, 32 KB when many workers' rows are written
-    args.run_log = c.da.logB == 62 && c.K > 32 ? 3 : 5;
     const int64_t pieces = (c.P + 31 + 1023) / 1024;       // 31: the largest head
-    const int64_t runs = (pieces + (static_cast<int64_t>(1) << args.run_log) - 1) >> args.run_log;
-    const int64_t blocks = (runs * c.K) << args.run_log;
+    int64_t run = pieces;
+    if (c.P * c.K > 30000000) {                            // smaller arrays stay in the caches
+        if (c.sa.logB != 62) run = c.K <= 32 ? 32 : 4;
+        else if (c.da.logB != 62 && c.K <= 16) run = 1;
+    }
+    const int64_t len = std::min(run, pieces);
+    const int64_t blocks = (pieces + len - 1) / len * len * c.K;
+    args.run_len = static_cast<uint32_t>(len);
     // a grid holds fewer than 2^32 threads along x: the rest goes along y
     const int64_t x = blocks < (1 << 23) ? blocks : (1 << 23), y = (blocks + x - 1) / x;
     if (y > 511) return GBMUF_EUNSUPPORTED;                // 17 TB: the kernel counts pieces in 32 bits

@@ -176,3 +176,18 @@ def test_what_bounds_a_final_average(K, values, bounded, place, aligned):
     P = values // K
     assert threads == 64 and blocks == -(-(P // 4) // 64) + (P % 4 > 0)
     assert (lds > 0) == (bounded and not (K <= 3 and place == "blocked"))
+
+
+# A copy launches a workgroup for every 4 KB of a row, or what rounds rows of a blocked source up to whole runs: no
+# multiple of the work where a row is shorter than a run (1024 x 1000 in runs of 32: 58 us, 13 as launched).
+@pytest.mark.gpu
+@pytest.mark.parametrize("to", ["rows", "blocked"])
+@pytest.mark.parametrize("frm", ["rows", "blocked"])
+@pytest.mark.parametrize("K,P", [(1, 5), (16, 1000), (64, 1000), (1024, 1000), (256, 3000), (1024, 40_000), (8, 200_000)])
+def test_a_copy_launches_no_more_than_its_rows(K, P, frm, to):
+    need_gpu()
+    pl = B.Plan([0, P], K, 0, 0, seed=0)
+    (blocks, threads, _), = launches(lambda s: pl.state_copy(fake_state(pl, to), fake_state(pl, frm), 1, s))
+    pieces, run = -(-(P + 31) // 1024), 32 if K <= 32 else 4
+    assert threads == 256 and pieces * K <= blocks
+    assert blocks <= (pieces if frm == "rows" or pieces <= run else -(-pieces // run) * run) * K
