@@ -201,12 +201,12 @@ def test_unsorted_caller_table_gives_the_same_result():
 SHAPES = [
     # K, p, q, offsets, stride_pad, base_shift (floats), rounds
     (4, 1, 1, [0, 5, 12, 12, 4099, 4100, 9001], 0, 0, 4),          # ragged, empty component, unaligned edges
-    (4, 1, 1, [0, 5, 12, 12, 4099, 4100, 9001], 3, 0, 3),          # stride % 4 != 0: 4-byte path
-    (4, 1, 1, [0, 5, 12, 12, 4099, 4100, 9001], 7, 1, 3),          # misaligned base: 4-byte path
+    (4, 1, 1, [0, 5, 12, 12, 4099, 4100, 9001], 3, 0, 3),          # stride % 4 != 0: 16-byte accesses at 4-byte addresses
+    (4, 1, 1, [0, 5, 12, 12, 4099, 4100, 9001], 7, 1, 3),          # misaligned base, the same
     (8, 2, 2, [0, 70000, 70001, 140003], 1, 0, 3),                 # several tiles + ragged tail
     (16, 3, 3, [0, 2048, 133120, 135168, 150000], 0, 0, 3),
     (16, 3, 0, [0, 999, 5000], 0, 0, 3),                           # q = 0: purely local block momentum
-    (16, 3, 6, [0, 999, 5000], 0, 0, 3),                           # q = 2p: local-BMUF, run-time q kernel
+    (16, 3, 6, [0, 999, 5000], 0, 0, 3),                           # q = 2p: local-BMUF
     (64, 5, 4, [0, 4096, 20000, 70001], 3, 0, 2),
     (64, -1, 63, [0, 300, 3001], 0, 0, 2),                         # every other worker: BMUF
     (5, 2, 3, [0, 17, 10000], 0, 0, 3),                            # K not a power of two
@@ -628,6 +628,7 @@ def test_config2_large_vocab_every_tile_rows():
     _run_per_tile(W.get(2), "rows", rounds=4)
 
 
+# rows of an odd length one after the other: every 16-byte access of most rows starts at a 4-byte address
 def test_config2_large_vocab_unpadded_stride_takes_the_4_byte_path():
     _need_gpu()
     w = W.get(2)

@@ -1,0 +1,81 @@
+"""The fused kernel's shapes over the numbers of workers and the sizes of launch that choose them, against the CPU
+oracle (needs an MI355X).  Both sides perform the same IEEE operations in the same order, so every float has to be
+equal.  Element columns do not interact: of large states the oracle replays one element of
+every stretch that is no wider than a tile, and both ends of every component."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1909_09010_amd import binding as B
+from paper_1909_09010_amd import workloads as W
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def check(K, q, off, layout, mode, stride=None, every=None, rounds=(0, 1)):
+    """Syncs in ascending and descending order; `every`: one element of so many is compared, None: all."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    off = np.asarray(off, dtype=np.int64)
+    P, seed, ma = int(off[-1]), 5 + K, mode == B.MODE_GOSSIP_MA
+    pl = B.Plan(off, K, q, (q + 1) // 2 if q > 2 else 0, seed=seed)
+    st = W.DeviceState(K, P, DEV, layout, stride=stride, plan=pl)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    for flat in [st.arena] if st.arena is not None else st.arrays:
+        flat.normal_(0, 0.05, generator=g)
+    cols, red = (np.arange(P, dtype=np.int64), off) if every is None else W.tile_columns(off, every, seed=K)
+    idx = torch.from_numpy(cols).to(DEV)
+    host = [np.ascontiguousarray(st.gather(a, idx).cpu().numpy()) for a in range(3)]
+    pads = [st.padding(a).clone() for a in range(3)]
+    for r in rounds:
+        if layout == "separate":
+            pl.sync(st.arrays[0], *([None, None] if ma else st.arrays[1:]), st.worker_stride, 0.9, 1.0, mode, r, None)
+        else:
+            pl.sync_state(st.desc(gossip_ma=ma), 0.9, 1.0, mode, r, None)
+        oracle.sync(red, K, pl.info.p, q, seed, r, host[0], *([None, None] if ma else host[1:]), np.float32(0.9),
+                    np.float32(1.0), mode)
+    torch.cuda.synchronize()
+    for a, name in enumerate(("theta", "omega", "delta")):
+        assert np.array_equal(st.gather(a, idx).cpu().numpy(), host[a]), (name, pl.info.tile_columns, pl.info.threads)
+        assert torch.equal(st.padding(a), pads[a]), "padding was touched"
+    pl.destroy()
+
+
+def stride_of(layout, P):
+    return None if layout != "odd" else P | 1
+
+
+# States that the caches hold.  Component edges inside tiles, on a block's edge (8192) and one float beside it; more than
+# 9216 floats, so that a rotation of the XCDs would pass its first 8 groups.
+@pytest.mark.parametrize("layout", ["blocked", "separate", "odd"])
+@pytest.mark.parametrize("mode", [B.MODE_PAPER, B.MODE_NO_RESTART, B.MODE_GOSSIP_MA])
+@pytest.mark.parametrize("K,q", [(3, 2), (5, 1), (6, 3), (9, 2), (10, 5), (13, 9), (17, 1), (19, 4), (21, 2), (22, 3), (24, 7), (25, 2), (29, 5),
+                                 (30, 1), (32, 9), (33, 3), (36, 2), (44, 1), (45, 4), (56, 2), (57, 7), (60, 0), (63, 5)])
+def test_small_launches(K, q, mode, layout):
+    off = [0, 5, 4099, 4100, 8192, 8193, 13001, 18437]
+    check(K, q, off, "separate" if layout == "odd" else layout, mode, stride_of(layout, off[-1]), rounds=(0, 1, 2))
+
+
+# Just above what the caches hold (20 M values, 60 M of gossip-MA).
+@pytest.mark.parametrize("layout", ["blocked", "rows", "odd"])
+@pytest.mark.parametrize("mode", [B.MODE_PAPER, B.MODE_GOSSIP_MA])
+@pytest.mark.parametrize("K,q", [(1, 0), (3, 2), (5, 1), (12, 3), (16, 9), (17, 2), (25, 5), (32, 1), (33, 2), (45, 3), (63, 4), (64, 7), (65, 2),
+                                 (128, 3), (129, 1), (300, 9), (512, 2), (513, 3), (1024, 2)])
+def test_middle_launches(K, q, mode, layout):
+    P = (64_000_000 if mode == B.MODE_GOSSIP_MA else 22_000_000) // K
+    off = [0, P // 3 | 1, P // 3 + 70 | 1, P // 3 * 2, P]
+    check(K, q, off, "separate" if layout == "odd" else layout, mode, stride_of(layout, P), every=128 if K <= 128 else 16)
+
+
+# Beyond 500 M values other shapes, orders of the tiles and a sampler launch of their own.
+@pytest.mark.parametrize("layout", ["blocked", "rows", "odd"])
+@pytest.mark.parametrize("K,q,mode", [(3, 1, B.MODE_PAPER), (14, 2, B.MODE_NO_RESTART), (24, 3, B.MODE_PAPER), (40, 1, B.MODE_PAPER), (64, 5, B.MODE_PAPER),
+                                      (100, 2, B.MODE_PAPER), (200, 9, B.MODE_PAPER), (300, 3, B.MODE_PAPER), (700, 2, B.MODE_PAPER),
+                                      (12, 2, B.MODE_GOSSIP_MA), (48, 3, B.MODE_GOSSIP_MA), (200, 1, B.MODE_GOSSIP_MA), (700, 2, B.MODE_GOSSIP_MA)])
+def test_large_launches(K, q, mode, layout):
+    P = 510_000_000 // K
+    off = [0, P // 5 | 1, P // 5 + 70 | 1, P // 3 * 2, P]
+    check(K, q, off, "separate" if layout == "odd" else layout, mode, stride_of(layout, P), every=128 if K <= 128 else 32)
