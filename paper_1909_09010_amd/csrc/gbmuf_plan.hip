@@ -242,6 +242,14 @@ Variant cached_variant(int K, int layout, int what)
     return v;
 }
 
+// log2 of the largest power of two T with K * T <= the shape's slots.
+int32_t widest_tile(const Variant &v, int K)
+{
+    int32_t lg = 0;
+    while ((static_cast<int64_t>(K) << (lg + 1)) <= static_cast<int64_t>(v.threads) * v.slots) ++lg;
+    return lg;
+}
+
 // Beyond the caches what decides is how the accesses that the chip has in flight at one time lie in memory, less how
 // many they are.  Blocked state is one address stream: a short stretch of it is fast, tiles of 512 bytes to 1 KB of
 // a worker row.  Rows are 3K streams: 1 KB and more.  Above 64 workers theta alone fills the tile and omega and
@@ -253,8 +261,10 @@ Variant cached_variant(int K, int layout, int what)
 //   rows: up to 4 workers 256 x 1 [4 %; 1024 x 1 9 %], 5-16 kSixtyFour [2 %; 1024 x 1 2 to 4 %], 17-64 1024 x 2 [1.5 %; 1024 x 4 2 %], large
 //     33-64 kMany [0.7 %; 1024 x 2 2 %], 65-512 1024 x 4 [0.5 %; kMany 1 %], 129-512 large kVeryMany [0.3 %; 1024 x 4 1 to 4 %],
 //     above at all sizes [0 %; 1024 x 4 20 to 50 %].
-//   gossip-MA: up to 16 256 x 4 [3 %; 512 x 2 6 %], 17-64 512 x 4 [1 %; 512 x 2 8 %], 65-512 1024 x 4 [1 %; kVeryMany 5 to 20 %], 129-512 large
-//     and above 512 kVeryMany [0.5 %; 1024 x 4 2 to 40 %].
+//   gossip-MA: 512 x 2 where K rows fill its slots to 7/8, as powers of two do (blocked 2, 4, 7, 8, 14-16, 28-32 [1 %; 256 x 4 5
+//     %]; rows 2, 4 [2 %; 256 x 4 6 %]), else 256 x 4, whose threads idle in whole slots (blocked 3-27 [2 %; 512 x 2 11 %], rows 3-16
+//     [1.5 %; 512 x 2 11 %]), rows 17-32 and blocked 33-64 512 x 4 [2 %; 512 x 2 12 to 20 %], 65-512 1024 x 4 [1 %; kVeryMany 5 to
+//     20 %], 129-512 large and above 512 kVeryMany [0.5 %; 1024 x 4 2 to 40 %].
 Variant default_variant(int K, int layout, int what, int size, bool few)
 {
     Variant v{1024, 4, 4};
@@ -262,7 +272,9 @@ Variant default_variant(int K, int layout, int what, int size, bool few)
     if (size == kCached) return cached_variant(K, layout, what);
     if (few && (K > 512 || (K > 128 && large && what == kBmuf))) return kVeryMany;
     if (what == kMa) {
-        if (K <= 16) find_variant(256, 4, &v);
+        const bool fills = (K << widest_tile({512, 2, 2}, K)) >= 896;
+        if (fills && K <= (layout == kBlocked ? 32 : 4)) find_variant(512, 2, &v);
+        else if (K <= (layout == kBlocked ? 32 : 16)) find_variant(256, 4, &v);
         else if (K <= (layout == kBlocked ? 64 : 32)) find_variant(512, 4, &v);
     } else if (layout == kBlocked) {
         if (K <= 4) find_variant(256, 1, &v);
@@ -324,14 +336,6 @@ void blocked_xcds(int K, int what, int size, LayoutCfg &cfg)
     const bool one_kb = what == kBmuf && ((K > 16 && K <= 32) || K > 128);
     cfg.xcd_columns_log = one_kb && size != kCached ? 6 : 0;
     cfg.rotate = K > 32 && K <= 64 && size != kCached && (what == kMa || size == kLarge);
-}
-
-// log2 of the largest power of two T with K * T <= the shape's slots.
-int32_t widest_tile(const Variant &v, int K)
-{
-    int32_t lg = 0;
-    while ((static_cast<int64_t>(K) << (lg + 1)) <= static_cast<int64_t>(v.threads) * v.slots) ++lg;
-    return lg;
 }
 
 int64_t count_tiles(const gbmuf_plan_s &pl, int32_t logT)

@@ -424,7 +424,7 @@ def test_plans_with_different_lds_needs_coexist():
     _need_gpu()
     off = np.array([0, 3000, 9001], dtype=np.int64)
     K, P, stride = 64, 9001, 9216
-    big = B.Plan(off, K, 40, -1, seed=1)             # run-time q kernel, 64*41 ids
+    big = B.Plan(off, K, 40, -1, seed=1)             # more than 7 neighbours, 64*41 ids
     small = B.Plan(off, K, 8, -1, seed=1)            # same kernel (q+1 > 5), 64*9 ids
     for pl, q in ((big, 40), (small, 8), (big, 40)):
         st = list(_random_state(K, P, stride, 3))
