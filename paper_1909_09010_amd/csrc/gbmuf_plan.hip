@@ -255,9 +255,10 @@ int32_t widest_tile(const Variant &v, int K)
 // a worker row.  Rows are 3K streams: 1 KB and more.  Above 64 workers theta alone fills the tile and omega and
 // Delta are streamed (sync_kernel); above 128 the widest tile wins once there are enough of them, and with more
 // than 7 neighbours it does not (2 to 10 %).
-//   blocked, middle: 5-16 512 x 1 [0.5 %; 256 x 2 2 %], 17-32 512 x 2 [1 %; 1024 x 1 1 %], 33-64 kSixtyFour [0.5 %; 1024 x 2 1 %,
-//     512 x 4 2 %], 65-128 kMany [0.3 %; 1024 x 4 3 %].  Large: 5-16 256 x 2 [0.5 %; 512 x 1 3 %], 17-32 512 x 2 [1 %; 1024 x 1 1 %],
-//     129-512 kVeryMany [0.5 %; kMany 5 %], above at all sizes [1 %; 1024 x 4 6 %].
+//   blocked, middle: 5-16 512 x 1 [0.5 %; 256 x 2 2 %], 17-32 512 x 2 [1 %; 1024 x 1 1 %], 33-39 1024 x 2, whose 64
+//     rows of 32 columns are at most 5/8 full, so that all three arrays may be in flight [33 workers, kSixtyFour 9 %, 36 3 %],
+//     40-64 kSixtyFour [0.5 %; 43 workers, 1024 x 2 3 %; 512 x 4 2 %], 65-128 kMany [0.3 %; 1024 x 4 3 %].
+//     Large: 5-16 256 x 2 [0.5 %; 512 x 1 3 %], 17-32 512 x 2 [1 %; 1024 x 1 1 %], 129-512 kVeryMany [0.5 %; kMany 5 %], above at all sizes [1 %; 1024 x 4 6 %].
 //   rows: up to 4 workers 256 x 1 [4 %; 1024 x 1 9 %], 5-16 kSixtyFour [2 %; 1024 x 1 2 to 4 %], 17-64 1024 x 2 [1.5 %; 1024 x 4 2 %], large
 //     33-64 kMany [0.7 %; 1024 x 2 2 %], 65-512 1024 x 4 [0.5 %; kMany 1 %], 129-512 large kVeryMany [0.3 %; 1024 x 4 1 to 4 %],
 //     above at all sizes [0 %; 1024 x 4 20 to 50 %].
@@ -280,6 +281,7 @@ Variant default_variant(int K, int layout, int what, int size, bool few)
         if (K <= 4) find_variant(256, 1, &v);
         else if (K <= 16) find_variant(large ? 256 : 512, large ? 2 : 1, &v);
         else if (K <= 32) find_variant(512, 2, &v);
+        else if (K < 40) find_variant(1024, 2, &v);
         else v = K <= 64 ? kSixtyFour : kMany;
     } else {
         if (K <= 4) find_variant(256, 1, &v);
