@@ -228,7 +228,8 @@ bool size_occurs(const gbmuf_plan_s &pl, int what, int size)
 //
 // kCached is bound by latency: one slot per thread, and no more threads than make a tile of 16 columns [2 %; the
 // shapes below 5 to 25 %].  More workers than that takes 1024 x 4 [10 %]; the wider kVeryMany leaves most CUs without
-// a tile, 256 workers x 0.023 M: 53 us, 1024 x 4 30.  Gossip-MA, with a third of the loads, takes two slots [3 %; one 6 %].
+// a tile, 256 workers x 0.023 M: 53 us, 1024 x 4 30.  Three states in turn, blocked, 256 x 1 / 512 x 1: 16 x 0.11 M 8.3 /
+// 8.8, 8 x 0.23 M 8.3 / 8.8, 4 x 0.08 M 4.4 / 4.3.  Gossip-MA, with a third of the loads, takes two slots [3 %; one 6 %].
 Variant cached_variant(int K, int layout, int what)
 {
     Variant v{1024, 4, 4};
@@ -236,7 +237,7 @@ Variant cached_variant(int K, int layout, int what)
         if (K <= 64) find_variant(K <= 32 ? 256 : 512, 2, &v);
         else if (K <= 128) find_variant(512, 4, &v);
     } else if (K <= 64) {
-        if (layout == kBlocked) find_variant(K <= 32 ? 512 : 1024, 1, &v);
+        if (layout == kBlocked) find_variant(K <= 16 ? 256 : K <= 32 ? 512 : 1024, 1, &v);
         else find_variant(K <= 16 ? 512 : 1024, K <= 32 ? 1 : 2, &v);
     }
     return v;
