@@ -144,7 +144,7 @@ void ring_of(int32_t w, int32_t K, int32_t p, std::vector<int32_t> &out)
 }
 
 // ---------------------------------------------------------------------------------------
-// Host writing of the sampler (the device has its own in gbmuf_kernels.hip; the tests
+// Host writing of the sampler (the device has its own in gbmuf_device.h; the tests
 // require the two, and the reference implementation, to agree bit for bit).
 // ---------------------------------------------------------------------------------------
 using Words4 = std::array<uint32_t, 4>;

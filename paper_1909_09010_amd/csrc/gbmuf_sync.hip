@@ -117,8 +117,8 @@ struct LdsRow {
     __device__ int32_t &operator()(int32_t x) const { return base[x]; }
 };
 
-// The rows of one tile.  begin() is called before the tile's loads are issued, so that the table's
-// loads, which return in order, are not queued behind them; finish() while they are in flight.
+// The rows of one tile.  begin() is called before the tile's loads are issued, finish() after.  The compiler moves the
+// clamping up and waits for the table first; with the table's loads behind the tile's the time is the same within 1 %.
 // a.nbr == nullptr: thread w draws for worker w.
 template <int NT, int Q1>
 struct Rows {
