@@ -304,7 +304,9 @@ __device__ __forceinline__ void do_tile(const SyncArgs &a, const TileDesc &td, v
             if (const unsigned mk = mask(n)) th[n] = load_col<WHOLE>(a.theta + at(n), mk, nt_load);
         // kSixtyFour: omega and Delta on top of theta would be more in flight per CU than HBM takes best.  64 workers x 115.5 M
         // in components of 1 M, blocked: 29350 us, all at once 29990; 48 workers 2 % less, rows of 5 to 16 within 1 %.
-        if (SLOTS == 2) __builtin_amdgcn_s_waitcnt(0x0F70);       // vmcnt(0)
+        // With more than 4 neighbours the registers leave one workgroup per CU, which needs all of them in flight: 42 workers x
+        // 32.0 M, 5 neighbours, 1.4 % less than theta first.
+        if (SLOTS == 2 && Q1 >= 1 && Q1 <= 5) __builtin_amdgcn_s_waitcnt(0x0F70);       // vmcnt(0)
     }
 #pragma unroll
     for (int n = 0; n < DEPTH; ++n) {
