@@ -118,7 +118,9 @@ typedef struct gbmuf_plan_desc {
                                        by K and layout; a pair that is not built in -> EINVAL     */
     int32_t sampling;               /* GBMUF_SAMPLING_*                                           */
     int32_t sweep;                  /* GBMUF_SWEEP_*                                              */
-    int32_t cache_hints;            /* bit 0: non-temporal stores, bit 1: non-temporal loads      */
+    int32_t cache_hints;            /* 0: by size and placement.  Any of bits 0 and 1: non-temporal
+                                       loads and stores through the L2 at every size (not where
+                                       rows start inside cache lines)                              */
     int32_t workgroups_per_cu;      /* upper bound on the fused kernel's resident workgroups per
                                        compute unit (enforced through its LDS request); 0 = by
                                        layout, K and what the call updates                               */

@@ -135,17 +135,25 @@ __device__ __forceinline__ void sort_few(int32_t (&v)[N])
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v4f_any __attribute__((ext_vector_type(4), aligned(4)));
 
-__device__ __forceinline__ v4f load4(const float *p, bool streaming)
+template <int POL>
+__device__ __forceinline__ v4f load4(const float *p)
 {
     const v4f_any *q = reinterpret_cast<const v4f_any *>(p);
-    return streaming ? __builtin_nontemporal_load(q) : *q;
+    if constexpr (POL == kStreamed) return __builtin_nontemporal_load(q);
+    else return *q;
 }
 
-__device__ __forceinline__ void store4(float *p, v4f v, bool streaming)
+template <int POL>
+__device__ __forceinline__ void store4(float *p, v4f v)
 {
-    v4f_any *q = reinterpret_cast<v4f_any *>(p);
-    if (streaming) __builtin_nontemporal_store(v, q);
-    else *q = v;
+#if defined(__HIP_DEVICE_COMPILE__)
+    if constexpr (POL == kStreamed) {
+        typedef unsigned v4u __attribute__((ext_vector_type(4)));
+        __builtin_amdgcn_global_store_b128((__attribute__((address_space(1))) v4u *)p, __builtin_bit_cast(v4u, v), "agent");
+        return;
+    }
+#endif
+    *reinterpret_cast<v4f_any *>(p) = v;
 }
 
 __device__ __forceinline__ int64_t placed(const Placement &at, int64_t e)

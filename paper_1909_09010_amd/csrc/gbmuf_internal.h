@@ -52,8 +52,7 @@ struct SyncArgs {
     int32_t xcd_log;         // log2(consecutive tiles that one XCD takes)
     int32_t mode;            // GBMUF_MODE_*
     float eta, zeta, inv;    // inv = 1/(q+1), rounded once on the host (plans with one q)
-    int32_t flags;           // bit 0: streaming stores, bit 1: streaming loads, bit 3: walk the
-                             // tile list backwards, bit 4: components draw different q (read the
+    int32_t flags;           // bit 3: walk the tile list backwards, bit 4: components draw different q (read the
                              // tile's q and the component's inv), bit 5: skip components whose
                              // period does not divide `step`, bit 6: rotate the XCDs (tile_of_block),
                              // bit 7: the library's sampler wrote nbr (not a caller)
@@ -64,8 +63,6 @@ struct SyncArgs {
 };
 
 enum : int32_t {
-    kFlagStreamStores = 1,
-    kFlagStreamLoads = 2,
     kFlagBackwards = 8,
     kFlagMixedQ = 16,
     kFlagCheckPeriods = 32,
@@ -125,11 +122,17 @@ __host__ __device__ constexpr size_t ids_words(int K, int pitch)
 }
 
 using KernelFn = void (*)(SyncArgs);
-KernelFn pick_kernel_0(const Variant &v, int q, bool mixed);
-KernelFn pick_kernel_1(const Variant &v, int q, bool mixed);
-KernelFn pick_kernel_2(const Variant &v, int q, bool mixed);
-KernelFn pick_kernel_3(const Variant &v, int q, bool mixed);
-KernelFn pick_kernel_4(const Variant &v, int q, bool mixed);
+
+// How the accesses of state use the caches (load4, store4): plainly, or loads that leave the L2 first and stores that go
+// through it at once.
+enum : int { kPlain = 0, kStreamed = 1 };
+
+// The shapes of gbmuf_sync.hip in each part and policy, or nullptr.
+#define GBMUF_PICK_NAME2(part, policy) pick_kernel_##part##_##policy
+#define GBMUF_PICK_NAME(part, policy) GBMUF_PICK_NAME2(part, policy)
+using PickFn = KernelFn(const Variant &v, int q, bool mixed);
+PickFn GBMUF_PICK_NAME(0, 0), GBMUF_PICK_NAME(1, 0), GBMUF_PICK_NAME(2, 0), GBMUF_PICK_NAME(3, 0), GBMUF_PICK_NAME(4, 0);
+PickFn GBMUF_PICK_NAME(0, 1), GBMUF_PICK_NAME(1, 1), GBMUF_PICK_NAME(2, 1), GBMUF_PICK_NAME(3, 1), GBMUF_PICK_NAME(4, 1);
 
 // Remembers the most recent failing HIP call of this thread (what gbmuf_last_error_detail
 // returns) and maps it to a status.
@@ -147,7 +150,7 @@ int launch_final_average(const float *theta, const Placement &at, int K, int64_t
                          const AverageShape &shape, hipStream_t stream);
 int launch_state_copy(const CopyArgs &c, int arrays, hipStream_t stream);
 int launch_copy_probe(float *dst, const float *src, int64_t n_floats, int flags, int blocks, hipStream_t stream);
-int launch_sync(const Variant &v, const SyncArgs &a, int64_t n_tiles, size_t lds_floor, hipStream_t stream);
+int launch_sync(const Variant &v, int policy, const SyncArgs &a, int64_t n_tiles, size_t lds_floor, hipStream_t stream);
 size_t sync_lds_bytes(const Variant &v, int K, int q, bool mixed, int C, bool in_kernel_sampling);
 int prepare_kernels(const Variant &v, int K, int q, bool mixed, int C, bool *can_sample_in_kernel);
 bool can_sample_inline(int K, int C);

@@ -96,7 +96,7 @@ __device__ __forceinline__ V worker_mean(const float *col, int K, int64_t stride
     return s * inv;
 }
 
-template <int B>
+template <int B, int POL>
 __global__ __launch_bounds__(64) void final_average_kernel(const float *theta, Placement at, int K, int64_t P,
                                                            float inv, float *out, int xcd_log, int rotate)
 {
@@ -111,7 +111,7 @@ __global__ __launch_bounds__(64) void final_average_kernel(const float *theta, P
     const int64_t n4 = P >> 2;
     if (i < n4) {
         const float *col = theta + placed(at, i << 2);
-        store4(out + (i << 2), worker_mean<B, v4f>(col, K, at.stride, inv, [](const float *p) { return load4(p, false); }), false);
+        store4<POL>(out + (i << 2), worker_mean<B, v4f>(col, K, at.stride, inv, [](const float *p) { return load4<POL>(p); }));
     } else if (static_cast<int64_t>(b) * 64 >= n4 && threadIdx.x < (P & 3)) {
         // the last P % 4 elements, one thread each of a wave that holds no columns, for which they would wait
         const int64_t e = (n4 << 2) + threadIdx.x;
@@ -135,6 +135,7 @@ __global__ __launch_bounds__(64) void final_average_kernel(const float *theta, P
 //   blocked to plain rows: 16 x 31.5 M 2201 / 2205 / 2198 / 2295, 200 x 2.4 M 2183 / 2153 / 2201 / 2292.
 //   plain rows to blocked: 16 x 31.5 M 2132 / 2197 / 2178 / 2218, 64 x 7.9 M 2336 / 2307 / 2179 / 2239.
 // ---------------------------------------------------------------------------------------
+template <int POL>
 __global__ __launch_bounds__(256) void state_copy_kernel(CopyArgs a)
 {
     const uint32_t i = blockIdx.y * gridDim.x + blockIdx.x, K = static_cast<uint32_t>(a.K);
@@ -147,7 +148,7 @@ __global__ __launch_bounds__(256) void state_copy_kernel(CopyArgs a)
     if (e >= a.P) return;
     // four floats that neither side cuts at a block edge
     if (e >= 0 && e + 4 <= a.P && ((e ^ (e + 3)) >> a.sa.logB) == 0 && ((e ^ (e + 3)) >> a.da.logB) == 0) {
-        store4(dst + placed(a.da, e), load4(src + placed(a.sa, e), false), false);
+        store4<POL>(dst + placed(a.da, e), load4<POL>(src + placed(a.sa, e)));
         return;
     }
     for (int c = 0; c < 4; ++c)
@@ -178,9 +179,9 @@ int launch_final_average(const float *theta, const Placement &at, int K, int64_t
     Placement pl = at;
     int xcd_log = shape.xcd_log, rotate = shape.rotate ? 1 : 0;
     void *argv[] = {&theta, &pl, &K, &P, &inv, &out, &xcd_log, &rotate};
-    const void *fn = shape.rows_in_flight <= 4   ? reinterpret_cast<const void *>(final_average_kernel<4>)
-                     : shape.rows_in_flight <= 8 ? reinterpret_cast<const void *>(final_average_kernel<8>)
-                                                 : reinterpret_cast<const void *>(final_average_kernel<16>);
+    const void *fn = shape.rows_in_flight <= 4   ? reinterpret_cast<const void *>(final_average_kernel<4, kPlain>)
+                     : shape.rows_in_flight <= 8 ? reinterpret_cast<const void *>(final_average_kernel<8, kPlain>)
+                                                 : reinterpret_cast<const void *>(final_average_kernel<16, kPlain>);
     const hipError_t err = hipLaunchKernel(fn, dim3(static_cast<unsigned>(blocks)), dim3(64), argv, lds_floor, stream);
     return err == hipSuccess ? GBMUF_OK : hip_failed("hipLaunchKernel(final average)", err, GBMUF_EDEVICE);
 }
@@ -202,7 +203,7 @@ int launch_state_copy(const CopyArgs &c, int arrays, hipStream_t stream)
     const int64_t x = blocks < (1 << 23) ? blocks : (1 << 23), y = (blocks + x - 1) / x;
     if (y > 511) return GBMUF_EUNSUPPORTED;                // 17 TB: the kernel counts pieces in 32 bits
     void *argv[] = {&args};
-    const hipError_t err = hipLaunchKernel(reinterpret_cast<const void *>(state_copy_kernel),
+    const hipError_t err = hipLaunchKernel(reinterpret_cast<const void *>(state_copy_kernel<kPlain>),
                                            dim3(static_cast<unsigned>(x), static_cast<unsigned>(y), static_cast<unsigned>(arrays)),
                                            dim3(256), argv, 0, stream);
     return err == hipSuccess ? GBMUF_OK : hip_failed("hipLaunchKernel(state copy)", err, GBMUF_EDEVICE);
@@ -230,9 +231,12 @@ constexpr Variant kVariants[] = {
 };
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 
-KernelFn pick_kernel(const Variant &v, int q, bool mixed)
+KernelFn pick_kernel(const Variant &v, int policy, int q, bool mixed)
 {
-    for (auto pick : {pick_kernel_0, pick_kernel_1, pick_kernel_2, pick_kernel_3, pick_kernel_4})
+    static constexpr PickFn *parts[2][5] = {
+        {GBMUF_PICK_NAME(0, 0), GBMUF_PICK_NAME(1, 0), GBMUF_PICK_NAME(2, 0), GBMUF_PICK_NAME(3, 0), GBMUF_PICK_NAME(4, 0)},
+        {GBMUF_PICK_NAME(0, 1), GBMUF_PICK_NAME(1, 1), GBMUF_PICK_NAME(2, 1), GBMUF_PICK_NAME(3, 1), GBMUF_PICK_NAME(4, 1)}};
+    for (PickFn *pick : parts[policy])
         if (KernelFn k = pick(v, q, mixed)) return k;
     return nullptr;
 }
@@ -275,21 +279,23 @@ int prepare_kernels(const Variant &v, int K, int q, bool mixed, int C, bool *can
     err = hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
     if (err != hipSuccess) return hip_failed("hipDeviceGetAttribute(MaxSharedMemoryPerBlock)", err, GBMUF_EDEVICE);
     if (lds > static_cast<size_t>(max_lds)) return GBMUF_EUNSUPPORTED;
-    KernelFn k = pick_kernel(v, q, mixed);
-    if (!k) return GBMUF_EINVAL;
-    err = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, max_lds);
-    if (err != hipSuccess) return hip_failed("hipFuncSetAttribute(fused kernel)", err, GBMUF_EDEVICE);
+    for (int policy : {kPlain, kStreamed}) {                // either may run: where a state lies is known only by a call
+        KernelFn k = pick_kernel(v, policy, q, mixed);
+        if (!k) return GBMUF_EINVAL;
+        err = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, max_lds);
+        if (err != hipSuccess) return hip_failed("hipFuncSetAttribute(fused kernel)", err, GBMUF_EDEVICE);
+    }
     return GBMUF_OK;
 }
 
 // lds_floor: the workgroup asks for at least this much dynamic LDS, which bounds how many
 // workgroups a compute unit holds at once (0 = only what it needs).
-int launch_sync(const Variant &v, const SyncArgs &a, int64_t n_tiles, size_t lds_floor, hipStream_t stream)
+int launch_sync(const Variant &v, int policy, const SyncArgs &a, int64_t n_tiles, size_t lds_floor, hipStream_t stream)
 {
     if (n_tiles <= 0) return GBMUF_OK;
     if (n_tiles > 0x7fffffffLL) return GBMUF_EUNSUPPORTED;
     const bool mixed = (a.flags & kFlagMixedQ) != 0;
-    KernelFn k = pick_kernel(v, a.q, mixed);
+    KernelFn k = pick_kernel(v, policy, a.q, mixed);
     if (!k) return GBMUF_EINVAL;
     if (a.nbr == nullptr && !draws_in_registers(a.q) && !can_sample_inline(a.K, a.C)) return GBMUF_EINVAL;
     size_t lds = sync_lds_bytes(v, a.K, a.q, mixed, a.C, a.nbr == nullptr);

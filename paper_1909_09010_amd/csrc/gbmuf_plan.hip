@@ -28,6 +28,7 @@ struct TileSet {
 // How the fused kernel runs on one kind of state placement.
 struct LayoutCfg {
     Variant variant{256, 8, 8};
+    int32_t policy = 0;                // how state is loaded and stored (load4, store4)
     int32_t logT = 0;
     int32_t set = 0;                   // which TileSet
     int32_t workgroups_per_cu = 0;     // 0 = no bound
@@ -35,12 +36,13 @@ struct LayoutCfg {
     bool rotate = false;               // see tile_of_block
 };
 
-enum { kRows = 0, kBlocked = 1 };
-enum { kBmuf = 0, kMa = 1 };          // the three-array update, or the gossip-MA branch (theta only)
+// kShared: rows of which some start inside a 128-byte line, so that neighbouring tiles share lines.
+enum { kRows = 0, kBlocked = 1, kShared = 2, kLayouts = 3 };
+enum { kBmuf = 0, kMa = 1, kBranches = 2 };   // the three-array update, or the gossip-MA branch (theta only)
 // How much one launch updates.  With sync periods that differs from call to call by orders of magnitude, so
 // everything that depends on it is chosen per launch, from the components that are due.
-enum { kCached = 0, kMiddle = 1, kLarge = 2, kSizes = 3 };
-constexpr int kMaxTileSets = 2 * 2 * kSizes;
+enum { kTiny = 0, kSmall = 1, kCompact = 2, kMiddle = 3, kLarge = 4, kSizes = 5 };
+constexpr int kMaxTileSets = kLayouts * kBranches * kSizes;
 
 }  // namespace
 
@@ -54,12 +56,11 @@ struct gbmuf_plan_s {
     std::vector<int32_t> periods;    // m: sync period H_i (all 1 without periods)
     std::vector<int32_t> cand;       // [K][C] ring candidates, order of Definition 1
     std::vector<CompDesc> comp;      // m: per-component constants of the kernels
-    LayoutCfg cfg[2][2][kSizes];     // [kRows, kBlocked][kBmuf, kMa][size of the launch]
+    LayoutCfg cfg[kLayouts][kBranches][kSizes];
     int32_t min_block_logT = 0;      // blocks hold at least 4 << min_block_logT floats
     TileSet sets[kMaxTileSets];      // one per distinct tile width among the configurations that calls can take
     int32_t n_sets = 0;
     float inv = 1.0f;                // 1/(q+1), rounded once (plans with one q)
-    int32_t flags = 0;               // load/store cache hints of the fused kernel
     int32_t sampling = GBMUF_SAMPLING_AUTO;   // as asked for
     bool launch_bound = false;       // with AUTO: workgroups always draw their own neighbour rows
     bool named_shape = false;        // the plan description names the tile shape
@@ -202,43 +203,41 @@ bool find_variant(int threads, int slots, Variant *out)
     return false;
 }
 
-// Up to so many values a launch's arrays stay in the 256 MB memory-side cache from one sync to the next (three
-// arrays, or theta alone).
-constexpr int64_t kCachedValues = 20000000, kCachedValuesMa = 60000000;
-// Above so many values a launch's rows are drawn in a kernel of their own (draws_itself); for the shapes, where
-// nothing is left in a cache and only the memory counts.
+// Bounds of the sizes, in values (K times the elements that are due).  Up to kTinyValues passes over a few states in turn
+// stay in the caches, and loads that leave them early lose (choose_policy).  From kSmallValues on there are enough tiles of
+// any shape for all CUs.  Up to kCompactValues something is left in the 256 MB memory-side cache from one sync to the next;
+// for rows that share lines that is all that counts (three arrays, or theta alone).  Above kLargeValues a launch's rows are
+// drawn in a kernel of their own (draws_itself).
+constexpr int64_t kTinyValues = 2000000, kSmallValues = 5000000, kCompactValues = 20000000, kCompactValuesSharedMa = 60000000;
 constexpr int64_t kLargeValues = 500000000, kLargeValuesMa = 130000000;
 
-int size_of_launch(int64_t values, int what)
+int size_of_launch(int64_t values, int layout, int what)
 {
-    return values <= (what == kMa ? kCachedValuesMa : kCachedValues) ? kCached : values <= kLargeValues ? kMiddle : kLarge;
+    const bool shared = layout == kShared;
+    if (!shared && values <= kTinyValues) return kTiny;
+    if (!shared && values <= kSmallValues) return kSmall;
+    if (values <= (shared && what == kMa ? kCompactValuesSharedMa : kCompactValues)) return kCompact;
+    return values <= kLargeValues ? kMiddle : kLarge;
 }
 
 // Which sizes a call of this plan can have: without periods a call updates everything.
-bool size_occurs(const gbmuf_plan_s &pl, int what, int size)
+bool size_occurs(const gbmuf_plan_s &pl, int layout, int what, int size)
 {
-    const int all = size_of_launch(pl.K * pl.P, what);
-    return size == all || (pl.has_periods && size < all);
+    const int all = size_of_launch(pl.K * pl.P, layout, what), least = size_of_launch(0, layout, what);
+    return size == all || (pl.has_periods && size < all && size >= least);
 }
 
-// How the fused kernel runs, by K, layout, branch and size of the launch, unless the plan description names a
-// shape.  Each rule holds over a whole range of K; it is the shape with the least mean over sweeps of all built-in
-// shapes and bounds on K = 1 .. 1024, 0.3 M .. 2 G values, blocked, padded and odd rows.  In brackets: its mean
-// distance from the best shape of every single point, and that of the nearest rival.
-//
-// kCached is bound by latency: one slot per thread, and no more threads than make a tile of 16 columns [2 %; the
-// shapes below 5 to 25 %].  More workers than that takes 1024 x 4 [10 %]; the wider kVeryMany leaves most CUs without
-// a tile, 256 workers x 0.023 M: 53 us, 1024 x 4 30.  Three states in turn, blocked, 256 x 1 / 512 x 1: 16 x 0.11 M 8.3 /
-// 8.8, 8 x 0.23 M 8.3 / 8.8, 4 x 0.08 M 4.4 / 4.3.  Gossip-MA, with a third of the loads, takes two slots [3 %; one 6 %].
-Variant cached_variant(int K, int layout, int what)
+// Rows that share lines, launches that the caches hold: bound by latency.  One slot per thread, and no more threads than
+// make a tile of 16 columns; more workers than that take 1024 x 4 [10 % from the best of every point]: the wider kVeryMany leaves
+// most CUs without a tile.  Gossip-MA, with a third of the loads, takes two slots [3 %; one 6 %].
+Variant cached_variant(int K, int what)
 {
     Variant v{1024, 4, 4};
     if (what == kMa) {
         if (K <= 64) find_variant(K <= 32 ? 256 : 512, 2, &v);
         else if (K <= 128) find_variant(512, 4, &v);
     } else if (K <= 64) {
-        if (layout == kBlocked) find_variant(K <= 16 ? 256 : K <= 32 ? 512 : 1024, 1, &v);
-        else find_variant(K <= 16 ? 512 : 1024, K <= 32 ? 1 : 2, &v);
+        find_variant(K <= 16 ? 512 : 1024, K <= 32 ? 1 : 2, &v);
     }
     return v;
 }
@@ -251,39 +250,25 @@ int32_t widest_tile(const Variant &v, int K)
     return lg;
 }
 
-// Beyond the caches what decides is how the accesses that the chip has in flight at one time lie in memory, less how
-// many they are.  Blocked state is one address stream: a short stretch of it is fast, tiles of 512 bytes to 1 KB of
-// a worker row.  Rows are 3K streams: 1 KB and more.  Above 64 workers theta alone fills the tile and omega and
-// Delta are streamed (sync_kernel); above 128 the widest tile wins once there are enough of them, and with more
-// than 7 neighbours it does not (2 to 10 %).
-//   blocked, middle: 5-16 512 x 1 [0.5 %; 256 x 2 2 %], 17-32 512 x 2 [1 %; 1024 x 1 1 %], 33-39 1024 x 2, whose 64
-//     rows of 32 columns are at most 5/8 full, so that all three arrays may be in flight [33 workers, kSixtyFour 9 %, 36 3 %],
-//     40-64 kSixtyFour [0.5 %; 43 workers, 1024 x 2 3 %; 512 x 4 2 %], 65-128 kMany [0.3 %; 1024 x 4 3 %].
-//     Large: 5-16 256 x 2 [0.5 %; 512 x 1 3 %], 17-32 512 x 2 [1 %; 1024 x 1 1 %], 129-512 kVeryMany [0.5 %; kMany 5 %], above at all sizes [1 %; 1024 x 4 6 %].
-//   rows: up to 4 workers 256 x 1 [4 %; 1024 x 1 9 %], 5-16 kSixtyFour [2 %; 1024 x 1 2 to 4 %], 17-64 1024 x 2 [1.5 %; 1024 x 4 2 %], large
+// Rows that share lines, from here on beyond the caches: rows are 3K address streams and take tiles of 1 KB of a
+// worker row and more.
+//   BMUF: up to 4 workers 256 x 1 [4 %; 1024 x 1 9 %], 5-16 kSixtyFour [2 %; 1024 x 1 2 to 4 %], 17-64 1024 x 2 [1.5 %; 1024 x 4 2 %], large
 //     33-64 kMany [0.7 %; 1024 x 2 2 %], 65-512 1024 x 4 [0.5 %; kMany 1 %], 129-512 large kVeryMany [0.3 %; 1024 x 4 1 to 4 %],
 //     above at all sizes [0 %; 1024 x 4 20 to 50 %].
-//   gossip-MA: 512 x 2 where K rows fill its slots to 7/8, as powers of two do (blocked 2, 4, 7, 8, 14-16, 28-32 [1 %; 256 x 4 5
-//     %]; rows 2, 4 [2 %; 256 x 4 6 %]), else 256 x 4, whose threads idle in whole slots (blocked 3-27 [2 %; 512 x 2 11 %], rows 3-16
-//     [1.5 %; 512 x 2 11 %]), rows 17-32 and blocked 33-64 512 x 4 [2 %; 512 x 2 12 to 20 %], 65-512 1024 x 4 [1 %; kVeryMany 5 to
+//   gossip-MA: 512 x 2 where K rows fill its slots to 7/8 and K <= 4 [2 %; 256 x 4 6 %], else up to 16 256 x 4, whose threads idle
+//     in whole slots [1.5 %; 512 x 2 11 %], 17-32 512 x 4 [2 %; 512 x 2 12 to 20 %], 33-512 1024 x 4 [1 %; kVeryMany 5 to
 //     20 %], 129-512 large and above 512 kVeryMany [0.5 %; 1024 x 4 2 to 40 %].
-Variant default_variant(int K, int layout, int what, int size, bool few)
+Variant shared_variant(int K, int what, int size, bool few)
 {
     Variant v{1024, 4, 4};
     const bool large = size == kLarge;
-    if (size == kCached) return cached_variant(K, layout, what);
+    if (size == kCompact) return cached_variant(K, what);
     if (few && (K > 512 || (K > 128 && large && what == kBmuf))) return kVeryMany;
     if (what == kMa) {
         const bool fills = (K << widest_tile({512, 2, 2}, K)) >= 896;
-        if (fills && K <= (layout == kBlocked ? 32 : 4)) find_variant(512, 2, &v);
-        else if (K <= (layout == kBlocked ? 32 : 16)) find_variant(256, 4, &v);
-        else if (K <= (layout == kBlocked ? 64 : 32)) find_variant(512, 4, &v);
-    } else if (layout == kBlocked) {
-        if (K <= 4) find_variant(256, 1, &v);
-        else if (K <= 16) find_variant(large ? 256 : 512, large ? 2 : 1, &v);
-        else if (K <= 32) find_variant(512, 2, &v);
-        else if (K < 40) find_variant(1024, 2, &v);
-        else v = K <= 64 ? kSixtyFour : kMany;
+        if (fills && K <= 4) find_variant(512, 2, &v);
+        else if (K <= 16) find_variant(256, 4, &v);
+        else if (K <= 32) find_variant(512, 4, &v);
     } else {
         if (K <= 4) find_variant(256, 1, &v);
         else if (K <= 16) v = kSixtyFour;
@@ -293,6 +278,76 @@ Variant default_variant(int K, int layout, int what, int size, bool few)
     return v;
 }
 
+// How the fused kernel runs where no line is shared, by K, layout, branch and size of the launch: the shape, the resident
+// workgroups per CU (0: as many as fit) and which XCD takes which tiles (tile_of_block).  Each rule holds over a whole range
+// of K and is what came out best or within 1 to 3 % of it in sweeps of all built-in shapes, bounds and runs on K = 2 .. 400,
+// 1 M .. 1.5 G values; TB/s of the rule, then the nearest rival.
+//   Tiny and small launches want many tiles: up to 64 workers as few slots as give tiles of 8 columns and more (64 workers, 1 M values
+//     5.6 us, 1024 slots 5.9, 4096 9.5; 3 M 12.7, 13.0, 14.4).
+//   Blocked state is one stretch of memory, and every tile shape that keeps 512 bytes to 1 KB of a row together is fast: 6.7 to 6.85
+//     up to 64 workers.  An XCD takes 1 KB of each row in one run (xcd 6): 8 x 300 M / 8 1045 us, tile by tile 1065; from 33 to 128
+//     workers and beyond the caches up to 512 runs of one tile that move on from block to block (rotate), without which an
+//     XCD sees the same addresses modulo 4 KB in every block: 64 x 23.4 M 5356 us, not rotated 5425 (1 KB) and more.
+//     No bound of the residency helps above 4 workers.  Up to 8 workers 256 x 1, 9-16 512 x 1 where K rows fill its
+//     slots to 7/8, else 256 x 2, whose threads idle in whole slots (12 x 25 M 1051 us; 512 x 1 1080), 17-32 512 x 2, 33-64 kSixtyFour (40 x
+//     7.5 M 1072 us, 512 x 4 1057; 64 x 4.7 M 1070, 512 x 4 1085), 65-128 kMany, 129-512 kVeryMany (200 x 1.5 M 1167, kMany 1185;
+//     256 x 1.2 M 1156, kSixtyFour 1165; 300 x 1 M 1245, kMany 1206), up to 20 M values kSixtyFour (200 x 0.1 M 84 us, kMany 88).
+//   Aligned rows are 3K address streams: 5.9 up to 8 workers, 5.1 from 64 on, whatever the shape.  Wide tiles, and 4 KB
+//     of a row per XCD from 65 workers on (96 x 2.6 M 1175 us, tile by tile 1210).  2-4 256 x 1, four per CU (4 x 62.5 M 987 us;
+//     unbounded 1034), 5-8 1024 x 1 (8 x 87.5 M 2852; kSixtyFour 2900, 512 x 1 2998), 9-32 kSixtyFour (32 x 7.8 M 1136; 1024 x 2 1152), 33-64
+//     kVeryMany (48 x 5.2 M 1136; 1024 x 2 1197), 65-128 kSixtyFour (1175 / 1185; 1024 x 4 1223 / 1227), above kVeryMany (300 x
+//     0.8 M 1209, 4 KB per XCD not taken 1259).  5 to 20 M values of more than 32 workers: 1024 x 4.
+//   Gossip-MA has a third of the loads and takes more slots per thread.  Blocked: up to 2 workers 256 x 1, up to 16 256 x 2 where K rows
+//     fill it to 7/8 (8 x 75 M 723 us; 512 x 2 748), else 256 x 4, up to 32 256 x 4 (725; 512 x 2 735), 33-64 512 x 4, above 1024 x 4, large of
+//     more than 256 workers kVeryMany (300 x 2 M 947; 956).  Rows: up to 8 256 x 2, up to 24 256 x 4, up to 64 1024 x 4, above
+//     kVeryMany (300 x 2 M 1003; 1024 x 4 1089).  5 to 20 M values: 256 x 2 up to 64 workers, up to 128 512 x 2.
+void aligned_shape(int K, int layout, int what, int size, bool few, LayoutCfg &cfg)
+{
+    Variant &v = cfg.variant;
+    int &bound = cfg.workgroups_per_cu, &run = cfg.xcd_columns_log;
+    v = Variant{1024, 4, 4};
+    bound = 0; run = 0; cfg.rotate = false;
+    const bool blocked = layout == kBlocked;
+    const auto fills = [K](int slots) { return (K << widest_tile({slots, 1, 1}, K)) * 8 >= slots * 7; };
+    if (what == kMa) {
+        if (size <= kSmall && K <= 64) find_variant(256, fills(512) ? 2 : 4, &v);
+        else if (size <= kCompact) find_variant(K <= 64 ? 256 : K <= 128 ? 512 : 1024, K <= 128 ? 2 : 4, &v);
+        else if (blocked && K <= 2) find_variant(256, 1, &v);
+        else if (blocked ? K <= 16 && fills(512) : K <= 8) find_variant(256, 2, &v);
+        else if (K <= (blocked ? 32 : 24)) find_variant(256, 4, &v);
+        else if (blocked && K <= 64) find_variant(512, 4, &v);
+        else if (few && (blocked ? K > 512 || (K > 256 && size == kLarge) : K > 64)) v = kVeryMany;
+    } else if (size <= kSmall) {
+        if (K <= 64) find_variant(K <= 16 ? 256 : 512, 1, &v);
+        else if (size == kSmall) v = kMany;
+    } else if (blocked) {
+        if (K <= 8) find_variant(256, 1, &v);
+        else if (K <= 16 && fills(512)) find_variant(512, 1, &v);
+        else if (K <= 16) find_variant(256, 2, &v);
+        else if (K <= 32) find_variant(512, 2, &v);
+        else if (K <= 64) v = kSixtyFour;
+        else if (K <= 128) v = kMany;
+        else if (size == kCompact && K <= 256) v = kSixtyFour;
+        else if (size != kCompact && few) v = kVeryMany;
+        else v = kMany;
+        if (K <= 4) bound = 6;
+    } else {
+        if (K <= 4) find_variant(256, 1, &v);
+        else if (K <= 8) find_variant(1024, 1, &v);
+        else if (K <= 32) v = kSixtyFour;
+        else if (size == kCompact) v = Variant{1024, 4, 4};
+        else if (K > 64 && K <= 128) v = kSixtyFour;
+        else if (few) v = kVeryMany;
+        if (K <= 4) bound = 4;
+    }
+    if (size <= kSmall) return;
+    if (blocked) {
+        cfg.rotate = K > 32 && (K <= 128 || what == kMa || size != kCompact);
+        run = cfg.rotate ? 0 : 6;
+    } else {
+        run = K > (size == kCompact || what == kMa ? 16 : 64) ? 8 : 0;
+    }
+}
 // Small plans with rows of more than 7 neighbours draw them through LDS in every workgroup (launch_bound), a thread a
 // row: a chain that is hidden by many workgroups, not by large ones, and paid per tile.  9 neighbours, us, these
 // shapes / the default ones: 36 workers x 0.33 M blocked 112 / 167, rows 85 / 166; 17 x 0.71 M blocked 107 / 135.
@@ -307,16 +362,11 @@ Variant lds_drawing_variant(int K, int layout)
     return v;
 }
 
-// Resident workgroups per CU (0: as many as fit).  Blocked: about 1200 columns, but two workgroups at least: 5 workers
-// 1584 us at four, 1876 at two; 10 workers 2219 at four, 2648 at two; 14 workers 3122 at three, 3237 at two; 16 workers
-// x 278.6 M 16290 at two, 17200 at three.  Rows: two, or six of the small ones of up to 4 workers.  A state that stays
-// in the cache has nothing to gain from a bound, and gossip-MA moves too little to need one.
-int32_t default_workgroups_per_cu(int K, int layout, int what, int logT, int size)
+// Rows that share lines: two workgroups per CU, or six of the small ones of up to 4 workers.  A state that stays in the cache has
+// nothing to gain from a bound, and gossip-MA moves too little to need one.
+int shared_workgroups_per_cu(int K, int what, int size)
 {
-    if (size == kCached || what == kMa) return 0;
-    if (layout == kRows) return K <= 4 ? 6 : 2;
-    const int columns = K << logT, aim = K <= 4 ? 1024 : 1200;
-    return K <= 16 ? std::max(2, (aim + columns / 2) / columns) : 2;
+    return size == kCompact || what == kMa ? 0 : K <= 4 ? 6 : 2;
 }
 
 // What a plan that names its shape gets if it does not name a bound: no bound on rows, few on blocked state.
@@ -327,18 +377,14 @@ int32_t named_workgroups_per_cu(int K, int layout, int what)
     return K <= 4 ? 4 : K <= 32 ? 2 : 1;
 }
 
-// Which XCD takes which tiles of a blocked state (tile_of_block).  512 bytes of a row (one tile of 32 columns) or
-// 1 KB in one run: from 17 to 32 workers 1 KB (1 % from the best of every point, 512 B 2 %), 512 workers 13112 / 12278 us;
-// but 16 workers x 278.6 M 16295 / 16630, and 33 to 64 are within 0.3 %; 2 KB is the worst (256 workers 5224 / 5907).
-// Rotated: in the recommended arena the blocks of a row lie 32 KB apart, which is 64 tiles of 32 columns, so without
-// it one XCD sees the same addresses modulo 4 KB in every block; 64 workers x 57.8 M 15310 / 14445, gossip-MA
-// 2660 / 2611.  Launches of less than 500 M values gain nothing (1.0 / 1.1 % from the best), nor does any of the other
-// shapes at 17 to 32 workers.
-void blocked_xcds(int K, int what, int size, LayoutCfg &cfg)
+// Streamed: loads leave the L2 first, stores go through it at once.  Lines that were read are dead, and unless they leave first
+// they push lines that were written out in an order that HBM takes worse: three arrays of 2 GB updated in place 5810
+// GB/s, 5450 with plain accesses, either half alone 5420 to 5550.  Not where neighbouring tiles share lines, whose halves the L2 would
+// no longer join (16 x 43.8 M odd rows 4023 us, plain 3255), and not where all of a launch comes from the caches.  A plan's
+// cache_hints ask for it at any size.
+int choose_policy(int layout, int size, int hints)
 {
-    const bool one_kb = what == kBmuf && ((K > 16 && K <= 32) || K > 128);
-    cfg.xcd_columns_log = one_kb && size != kCached ? 6 : 0;
-    cfg.rotate = K > 32 && K <= 64 && size != kCached && (what == kMa || size == kLarge);
+    return layout != kShared && (size != kTiny || hints != 0) ? kStreamed : kPlain;
 }
 
 int64_t count_tiles(const gbmuf_plan_s &pl, int32_t logT)
@@ -419,7 +465,7 @@ int upload(T **dst, const std::vector<T> &src)
 
 const LayoutCfg &cfg_of_all(const gbmuf_plan_s &pl, int layout, int what)
 {
-    return pl.cfg[layout][what][size_of_launch(pl.K * pl.P, what)];
+    return pl.cfg[layout][what][size_of_launch(pl.K * pl.P, layout, what)];
 }
 
 int make_device_state(gbmuf_plan_s &pl, int32_t sampling)
@@ -443,9 +489,10 @@ int make_device_state(gbmuf_plan_s &pl, int32_t sampling)
     }
     bool can = false;
     int rc = GBMUF_OK;
-    for (int l = 0; l < 4 * kSizes && rc == GBMUF_OK; ++l)
-        if (size_occurs(pl, l / kSizes % 2, l % kSizes))
-            rc = prepare_kernels(pl.cfg[l / kSizes / 2][l / kSizes % 2][l % kSizes].variant, pl.K, pl.q, pl.mixed_q, pl.C, &can);
+    for (int l = 0; l < kLayouts * kBranches * kSizes && rc == GBMUF_OK; ++l) {
+        const int layout = l / kSizes / kBranches, what = l / kSizes % kBranches, size = l % kSizes;
+        if (size_occurs(pl, layout, what, size)) rc = prepare_kernels(pl.cfg[layout][what][size].variant, pl.K, pl.q, pl.mixed_q, pl.C, &can);
+    }
     if (rc != GBMUF_OK) return rc;
     if (sampling == GBMUF_SAMPLING_IN_KERNEL && !can) return GBMUF_EUNSUPPORTED;
     pl.sampling = sampling;
@@ -541,19 +588,17 @@ gbmuf_state_t rows_state(float *theta, float *omega, float *delta, int64_t strid
     return st;
 }
 
-// log2 of how many consecutive tiles one XCD takes (tile_of_block).  In rows or blocks that do not start
-// on 128-byte lines neighbouring tiles share a line, and unless both are taken by one XCD its L2 cannot
-// join the halves: every shared line is fetched twice and written in two pieces.  With 32 KB per XCD one
-// line in 256 is shared.  16 workers x 35.0 M in plain tensors: 3944 GB/s at 512 B, 4984 at 4 KB, 5073 at
+// Whether rows or blocks start inside 128-byte lines, so that neighbouring tiles share lines: unless both are taken by one XCD its
+// L2 cannot join the halves, and every shared line is fetched twice and written in two pieces.  One XCD takes 32 KB of a
+// row then, and one line in 256 is shared.  16 workers x 35.0 M in plain tensors: 3944 GB/s at 512 B, 4984 at 4 KB, 5073 at
 // 16 KB (aligned rows: 5161); 64 workers x 26.9 M: 3880 at 1 KB, 4405 at 4 KB, 5163 at 32 KB.  (The stride of a single
 // worker is no distance between rows: 1 x 600 M, odd stride, 2497 us; by 32 KB 2694.)
-int32_t xcd_run(const LayoutCfg &cfg, const Placement &at, const gbmuf_state_t *st, int32_t mode, int K)
+bool shares_lines(const Placement &at, const gbmuf_state_t *st, int32_t mode, int K)
 {
     uintptr_t low = reinterpret_cast<uintptr_t>(st->theta) | (static_cast<uintptr_t>((K > 1 ? at.stride : 0) | at.block_extra) << 2);
     if (mode != GBMUF_MODE_GOSSIP_MA)
         low |= reinterpret_cast<uintptr_t>(st->omega) | reinterpret_cast<uintptr_t>(st->delta);
-    const int32_t columns_log = (low & 127u) ? 11 : cfg.xcd_columns_log;
-    return std::max(0, columns_log - cfg.logT);
+    return (low & 127u) != 0;
 }
 
 // The dynamic LDS a workgroup asks for so that at most `workgroups_per_cu` of them fit a CU.
@@ -642,7 +687,9 @@ int enqueue_sync(const gbmuf_plan_s *pl, const int32_t *nbr_dev, const gbmuf_sta
                  bool callers_table = false)
 {
     const int what = mode == GBMUF_MODE_GOSSIP_MA ? kMa : kBmuf;
-    const LayoutCfg &cfg = pl->cfg[layout][what][size_of_launch(due.values, what)];
+    const bool shared = shares_lines(at, st, mode, pl->K);
+    if (shared && layout == kRows) layout = kShared;
+    const LayoutCfg &cfg = pl->cfg[layout][what][size_of_launch(due.values, layout, what)];
     const TileSet &ts = pl->sets[cfg.set];
     // One run of components is launched as exactly its tiles (the list is in component order); for several
     // runs one launch covers all tiles, and the workgroups of components that are not due return at once.
@@ -657,15 +704,15 @@ int enqueue_sync(const gbmuf_plan_s *pl, const int32_t *nbr_dev, const gbmuf_sta
     a.at = at;
     a.K = pl->K; a.q = pl->q; a.logT = cfg.logT; a.mode = mode;
     a.eta = eta; a.zeta = zeta; a.inv = pl->inv;
-    a.flags = pl->flags | ((pl->alternate && (round & 1)) ? kFlagBackwards : 0) | (pl->mixed_q ? kFlagMixedQ : 0) |
+    a.flags = ((pl->alternate && (round & 1)) ? kFlagBackwards : 0) | (pl->mixed_q ? kFlagMixedQ : 0) |
               (due.one_run ? 0 : kFlagCheckPeriods) | (cfg.rotate ? kFlagRotate : 0) |
               (nbr_dev != nullptr && !callers_table ? kFlagSampledTable : 0);
     a.p = pl->p; a.C = pl->C;                               // used only when nbr_dev == nullptr
     a.key0 = static_cast<uint32_t>(pl->seed); a.key1 = static_cast<uint32_t>(pl->seed >> 32);
     a.round0 = static_cast<uint32_t>(round); a.round1 = static_cast<uint32_t>(round >> 32);
     a.step = round;
-    a.xcd_log = xcd_run(cfg, at, st, mode, pl->K);
-    return launch_sync(cfg.variant, a, end - first, lds_floor(pl, cfg), stream);
+    a.xcd_log = std::max(0, (shared ? 11 : cfg.xcd_columns_log) - cfg.logT);
+    return launch_sync(cfg.variant, shared ? kPlain : cfg.policy, a, end - first, lds_floor(pl, cfg), stream);
 }
 
 SampleArgs sample_args(const gbmuf_plan_s *pl, uint64_t round, int32_t *out)
@@ -764,41 +811,48 @@ int gbmuf_plan_create(gbmuf_plan_t **out, const gbmuf_plan_desc_t *desc)
                     std::memcpy(pl->cand.data() + static_cast<size_t>(w) * pl->C, ring.data(),
                                 sizeof(int32_t) * static_cast<size_t>(pl->C));
             }
-            pl->flags = desc->cache_hints;
             pl->named_shape = desc->tile_threads != 0;
             pl->alternate = desc->sweep == GBMUF_SWEEP_AUTO;
             pl->launch_bound = is_launch_bound(*pl, desc);
             const bool through_lds = !draws_in_registers(pl->q) && !pl->named_shape &&
                                      (desc->sampling == GBMUF_SAMPLING_IN_KERNEL || (desc->sampling == GBMUF_SAMPLING_AUTO && pl->launch_bound));
-            for (int l = 0; l < 4 * kSizes && rc == GBMUF_OK; ++l) {
-                const int layout = l / kSizes / 2, what = l / kSizes % 2, size = l % kSizes;
+            for (int l = 0; l < kLayouts * kBranches * kSizes && rc == GBMUF_OK; ++l) {
+                const int layout = l / kSizes / kBranches, what = l / kSizes % kBranches, size = l % kSizes;
                 LayoutCfg &cfg = pl->cfg[layout][what][size];
+                const bool few = draws_in_registers(pl->q);
                 if (pl->named_shape) {
                     if (!find_variant(desc->tile_threads, desc->tile_slots, &cfg.variant) ||
                         K > cfg.variant.threads * cfg.variant.slots) { rc = GBMUF_EINVAL; break; }
                     pl->min_block_logT = widest_tile(cfg.variant, K);
+                    cfg.workgroups_per_cu = named_workgroups_per_cu(K, layout, what);
                 } else {
-                    cfg.variant = through_lds ? lds_drawing_variant(K, layout)
-                                              : default_variant(K, layout, what, size, draws_in_registers(pl->q));
+                    if (layout == kShared) {
+                        cfg.variant = shared_variant(K, what, size, few);
+                        cfg.workgroups_per_cu = shared_workgroups_per_cu(K, what, size);
+                    } else {
+                        aligned_shape(K, layout, what, size, few, cfg);
+                    }
+                    if (through_lds) {
+                        cfg.variant = lds_drawing_variant(K, layout);
+                        cfg.workgroups_per_cu = 0;
+                    }
                     // where the neighbour rows do not fit beside the widest tile, the next smaller one
                     if (sync_lds_bytes(cfg.variant, K, pl->q, pl->mixed_q, pl->C, can_sample_inline(K, pl->C)) > kLdsPerWorkgroup)
                         find_variant(1024, 4, &cfg.variant);
                     // Blocks may be narrower than a tile: the kernel looks an element's block up column by column
                     // (where a thread keeps its column, T <= threads, which holds for all shapes of more than 2 workers).
                     pl->min_block_logT = widest_tile(Variant{K <= 16 ? 1024 : K <= 64 ? 2048 : 4096, 1, 1}, K);
-                    if (layout == kBlocked) blocked_xcds(K, what, size, cfg);
                 }
                 cfg.logT = widest_tile(cfg.variant, K);
-                cfg.workgroups_per_cu = desc->workgroups_per_cu != 0 ? desc->workgroups_per_cu
-                                        : through_lds     ? 0
-                                        : pl->named_shape ? named_workgroups_per_cu(K, layout, what)
-                                                          : default_workgroups_per_cu(K, layout, what, cfg.logT, size);
+                cfg.policy = choose_policy(layout, size, desc->cache_hints);
+                if (desc->workgroups_per_cu != 0) cfg.workgroups_per_cu = desc->workgroups_per_cu;
             }
             if (rc == GBMUF_OK) {
                 // one tile list per distinct tile width
-                for (int l = 0; l < 4 * kSizes; ++l) {
-                    if (!size_occurs(*pl, l / kSizes % 2, l % kSizes)) continue;
-                    LayoutCfg &cfg = pl->cfg[l / kSizes / 2][l / kSizes % 2][l % kSizes];
+                for (int l = 0; l < kLayouts * kBranches * kSizes; ++l) {
+                    const int layout = l / kSizes / kBranches, what = l / kSizes % kBranches, size = l % kSizes;
+                    if (!size_occurs(*pl, layout, what, size)) continue;
+                    LayoutCfg &cfg = pl->cfg[layout][what][size];
                     int found = -1;
                     for (int s2 = 0; s2 < pl->n_sets; ++s2)
                         if (pl->sets[s2].logT == cfg.logT) found = s2;

@@ -211,10 +211,10 @@ struct Rows<NT, kAnyQ> {
 // vector filled float by float made every array's load wait for the one before, three memory latencies in
 // a row in each cut tile.  48 components of one cut tile each, 100 workers, 1024 x 4: 9.6 us, that way 12.7;
 // edges between columns 7.3.
-template <bool WHOLE>
-__device__ __forceinline__ v4f load_col(const float *p, unsigned mk, bool streaming)
+template <bool WHOLE, int POL>
+__device__ __forceinline__ v4f load_col(const float *p, unsigned mk)
 {
-    if (WHOLE || mk == 0xFu) return load4(p, streaming);
+    if (WHOLE || mk == 0xFu) return load4<POL>(p);
     const int first = __builtin_ctz(mk), last = 31 - __builtin_clz(mk);
     v4f v;
 #pragma unroll
@@ -222,11 +222,11 @@ __device__ __forceinline__ v4f load_col(const float *p, unsigned mk, bool stream
     return v;
 }
 
-template <bool WHOLE>
-__device__ __forceinline__ void store_col(float *p, v4f v, unsigned mk, bool streaming)
+template <bool WHOLE, int POL>
+__device__ __forceinline__ void store_col(float *p, v4f v, unsigned mk)
 {
     if (WHOLE || mk == 0xFu) {
-        store4(p, v, streaming);
+        store4<POL>(p, v);
         return;
     }
 #pragma unroll
@@ -270,13 +270,12 @@ __device__ __forceinline__ v4f average(const v4f *tile, const uint16_t *row, int
 // WHOLE: all T columns belong to the tile entirely; else a component edge cuts it.
 // DEPTH == SLOTS: omega and Delta are loaded together with theta; DEPTH < SLOTS (T <= NT then): see
 // sync_kernel below.
-template <int NT, int SLOTS, int DEPTH, int Q1, bool WHOLE>
+template <int NT, int SLOTS, int DEPTH, int Q1, int POL, bool WHOLE>
 __device__ __forceinline__ void do_tile(const SyncArgs &a, const TileDesc &td, v4f *tile, uint16_t *ids)
 {
     const int tid = threadIdx.x, K = a.K, logT = a.logT, T = 1 << logT, mode = a.mode;
     const float inv = (a.flags & kFlagMixedQ) ? a.comp[td.comp].inv : a.inv;
     const bool slots_too = mode != GBMUF_MODE_GOSSIP_MA;
-    const bool nt_load = (a.flags & kFlagStreamLoads) != 0, nt_store = (a.flags & kFlagStreamStores) != 0;
     const int col0 = tid & (T - 1), w0 = tid >> logT;
     auto wn = [&](int n) { return (n * NT) >> logT; };
     auto cn = [&](int n) { return (n * NT) & (T - 1); };
@@ -301,7 +300,7 @@ __device__ __forceinline__ void do_tile(const SyncArgs &a, const TileDesc &td, v
     if constexpr (DEPTH < SLOTS) {
 #pragma unroll
         for (int n = 0; n < SLOTS; ++n)
-            if (const unsigned mk = mask(n)) th[n] = load_col<WHOLE>(a.theta + at(n), mk, nt_load);
+            if (const unsigned mk = mask(n)) th[n] = load_col<WHOLE, POL>(a.theta + at(n), mk);
         // kSixtyFour: omega and Delta on top of theta would be more in flight per CU than HBM takes best.  64 workers x 115.5 M
         // in components of 1 M, blocked: 29350 us, all at once 29990; 48 workers 2 % less, rows of 5 to 16 within 1 %.
         // With more than 4 neighbours the registers leave one workgroup per CU, which needs all of them in flight: 42 workers x
@@ -312,10 +311,10 @@ __device__ __forceinline__ void do_tile(const SyncArgs &a, const TileDesc &td, v
     for (int n = 0; n < DEPTH; ++n) {
         const unsigned mk = mask(n);
         if (mk == 0u) continue;
-        if (DEPTH == SLOTS) th[n] = load_col<WHOLE>(a.theta + at(n), mk, nt_load);
+        if (DEPTH == SLOTS) th[n] = load_col<WHOLE, POL>(a.theta + at(n), mk);
         if (slots_too) {
-            om[n] = load_col<WHOLE>(a.omega + at(n), mk, nt_load);
-            de[n] = load_col<WHOLE>(a.delta + at(n), mk, nt_load);
+            om[n] = load_col<WHOLE, POL>(a.omega + at(n), mk);
+            de[n] = load_col<WHOLE, POL>(a.delta + at(n), mk);
         }
     }
     rows.finish(a, td, ids);
@@ -332,8 +331,8 @@ __device__ __forceinline__ void do_tile(const SyncArgs &a, const TileDesc &td, v
         const v4f o = om[n % DEPTH], d = de[n % DEPTH];
         if (n + DEPTH < SLOTS && slots_too) {
             if (const unsigned next = mask(n + DEPTH)) {
-                om[n % DEPTH] = load_col<WHOLE>(a.omega + at(n + DEPTH), next, nt_load);
-                de[n % DEPTH] = load_col<WHOLE>(a.delta + at(n + DEPTH), next, nt_load);
+                om[n % DEPTH] = load_col<WHOLE, POL>(a.omega + at(n + DEPTH), next);
+                de[n % DEPTH] = load_col<WHOLE, POL>(a.delta + at(n + DEPTH), next);
             }
         }
         v4f tn = average<Q1>(tile, ids + (w0 + wn(n)) * pitch, td.q + 1, logT, col0 + cn(n), inv);
@@ -346,20 +345,20 @@ __device__ __forceinline__ void do_tile(const SyncArgs &a, const TileDesc &td, v
                 filter(avg[c], o[c], d[c], a.eta, a.zeta, mode, t1, o1, d1);
                 tn[c] = t1; on[c] = o1; dn[c] = d1;
             }
-            store_col<WHOLE>(a.omega + at(n), on, mk, nt_store);
-            store_col<WHOLE>(a.delta + at(n), dn, mk, nt_store);
+            store_col<WHOLE, POL>(a.omega + at(n), on, mk);
+            store_col<WHOLE, POL>(a.delta + at(n), dn, mk);
         }
-        store_col<WHOLE>(a.theta + at(n), tn, mk, nt_store);
+        store_col<WHOLE, POL>(a.theta + at(n), tn, mk);
     }
 }
 
-template <int NT, int SLOTS, int DEPTH, int Q1>
+template <int NT, int SLOTS, int DEPTH, int Q1, int POL>
 __device__ __forceinline__ void any_tile(const SyncArgs &a, const TileDesc &td, v4f *tile, uint16_t *ids)
 {
     if (((td.lo & 3) | (td.n & ~(4 << a.logT))) == 0)             // n is T columns exactly
-        do_tile<NT, SLOTS, DEPTH, Q1, true>(a, td, tile, ids);
+        do_tile<NT, SLOTS, DEPTH, Q1, POL, true>(a, td, tile, ids);
     else
-        do_tile<NT, SLOTS, DEPTH, Q1, false>(a, td, tile, ids);
+        do_tile<NT, SLOTS, DEPTH, Q1, POL, false>(a, td, tile, ids);
 }
 
 // DEPTH < SLOTS is for many workers.  A tile holds theta of all K workers, so its width is what K
@@ -368,7 +367,7 @@ __device__ __forceinline__ void any_tile(const SyncArgs &a, const TileDesc &td, 
 // loaded and parked first, and omega and Delta, whose values no other worker needs, are not held for
 // the whole tile but streamed through DEPTH slots of registers.  256 workers x 6.2 M (19 GB, blocked),
 // T = 32: 6290 us (6040 GB/s); T = 16, all that the registers hold of three arrays: 7576 us.
-template <int NT, int SLOTS, int DEPTH, int Q1>
+template <int NT, int SLOTS, int DEPTH, int Q1, int POL>
 __global__ __launch_bounds__(NT) void sync_kernel(SyncArgs a)
 {
     extern __shared__ float4 lds4[];
@@ -379,15 +378,15 @@ __global__ __launch_bounds__(NT) void sync_kernel(SyncArgs a)
         return;                                                   // not due: the whole workgroup leaves
     if constexpr (Q1 == kMixed) {
         switch (td.q) {
-            case 0: return any_tile<NT, SLOTS, DEPTH, 1>(a, td, tile, ids);
-            case 1: return any_tile<NT, SLOTS, DEPTH, 2>(a, td, tile, ids);
-            case 2: return any_tile<NT, SLOTS, DEPTH, 3>(a, td, tile, ids);
-            case 3: return any_tile<NT, SLOTS, DEPTH, 4>(a, td, tile, ids);
-            case 4: return any_tile<NT, SLOTS, DEPTH, 5>(a, td, tile, ids);
-            default: return any_tile<NT, SLOTS, DEPTH, kUpTo8>(a, td, tile, ids);
+            case 0: return any_tile<NT, SLOTS, DEPTH, 1, POL>(a, td, tile, ids);
+            case 1: return any_tile<NT, SLOTS, DEPTH, 2, POL>(a, td, tile, ids);
+            case 2: return any_tile<NT, SLOTS, DEPTH, 3, POL>(a, td, tile, ids);
+            case 3: return any_tile<NT, SLOTS, DEPTH, 4, POL>(a, td, tile, ids);
+            case 4: return any_tile<NT, SLOTS, DEPTH, 5, POL>(a, td, tile, ids);
+            default: return any_tile<NT, SLOTS, DEPTH, kUpTo8, POL>(a, td, tile, ids);
         }
     } else {
-        any_tile<NT, SLOTS, DEPTH, Q1>(a, td, tile, ids);
+        any_tile<NT, SLOTS, DEPTH, Q1, POL>(a, td, tile, ids);
     }
 }
 
@@ -395,14 +394,14 @@ template <int NT, int SLOTS, int DEPTH>
 KernelFn pick_q(int Q1)
 {
     switch (Q1) {
-        case 1: return sync_kernel<NT, SLOTS, DEPTH, 1>;
-        case 2: return sync_kernel<NT, SLOTS, DEPTH, 2>;
-        case 3: return sync_kernel<NT, SLOTS, DEPTH, 3>;
-        case 4: return sync_kernel<NT, SLOTS, DEPTH, 4>;
-        case 5: return sync_kernel<NT, SLOTS, DEPTH, 5>;
-        case kUpTo8: return sync_kernel<NT, SLOTS, DEPTH, kUpTo8>;
-        case kMixed: return sync_kernel<NT, SLOTS, DEPTH, kMixed>;
-        default: return sync_kernel<NT, SLOTS, DEPTH, kAnyQ>;
+        case 1: return sync_kernel<NT, SLOTS, DEPTH, 1, GBMUF_POLICY>;
+        case 2: return sync_kernel<NT, SLOTS, DEPTH, 2, GBMUF_POLICY>;
+        case 3: return sync_kernel<NT, SLOTS, DEPTH, 3, GBMUF_POLICY>;
+        case 4: return sync_kernel<NT, SLOTS, DEPTH, 4, GBMUF_POLICY>;
+        case 5: return sync_kernel<NT, SLOTS, DEPTH, 5, GBMUF_POLICY>;
+        case kUpTo8: return sync_kernel<NT, SLOTS, DEPTH, kUpTo8, GBMUF_POLICY>;
+        case kMixed: return sync_kernel<NT, SLOTS, DEPTH, kMixed, GBMUF_POLICY>;
+        default: return sync_kernel<NT, SLOTS, DEPTH, kAnyQ, GBMUF_POLICY>;
     }
 }
 
@@ -412,7 +411,7 @@ KernelFn pick_q(int Q1)
     if (v.threads == NT && v.slots == SL && v.depth == D) return pick_q<NT, SL, D>(kernel_q1(q, mixed));
 
 #if GBMUF_PART == 0
-KernelFn pick_kernel_0(const Variant &v, int q, bool mixed)
+KernelFn GBMUF_PICK_NAME(0, GBMUF_POLICY)(const Variant &v, int q, bool mixed)
 {
     GBMUF_CASE(256, 16, 16)
     GBMUF_CASE(256, 2, 2)
@@ -420,7 +419,7 @@ KernelFn pick_kernel_0(const Variant &v, int q, bool mixed)
     return nullptr;
 }
 #elif GBMUF_PART == 1
-KernelFn pick_kernel_1(const Variant &v, int q, bool mixed)
+KernelFn GBMUF_PICK_NAME(1, GBMUF_POLICY)(const Variant &v, int q, bool mixed)
 {
     GBMUF_CASE(512, 16, 4)
     GBMUF_CASE(512, 1, 1)
@@ -428,7 +427,7 @@ KernelFn pick_kernel_1(const Variant &v, int q, bool mixed)
     return nullptr;
 }
 #elif GBMUF_PART == 2
-KernelFn pick_kernel_2(const Variant &v, int q, bool mixed)
+KernelFn GBMUF_PICK_NAME(2, GBMUF_POLICY)(const Variant &v, int q, bool mixed)
 {
     GBMUF_CASE(256, 8, 8)
     GBMUF_CASE(256, 4, 4)
@@ -437,7 +436,7 @@ KernelFn pick_kernel_2(const Variant &v, int q, bool mixed)
     return nullptr;
 }
 #elif GBMUF_PART == 3
-KernelFn pick_kernel_3(const Variant &v, int q, bool mixed)
+KernelFn GBMUF_PICK_NAME(3, GBMUF_POLICY)(const Variant &v, int q, bool mixed)
 {
     GBMUF_CASE(512, 8, 8)
     GBMUF_CASE(1024, 2, 2)
@@ -445,7 +444,7 @@ KernelFn pick_kernel_3(const Variant &v, int q, bool mixed)
     return nullptr;
 }
 #elif GBMUF_PART == 4
-KernelFn pick_kernel_4(const Variant &v, int q, bool mixed)
+KernelFn GBMUF_PICK_NAME(4, GBMUF_POLICY)(const Variant &v, int q, bool mixed)
 {
     GBMUF_CASE(1024, 4, 4)
     GBMUF_CASE(1024, 4, 2)

@@ -14,13 +14,13 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-def check(K, q, off, layout, mode, stride=None, every=None, rounds=(0, 1)):
+def check(K, q, off, layout, mode, stride=None, every=None, rounds=(0, 1), **plan):
     """Syncs in ascending and descending order; `every`: one element of so many is compared, None: all."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     off = np.asarray(off, dtype=np.int64)
     P, seed, ma = int(off[-1]), 5 + K, mode == B.MODE_GOSSIP_MA
-    pl = B.Plan(off, K, q, (q + 1) // 2 if q > 2 else 0, seed=seed)
+    pl = B.Plan(off, K, q, (q + 1) // 2 if q > 2 else 0, seed=seed, **plan)
     st = W.DeviceState(K, P, DEV, layout, stride=stride, plan=pl)
     g = torch.Generator(device=DEV)
     g.manual_seed(seed)
@@ -59,7 +59,27 @@ def test_small_launches(K, q, mode, layout):
     check(K, q, off, "separate" if layout == "odd" else layout, mode, stride_of(layout, off[-1]), rounds=(0, 1, 2))
 
 
-# Just above what the caches hold (20 M values, 60 M of gossip-MA).
+# The sizes between: 2 to 5 M values, 5 to 20 M, and gossip-MA above that, in shapes of their own.
+@pytest.mark.parametrize("layout", ["blocked", "rows", "odd"])
+@pytest.mark.parametrize("values,mode", [(3_100_000, B.MODE_PAPER), (11_000_000, B.MODE_PAPER), (3_100_000, B.MODE_GOSSIP_MA),
+                                         (11_000_000, B.MODE_GOSSIP_MA), (22_000_000, B.MODE_GOSSIP_MA)])
+@pytest.mark.parametrize("K,q", [(1, 0), (2, 1), (4, 1), (7, 2), (8, 3), (12, 2), (16, 4), (24, 5), (32, 3), (47, 9), (64, 2), (96, 3), (128, 1), (200, 2),
+                                 (300, 3), (600, 1)])
+def test_launches_between(K, q, values, mode, layout):
+    P = values // K
+    off = [0, P // 3 | 1, P // 3 + 70 | 1, P // 3 * 2, P]
+    check(K, q, off, "separate" if layout == "odd" else layout, mode, stride_of(layout, P), every=128 if K <= 128 else 16)
+
+
+# Streamed accesses at sizes that take plain ones by themselves.
+@pytest.mark.parametrize("layout", ["blocked", "separate", "odd"])
+@pytest.mark.parametrize("K,q,mode", [(3, 2, B.MODE_PAPER), (16, 3, B.MODE_LITERAL), (24, 9, B.MODE_PAPER), (64, 5, B.MODE_GOSSIP_MA), (300, 2, B.MODE_PAPER)])
+def test_cache_hints(K, q, mode, layout):
+    off = [0, 5, 4099, 4100, 8192, 8193, 13001, 18437]
+    check(K, q, off, layout if layout == "blocked" else "separate", mode, stride_of(layout, off[-1]), cache_hints=3)
+
+
+# Just above 20 M values; 60 M of gossip-MA on rows that share lines.
 @pytest.mark.parametrize("layout", ["blocked", "rows", "odd"])
 @pytest.mark.parametrize("mode", [B.MODE_PAPER, B.MODE_GOSSIP_MA])
 @pytest.mark.parametrize("K,q", [(1, 0), (3, 2), (5, 1), (12, 3), (16, 9), (17, 2), (25, 5), (32, 1), (33, 2), (45, 3), (63, 4), (64, 7), (65, 2),
