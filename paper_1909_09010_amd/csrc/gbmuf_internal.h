@@ -93,6 +93,7 @@ struct CopyArgs {
     int64_t P;
     int32_t K;
     uint32_t run_len;        // pieces of one worker that follow each other (set by the launch)
+    uint32_t fold;           // arrays whose runs follow each other (set by the launch)
 };
 
 // One tile shape of the fused kernel: threads per workgroup and 16-byte slots per thread.
@@ -144,7 +145,7 @@ struct AverageShape {
     int rows_in_flight;      // 16-byte loads a thread keeps in flight: 4, 8 or 16
     size_t lds_floor;        // bounds the resident one-wave workgroups per compute unit like in launch_sync
     int xcd_log;             // log2 of the consecutive workgroups that one XCD takes
-    bool rotate;
+    int policy;              // kPlain or kStreamed
 };
 int launch_final_average(const float *theta, const Placement &at, int K, int64_t P, float inv, float *out,
                          const AverageShape &shape, hipStream_t stream);

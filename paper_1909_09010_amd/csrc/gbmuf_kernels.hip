@@ -98,14 +98,14 @@ __device__ __forceinline__ V worker_mean(const float *col, int K, int64_t stride
 
 template <int B, int POL>
 __global__ __launch_bounds__(64) void final_average_kernel(const float *theta, Placement at, int K, int64_t P,
-                                                           float inv, float *out, int xcd_log, int rotate)
+                                                           float inv, float *out, int xcd_log)
 {
     // as in the fused kernel, XCD r takes the r-th run of 2^xcd_log workgroups in every group of 8 runs
     const unsigned lg = static_cast<unsigned>(xcd_log), whole = (gridDim.x >> (3 + lg)) << (3 + lg);
     unsigned b = blockIdx.x;
     if (b < whole) {
-        const unsigned i = b >> 3, group = i >> lg, r = (b + (rotate ? group >> 3 : 0u)) & 7u;
-        b = (((group << 3) | r) << lg) | (i & ((1u << lg) - 1u));
+        const unsigned i = b >> 3, group = i >> lg;
+        b = (((group << 3) | (b & 7u)) << lg) | (i & ((1u << lg) - 1u));
     }
     const int64_t i = static_cast<int64_t>(b) * 64 + threadIdx.x;
     const int64_t n4 = P >> 2;
@@ -120,35 +120,30 @@ __global__ __launch_bounds__(64) void final_average_kernel(const float *theta, P
 }
 
 // ---------------------------------------------------------------------------------------
-// Copy of up to three state arrays between two placements (blockIdx.z = array), one 16-byte column
+// Copy of up to three state arrays between two placements, one 16-byte column
 // per thread, one load and one store in flight each: more of either per thread is slower here (5.6
 // against 6.2 TB/s on a plain copy).  The rows are cut into pieces of 256 columns (4 KB); the pieces
-// are walked in runs of run_len pieces of one worker, then the same run of the next worker.  Columns are counted from
+// are walked in runs of run_len pieces of one worker, then the same run of the next worker, and of `fold` arrays one after the
+// other before the next run; blockIdx.z counts the arrays that are not folded.  Columns are counted from
 // the destination row's 128-byte line, so that stores cover whole lines; the loads take any 4-byte address.
-// Bound by HBM, which takes two long streams best: rows are copied whole, worker by worker, and so are arrays that the
-// caches hold (10 x 1.2 M to blocked 18 us, in pieces 22).  In a blocked source every
-// 32 KB of a row is followed by 32 KB of the next worker, and runs of a few blocks walk it nearly in its own order; into
-// a blocked destination a piece at a time does the same for few workers.  us for three arrays, runs of 4 KB / 16 KB /
-// 128 KB / whole rows:
-//   padded rows: 4 workers x 128 M 1985 / 2045 / 2072 / 1987, 64 x 7.9 M 2278 / 2343 / 2378 / 1966.
-//   blocked to blocked: 16 x 31.5 M 2288 / 2093 / 2025 / 2390, 64 x 7.9 M 2275 / 2052 / 2173 / 2378.
-//   blocked to plain rows: 16 x 31.5 M 2201 / 2205 / 2198 / 2295, 200 x 2.4 M 2183 / 2153 / 2201 / 2292.
-//   plain rows to blocked: 16 x 31.5 M 2132 / 2197 / 2178 / 2218, 64 x 7.9 M 2336 / 2307 / 2179 / 2239.
+//
+// Bound by HBM, which takes two long streams best.  Stores go through the L2 at once, and beyond the caches loads leave it
+// first (choose_policy on the host says why; 1 M values 5.0 us, plain stores 5.7).  The host chooses the walk.
 // ---------------------------------------------------------------------------------------
-template <int POL>
+template <int LOADS>
 __global__ __launch_bounds__(256) void state_copy_kernel(CopyArgs a)
 {
-    const uint32_t i = blockIdx.y * gridDim.x + blockIdx.x, K = static_cast<uint32_t>(a.K);
-    const uint32_t run = i / a.run_len, group = run / K, w = run - group * K;
+    const uint32_t i = blockIdx.y * gridDim.x + blockIdx.x, K = static_cast<uint32_t>(a.K), rows = K * a.fold;
+    const uint32_t run = i / a.run_len, group = run / rows, row = run - group * rows, array = row / K, w = row - array * K;
     const int64_t piece = static_cast<int64_t>(group) * a.run_len + (i - run * a.run_len);
-    const float *src = a.src[blockIdx.z] + w * a.sa.stride;
-    float *dst = a.dst[blockIdx.z] + w * a.da.stride;
+    const float *src = a.src[blockIdx.z + array] + w * a.sa.stride;
+    float *dst = a.dst[blockIdx.z + array] + w * a.da.stride;
     const int64_t head = static_cast<int64_t>((reinterpret_cast<uintptr_t>(dst) >> 2) & 31u);
     const int64_t e = (piece * 256 + threadIdx.x) * 4 - head;
     if (e >= a.P) return;
     // four floats that neither side cuts at a block edge
     if (e >= 0 && e + 4 <= a.P && ((e ^ (e + 3)) >> a.sa.logB) == 0 && ((e ^ (e + 3)) >> a.da.logB) == 0) {
-        store4<POL>(dst + placed(a.da, e), load4<POL>(src + placed(a.sa, e)));
+        store4<kStreamed>(dst + placed(a.da, e), load4<LOADS>(src + placed(a.sa, e)));
         return;
     }
     for (int c = 0; c < 4; ++c)
@@ -177,34 +172,57 @@ int launch_final_average(const float *theta, const Placement &at, int K, int64_t
     const int64_t blocks = ((P >> 2) + 63) / 64 + ((P & 3) != 0);
     if (blocks > 0x7fffffffLL) return GBMUF_EUNSUPPORTED;
     Placement pl = at;
-    int xcd_log = shape.xcd_log, rotate = shape.rotate ? 1 : 0;
-    void *argv[] = {&theta, &pl, &K, &P, &inv, &out, &xcd_log, &rotate};
-    const void *fn = shape.rows_in_flight <= 4   ? reinterpret_cast<const void *>(final_average_kernel<4, kPlain>)
-                     : shape.rows_in_flight <= 8 ? reinterpret_cast<const void *>(final_average_kernel<8, kPlain>)
-                                                 : reinterpret_cast<const void *>(final_average_kernel<16, kPlain>);
+    int xcd_log = shape.xcd_log;
+    void *argv[] = {&theta, &pl, &K, &P, &inv, &out, &xcd_log};
+    const bool streamed = shape.policy == kStreamed;
+    using Fn = void (*)(const float *, Placement, int, int64_t, float, float *, int);
+    const Fn kernel = shape.rows_in_flight <= 4   ? (streamed ? final_average_kernel<4, kStreamed> : final_average_kernel<4, kPlain>)
+                      : shape.rows_in_flight <= 8 ? final_average_kernel<8, kPlain>
+                                                  : (streamed ? final_average_kernel<16, kStreamed> : final_average_kernel<16, kPlain>);
+    const void *fn = reinterpret_cast<const void *>(kernel);
     const hipError_t err = hipLaunchKernel(fn, dim3(static_cast<unsigned>(blocks)), dim3(64), argv, lds_floor, stream);
     return err == hipSuccess ? GBMUF_OK : hip_failed("hipLaunchKernel(final average)", err, GBMUF_EDEVICE);
 }
 
+// The walk of a copy.  Rows to rows are copied whole, array by array: two long streams.  A blocked side is one stretch of memory where
+// the arrays of a run follow each other.  us for three arrays, now / runs of 4 KB to 128 KB or whole rows, array by array, at their best:
+//   blocked to blocked, 32 KB, folded, 400 M values: 3 workers 1420 / 1625, 44 workers 1418 / 1751, 300 workers 1411 / 1463.
+//   rows to blocked, folded, up to 32 workers 128 KB: 3 x 133 M odd rows 1528 / 1713, 24 x 16.7 M 1602 / 1633; more workers 32 KB: 44 x 9.1 M 1610
+//     / 1678, 128 x 3.1 M 1582 / 1633; at 128 KB 1662 and more than 1690.  More than 32 workers and up to 40 M values whole rows: 64 x
+//     0.47 M 121 / folded 131.
+//   blocked to rows, array by array: aligned rows of up to 16 workers 32 KB, 12 x 33 M 1469 / whole rows 1505, of more whole rows, 44 x 9.1 M
+//     1513 / 1631; rows that share lines of up to 48 workers 4 KB, 24 x 16.7 M 1629 / whole rows 1710, 44 x 9.1 M 1745 / 1782, of
+//     more whole rows, 100 x 4 M 1673 / 4 KB 1860.
+//   Up to 4 M values the caches hold them: whole rows, which stay there.
 int launch_state_copy(const CopyArgs &c, int arrays, hipStream_t stream)
 {
     if (c.P <= 0 || c.K <= 0 || arrays <= 0) return GBMUF_OK;
     CopyArgs args = c;
-    const int64_t pieces = (c.P + 31 + 1023) / 1024;       // 31: the largest head
+    const int64_t pieces = (c.P + 31 + 1023) / 1024, values = c.P * c.K;       // 31: the largest head
+    const bool from = c.sa.logB != 62, to = c.da.logB != 62, streamed = values > 4000000;
     int64_t run = pieces;
-    if (c.P * c.K > 30000000) {                            // smaller arrays stay in the caches
-        if (c.sa.logB != 62) run = c.K <= 32 ? 32 : 4;
-        else if (c.da.logB != 62 && c.K <= 16) run = 1;
+    bool fold = false;
+    if (streamed && to && (from || c.K <= 32 || values > 40000000)) {
+        run = !from && c.K <= 32 ? 32 : 8;
+        fold = true;
+    } else if (streamed && from && !to) {
+        bool shared = c.K > 1 && c.da.stride % 32 != 0;
+        for (int n = 0; n < arrays; ++n) shared = shared || reinterpret_cast<uintptr_t>(c.dst[n]) % 128 != 0;
+        if (c.K <= (shared ? 48 : 16)) run = shared ? 1 : 8;
     }
     const int64_t len = std::min(run, pieces);
-    const int64_t blocks = (pieces + len - 1) / len * len * c.K;
+    int64_t blocks = (pieces + len - 1) / len * len * c.K;
+    if (fold && blocks * arrays > (static_cast<int64_t>(511) << 23)) fold = false;
     args.run_len = static_cast<uint32_t>(len);
+    args.fold = fold ? static_cast<uint32_t>(arrays) : 1u;
+    blocks *= args.fold;
     // a grid holds fewer than 2^32 threads along x: the rest goes along y
     const int64_t x = blocks < (1 << 23) ? blocks : (1 << 23), y = (blocks + x - 1) / x;
     if (y > 511) return GBMUF_EUNSUPPORTED;                // 17 TB: the kernel counts pieces in 32 bits
+    const unsigned z = fold ? 1u : static_cast<unsigned>(arrays);
     void *argv[] = {&args};
-    const hipError_t err = hipLaunchKernel(reinterpret_cast<const void *>(state_copy_kernel<kPlain>),
-                                           dim3(static_cast<unsigned>(x), static_cast<unsigned>(y), static_cast<unsigned>(arrays)),
+    const auto kernel = streamed ? state_copy_kernel<kStreamed> : state_copy_kernel<kPlain>;
+    const hipError_t err = hipLaunchKernel(reinterpret_cast<const void *>(kernel), dim3(static_cast<unsigned>(x), static_cast<unsigned>(y), z),
                                            dim3(256), argv, 0, stream);
     return err == hipSuccess ? GBMUF_OK : hip_failed("hipLaunchKernel(state copy)", err, GBMUF_EDEVICE);
 }

@@ -610,34 +610,34 @@ size_t lds_floor(const gbmuf_plan_s *pl, const LayoutCfg &cfg)
     return share > 0 ? static_cast<size_t>(share) : 0;
 }
 
-// Rows in flight per thread, resident one-wave workgroups per CU (32: as many as fit) and who reads what, for a final
+// Rows in flight per thread, resident one-wave workgroups per CU (32: as many as fit), who reads what and how, for a final
 // average.  us on MI355X, in the order of the rules:
-//   sums of up to 60 M values come from the caches, whose latency more waves hide, with enough rows per thread that few
-//     workers take one pass: 8 x 4.2 M padded 25 (16 rows x 3 waves 33), 64 x 0.6 M 26 (4 x 8: 30), 1024 x 36 K 66 (8
-//     rows 87).
+//   sums of up to 20 M values come from the caches, which plain loads leave them in (64 x 0.16 M 7.4, streamed 8.1) and whose latency
+//     more waves hide, with enough rows per thread that few workers take one pass: 8 x 4.2 M padded 25 (16 rows x 3 waves 33),
+//     1024 x 36 K 66 (8 rows 87).
+//   beyond, streamed: 8 x 25 M blocked 127, plain 145; 64 x 15.6 M padded 607, plain 674.  Up to 60 M without bound.
 //   one worker is a copy: 590 M 746, 16 waves 770, 8 waves 1303.
-//   blocked: as many loads as HBM takes best, fewer waves the more rows each has in flight: 8 x 16.1 M 97 (8 rows x 8; x
-//     32 107), 16 x 31.8 M 355 (16 x 6; x 32 383), 32 x 16.2 M 340 (16 x 4; x 32 376), 64 x 9.4 M 385 (8 x 4, XCDs
-//     rotated; x 8 399), 128 x 3.9 M 317 (16 x 3; x 32 336).
-//   rows: 2 x 61.6 M 123 (4 x 16; x 8 156), 4 x 134 M 433 (4 x 12; x 8 449), 8 x 16.1 M 100 (4 x 8; x 32 108), 16 x 31.8 M 362 (x
-//     32 400), 64 x 9.4 M 395 (x 32 424), 512 x 1 M 339 (16 x 6; 4 x 8 366).  Rows that share cache lines (xcd_run): 4 KB
-//     per XCD, 4 x 134 M 442, workgroup by workgroup 447.
+//   larger sums take 4 rows at a time, and the fewer waves the more workers there are: blocked 4 x 50 M 142 (12 waves), 64 x 3.1 M 119 (6;
+//     8 rows x 4 125), 128 x 7.8 M 577 (6; 16 rows x 3 591); padded 16 x 62 M 630 (8), 128 x 1.6 M 122 (8; 16 rows x 6 134).  4 KB per
+//     XCD where rows share lines (2 x 100 M 185, workgroup by workgroup 191) and for 9 to 64 workers of blocked state (16 x 62 M
+//     601 / 614, 64 x 15.6 M 599 / 607).
 AverageShape average_shape(const gbmuf_plan_s *pl, int layout, bool shared_lines)
 {
     const int K = pl->K;
+    const int64_t values = static_cast<int64_t>(K) * pl->P;
     AverageShape s{};
     int waves = 32;
-    if (static_cast<int64_t>(K) * pl->P <= 60000000) {
+    if (values <= kCompactValues) {
         s.rows_in_flight = K <= 4 ? 4 : K <= 16 ? 8 : 16;
         s.xcd_log = K > 1 ? 2 : 0;
-    } else if (layout == kBlocked) {
-        s.rows_in_flight = K <= 3 ? 4 : K <= 8 || (K > 32 && K <= 64) ? 8 : 16;
-        waves = K <= 3 ? 32 : K <= 8 ? 8 : K <= 16 ? 6 : K <= 64 ? 4 : 3;
-        s.rotate = K > 32 && K <= 64;
     } else {
-        s.rows_in_flight = K <= 64 ? 4 : 16;
-        waves = K == 1 ? 32 : K <= 3 ? 16 : K <= 7 ? 12 : K <= 64 ? 8 : 6;
-        s.xcd_log = K > 1 && shared_lines ? 2 : 0;
+        s.policy = kStreamed;
+        s.rows_in_flight = K <= 64 || values > 60000000 ? 4 : 16;
+        if (values > 60000000) {
+            if (layout == kBlocked) waves = K <= 3 ? 32 : K <= 7 ? 12 : K <= 16 ? 8 : 6;
+            else waves = K == 1 ? 32 : K <= 3 ? 16 : K <= 7 ? 12 : K <= 128 ? 8 : 6;
+        }
+        s.xcd_log = (K > 1 && shared_lines) || (layout == kBlocked && K > 8 && K <= 64) ? 2 : 0;
     }
     if (waves < 32 && pl->lds_per_cu > 0) s.lds_floor = static_cast<size_t>(std::max(0, pl->lds_per_cu / waves - 2048));
     return s;

@@ -64,13 +64,13 @@ def test_every_tile_is_taken_once_around_the_xcd_groups(K, tiles, odd):
     assert mode == B.MODE_GOSSIP_MA or info.n_tiles in (n, n + 1)         # the component edge cuts one tile
 
 
-# one piece is 256 columns of 4 floats; the destination's first column starts up to 31 floats before the row; above 30 M
-# floats an array is copied in runs: from a blocked one of 32 pieces of up to 32 workers, 4 of more, into a blocked one of
-# 1 piece of up to 16 workers; else row by row
+# one piece is 256 columns of 4 floats; the destination's first column starts up to 31 floats before the row; above 4 M
+# floats an array is copied in runs of 1, 8 or 32 pieces or whole rows, by kind, workers and size, into a blocked one all arrays together
 @pytest.mark.parametrize("K,P", [(K, P) for K in (1, 3, 16, 33, 64) for P in (1, 3, 1023, 1024, 1057, 32 * 1024 - 1, 32 * 1024 + 5,
                                                                               3 * 32 * 1024 + 1021)] + [
     (1, 30_000_001), (3, 10_012_677), (16, 1_900_545), (17, 1_773_529), (32, 950_273), (33, 917_509), (64, 470_017),
-    (128, 262_149), (1024, 33_797)])
+    (128, 262_149), (1024, 33_797), (1, 4_000_001), (3, 1_400_001), (16, 250_007), (17, 240_001), (32, 125_003), (33, 125_001),
+    (48, 91_001), (49, 90_003), (33, 1_230_001), (300, 136_003)])
 @pytest.mark.parametrize("which", [7, 2, 5])
 def test_state_copy_at_the_edges_of_its_pieces(K, P, which):
     _need_gpu()
