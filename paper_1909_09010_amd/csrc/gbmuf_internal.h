@@ -145,6 +145,7 @@ struct AverageShape {
     int rows_in_flight;      // 16-byte loads a thread keeps in flight: 4, 8 or 16
     size_t lds_floor;        // bounds the resident one-wave workgroups per compute unit like in launch_sync
     int xcd_log;             // log2 of the consecutive workgroups that one XCD takes
+    bool rotate;             // see the fused kernel's tile_of_block
     int policy;              // kPlain or kStreamed
 };
 int launch_final_average(const float *theta, const Placement &at, int K, int64_t P, float inv, float *out,

@@ -98,14 +98,14 @@ __device__ __forceinline__ V worker_mean(const float *col, int K, int64_t stride
 
 template <int B, int POL>
 __global__ __launch_bounds__(64) void final_average_kernel(const float *theta, Placement at, int K, int64_t P,
-                                                           float inv, float *out, int xcd_log)
+                                                           float inv, float *out, int xcd_log, int rotate)
 {
     // as in the fused kernel, XCD r takes the r-th run of 2^xcd_log workgroups in every group of 8 runs
     const unsigned lg = static_cast<unsigned>(xcd_log), whole = (gridDim.x >> (3 + lg)) << (3 + lg);
     unsigned b = blockIdx.x;
     if (b < whole) {
-        const unsigned i = b >> 3, group = i >> lg;
-        b = (((group << 3) | (b & 7u)) << lg) | (i & ((1u << lg) - 1u));
+        const unsigned i = b >> 3, group = i >> lg, r = (b + (rotate ? group >> 3 : 0u)) & 7u;
+        b = (((group << 3) | r) << lg) | (i & ((1u << lg) - 1u));
     }
     const int64_t i = static_cast<int64_t>(b) * 64 + threadIdx.x;
     const int64_t n4 = P >> 2;
@@ -172,10 +172,10 @@ int launch_final_average(const float *theta, const Placement &at, int K, int64_t
     const int64_t blocks = ((P >> 2) + 63) / 64 + ((P & 3) != 0);
     if (blocks > 0x7fffffffLL) return GBMUF_EUNSUPPORTED;
     Placement pl = at;
-    int xcd_log = shape.xcd_log;
-    void *argv[] = {&theta, &pl, &K, &P, &inv, &out, &xcd_log};
+    int xcd_log = shape.xcd_log, rotate = shape.rotate ? 1 : 0;
+    void *argv[] = {&theta, &pl, &K, &P, &inv, &out, &xcd_log, &rotate};
     const bool streamed = shape.policy == kStreamed;
-    using Fn = void (*)(const float *, Placement, int, int64_t, float, float *, int);
+    using Fn = void (*)(const float *, Placement, int, int64_t, float, float *, int, int);
     const Fn kernel = shape.rows_in_flight <= 4   ? (streamed ? final_average_kernel<4, kStreamed> : final_average_kernel<4, kPlain>)
                       : shape.rows_in_flight <= 8 ? final_average_kernel<8, kPlain>
                                                   : (streamed ? final_average_kernel<16, kStreamed> : final_average_kernel<16, kPlain>);

@@ -293,10 +293,10 @@ Variant shared_variant(int K, int what, int size, bool few)
 //     7.5 M 1072 us, 512 x 4 1057; 64 x 4.7 M 1070, 512 x 4 1085), 65-128 kMany, 129-512 kVeryMany (200 x 1.5 M 1167, kMany 1185;
 //     256 x 1.2 M 1156, kSixtyFour 1165; 300 x 1 M 1245, kMany 1206), up to 20 M values kSixtyFour (200 x 0.1 M 84 us, kMany 88).
 //   Aligned rows are 3K address streams: 5.9 up to 8 workers, 5.1 from 64 on, whatever the shape.  Wide tiles, and 4 KB
-//     of a row per XCD from 65 workers on (96 x 2.6 M 1175 us, tile by tile 1210).  2-4 256 x 1, four per CU (4 x 62.5 M 987 us;
+//     of a row per XCD from 65 workers on, from 129 above 500 M values (96 x 2.6 M 1167 us, tile by tile 1210).  2-4 256 x 1, four per CU (4 x 62.5 M 987 us;
 //     unbounded 1034), 5-8 1024 x 1 (8 x 87.5 M 2852; kSixtyFour 2900, 512 x 1 2998), 9-32 kSixtyFour (32 x 7.8 M 1136; 1024 x 2 1152), 33-64
-//     kVeryMany (48 x 5.2 M 1136; 1024 x 2 1197), 65-128 kSixtyFour (1175 / 1185; 1024 x 4 1223 / 1227), above kVeryMany (300 x
-//     0.8 M 1209, 4 KB per XCD not taken 1259).  5 to 20 M values of more than 32 workers: 1024 x 4.
+//     kVeryMany (48 x 5.2 M 1136; 1024 x 2 1197), 65-128 512 x 4 (96 x 2.6 M 1167, 1024 x 4 1223), above 500 M values kVeryMany (88 x 22.7 M 7895,
+//     1024 x 4 8075), above 128 workers kVeryMany (300 x 0.8 M 1209, 4 KB per XCD not taken 1259).  5 to 20 M values of more than 32 workers: 1024 x 4.
 //   Gossip-MA has a third of the loads and takes more slots per thread.  Blocked: up to 2 workers 256 x 1, up to 16 256 x 2 where K rows
 //     fill it to 7/8 (8 x 75 M 723 us; 512 x 2 748), else 256 x 4, up to 32 256 x 4 (725; 512 x 2 735), 33-64 512 x 4, above 1024 x 4, large of
 //     more than 256 workers kVeryMany (300 x 2 M 947; 956).  Rows: up to 8 256 x 2, up to 24 256 x 4, up to 64 1024 x 4, above
@@ -336,7 +336,7 @@ void aligned_shape(int K, int layout, int what, int size, bool few, LayoutCfg &c
         else if (K <= 8) find_variant(1024, 1, &v);
         else if (K <= 32) v = kSixtyFour;
         else if (size == kCompact) v = Variant{1024, 4, 4};
-        else if (K > 64 && K <= 128) v = kSixtyFour;
+        else if (K > 64 && K <= 128 && size != kLarge) find_variant(512, 4, &v);
         else if (few) v = kVeryMany;
         if (K <= 4) bound = 4;
     }
@@ -345,7 +345,7 @@ void aligned_shape(int K, int layout, int what, int size, bool few, LayoutCfg &c
         cfg.rotate = K > 32 && (K <= 128 || what == kMa || size != kCompact);
         run = cfg.rotate ? 0 : 6;
     } else {
-        run = K > (size == kCompact || what == kMa ? 16 : 64) ? 8 : 0;
+        run = K > (size == kCompact || what == kMa ? 16 : size == kLarge ? 128 : 64) ? 8 : 0;
     }
 }
 // Small plans with rows of more than 7 neighbours draw them through LDS in every workgroup (launch_bound), a thread a
@@ -618,9 +618,10 @@ size_t lds_floor(const gbmuf_plan_s *pl, const LayoutCfg &cfg)
 //   beyond, streamed: 8 x 25 M blocked 127, plain 145; 64 x 15.6 M padded 607, plain 674.  Up to 60 M without bound.
 //   one worker is a copy: 590 M 746, 16 waves 770, 8 waves 1303.
 //   larger sums take 4 rows at a time, and the fewer waves the more workers there are: blocked 4 x 50 M 142 (12 waves), 64 x 3.1 M 119 (6;
-//     8 rows x 4 125), 128 x 7.8 M 577 (6; 16 rows x 3 591); padded 16 x 62 M 630 (8), 128 x 1.6 M 122 (8; 16 rows x 6 134).  4 KB per
-//     XCD where rows share lines (2 x 100 M 185, workgroup by workgroup 191) and for 9 to 64 workers of blocked state (16 x 62 M
-//     601 / 614, 64 x 15.6 M 599 / 607).
+//     8 rows x 4 125), 128 x 7.8 M 577 (6; 16 rows x 3 591); padded 16 x 62 M 630 (8), 128 x 1.6 M 122 (8; 16 rows x 6 134).  Blocked 9 to 16
+//     workers: 16 rows x 4 waves (16 x 231 M 2177, 4 x 8 2250).  4 KB per XCD where rows share lines (2 x 100 M 185, workgroup by
+//     workgroup 191) and for 9 to 64 workers of blocked state (32 x 116 M 2092 / 2130), but 33 to 64 of more than 500 M
+//     values move on by an XCD from block to block as in the fused kernel (64 x 57.8 M 2177, 4 KB per XCD 2250; 64 x 3.1 M 121 / 119).
 AverageShape average_shape(const gbmuf_plan_s *pl, int layout, bool shared_lines)
 {
     const int K = pl->K;
@@ -633,11 +634,17 @@ AverageShape average_shape(const gbmuf_plan_s *pl, int layout, bool shared_lines
     } else {
         s.policy = kStreamed;
         s.rows_in_flight = K <= 64 || values > 60000000 ? 4 : 16;
-        if (values > 60000000) {
-            if (layout == kBlocked) waves = K <= 3 ? 32 : K <= 7 ? 12 : K <= 16 ? 8 : 6;
-            else waves = K == 1 ? 32 : K <= 3 ? 16 : K <= 7 ? 12 : K <= 128 ? 8 : 6;
-        }
         s.xcd_log = (K > 1 && shared_lines) || (layout == kBlocked && K > 8 && K <= 64) ? 2 : 0;
+        if (values > 60000000) {
+            if (layout == kBlocked) {
+                waves = K <= 3 ? 32 : K <= 7 ? 12 : K <= 8 ? 8 : K <= 16 ? 4 : 6;
+                if (K > 8 && K <= 16) s.rows_in_flight = 16;
+                s.rotate = K > 32 && K <= 64 && values > kLargeValues;
+                if (s.rotate) s.xcd_log = 0;
+            } else {
+                waves = K == 1 ? 32 : K <= 3 ? 16 : K <= 7 ? 12 : K <= 128 ? 8 : 6;
+            }
+        }
     }
     if (waves < 32 && pl->lds_per_cu > 0) s.lds_floor = static_cast<size_t>(std::max(0, pl->lds_per_cu / waves - 2048));
     return s;
