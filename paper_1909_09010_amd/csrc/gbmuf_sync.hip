@@ -42,6 +42,14 @@ __device__ __forceinline__ void filter(float avg, float om, float de, float eta,
     th_out = tn; om_out = on; de_out = dn;
 }
 
+// Keeps the compiler from moving the computation of a uniform value into a branch, or its load apart.
+__device__ __forceinline__ void hold(uint32_t &x)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm("" : "+s"(x));
+#endif
+}
+
 // Which tile this workgroup takes.  Workgroups are dealt round-robin to the 8 XCDs (blockIdx mod 8);
 // the list is cut into groups of 8 * 2^xcd_log consecutive tiles, and in every group XCD r takes the
 // r-th run of 2^xcd_log tiles; with the rotate flag the runs move on by one XCD every 8 groups
@@ -50,22 +58,33 @@ __device__ __forceinline__ void filter(float avg, float om, float de, float eta,
 // previous sync wrote last is read first, while it may still be in the 256 MB memory-side cache (it
 // is for states of up to a few GB; larger states neither gain nor lose); the XCD of a tile stays the
 // same up to the rotation.  Tiles beyond the last whole group are taken in order.
+//
+// This and the load of the descriptor stand before a workgroup's first access of state and are not hidden where one or two
+// workgroups fill a CU: nothing here branches, so that all arguments are fetched at once, and the descriptor is one scalar load.
 __device__ __forceinline__ unsigned tile_of_block(const SyncArgs &a)
 {
-    const unsigned n = gridDim.x, lg = static_cast<unsigned>(a.xcd_log);
+    const unsigned n = gridDim.x, lg = static_cast<unsigned>(a.xcd_log), b = blockIdx.x;
+    const unsigned back = (a.flags & kFlagBackwards) ? ~0u : 0u;  // a mask: x ^ back is x or -1 - x
     const unsigned whole = (n >> (3 + lg)) << (3 + lg);           // tiles in whole groups
-    unsigned b = blockIdx.x, i;
-    if (a.flags & kFlagBackwards) {
-        const unsigned rest = n - whole;                          // these come first
-        if (b < rest) return n - 1u - b;
-        i = (whole >> 3) - 1u - ((b - rest) >> 3);
-    } else {
-        if (b >= whole) return b;
-        i = b >> 3;
-    }
+    const unsigned rest = back & (n - whole);                     // backwards the others come first
+    const unsigned i = (back & (whole >> 3)) + (((b - rest) >> 3) ^ back);
     const unsigned group = i >> lg;
     const unsigned r = (b + ((a.flags & kFlagRotate) ? group >> 3 : 0u)) & 7u;
-    return (((group << 3) | r) << lg) | (i & ((1u << lg) - 1u));
+    unsigned in_group = (((group << 3) | r) << lg) | (i & ((1u << lg) - 1u)), alone = (back & n) + (b ^ back);
+    hold(in_group);
+    hold(alone);
+    return b - rest < whole ? in_group : alone;                   // backwards b < rest wraps to beyond whole
+}
+
+__device__ __forceinline__ TileDesc load_tile(const TileDesc *p)
+{
+    typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+    const v4u v = *reinterpret_cast<const v4u *>(p);
+    uint32_t w[4] = {v[0], v[1], v[2], v[3]};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) hold(w[i]);                       // else it is taken apart into loads of each field
+    return TileDesc{static_cast<int64_t>(w[0] | (static_cast<uint64_t>(w[1]) << 32)), static_cast<uint16_t>(w[2] & 0xFFFFu),
+                    static_cast<uint16_t>(w[2] >> 16), static_cast<int32_t>(w[3])};
 }
 
 // ---------------------------------------------------------------------------------------
@@ -117,32 +136,42 @@ struct LdsRow {
     __device__ int32_t &operator()(int32_t x) const { return base[x]; }
 };
 
-// The rows of one tile.  begin() is called before the tile's loads are issued, finish() after.  The compiler moves the
-// clamping up and waits for the table first; with the table's loads behind the tile's the time is the same within 1 %.
+// The rows of one tile.  begin() is called before the tile's loads are issued, finish() after.
 // a.nbr == nullptr: thread w draws for worker w.
 template <int NT, int Q1>
 struct Rows {
     int32_t v[Q1];
     __device__ __forceinline__ void begin(const SyncArgs &a, const TileDesc &td)
     {
-        const int tid = threadIdx.x, q = Q1 == kUpTo8 ? td.q : Q1 - 1;
-        if (a.nbr != nullptr && tid < a.K) load_row<Q1>(v, a, td.comp, tid, q);
+        const int q = Q1 == kUpTo8 ? td.q : Q1 - 1;
+        if (a.nbr != nullptr) load_row<Q1>(v, a, td.comp, min(static_cast<int>(threadIdx.x), a.K - 1), q);
+    }
+    __device__ __forceinline__ void put(const SyncArgs &a, const TileDesc &td, uint16_t *ids, int w, int q)
+    {
+        if (a.nbr != nullptr) {
+#if defined(__HIP_DEVICE_COMPILE__)
+            // the row is first looked at here: the compiler would move the clamping up to its load and wait for it
+            // before the tile's loads are issued
+#pragma unroll
+            for (int j = 0; j < Q1 - 1; ++j) asm volatile("" : "+v"(v[j]));
+#endif
+            clamp_row<Q1>(v, a.K);
+        } else if constexpr (Q1 > 1) {
+            int32_t picked[Q1 - 1];
+            draw_few<Q1 - 1>(picked, a.K, a.p, a.C, q, DrawKey{a.key0, a.key1, a.round0, a.round1},
+                             static_cast<uint32_t>(td.comp), w);
+#pragma unroll
+            for (int j = 0; j < Q1 - 1; ++j) v[j] = picked[j];
+        }
+        put_row<Q1>(ids + w * ids_pitch(Q1, 0), v, w, q);
     }
     __device__ __forceinline__ void finish(const SyncArgs &a, const TileDesc &td, uint16_t *ids)
     {
-        const int K = a.K, q = Q1 == kUpTo8 ? td.q : Q1 - 1;
-        for (int w = threadIdx.x; w < K; w += NT) {
-            if (a.nbr != nullptr) {
-                if (w >= NT) load_row<Q1>(v, a, td.comp, w, q);
-                clamp_row<Q1>(v, K);
-            } else if constexpr (Q1 > 1) {
-                int32_t picked[Q1 - 1];
-                draw_few<Q1 - 1>(picked, K, a.p, a.C, q, DrawKey{a.key0, a.key1, a.round0, a.round1},
-                                 static_cast<uint32_t>(td.comp), w);
-#pragma unroll
-                for (int j = 0; j < Q1 - 1; ++j) v[j] = picked[j];
-            }
-            put_row<Q1>(ids + w * ids_pitch(Q1, 0), v, w, q);
+        const int K = a.K, q = Q1 == kUpTo8 ? td.q : Q1 - 1, first = threadIdx.x;
+        if (first < K) put(a, td, ids, first, q);
+        for (int w = first + NT; w < K; w += NT) {
+            if (a.nbr != nullptr) load_row<Q1>(v, a, td.comp, w, q);
+            put(a, td, ids, w, q);
         }
     }
 };
@@ -211,10 +240,10 @@ struct Rows<NT, kAnyQ> {
 // vector filled float by float made every array's load wait for the one before, three memory latencies in
 // a row in each cut tile.  48 components of one cut tile each, 100 workers, 1024 x 4: 9.6 us, that way 12.7;
 // edges between columns 7.3.
-template <bool WHOLE, int POL>
+template <int POL>
 __device__ __forceinline__ v4f load_col(const float *p, unsigned mk)
 {
-    if (WHOLE || mk == 0xFu) return load4<POL>(p);
+    if (mk == 0xFu) return load4<POL>(p);
     const int first = __builtin_ctz(mk), last = 31 - __builtin_clz(mk);
     v4f v;
 #pragma unroll
@@ -222,10 +251,10 @@ __device__ __forceinline__ v4f load_col(const float *p, unsigned mk)
     return v;
 }
 
-template <bool WHOLE, int POL>
+template <int POL>
 __device__ __forceinline__ void store_col(float *p, v4f v, unsigned mk)
 {
-    if (WHOLE || mk == 0xFu) {
+    if (mk == 0xFu) {
         store4<POL>(p, v);
         return;
     }
@@ -270,7 +299,7 @@ __device__ __forceinline__ v4f average(const v4f *tile, const uint16_t *row, int
 // WHOLE: all T columns belong to the tile entirely; else a component edge cuts it.
 // DEPTH == SLOTS: omega and Delta are loaded together with theta; DEPTH < SLOTS (T <= NT then): see
 // sync_kernel below.
-template <int NT, int SLOTS, int DEPTH, int Q1, int POL, bool WHOLE>
+template <int NT, int SLOTS, int DEPTH, int Q1, int POL>
 __device__ __forceinline__ void do_tile(const SyncArgs &a, const TileDesc &td, v4f *tile, uint16_t *ids)
 {
     const int tid = threadIdx.x, K = a.K, logT = a.logT, T = 1 << logT, mode = a.mode;
@@ -286,7 +315,6 @@ __device__ __forceinline__ void do_tile(const SyncArgs &a, const TileDesc &td, v
     auto mask = [&](int n) {
         unsigned mk = 0;
         if (w0 + wn(n) < K) {
-            if (WHOLE) return 0xFu;
             const int64_t e = e0 + 4 * cn(n);
 #pragma unroll
             for (int c = 0; c < 4; ++c) mk |= (e + c >= td.lo && e + c < td.lo + td.n) ? (1u << c) : 0u;
@@ -300,21 +328,16 @@ __device__ __forceinline__ void do_tile(const SyncArgs &a, const TileDesc &td, v
     if constexpr (DEPTH < SLOTS) {
 #pragma unroll
         for (int n = 0; n < SLOTS; ++n)
-            if (const unsigned mk = mask(n)) th[n] = load_col<WHOLE, POL>(a.theta + at(n), mk);
-        // kSixtyFour: omega and Delta on top of theta would be more in flight per CU than HBM takes best.  64 workers x 115.5 M
-        // in components of 1 M, blocked: 29350 us, all at once 29990; 48 workers 2 % less, rows of 5 to 16 within 1 %.
-        // With more than 4 neighbours the registers leave one workgroup per CU, which needs all of them in flight: 42 workers x
-        // 32.0 M, 5 neighbours, 1.4 % less than theta first.
-        if (SLOTS == 2 && Q1 >= 1 && Q1 <= 5) __builtin_amdgcn_s_waitcnt(0x0F70);       // vmcnt(0)
+            if (const unsigned mk = mask(n)) th[n] = load_col<POL>(a.theta + at(n), mk);
     }
 #pragma unroll
     for (int n = 0; n < DEPTH; ++n) {
         const unsigned mk = mask(n);
         if (mk == 0u) continue;
-        if (DEPTH == SLOTS) th[n] = load_col<WHOLE, POL>(a.theta + at(n), mk);
+        if (DEPTH == SLOTS) th[n] = load_col<POL>(a.theta + at(n), mk);
         if (slots_too) {
-            om[n] = load_col<WHOLE, POL>(a.omega + at(n), mk);
-            de[n] = load_col<WHOLE, POL>(a.delta + at(n), mk);
+            om[n] = load_col<POL>(a.omega + at(n), mk);
+            de[n] = load_col<POL>(a.delta + at(n), mk);
         }
     }
     rows.finish(a, td, ids);
@@ -331,8 +354,8 @@ __device__ __forceinline__ void do_tile(const SyncArgs &a, const TileDesc &td, v
         const v4f o = om[n % DEPTH], d = de[n % DEPTH];
         if (n + DEPTH < SLOTS && slots_too) {
             if (const unsigned next = mask(n + DEPTH)) {
-                om[n % DEPTH] = load_col<WHOLE, POL>(a.omega + at(n + DEPTH), next);
-                de[n % DEPTH] = load_col<WHOLE, POL>(a.delta + at(n + DEPTH), next);
+                om[n % DEPTH] = load_col<POL>(a.omega + at(n + DEPTH), next);
+                de[n % DEPTH] = load_col<POL>(a.delta + at(n + DEPTH), next);
             }
         }
         v4f tn = average<Q1>(tile, ids + (w0 + wn(n)) * pitch, td.q + 1, logT, col0 + cn(n), inv);
@@ -345,20 +368,132 @@ __device__ __forceinline__ void do_tile(const SyncArgs &a, const TileDesc &td, v
                 filter(avg[c], o[c], d[c], a.eta, a.zeta, mode, t1, o1, d1);
                 tn[c] = t1; on[c] = o1; dn[c] = d1;
             }
-            store_col<WHOLE, POL>(a.omega + at(n), on, mk);
-            store_col<WHOLE, POL>(a.delta + at(n), dn, mk);
+            store_col<POL>(a.omega + at(n), on, mk);
+            store_col<POL>(a.delta + at(n), dn, mk);
         }
-        store_col<WHOLE, POL>(a.theta + at(n), tn, mk);
+        store_col<POL>(a.theta + at(n), tn, mk);
     }
 }
+
+// A tile that no component edge cuts.  The same slots, but no load stands behind a branch: where one may have been left out
+// the compiler cannot count how many are under way, and waits for all of them instead of the oldest, which took
+// the streamed omega and Delta their depth.  T is the widest power of two, so that slots 0 to SLOTS / 2 - 1 hold rows for every thread,
+// and only the last of the N that are used may hold none for some: those threads all load the tile's first column of row
+// K - 1, one line for the whole wave, and store nothing.
+template <int NT, int SLOTS, int DEPTH, int Q1, int POL, bool MA>
+struct WholeTile {
+    const SyncArgs &a;
+    const TileDesc &td;
+    v4f *tile;
+    uint16_t *ids;
+    int N, w0, col0;
+    int64_t col_at, spare;                                        // where the thread's first column lies in row 0; what is loaded without a row
+    float inv;
+    v4f om[DEPTH], de[DEPTH];
+
+    __device__ __forceinline__ WholeTile(const SyncArgs &args, const TileDesc &desc, v4f *lds, uint16_t *rows)
+        : a(args), td(desc), tile(lds), ids(rows) {}
+    __device__ __forceinline__ int worker(int n) const { return w0 + ((n * NT) >> a.logT); }
+    __device__ __forceinline__ int column(int n) const { return (n * NT) & ((1 << a.logT) - 1); }
+    __device__ __forceinline__ int64_t at(int n) const
+    {
+        const int64_t p = col_at + static_cast<int64_t>(worker(n)) * a.at.stride + 4 * column(n);
+        return n < SLOTS / 2 || worker(n) < a.K ? p : spare;
+    }
+    __device__ __forceinline__ void load_slots(int n)
+    {
+        if (MA) return;
+        om[n % DEPTH] = load4<POL>(a.omega + at(n));
+        de[n % DEPTH] = load4<POL>(a.delta + at(n));
+    }
+    // Slot n; `next`: the slot whose omega and Delta take its registers, or 0.  GUARD: some threads may have no row.
+    template <bool GUARD>
+    __device__ __forceinline__ void slot(int n, int next)
+    {
+        const v4f o = om[n % DEPTH], d = de[n % DEPTH];
+        if (next) load_slots(next);
+        const int w = GUARD ? min(worker(n), a.K - 1) : worker(n);
+        const int64_t p = at(n);
+        v4f tn = average<Q1>(tile, ids + w * ids_pitch(Q1, a.q), td.q + 1, a.logT, col0 + column(n), inv), on, dn;
+        if (!MA) {
+            const v4f avg = tn;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                float t1, o1, d1;
+                filter(avg[c], o[c], d[c], a.eta, a.zeta, a.mode, t1, o1, d1);
+                tn[c] = t1; on[c] = o1; dn[c] = d1;
+            }
+        }
+        if (!GUARD || worker(n) < a.K) {
+            if (!MA) {
+                store4<POL>(a.omega + p, on);
+                store4<POL>(a.delta + p, dn);
+            }
+            store4<POL>(a.theta + p, tn);
+        }
+    }
+    // Slots n on, one after the other, until only those are left whose omega and Delta are under way.
+    template <int n>
+    __device__ __forceinline__ void stream()
+    {
+        if constexpr (n + DEPTH < SLOTS) {
+            if (n + DEPTH <= SLOTS / 2 || n + DEPTH < N) {
+                slot<false>(n, n + DEPTH);
+                return stream<n + 1>();
+            }
+        }
+#pragma unroll
+        for (int m = n; m < n + DEPTH; ++m) {
+            if (DEPTH == SLOTS && m > SLOTS / 2 && m >= N) break;
+            if (m >= SLOTS / 2 && (DEPTH == SLOTS || m == n + DEPTH - 1)) slot<true>(m, 0);
+            else slot<false>(m, 0);
+        }
+    }
+    __device__ __forceinline__ void run()
+    {
+        const int tid = threadIdx.x, T = 1 << a.logT;
+        N = ((a.K << a.logT) + NT - 1) / NT;
+        col0 = tid & (T - 1);
+        w0 = tid >> a.logT;
+        inv = (a.flags & kFlagMixedQ) ? a.comp[td.comp].inv : a.inv;
+        col_at = placed(a.at, td.lo + 4 * col0);
+        spare = placed(a.at, td.lo) + static_cast<int64_t>(a.K - 1) * a.at.stride;
+        Rows<NT, Q1> rows;
+        rows.begin(a, td);
+        v4f th[SLOTS];
+#pragma unroll
+        for (int n = 0; n < SLOTS; ++n)
+            if (n <= SLOTS / 2 || n < N) th[n] = load4<POL>(a.theta + at(n));
+        // kSixtyFour: omega and Delta on top of theta would be more in flight per CU than HBM takes best.  64 workers x 57.8 M
+        // in components of 1 M, blocked: 13350 us, all at once 13515; 16 x 35.0 M odd rows 2330 / 2436.  With more than 4 neighbours the
+        // registers leave one workgroup per CU, which needs all of them in flight.
+        if (DEPTH == 1 && SLOTS == 2 && Q1 >= 1 && Q1 <= 5) __builtin_amdgcn_s_waitcnt(0x0F70);     // vmcnt(0)
+#pragma unroll
+        for (int n = 0; n < DEPTH; ++n)
+            if (n <= SLOTS / 2 || n < N) load_slots(n);
+        rows.finish(a, td, ids);
+#pragma unroll
+        for (int n = 0; n < SLOTS; ++n)
+            if (n <= SLOTS / 2 || n < N) tile[tid + n * NT] = th[n];
+        __syncthreads();
+        stream<0>();
+    }
+};
 
 template <int NT, int SLOTS, int DEPTH, int Q1, int POL>
 __device__ __forceinline__ void any_tile(const SyncArgs &a, const TileDesc &td, v4f *tile, uint16_t *ids)
 {
-    if (((td.lo & 3) | (td.n & ~(4 << a.logT))) == 0)             // n is T columns exactly
-        do_tile<NT, SLOTS, DEPTH, Q1, POL, true>(a, td, tile, ids);
-    else
-        do_tile<NT, SLOTS, DEPTH, Q1, POL, false>(a, td, tile, ids);
+    // vmcnt(0) behind each path: to the compiler one path's loads may still be under way where another begins, and it would
+    // wait there for the registers they share, between one array's loads and the next
+    if (((td.lo & 3) | (td.n & ~(4 << a.logT))) != 0) {           // n is less than T columns
+        do_tile<NT, SLOTS, DEPTH, Q1, POL>(a, td, tile, ids);
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+    } else if (a.mode == GBMUF_MODE_GOSSIP_MA) {
+        WholeTile<NT, SLOTS, DEPTH, Q1, POL, true>(a, td, tile, ids).run();
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+    } else {
+        WholeTile<NT, SLOTS, DEPTH, Q1, POL, false>(a, td, tile, ids).run();
+    }
 }
 
 // DEPTH < SLOTS is for many workers.  A tile holds theta of all K workers, so its width is what K
@@ -373,7 +508,10 @@ __global__ __launch_bounds__(NT) void sync_kernel(SyncArgs a)
     extern __shared__ float4 lds4[];
     v4f *tile = reinterpret_cast<v4f *>(lds4);
     uint16_t *ids = reinterpret_cast<uint16_t *>(lds4 + NT * SLOTS);
-    const TileDesc td = a.tiles[tile_of_block(a)];
+    uint32_t logB = static_cast<uint32_t>(a.at.logB);
+    hold(logB);                                                   // fetched with the other arguments, not after the descriptor
+    a.at.logB = static_cast<int32_t>(logB);
+    const TileDesc td = load_tile(a.tiles + tile_of_block(a));
     if ((a.flags & kFlagCheckPeriods) && a.step % static_cast<uint64_t>(a.comp[td.comp].period) != 0)
         return;                                                   // not due: the whole workgroup leaves
     if constexpr (Q1 == kMixed) {
