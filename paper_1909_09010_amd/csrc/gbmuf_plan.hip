@@ -250,30 +250,30 @@ int32_t widest_tile(const Variant &v, int K)
     return lg;
 }
 
-// Rows that share lines, from here on beyond the caches: rows are 3K address streams and take tiles of 1 KB of a
-// worker row and more.
-//   BMUF: up to 4 workers 256 x 1 [4 %; 1024 x 1 9 %], 5-16 kSixtyFour [2 %; 1024 x 1 2 to 4 %], 17-64 1024 x 2 [1.5 %; 1024 x 4 2 %], large
-//     33-64 kMany [0.7 %; 1024 x 2 2 %], 65-512 1024 x 4 [0.5 %; kMany 1 %], 129-512 large kVeryMany [0.3 %; 1024 x 4 1 to 4 %],
-//     above at all sizes [0 %; 1024 x 4 20 to 50 %].
-//   gossip-MA: 512 x 2 where K rows fill its slots to 7/8 and K <= 4 [2 %; 256 x 4 6 %], else up to 16 256 x 4, whose threads idle
-//     in whole slots [1.5 %; 512 x 2 11 %], 17-32 512 x 4 [2 %; 512 x 2 12 to 20 %], 33-512 1024 x 4 [1 %; kVeryMany 5 to
-//     20 %], 129-512 large and above 512 kVeryMany [0.5 %; 1024 x 4 2 to 40 %].
+// Rows that share lines, beyond the caches: 3K address streams, of which each access touches one line more than it needs.  All wide
+// shapes end within 5 % of each other: 5.4 TB/s with 4 workers, 5.1 with 16 and 4.9 from 64 on.
+//   BMUF: up to 3 workers 256 x 1 (2 x 350 M 3131 us, 1024 x 1 3310), up to 16 1024 x 1 where K rows fill its slots to 7/8 (8 x 75 M 2735, kSixtyFour
+//     2870; 16 x 37.5 M 2819 / 2873), else kSixtyFour, whose threads idle in whole slots (12 x 58 M 3218; 1024 x 1 3373), up to 64 kSixtyFour (32 x
+//     18.8 M 2887, 1024 x 2 2948; 48 x 12.5 M 2885 / 2965), above 1024 x 4 (200 x 3 M 2970, kVeryMany 2988), large up to 128 kMany (96 x 6.2 M 2929,
+//     1024 x 4 3008; 128 x 0.5 M 366 / 356), large above 256 kVeryMany (300 x 2 M 3100), above 512 at all sizes (1024 x 4 20 to 50 % more).
+//   gossip-MA: up to 4 workers 512 x 2 (2 x 70 M 191, 1024 x 4 206), up to 16 256 x 2 (16 x 25 M 600, 256 x 4 609), up to 32 256 x 4, up to
+//     64 512 x 4 (64 x 6.2 M 629, 1024 x 4 632), up to 128 1024 x 4, above kVeryMany (200 x 2 M 657, 1024 x 4 710).
 Variant shared_variant(int K, int what, int size, bool few)
 {
     Variant v{1024, 4, 4};
     const bool large = size == kLarge;
     if (size == kCompact) return cached_variant(K, what);
-    if (few && (K > 512 || (K > 128 && large && what == kBmuf))) return kVeryMany;
     if (what == kMa) {
-        const bool fills = (K << widest_tile({512, 2, 2}, K)) >= 896;
-        if (fills && K <= 4) find_variant(512, 2, &v);
-        else if (K <= 16) find_variant(256, 4, &v);
-        else if (K <= 32) find_variant(512, 4, &v);
+        if (few && K > 128) return kVeryMany;
+        if (K <= 4) find_variant(512, 2, &v);
+        else if (K <= 32) find_variant(256, K <= 16 ? 2 : 4, &v);
+        else if (K <= 64) find_variant(512, 4, &v);
     } else {
-        if (K <= 4) find_variant(256, 1, &v);
-        else if (K <= 16) v = kSixtyFour;
-        else if (K > 32 && K <= 64 && large) v = kMany;
-        else if (K <= 64) find_variant(1024, 2, &v);
+        if (few && (K > 512 || (K > 256 && large))) return kVeryMany;
+        if (K <= 3) find_variant(256, 1, &v);
+        else if (K <= 16 && (K << widest_tile({1024, 1, 1}, K)) >= 896) find_variant(1024, 1, &v);
+        else if (K <= 64) v = kSixtyFour;
+        else if (K <= 128 && large) v = kMany;
     }
     return v;
 }
@@ -310,7 +310,7 @@ void aligned_shape(int K, int layout, int what, int size, bool few, LayoutCfg &c
     const bool blocked = layout == kBlocked;
     const auto fills = [K](int slots) { return (K << widest_tile({slots, 1, 1}, K)) * 8 >= slots * 7; };
     if (what == kMa) {
-        if (size <= kSmall && K <= 64) find_variant(256, fills(512) ? 2 : 4, &v);
+        if (size <= kSmall) v = cached_variant(K, what);
         else if (size <= kCompact) find_variant(K <= 64 ? 256 : K <= 128 ? 512 : 1024, K <= 128 ? 2 : 4, &v);
         else if (blocked && K <= 2) find_variant(256, 1, &v);
         else if (blocked ? K <= 16 && fills(512) : K <= 8) find_variant(256, 2, &v);
@@ -362,11 +362,11 @@ Variant lds_drawing_variant(int K, int layout)
     return v;
 }
 
-// Rows that share lines: two workgroups per CU, or six of the small ones of up to 4 workers.  A state that stays in the cache has
+// Rows that share lines: six workgroups per CU of the small ones of up to 3 workers, one of kMany (96 workers x 6.2 M 2929 us, two 2976), else two.  A state that stays in the cache has
 // nothing to gain from a bound, and gossip-MA moves too little to need one.
 int shared_workgroups_per_cu(int K, int what, int size)
 {
-    return size == kCompact || what == kMa ? 0 : K <= 4 ? 6 : 2;
+    return size == kCompact || what == kMa ? 0 : K <= 3 ? 6 : K > 64 && K <= 128 && size == kLarge ? 1 : 2;
 }
 
 // What a plan that names its shape gets if it does not name a bound: no bound on rows, few on blocked state.
@@ -380,11 +380,11 @@ int32_t named_workgroups_per_cu(int K, int layout, int what)
 // Streamed: loads leave the L2 first, stores go through it at once.  Lines that were read are dead, and unless they leave first
 // they push lines that were written out in an order that HBM takes worse: three arrays of 2 GB updated in place 5810
 // GB/s, 5450 with plain accesses, either half alone 5420 to 5550.  Not where neighbouring tiles share lines, whose halves the L2 would
-// no longer join (16 x 43.8 M odd rows 4023 us, plain 3255), and not where all of a launch comes from the caches.  A plan's
+// no longer join (16 x 43.8 M odd rows 4023 us, plain 3255; tiles of 64 bytes, 1024 x 3 K 24 / 12), and not where all of a launch comes from the caches.  A plan's
 // cache_hints ask for it at any size.
-int choose_policy(int layout, int size, int hints)
+int choose_policy(int layout, int size, int logT, int hints)
 {
-    return layout != kShared && (size != kTiny || hints != 0) ? kStreamed : kPlain;
+    return layout != kShared && logT >= 3 && (size != kTiny || hints != 0) ? kStreamed : kPlain;
 }
 
 int64_t count_tiles(const gbmuf_plan_s &pl, int32_t logT)
@@ -615,7 +615,9 @@ size_t lds_floor(const gbmuf_plan_s *pl, const LayoutCfg &cfg)
 //   sums of up to 20 M values come from the caches, which plain loads leave them in (64 x 0.16 M 7.4, streamed 8.1) and whose latency
 //     more waves hide, with enough rows per thread that few workers take one pass: 8 x 4.2 M padded 25 (16 rows x 3 waves 33),
 //     1024 x 36 K 66 (8 rows 87).
-//   beyond, streamed: 8 x 25 M blocked 127, plain 145; 64 x 15.6 M padded 607, plain 674.  Up to 60 M without bound.
+//     More than 64 workers up to 35 M (300 x 83 K 22.7, streamed 24.0).
+//   beyond, streamed: 8 x 25 M blocked 127, plain 145; 64 x 15.6 M padded 607, plain 674.  Up to 60 M, and where rows are too short to fill the
+//     chip with waves, without bound and with 16 rows of more than 64 workers in flight (1024 x 195 K 122, 4 rows x 6 waves 157).
 //   one worker is a copy: 590 M 746, 16 waves 770, 8 waves 1303.
 //   larger sums take 4 rows at a time, and the fewer waves the more workers there are: blocked 4 x 50 M 142 (12 waves), 64 x 3.1 M 119 (6;
 //     8 rows x 4 125), 128 x 7.8 M 577 (6; 16 rows x 3 591); padded 16 x 62 M 630 (8), 128 x 1.6 M 122 (8; 16 rows x 6 134).  Blocked 9 to 16
@@ -628,14 +630,15 @@ AverageShape average_shape(const gbmuf_plan_s *pl, int layout, bool shared_lines
     const int64_t values = static_cast<int64_t>(K) * pl->P;
     AverageShape s{};
     int waves = 32;
-    if (values <= kCompactValues) {
+    const bool short_rows = pl->P <= 250000;                  // fewer than 1000 waves
+    if (values <= (K <= 64 ? kCompactValues : 35000000)) {
         s.rows_in_flight = K <= 4 ? 4 : K <= 16 ? 8 : 16;
         s.xcd_log = K > 1 ? 2 : 0;
     } else {
         s.policy = kStreamed;
-        s.rows_in_flight = K <= 64 || values > 60000000 ? 4 : 16;
+        s.rows_in_flight = K <= 64 || (values > 60000000 && !short_rows) ? 4 : 16;
         s.xcd_log = (K > 1 && shared_lines) || (layout == kBlocked && K > 8 && K <= 64) ? 2 : 0;
-        if (values > 60000000) {
+        if (values > 60000000 && !short_rows) {
             if (layout == kBlocked) {
                 waves = K <= 3 ? 32 : K <= 7 ? 12 : K <= 8 ? 8 : K <= 16 ? 4 : 6;
                 if (K > 8 && K <= 16) s.rows_in_flight = 16;
@@ -709,6 +712,7 @@ int enqueue_sync(const gbmuf_plan_s *pl, const int32_t *nbr_dev, const gbmuf_sta
     a.comp = pl->d_comp;
     a.theta = st->theta; a.omega = st->omega; a.delta = st->delta;
     a.at = at;
+    a.row_end = layout == kBlocked ? INT64_MAX : pl->P;
     a.K = pl->K; a.q = pl->q; a.logT = cfg.logT; a.mode = mode;
     a.eta = eta; a.zeta = zeta; a.inv = pl->inv;
     a.flags = ((pl->alternate && (round & 1)) ? kFlagBackwards : 0) | (pl->mixed_q ? kFlagMixedQ : 0) |
@@ -851,7 +855,7 @@ int gbmuf_plan_create(gbmuf_plan_t **out, const gbmuf_plan_desc_t *desc)
                     pl->min_block_logT = widest_tile(Variant{K <= 16 ? 1024 : K <= 64 ? 2048 : 4096, 1, 1}, K);
                 }
                 cfg.logT = widest_tile(cfg.variant, K);
-                cfg.policy = choose_policy(layout, size, desc->cache_hints);
+                cfg.policy = choose_policy(layout, size, cfg.logT, desc->cache_hints);
                 if (desc->workgroups_per_cu != 0) cfg.workgroups_per_cu = desc->workgroups_per_cu;
             }
             if (rc == GBMUF_OK) {

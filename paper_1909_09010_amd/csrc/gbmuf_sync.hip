@@ -240,10 +240,9 @@ struct Rows<NT, kAnyQ> {
 // vector filled float by float made every array's load wait for the one before, three memory latencies in
 // a row in each cut tile.  48 components of one cut tile each, 100 workers, 1024 x 4: 9.6 us, that way 12.7;
 // edges between columns 7.3.
-template <int POL>
 __device__ __forceinline__ v4f load_col(const float *p, unsigned mk)
 {
-    if (mk == 0xFu) return load4<POL>(p);
+    if (mk == 0xFu) return load4<kPlain>(p);
     const int first = __builtin_ctz(mk), last = 31 - __builtin_clz(mk);
     v4f v;
 #pragma unroll
@@ -251,11 +250,10 @@ __device__ __forceinline__ v4f load_col(const float *p, unsigned mk)
     return v;
 }
 
-template <int POL>
 __device__ __forceinline__ void store_col(float *p, v4f v, unsigned mk)
 {
     if (mk == 0xFu) {
-        store4<POL>(p, v);
+        store4<kPlain>(p, v);
         return;
     }
 #pragma unroll
@@ -293,13 +291,10 @@ __device__ __forceinline__ v4f average(const v4f *tile, const uint16_t *row, int
     return s * inv;
 }
 
-// One tile.  Slot n of a thread is worker w0 + wn(n), column col0 + cn(n) with the same wn, cn for all
-// threads: with T <= NT a thread keeps its column and visits every (NT/T)-th worker, with T > NT (few
+// A tile that a component edge cuts, all arrays in flight at once.  Slot n of a thread is worker w0 + wn(n), column col0 + cn(n) with
+// the same wn, cn for all threads: with T <= NT a thread keeps its column and visits every (NT/T)-th worker, with T > NT (few
 // workers in a wide shape) slot n is one stretch of one worker's row.
-// WHOLE: all T columns belong to the tile entirely; else a component edge cuts it.
-// DEPTH == SLOTS: omega and Delta are loaded together with theta; DEPTH < SLOTS (T <= NT then): see
-// sync_kernel below.
-template <int NT, int SLOTS, int DEPTH, int Q1, int POL>
+template <int NT, int SLOTS, int Q1>
 __device__ __forceinline__ void do_tile(const SyncArgs &a, const TileDesc &td, v4f *tile, uint16_t *ids)
 {
     const int tid = threadIdx.x, K = a.K, logT = a.logT, T = 1 << logT, mode = a.mode;
@@ -324,20 +319,15 @@ __device__ __forceinline__ void do_tile(const SyncArgs &a, const TileDesc &td, v
 
     Rows<NT, Q1> rows;
     rows.begin(a, td);
-    v4f th[SLOTS], om[DEPTH], de[DEPTH];
-    if constexpr (DEPTH < SLOTS) {
+    v4f th[SLOTS], om[SLOTS], de[SLOTS];
 #pragma unroll
-        for (int n = 0; n < SLOTS; ++n)
-            if (const unsigned mk = mask(n)) th[n] = load_col<POL>(a.theta + at(n), mk);
-    }
-#pragma unroll
-    for (int n = 0; n < DEPTH; ++n) {
+    for (int n = 0; n < SLOTS; ++n) {
         const unsigned mk = mask(n);
         if (mk == 0u) continue;
-        if (DEPTH == SLOTS) th[n] = load_col<POL>(a.theta + at(n), mk);
+        th[n] = load_col(a.theta + at(n), mk);
         if (slots_too) {
-            om[n] = load_col<POL>(a.omega + at(n), mk);
-            de[n] = load_col<POL>(a.delta + at(n), mk);
+            om[n] = load_col(a.omega + at(n), mk);
+            de[n] = load_col(a.delta + at(n), mk);
         }
     }
     rows.finish(a, td, ids);
@@ -351,16 +341,9 @@ __device__ __forceinline__ void do_tile(const SyncArgs &a, const TileDesc &td, v
     for (int n = 0; n < SLOTS; ++n) {
         const unsigned mk = mask(n);
         if (mk == 0u) continue;
-        const v4f o = om[n % DEPTH], d = de[n % DEPTH];
-        if (n + DEPTH < SLOTS && slots_too) {
-            if (const unsigned next = mask(n + DEPTH)) {
-                om[n % DEPTH] = load_col<POL>(a.omega + at(n + DEPTH), next);
-                de[n % DEPTH] = load_col<POL>(a.delta + at(n + DEPTH), next);
-            }
-        }
         v4f tn = average<Q1>(tile, ids + (w0 + wn(n)) * pitch, td.q + 1, logT, col0 + cn(n), inv);
         if (slots_too) {
-            const v4f avg = tn;
+            const v4f avg = tn, o = om[n], d = de[n];
             v4f on, dn;
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
@@ -368,49 +351,81 @@ __device__ __forceinline__ void do_tile(const SyncArgs &a, const TileDesc &td, v
                 filter(avg[c], o[c], d[c], a.eta, a.zeta, mode, t1, o1, d1);
                 tn[c] = t1; on[c] = o1; dn[c] = d1;
             }
-            store_col<POL>(a.omega + at(n), on, mk);
-            store_col<POL>(a.delta + at(n), dn, mk);
+            store_col(a.omega + at(n), on, mk);
+            store_col(a.delta + at(n), dn, mk);
         }
-        store_col<POL>(a.theta + at(n), tn, mk);
+        store_col(a.theta + at(n), tn, mk);
     }
 }
 
-// A tile that no component edge cuts.  The same slots, but no load stands behind a branch: where one may have been left out
+// A tile whose columns are loaded as they are.  The same slots, but no load stands behind a branch: where one may have been left out
 // the compiler cannot count how many are under way, and waits for all of them instead of the oldest, which took
-// the streamed omega and Delta their depth.  T is the widest power of two, so that slots 0 to SLOTS / 2 - 1 hold rows for every thread,
-// and only the last of the N that are used may hold none for some: those threads all load the tile's first column of row
-// K - 1, one line for the whole wave, and store nothing.
-template <int NT, int SLOTS, int DEPTH, int Q1, int POL, bool MA>
+// the streamed omega and Delta their depth.  T is the widest power of two, so that more than SLOTS / 2 slots hold rows for every thread.
+// Where all arrays are in flight at once the slots beyond the N that hold rows are left out; where omega and Delta are
+// streamed, blocks of DEPTH slots are left out in front, so that the stream ends in the same slots for any K.  A thread
+// that has no row in a slot loads the tile's first column of row K - 1, one line for the whole wave, and stores nothing.
+// CUT (T <= NT): component edges cut the tile.  A column that is not the tile's at all is treated like a missing row.  Of a cut column
+// all four floats are loaded, those of other tiles to no use, and the tile's own are stored one by one; the column at the end of
+// a row, where less than four floats may be left, is loaded from the row's last four and moved.
+template <int NT, int SLOTS, int DEPTH, int Q1, int POL, bool MA, bool CUT>
 struct WholeTile {
     const SyncArgs &a;
     const TileDesc &td;
     v4f *tile;
     uint16_t *ids;
-    int N, w0, col0;
+    int N, skipped, w0, col0;                                     // slots with rows; DEPTH < SLOTS: the first slot that is used
     int64_t col_at, spare;                                        // where the thread's first column lies in row 0; what is loaded without a row
     float inv;
+    unsigned mine;                                                // CUT: which floats of the thread's column are the tile's
+    int back;                                                     // CUT: by how many floats its load starts before it
     v4f om[DEPTH], de[DEPTH];
 
     __device__ __forceinline__ WholeTile(const SyncArgs &args, const TileDesc &desc, v4f *lds, uint16_t *rows)
         : a(args), td(desc), tile(lds), ids(rows) {}
-    __device__ __forceinline__ int worker(int n) const { return w0 + ((n * NT) >> a.logT); }
-    __device__ __forceinline__ int column(int n) const { return (n * NT) & ((1 << a.logT) - 1); }
+    __device__ __forceinline__ int worker(int n) const { return w0 + (((n - skipped) * NT) >> a.logT); }
+    __device__ __forceinline__ int column(int n) const { return ((n - skipped) * NT) & ((1 << a.logT) - 1); }
+    // slots that may be unused, or hold no row for some threads
+    static __device__ __forceinline__ constexpr bool may_lack(int n) { return n >= (DEPTH == SLOTS ? SLOTS / 2 : SLOTS - DEPTH); }
+    __device__ __forceinline__ bool used(int n) const
+    {
+        return DEPTH == SLOTS ? n <= SLOTS / 2 || n < N : n >= SLOTS / 2 || n >= skipped;
+    }
     __device__ __forceinline__ int64_t at(int n) const
     {
         const int64_t p = col_at + static_cast<int64_t>(worker(n)) * a.at.stride + 4 * column(n);
-        return n < SLOTS / 2 || worker(n) < a.K ? p : spare;
+        return (!may_lack(n) || worker(n) < a.K) && (!CUT || mine) ? p : spare;
     }
-    __device__ __forceinline__ void load_slots(int n)
+    // The floats of a column as they were loaded, in their places.
+    __device__ __forceinline__ v4f moved(v4f v) const
+    {
+        if (!CUT) return v;
+        v4f r;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) r[c] = back == 0 ? v[c] : back == 1 ? v[c < 3 ? c + 1 : 3] : back == 2 ? v[c < 2 ? c + 2 : 3] : v[3];
+        return r;
+    }
+    __device__ __forceinline__ void store(float *p, v4f v) const
+    {
+        if (!CUT || mine == 0xFu) {
+            store4<POL>(p, v);
+            return;
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            if (mine & (1u << c)) p[back + c] = v[c];
+    }
+    __device__ __forceinline__ void load_slots(int n) { load_slots(n, n % DEPTH); }
+    __device__ __forceinline__ void load_slots(int n, int to)
     {
         if (MA) return;
-        om[n % DEPTH] = load4<POL>(a.omega + at(n));
-        de[n % DEPTH] = load4<POL>(a.delta + at(n));
+        om[to] = load4<POL>(a.omega + at(n));
+        de[to] = load4<POL>(a.delta + at(n));
     }
     // Slot n; `next`: the slot whose omega and Delta take its registers, or 0.  GUARD: some threads may have no row.
     template <bool GUARD>
     __device__ __forceinline__ void slot(int n, int next)
     {
-        const v4f o = om[n % DEPTH], d = de[n % DEPTH];
+        const v4f o = moved(om[n % DEPTH]), d = moved(de[n % DEPTH]);
         if (next) load_slots(next);
         const int w = GUARD ? min(worker(n), a.K - 1) : worker(n);
         const int64_t p = at(n);
@@ -424,76 +439,90 @@ struct WholeTile {
                 tn[c] = t1; on[c] = o1; dn[c] = d1;
             }
         }
-        if (!GUARD || worker(n) < a.K) {
+        if ((!GUARD || worker(n) < a.K) && (!CUT || mine)) {
             if (!MA) {
-                store4<POL>(a.omega + p, on);
-                store4<POL>(a.delta + p, dn);
+                store(a.omega + p, on);
+                store(a.delta + p, dn);
             }
-            store4<POL>(a.theta + p, tn);
-        }
-    }
-    // Slots n on, one after the other, until only those are left whose omega and Delta are under way.
-    template <int n>
-    __device__ __forceinline__ void stream()
-    {
-        if constexpr (n + DEPTH < SLOTS) {
-            if (n + DEPTH <= SLOTS / 2 || n + DEPTH < N) {
-                slot<false>(n, n + DEPTH);
-                return stream<n + 1>();
-            }
-        }
-#pragma unroll
-        for (int m = n; m < n + DEPTH; ++m) {
-            if (DEPTH == SLOTS && m > SLOTS / 2 && m >= N) break;
-            if (m >= SLOTS / 2 && (DEPTH == SLOTS || m == n + DEPTH - 1)) slot<true>(m, 0);
-            else slot<false>(m, 0);
+            store(a.theta + p, tn);
         }
     }
     __device__ __forceinline__ void run()
     {
         const int tid = threadIdx.x, T = 1 << a.logT;
         N = ((a.K << a.logT) + NT - 1) / NT;
+        skipped = DEPTH == SLOTS ? 0 : (SLOTS - N) / DEPTH * DEPTH;
         col0 = tid & (T - 1);
         w0 = tid >> a.logT;
         inv = (a.flags & kFlagMixedQ) ? a.comp[td.comp].inv : a.inv;
-        col_at = placed(a.at, td.lo + 4 * col0);
-        spare = placed(a.at, td.lo) + static_cast<int64_t>(a.K - 1) * a.at.stride;
+        const int64_t first = td.lo & ~static_cast<int64_t>(3), e = first + 4 * col0;
+        const auto beyond = [this](int64_t x) { return a.row_end < x + 4 ? x + 4 - a.row_end : 0; };
+        mine = 0u;
+        back = 0;
+        if constexpr (CUT) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) mine |= e + c >= td.lo && e + c < td.lo + td.n ? 1u << c : 0u;
+            if (mine) back = static_cast<int>(beyond(e));
+        }
+        col_at = placed(a.at, e) - back;
+        spare = placed(a.at, first) - (CUT ? beyond(first) : 0) + static_cast<int64_t>(a.K - 1) * a.at.stride;
         Rows<NT, Q1> rows;
         rows.begin(a, td);
         v4f th[SLOTS];
 #pragma unroll
         for (int n = 0; n < SLOTS; ++n)
-            if (n <= SLOTS / 2 || n < N) th[n] = load4<POL>(a.theta + at(n));
+            if (used(n)) th[n] = load4<POL>(a.theta + at(n));
         // kSixtyFour: omega and Delta on top of theta would be more in flight per CU than HBM takes best.  64 workers x 57.8 M
         // in components of 1 M, blocked: 13350 us, all at once 13515; 16 x 35.0 M odd rows 2330 / 2436.  With more than 4 neighbours the
         // registers leave one workgroup per CU, which needs all of them in flight.
         if (DEPTH == 1 && SLOTS == 2 && Q1 >= 1 && Q1 <= 5) __builtin_amdgcn_s_waitcnt(0x0F70);     // vmcnt(0)
+        if constexpr (DEPTH == SLOTS) {
 #pragma unroll
-        for (int n = 0; n < DEPTH; ++n)
-            if (n <= SLOTS / 2 || n < N) load_slots(n);
+            for (int n = 0; n < SLOTS; ++n)
+                if (used(n)) load_slots(n);
+        } else {
+#pragma unroll
+            for (int n = 0; n < DEPTH; ++n) load_slots(skipped + n, n);
+        }
         rows.finish(a, td, ids);
 #pragma unroll
         for (int n = 0; n < SLOTS; ++n)
-            if (n <= SLOTS / 2 || n < N) tile[tid + n * NT] = th[n];
+            if (used(n)) tile[tid + (n - skipped) * NT] = moved(th[n]);
         __syncthreads();
-        stream<0>();
+#pragma unroll
+        for (int n = 0; n < SLOTS; ++n) {
+            if (!used(n)) continue;
+            if (may_lack(n)) slot<true>(n, 0);
+            else slot<false>(n, n + DEPTH < SLOTS ? n + DEPTH : 0);
+        }
     }
 };
 
 template <int NT, int SLOTS, int DEPTH, int Q1, int POL>
 __device__ __forceinline__ void any_tile(const SyncArgs &a, const TileDesc &td, v4f *tile, uint16_t *ids)
 {
-    // vmcnt(0) behind each path: to the compiler one path's loads may still be under way where another begins, and it would
-    // wait there for the registers they share, between one array's loads and the next
-    if (((td.lo & 3) | (td.n & ~(4 << a.logT))) != 0) {           // n is less than T columns
-        do_tile<NT, SLOTS, DEPTH, Q1, POL>(a, td, tile, ids);
-        __builtin_amdgcn_s_waitcnt(0x0F70);
-    } else if (a.mode == GBMUF_MODE_GOSSIP_MA) {
-        WholeTile<NT, SLOTS, DEPTH, Q1, POL, true>(a, td, tile, ids).run();
-        __builtin_amdgcn_s_waitcnt(0x0F70);
-    } else {
-        WholeTile<NT, SLOTS, DEPTH, Q1, POL, false>(a, td, tile, ids).run();
+    // Cut tiles take plain accesses: they share lines, and a store that goes through the L2 is counted as under way until memory has
+    // it, for which loads issued behind it wait (128 workers x 54 K in 9 components 50 us, plain TBD).
+    // Each path ends the program: did they meet, to the compiler one path's loads could still be under way where another
+    // begins, and it would wait there for the registers they share, between one array's loads and the next.
+    const bool cut = ((td.lo & 3) | (td.n & ~(4 << a.logT))) != 0;      // n is less than T columns
+    if (cut) {
+        if constexpr (DEPTH == SLOTS) {
+            do_tile<NT, SLOTS, Q1>(a, td, tile, ids);
+        } else if (a.mode == GBMUF_MODE_GOSSIP_MA) {
+            WholeTile<NT, SLOTS, DEPTH, Q1, kPlain, true, true>(a, td, tile, ids).run();
+            __builtin_amdgcn_endpgm();
+        } else {
+            WholeTile<NT, SLOTS, DEPTH, Q1, kPlain, false, true>(a, td, tile, ids).run();
+        }
+        __builtin_amdgcn_endpgm();
     }
+    if (a.mode == GBMUF_MODE_GOSSIP_MA) {
+        WholeTile<NT, SLOTS, DEPTH, Q1, POL, true, false>(a, td, tile, ids).run();
+        __builtin_amdgcn_endpgm();
+    }
+    WholeTile<NT, SLOTS, DEPTH, Q1, POL, false, false>(a, td, tile, ids).run();
+    __builtin_amdgcn_endpgm();
 }
 
 // DEPTH < SLOTS is for many workers.  A tile holds theta of all K workers, so its width is what K
