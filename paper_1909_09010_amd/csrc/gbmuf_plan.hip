@@ -252,11 +252,12 @@ int32_t widest_tile(const Variant &v, int K)
 
 // Rows that share lines, beyond the caches: 3K address streams, of which each access touches one line more than it needs.  All wide
 // shapes end within 5 % of each other: 5.4 TB/s with 4 workers, 5.1 with 16 and 4.9 from 64 on.
-//   BMUF: up to 3 workers 256 x 1 (2 x 350 M 3131 us, 1024 x 1 3310), up to 16 1024 x 1 where K rows fill its slots to 7/8 (8 x 75 M 2735, kSixtyFour
-//     2870; 16 x 37.5 M 2819 / 2873), else kSixtyFour, whose threads idle in whole slots (12 x 58 M 3218; 1024 x 1 3373), up to 64 kSixtyFour (32 x
+//   BMUF: up to 2 workers 512 x 2, one per CU (2 x 350 M 3069 us, 256 x 1 3250), up to 16 1024 x 1 where K rows fill its slots to 7/8 (8 x 75 M 2735,
+//     kSixtyFour 2870; 16 x 37.5 M 2819 / 2873), and with 3 workers (3 x 233 M 3132, 512 x 1 3179), else 512 x 1 (6 x 33 M
+//     914, kSixtyFour 931; 12 x 16.7 M 927 / 938), up to 64 kSixtyFour (32 x
 //     18.8 M 2887, 1024 x 2 2948; 48 x 12.5 M 2885 / 2965), above 1024 x 4 (200 x 3 M 2970, kVeryMany 2988), large up to 128 kMany (96 x 6.2 M 2929,
 //     1024 x 4 3008; 128 x 0.5 M 366 / 356), large above 256 kVeryMany (300 x 2 M 3100), above 512 at all sizes (1024 x 4 20 to 50 % more).
-//   gossip-MA: up to 4 workers 512 x 2 (2 x 70 M 191, 1024 x 4 206), up to 16 256 x 2 (16 x 25 M 600, 256 x 4 609), up to 32 256 x 4, up to
+//   gossip-MA: up to 4 workers 512 x 2, large 1024 x 4 (2 x 250 M 692, 512 x 2 733), up to 16 256 x 2 (16 x 25 M 600, 256 x 4 609), up to 32 256 x 4, up to
 //     64 512 x 4 (64 x 6.2 M 629, 1024 x 4 632), up to 128 1024 x 4, above kVeryMany (200 x 2 M 657, 1024 x 4 710).
 Variant shared_variant(int K, int what, int size, bool few)
 {
@@ -265,13 +266,14 @@ Variant shared_variant(int K, int what, int size, bool few)
     if (size == kCompact) return cached_variant(K, what);
     if (what == kMa) {
         if (few && K > 128) return kVeryMany;
-        if (K <= 4) find_variant(512, 2, &v);
-        else if (K <= 32) find_variant(256, K <= 16 ? 2 : 4, &v);
-        else if (K <= 64) find_variant(512, 4, &v);
+        if (K <= 4 && !large) find_variant(512, 2, &v);
+        else if (K > 4 && K <= 32) find_variant(256, K <= 16 ? 2 : 4, &v);
+        else if (K > 32 && K <= 64) find_variant(512, 4, &v);
     } else {
         if (few && (K > 512 || (K > 256 && large))) return kVeryMany;
-        if (K <= 3) find_variant(256, 1, &v);
-        else if (K <= 16 && (K << widest_tile({1024, 1, 1}, K)) >= 896) find_variant(1024, 1, &v);
+        if (K <= 2) find_variant(512, 2, &v);
+        else if (K == 3 || (K <= 16 && (K << widest_tile({1024, 1, 1}, K)) >= 896)) find_variant(1024, 1, &v);
+        else if (K <= 16) find_variant(512, 1, &v);
         else if (K <= 64) v = kSixtyFour;
         else if (K <= 128 && large) v = kMany;
     }
@@ -288,15 +290,16 @@ Variant shared_variant(int K, int what, int size, bool few)
 //     up to 64 workers.  An XCD takes 1 KB of each row in one run (xcd 6): 8 x 300 M / 8 1045 us, tile by tile 1065; from 33 to 128
 //     workers and beyond the caches up to 512 runs of one tile that move on from block to block (rotate), without which an
 //     XCD sees the same addresses modulo 4 KB in every block: 64 x 23.4 M 5356 us, not rotated 5425 (1 KB) and more.
-//     No bound of the residency helps above 4 workers.  Up to 8 workers 256 x 1, 9-16 512 x 1 where K rows fill its
+//     No bound of the residency helps above 4 workers; up to 2 three per CU (2 x 300 M 2165 us, six 2517).  Up to 8 workers 256 x 1, 9-16 512 x 1 where K rows fill its
 //     slots to 7/8, else 256 x 2, whose threads idle in whole slots (12 x 25 M 1051 us; 512 x 1 1080), 17-32 512 x 2, 33-64 kSixtyFour (40 x
 //     7.5 M 1072 us, 512 x 4 1057; 64 x 4.7 M 1070, 512 x 4 1085), 65-128 kMany, 129-512 kVeryMany (200 x 1.5 M 1167, kMany 1185;
 //     256 x 1.2 M 1156, kSixtyFour 1165; 300 x 1 M 1245, kMany 1206), up to 20 M values kSixtyFour (200 x 0.1 M 84 us, kMany 88).
 //   Aligned rows are 3K address streams: 5.9 up to 8 workers, 5.1 from 64 on, whatever the shape.  Wide tiles, and 4 KB
-//     of a row per XCD from 65 workers on, from 129 above 500 M values (96 x 2.6 M 1167 us, tile by tile 1210).  2-4 256 x 1, four per CU (4 x 62.5 M 987 us;
-//     unbounded 1034), 5-8 1024 x 1 (8 x 87.5 M 2852; kSixtyFour 2900, 512 x 1 2998), 9-32 kSixtyFour (32 x 7.8 M 1136; 1024 x 2 1152), 33-64
-//     kVeryMany (48 x 5.2 M 1136; 1024 x 2 1197), 65-128 512 x 4 (96 x 2.6 M 1167, 1024 x 4 1223), above 500 M values kVeryMany (88 x 22.7 M 7895,
-//     1024 x 4 8075), above 128 workers kVeryMany (300 x 0.8 M 1209, 4 KB per XCD not taken 1259).  5 to 20 M values of more than 32 workers: 1024 x 4.
+//     of a row per XCD from 33 workers on, from 129 above 500 M values (96 x 2.6 M 1167 us, tile by tile 1210).  2-4 256 x 1, four per CU (4 x
+//     62.5 M 987 us; unbounded 1034), 5-8 1024 x 1 (8 x 87.5 M 2852; kSixtyFour 2900, 512 x 1 2998), 9-32 kSixtyFour (32 x 7.8 M 1136; 1024 x 2
+//     1152), 33-128 512 x 4 (64 x 1.6 M 472, kVeryMany 483; 48 x 5.2 M 1158 / 1136; 96 x 2.6 M 1167, 1024 x 4 1223), above 500 M values
+//     kVeryMany (48 x 14.6 M 3204, 512 x 4 3273; 88 x 22.7 M 7895, 1024 x 4 8075), above 128 workers kVeryMany (300 x 0.8 M 1209, 4 KB per XCD
+//     not taken 1259).  5 to 20 M values of more than 32 workers: 1024 x 4.
 //   Gossip-MA has a third of the loads and takes more slots per thread.  Blocked: up to 2 workers 256 x 1, up to 16 256 x 2 where K rows
 //     fill it to 7/8 (8 x 75 M 723 us; 512 x 2 748), else 256 x 4, up to 32 256 x 4 (725; 512 x 2 735), 33-64 512 x 4, above 1024 x 4, large of
 //     more than 256 workers kVeryMany (300 x 2 M 947; 956).  Rows: up to 8 256 x 2, up to 24 256 x 4, up to 64 1024 x 4, above
@@ -317,8 +320,8 @@ void aligned_shape(int K, int layout, int what, int size, bool few, LayoutCfg &c
         else if (K <= (blocked ? 32 : 24)) find_variant(256, 4, &v);
         else if (blocked && K <= 64) find_variant(512, 4, &v);
         else if (few && (blocked ? K > 512 || (K > 256 && size == kLarge) : K > 64)) v = kVeryMany;
-    } else if (size <= kSmall) {
-        if (K <= 64) find_variant(K <= 16 ? 256 : 512, 1, &v);
+    } else if (size <= kSmall || (!blocked && K <= 2 && size == kCompact)) {
+        if (K <= 64) find_variant(K <= 16 && (blocked || K > 2) ? 256 : 512, 1, &v);
         else if (size == kSmall) v = kMany;
     } else if (blocked) {
         if (K <= 8) find_variant(256, 1, &v);
@@ -330,13 +333,13 @@ void aligned_shape(int K, int layout, int what, int size, bool few, LayoutCfg &c
         else if (size == kCompact && K <= 256) v = kSixtyFour;
         else if (size != kCompact && few) v = kVeryMany;
         else v = kMany;
-        if (K <= 4) bound = 6;
+        if (K <= 4) bound = K <= 2 ? 3 : 6;
     } else {
         if (K <= 4) find_variant(256, 1, &v);
         else if (K <= 8) find_variant(1024, 1, &v);
         else if (K <= 32) v = kSixtyFour;
         else if (size == kCompact) v = Variant{1024, 4, 4};
-        else if (K > 64 && K <= 128 && size != kLarge) find_variant(512, 4, &v);
+        else if (K <= 128 && size != kLarge) find_variant(512, 4, &v);
         else if (few) v = kVeryMany;
         if (K <= 4) bound = 4;
     }
@@ -345,7 +348,7 @@ void aligned_shape(int K, int layout, int what, int size, bool few, LayoutCfg &c
         cfg.rotate = K > 32 && (K <= 128 || what == kMa || size != kCompact);
         run = cfg.rotate ? 0 : 6;
     } else {
-        run = K > (size == kCompact || what == kMa ? 16 : size == kLarge ? 128 : 64) ? 8 : 0;
+        run = K > (size == kCompact || what == kMa ? 16 : size == kLarge ? 128 : 32) ? 8 : 0;
     }
 }
 // Small plans with rows of more than 7 neighbours draw them through LDS in every workgroup (launch_bound), a thread a
@@ -362,11 +365,13 @@ Variant lds_drawing_variant(int K, int layout)
     return v;
 }
 
-// Rows that share lines: six workgroups per CU of the small ones of up to 3 workers, one of kMany (96 workers x 6.2 M 2929 us, two 2976), else two.  A state that stays in the cache has
-// nothing to gain from a bound, and gossip-MA moves too little to need one.
+// Rows that share lines: one workgroup per CU with up to 2 workers (2 x 350 M 3069 us, two 3200) and of kMany (96 x 6.2 M 2929, two 2976), four of 512 x
+// 1, else two.  A state that stays in the cache has nothing to gain from a bound, and gossip-MA moves too little to need one.
 int shared_workgroups_per_cu(int K, int what, int size)
 {
-    return size == kCompact || what == kMa ? 0 : K <= 3 ? 6 : K > 64 && K <= 128 && size == kLarge ? 1 : 2;
+    if (size == kCompact || what == kMa) return 0;
+    if (K <= 2 || (K > 64 && K <= 128 && size == kLarge)) return 1;
+    return K > 4 && K <= 16 && (K << widest_tile({1024, 1, 1}, K)) < 896 ? 4 : 2;
 }
 
 // What a plan that names its shape gets if it does not name a bound: no bound on rows, few on blocked state.
@@ -640,7 +645,7 @@ AverageShape average_shape(const gbmuf_plan_s *pl, int layout, bool shared_lines
         s.xcd_log = (K > 1 && shared_lines) || (layout == kBlocked && K > 8 && K <= 64) ? 2 : 0;
         if (values > 60000000 && !short_rows) {
             if (layout == kBlocked) {
-                waves = K <= 3 ? 32 : K <= 7 ? 12 : K <= 8 ? 8 : K <= 16 ? 4 : 6;
+                waves = K <= 3 ? 32 : K <= 7 ? 12 : K <= 8 ? 8 : K <= 16 ? 4 : K > 64 && values < 100000000 ? 12 : 6;
                 if (K > 8 && K <= 16) s.rows_in_flight = 16;
                 s.rotate = K > 32 && K <= 64 && values > kLargeValues;
                 if (s.rotate) s.xcd_log = 0;

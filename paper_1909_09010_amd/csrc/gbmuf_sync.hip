@@ -144,7 +144,7 @@ struct Rows {
     __device__ __forceinline__ void begin(const SyncArgs &a, const TileDesc &td)
     {
         const int q = Q1 == kUpTo8 ? td.q : Q1 - 1;
-        if (a.nbr != nullptr) load_row<Q1>(v, a, td.comp, min(static_cast<int>(threadIdx.x), a.K - 1), q);
+        if (a.nbr != nullptr && static_cast<int>(threadIdx.x) < a.K) load_row<Q1>(v, a, td.comp, threadIdx.x, q);
     }
     __device__ __forceinline__ void put(const SyncArgs &a, const TileDesc &td, uint16_t *ids, int w, int q)
     {
@@ -502,7 +502,7 @@ template <int NT, int SLOTS, int DEPTH, int Q1, int POL>
 __device__ __forceinline__ void any_tile(const SyncArgs &a, const TileDesc &td, v4f *tile, uint16_t *ids)
 {
     // Cut tiles take plain accesses: they share lines, and a store that goes through the L2 is counted as under way until memory has
-    // it, for which loads issued behind it wait (128 workers x 54 K in 9 components 50 us, plain TBD).
+    // it, for which loads issued behind it wait (128 workers x 54 K in 9 components 50 us, with plain ones below 29).
     // Each path ends the program: did they meet, to the compiler one path's loads could still be under way where another
     // begins, and it would wait there for the registers they share, between one array's loads and the next.
     const bool cut = ((td.lo & 3) | (td.n & ~(4 << a.logT))) != 0;      // n is less than T columns
