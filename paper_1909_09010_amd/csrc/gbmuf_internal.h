@@ -140,7 +140,18 @@ PickFn GBMUF_PICK_NAME(0, 1), GBMUF_PICK_NAME(1, 1), GBMUF_PICK_NAME(2, 1), GBMU
 // returns) and maps it to a status.
 int hip_failed(const char *what, hipError_t err, int status);
 
+// Arguments of the kernel that writes a tile list.
+struct TileArgs {
+    const int64_t *off;      // m+1 component offsets
+    const int64_t *start;    // m+1: first tile of every component
+    const CompDesc *comp;
+    TileDesc *out;
+    int64_t n;               // tiles
+    int32_t m, logT;
+};
+
 // gbmuf_kernels.hip
+int launch_tiles(const TileArgs &a, hipStream_t stream);
 int launch_sampler(const SampleArgs &a, hipStream_t stream);
 struct AverageShape {
     int rows_in_flight;      // 16-byte loads a thread keeps in flight: 4, 8 or 16
@@ -155,7 +166,7 @@ int launch_state_copy(const CopyArgs &c, int arrays, hipStream_t stream);
 int launch_copy_probe(float *dst, const float *src, int64_t n_floats, int flags, int blocks, hipStream_t stream);
 int launch_sync(const Variant &v, int policy, const SyncArgs &a, int64_t n_tiles, size_t lds_floor, hipStream_t stream);
 size_t sync_lds_bytes(const Variant &v, int K, int q, bool mixed, int C, bool in_kernel_sampling);
-int prepare_kernels(const Variant &v, int K, int q, bool mixed, int C, bool *can_sample_in_kernel);
+int prepare_kernel(const Variant &v, int policy, int K, int q, bool mixed, int C, bool *can_sample_in_kernel);
 bool can_sample_inline(int K, int C);
 bool draws_in_registers(int q);
 const Variant *variant_table(int *count);          // the shapes a plan description can name

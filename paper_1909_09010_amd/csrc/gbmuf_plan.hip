@@ -20,9 +20,8 @@ namespace {
 // Work list of the fused kernel for one tile width, in component order.
 struct TileSet {
     int32_t logT = 0;
-    std::vector<TileDesc> tiles;
-    std::vector<int64_t> tile_start;   // m+1: first tile of every component
-    TileDesc *d_tiles = nullptr;
+    std::vector<int64_t> tile_start;   // m+1: first tile of every component, and how many there are
+    TileDesc *d_tiles = nullptr;       // in gbmuf_plan_s::d_tiles
 };
 
 // How the fused kernel runs on one kind of state placement.
@@ -70,6 +69,8 @@ struct gbmuf_plan_s {
     int device = -1;
     int32_t lds_per_cu = 0;
     CompDesc *d_comp = nullptr;
+    int64_t *d_starts = nullptr;     // off, then tile_start of every set
+    TileDesc *d_tiles = nullptr;     // the lists of all sets
     int32_t *d_nbr = nullptr;        // neighbour scratch of gbmuf_sync, [m][K][q]
 };
 
@@ -392,14 +393,14 @@ int choose_policy(int layout, int size, int logT, int hints)
     return layout != kShared && logT >= 3 && (size != kTiny || hints != 0) ? kStreamed : kPlain;
 }
 
+// Tiles of a component [a, b) at T columns each.
+int64_t tiles_of(int64_t a, int64_t b, int64_t T) { return a < b ? (((b + 3) >> 2) + T - 1) / T - (a >> 2) / T : 0; }
+
 int64_t count_tiles(const gbmuf_plan_s &pl, int32_t logT)
 {
-    const int64_t T = static_cast<int64_t>(1) << logT;
     int64_t count = 0;
-    for (int32_t i = 0; i < pl.m; ++i) {
-        const int64_t a = pl.off[static_cast<size_t>(i)], b = pl.off[static_cast<size_t>(i) + 1];
-        if (a < b) count += (((b + 3) >> 2) + T - 1) / T - (a >> 2) / T;
-    }
+    for (int32_t i = 0; i < pl.m; ++i)
+        count += tiles_of(pl.off[static_cast<size_t>(i)], pl.off[static_cast<size_t>(i) + 1], static_cast<int64_t>(1) << logT);
     return count;
 }
 
@@ -413,46 +414,24 @@ bool is_launch_bound(const gbmuf_plan_s &pl, const gbmuf_plan_desc_t *desc)
     return can_sample_inline(pl.K, pl.C) && pl.K <= slots && count_tiles(pl, widest_tile(Variant{slots, 1, 1}, pl.K)) <= 8192;
 }
 
-// Split every component into runs of at most T 16-byte columns (the fused kernel's work list).
+// Split every component into runs of at most T 16-byte columns (the fused kernel's work list).  Here only where every
+// component's tiles begin; the list itself is written on the GPU (tile_kernel).
 void build_tiles(const gbmuf_plan_s &pl, TileSet &ts)
 {
-    const int64_t T = static_cast<int64_t>(1) << ts.logT;
-    ts.tiles.clear();
     ts.tile_start.assign(static_cast<size_t>(pl.m) + 1, 0);
-    ts.tiles.reserve(static_cast<size_t>(count_tiles(pl, ts.logT)));     // a list of millions is not grown step by step
-    for (int32_t i = 0; i < pl.m; ++i) {
-        const int64_t a = pl.off[static_cast<size_t>(i)], b = pl.off[static_cast<size_t>(i) + 1];
-        ts.tile_start[static_cast<size_t>(i)] = static_cast<int64_t>(ts.tiles.size());
-        ts.tile_start[static_cast<size_t>(i) + 1] = static_cast<int64_t>(ts.tiles.size());
-        if (a >= b) continue;
-        // Tile boundaries sit at multiples of T columns counted from the row start, not from the
-        // component start: with rows aligned to T*16 bytes every interior tile then covers whole
-        // cache lines (a component that starts mid-line only gets a short first tile), and no tile
-        // crosses a block of a blocked state.  Tiles that straddle lines cost a quarter of the
-        // bandwidth on MI355X.
-        const int64_t ga = a >> 2, gb = (b + 3) >> 2;
-        for (int64_t g = ga; g < gb;) {
-            int64_t next = (g / T + 1) * T;
-            if (next > gb) next = gb;
-            const int64_t lo = (g << 2) > a ? (g << 2) : a;
-            const int64_t end = (next << 2) < b ? (next << 2) : b;
-            ts.tiles.push_back(TileDesc{lo, static_cast<uint16_t>(end - lo),
-                                        static_cast<uint16_t>(pl.qv[static_cast<size_t>(i)]), i});
-            g = next;
-        }
-        ts.tile_start[static_cast<size_t>(i) + 1] = static_cast<int64_t>(ts.tiles.size());
-    }
+    for (int32_t i = 0; i < pl.m; ++i)
+        ts.tile_start[static_cast<size_t>(i) + 1] = ts.tile_start[static_cast<size_t>(i)] +
+            tiles_of(pl.off[static_cast<size_t>(i)], pl.off[static_cast<size_t>(i) + 1], static_cast<int64_t>(1) << ts.logT);
 }
 
 void free_device(gbmuf_plan_s &pl)
 {
     if (pl.d_comp) (void)hipFree(pl.d_comp);
+    if (pl.d_starts) (void)hipFree(pl.d_starts);
+    if (pl.d_tiles) (void)hipFree(pl.d_tiles);
     if (pl.d_nbr) (void)hipFree(pl.d_nbr);
-    for (TileSet &ts : pl.sets) {
-        if (ts.d_tiles) (void)hipFree(ts.d_tiles);
-        ts.d_tiles = nullptr;
-    }
-    pl.d_comp = nullptr; pl.d_nbr = nullptr;
+    for (TileSet &ts : pl.sets) ts.d_tiles = nullptr;
+    pl.d_comp = nullptr; pl.d_starts = nullptr; pl.d_tiles = nullptr; pl.d_nbr = nullptr;
 }
 
 template <class T>
@@ -494,16 +473,52 @@ int make_device_state(gbmuf_plan_s &pl, int32_t sampling)
     }
     bool can = false;
     int rc = GBMUF_OK;
+    std::vector<LayoutCfg> done;                            // every kernel that a call can launch, once
     for (int l = 0; l < kLayouts * kBranches * kSizes && rc == GBMUF_OK; ++l) {
         const int layout = l / kSizes / kBranches, what = l / kSizes % kBranches, size = l % kSizes;
-        if (size_occurs(pl, layout, what, size)) rc = prepare_kernels(pl.cfg[layout][what][size].variant, pl.K, pl.q, pl.mixed_q, pl.C, &can);
+        if (!size_occurs(pl, layout, what, size)) continue;
+        for (int policy : {static_cast<int>(kPlain), pl.cfg[layout][what][size].policy}) {       // blocks may share lines: plain
+            LayoutCfg c = pl.cfg[layout][what][size];
+            c.policy = policy;
+            if (layout == kRows && policy != pl.cfg[layout][what][size].policy) continue;
+            bool seen = false;
+            for (const LayoutCfg &d : done)
+                seen = seen || (d.policy == c.policy && d.variant.threads == c.variant.threads && d.variant.slots == c.variant.slots &&
+                                d.variant.depth == c.variant.depth);
+            if (seen || rc != GBMUF_OK) continue;
+            done.push_back(c);
+            rc = prepare_kernel(c.variant, c.policy, pl.K, pl.q, pl.mixed_q, pl.C, &can);
+        }
     }
     if (rc != GBMUF_OK) return rc;
     if (sampling == GBMUF_SAMPLING_IN_KERNEL && !can) return GBMUF_EUNSUPPORTED;
     pl.sampling = sampling;
     if ((rc = upload(&pl.d_comp, pl.comp)) != GBMUF_OK) return rc;
-    for (int s = 0; s < pl.n_sets; ++s)
-        if ((rc = upload(&pl.sets[s].d_tiles, pl.sets[s].tiles)) != GBMUF_OK) return rc;
+    // The tile lists, 16 bytes a tile and millions of tiles for a large model, are written where they are used: 74 us for a
+    // plan of 8 x 19.8 M, 156 of 16 x 278.6 M; built here and copied 684 and 21076.
+    std::vector<int64_t> starts(pl.off);
+    int64_t tiles = 0;
+    for (int s = 0; s < pl.n_sets; ++s) {
+        starts.insert(starts.end(), pl.sets[s].tile_start.begin(), pl.sets[s].tile_start.end());
+        tiles += pl.sets[s].tile_start.back();
+    }
+    if ((rc = upload(&pl.d_starts, starts)) != GBMUF_OK) return rc;
+    err = hipMalloc(reinterpret_cast<void **>(&pl.d_tiles), static_cast<size_t>(tiles ? tiles : 1) * sizeof(TileDesc));
+    if (err != hipSuccess) {
+        pl.d_tiles = nullptr;
+        return hip_failed("hipMalloc(tile lists)", err, GBMUF_ENOMEM);
+    }
+    TileDesc *next = pl.d_tiles;
+    for (int s = 0; s < pl.n_sets; ++s) {
+        TileSet &ts = pl.sets[s];
+        ts.d_tiles = next;
+        next += ts.tile_start.back();
+        rc = launch_tiles(TileArgs{pl.d_starts, pl.d_starts + static_cast<int64_t>(s + 1) * (pl.m + 1), pl.d_comp, ts.d_tiles,
+                                   ts.tile_start.back(), pl.m, ts.logT}, nullptr);
+        if (rc != GBMUF_OK) return rc;
+    }
+    err = hipStreamSynchronize(nullptr);                   // calls may come on any stream
+    if (err != hipSuccess) return hip_failed("hipStreamSynchronize(tile lists)", err, GBMUF_EDEVICE);
     const size_t n = static_cast<size_t>(pl.m) * pl.K * pl.q;
     err = hipMalloc(reinterpret_cast<void **>(&pl.d_nbr), (n ? n : 1) * sizeof(int32_t));
     if (err != hipSuccess) {
@@ -710,7 +725,7 @@ int enqueue_sync(const gbmuf_plan_s *pl, const int32_t *nbr_dev, const gbmuf_sta
     // runs one launch covers all tiles, and the workgroups of components that are not due return at once.
     const int64_t first = due.one_run && due.last >= 0 ? ts.tile_start[static_cast<size_t>(due.first)] : 0;
     const int64_t end = due.one_run && due.last >= 0 ? ts.tile_start[static_cast<size_t>(due.last) + 1]
-                                                     : static_cast<int64_t>(ts.tiles.size());
+                                                     : ts.tile_start.back();
     SyncArgs a{};
     a.tiles = ts.d_tiles + first;
     a.nbr = nbr_dev;
@@ -925,7 +940,7 @@ int gbmuf_plan_info(const gbmuf_plan_t *plan, gbmuf_info_t *info)
     info->has_device = plan->has_device ? 1 : 0;
     info->P = plan->P;
     const LayoutCfg &rows = cfg_of_all(*plan, kRows, kBmuf), &blocked = cfg_of_all(*plan, kBlocked, kBmuf);
-    info->n_tiles = static_cast<int64_t>(plan->sets[rows.set].tiles.size());
+    info->n_tiles = plan->sets[rows.set].tile_start.back();
     info->tile_columns = 1 << rows.logT;
     info->threads = rows.variant.threads;
     info->seed = plan->seed;
