@@ -105,7 +105,7 @@ struct Variant {
     int slots;
     int depth;
 };
-// shapes that only the library's own rules take (default_variant)
+// shapes that only the library's own rules take (aligned_shape, shared_variant)
 constexpr Variant kSixtyFour = {1024, 2, 1};
 constexpr Variant kMany = {1024, 4, 2};
 constexpr Variant kVeryMany = {512, 16, 4};

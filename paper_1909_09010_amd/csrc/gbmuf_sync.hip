@@ -53,7 +53,7 @@ __device__ __forceinline__ void hold(uint32_t &x)
 // Which tile this workgroup takes.  Workgroups are dealt round-robin to the 8 XCDs (blockIdx mod 8);
 // the list is cut into groups of 8 * 2^xcd_log consecutive tiles, and in every group XCD r takes the
 // r-th run of 2^xcd_log tiles; with the rotate flag the runs move on by one XCD every 8 groups
-// (blocked_xcds and xcd_run on the host say when and why).  With the backwards flag (set on odd
+// (aligned_shape and shares_lines on the host say when and why).  With the backwards flag (set on odd
 // rounds unless the plan asked for forward sweeps) the list is walked backwards, so that what the
 // previous sync wrote last is read first, while it may still be in the 256 MB memory-side cache (it
 // is for states of up to a few GB; larger states neither gain nor lose); the XCD of a tile stays the
@@ -229,13 +229,13 @@ struct Rows<NT, kAnyQ> {
 // ---------------------------------------------------------------------------------------
 // The fused kernel.  A column is 4 consecutive floats, loaded and stored as one 16-byte access
 // wherever the row starts: global memory takes 16-byte accesses at any 4-byte address, and what a
-// misaligned row costs is only the cache lines that two tiles share (xcd_run on the host).
+// misaligned row costs is only the cache lines that two tiles share (shares_lines on the host).
 // Slot s of the tile (s = tid + n*NT) is worker s >> logT, column s & (T-1).
 //
 // Bound by HBM.  Measured on 16 workers x 35.0 M parameters (6.7 GB) in plain [K, P] tensors with an
-// odd P: 2483 us (5406 GB/s); with 4-byte accesses, tiles dealt to the XCDs one by one: 3230 us.
+// odd P: 2300 to 2480 us (5.4 to 5.8 TB/s); with 4-byte accesses, tiles dealt to the XCDs one by one: 3230 us.
 // ---------------------------------------------------------------------------------------
-// A column of which only the floats in `mk` are this tile's (all four if WHOLE; at least one).  Of a cut column
+// A column of which only the floats in `mk` are this tile's (at least one).  Of a cut column
 // the floats outside are read as copies of the nearest one inside, so that its four loads depend on nothing: a
 // vector filled float by float made every array's load wait for the one before, three memory latencies in
 // a row in each cut tile.  48 components of one cut tile each, 100 workers, 1024 x 4: 9.6 us, that way 12.7;
@@ -530,7 +530,7 @@ __device__ __forceinline__ void any_tile(const SyncArgs &a, const TileDesc &td, 
 // answers at two thirds of the rate of 512-byte pieces.  So the tile takes up to 128 KB, all of theta is
 // loaded and parked first, and omega and Delta, whose values no other worker needs, are not held for
 // the whole tile but streamed through DEPTH slots of registers.  256 workers x 6.2 M (19 GB, blocked),
-// T = 32: 6290 us (6040 GB/s); T = 16, all that the registers hold of three arrays: 7576 us.
+// T = 32: 5890 us (6450 GB/s), 6290 with plain accesses; T = 16, all that the registers hold of three arrays, 7576.
 template <int NT, int SLOTS, int DEPTH, int Q1, int POL>
 __global__ __launch_bounds__(NT) void sync_kernel(SyncArgs a)
 {
