@@ -47,7 +47,6 @@ struct SyncArgs {
     const CompDesc *comp;    // [m]
     float *theta, *omega, *delta;
     Placement at;
-    int64_t row_end;         // floats that a row holds: P, or no limit where rows end in whole blocks
     int32_t K, q;            // q: neighbours per component (the largest q_i when they differ)
     int32_t logT;            // log2(columns per tile)
     int32_t xcd_log;         // log2(consecutive tiles that one XCD takes)

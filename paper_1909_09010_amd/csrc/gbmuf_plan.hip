@@ -732,7 +732,6 @@ int enqueue_sync(const gbmuf_plan_s *pl, const int32_t *nbr_dev, const gbmuf_sta
     a.comp = pl->d_comp;
     a.theta = st->theta; a.omega = st->omega; a.delta = st->delta;
     a.at = at;
-    a.row_end = layout == kBlocked ? INT64_MAX : pl->P;
     a.K = pl->K; a.q = pl->q; a.logT = cfg.logT; a.mode = mode;
     a.eta = eta; a.zeta = zeta; a.inv = pl->inv;
     a.flags = ((pl->alternate && (round & 1)) ? kFlagBackwards : 0) | (pl->mixed_q ? kFlagMixedQ : 0) |

@@ -9,7 +9,9 @@
 // registers; every state byte is read once and written once.  Where an element lives is a
 // Placement: plain rows, or blocks of 2^logB floats whose same-index blocks of all workers lie
 // together (a thread looks the block of its column up once).
+
 #include "gbmuf_device.h"
+#include "gbmuf_cut.h"
 
 #include "../../include/gbmuf.h"
 
@@ -364,9 +366,8 @@ __device__ __forceinline__ void do_tile(const SyncArgs &a, const TileDesc &td, v
 // Where all arrays are in flight at once the slots beyond the N that hold rows are left out; where omega and Delta are
 // streamed, blocks of DEPTH slots are left out in front, so that the stream ends in the same slots for any K.  A thread
 // that has no row in a slot loads the tile's first column of row K - 1, one line for the whole wave, and stores nothing.
-// CUT (T <= NT): component edges cut the tile.  A column that is not the tile's at all is treated like a missing row.  Of a cut column
-// all four floats are loaded, those of other tiles to no use, and the tile's own are stored one by one; the column at the end of
-// a row, where less than four floats may be left, is loaded from the row's last four and moved.
+// CUT (T <= NT): component edges cut the tile, which is not thin.  A column that is not the tile's at all is treated like a missing row.
+// Of a cut column the four floats nearest to it that are the tile's are loaded and moved, and its own are stored one by one (cut_column).
 template <int NT, int SLOTS, int DEPTH, int Q1, int POL, bool MA, bool CUT>
 struct WholeTile {
     const SyncArgs &a;
@@ -377,7 +378,7 @@ struct WholeTile {
     int64_t col_at, spare;                                        // where the thread's first column lies in row 0; what is loaded without a row
     float inv;
     unsigned mine;                                                // CUT: which floats of the thread's column are the tile's
-    int back;                                                     // CUT: by how many floats its load starts before it
+    int from;                                                     // CUT: where its load starts, counted from it
     v4f om[DEPTH], de[DEPTH];
 
     __device__ __forceinline__ WholeTile(const SyncArgs &args, const TileDesc &desc, v4f *lds, uint16_t *rows)
@@ -399,10 +400,9 @@ struct WholeTile {
     __device__ __forceinline__ v4f moved(v4f v) const
     {
         if (!CUT) return v;
-        v4f r;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) r[c] = back == 0 ? v[c] : back == 1 ? v[c < 3 ? c + 1 : 3] : back == 2 ? v[c < 2 ? c + 2 : 3] : v[3];
-        return r;
+        const bool one = from & 1, two = from & 2;                // turned by `from`: float c comes from c - from, modulo 4
+        const v4f h = {one ? v[3] : v[0], one ? v[0] : v[1], one ? v[1] : v[2], one ? v[2] : v[3]};
+        return v4f{two ? h[2] : h[0], two ? h[3] : h[1], two ? h[0] : h[2], two ? h[1] : h[3]};
     }
     __device__ __forceinline__ void store(float *p, v4f v) const
     {
@@ -412,7 +412,7 @@ struct WholeTile {
         }
 #pragma unroll
         for (int c = 0; c < 4; ++c)
-            if (mine & (1u << c)) p[back + c] = v[c];
+            if (mine & (1u << c)) p[c - from] = v[c];
     }
     __device__ __forceinline__ void load_slots(int n) { load_slots(n, n % DEPTH); }
     __device__ __forceinline__ void load_slots(int n, int to)
@@ -456,16 +456,11 @@ struct WholeTile {
         w0 = tid >> a.logT;
         inv = (a.flags & kFlagMixedQ) ? a.comp[td.comp].inv : a.inv;
         const int64_t first = td.lo & ~static_cast<int64_t>(3), e = first + 4 * col0;
-        const auto beyond = [this](int64_t x) { return a.row_end < x + 4 ? x + 4 - a.row_end : 0; };
-        mine = 0u;
-        back = 0;
-        if constexpr (CUT) {
-#pragma unroll
-            for (int c = 0; c < 4; ++c) mine |= e + c >= td.lo && e + c < td.lo + td.n ? 1u << c : 0u;
-            if (mine) back = static_cast<int>(beyond(e));
-        }
-        col_at = placed(a.at, e) - back;
-        spare = placed(a.at, first) - (CUT ? beyond(first) : 0) + static_cast<int64_t>(a.K - 1) * a.at.stride;
+        const CutColumn cut = CUT ? cut_column(e, td.lo, td.n) : CutColumn{0xFu, 0};
+        mine = cut.mine;
+        from = cut.from;
+        col_at = placed(a.at, e + from);
+        spare = placed(a.at, td.lo) + static_cast<int64_t>(a.K - 1) * a.at.stride;
         Rows<NT, Q1> rows;
         rows.begin(a, td);
         v4f th[SLOTS];
@@ -498,6 +493,44 @@ struct WholeTile {
     }
 };
 
+// A cut tile of the streamed shapes whose columns are not loaded whole (is_thin): one column of one worker at a time.
+template <int NT, int Q1>
+__device__ __forceinline__ void thin_tile(const SyncArgs &a, const TileDesc &td, v4f *tile, uint16_t *ids)
+{
+    const float inv = (a.flags & kFlagMixedQ) ? a.comp[td.comp].inv : a.inv;
+    const bool slots_too = a.mode != GBMUF_MODE_GOSSIP_MA;
+    const int T = 1 << a.logT, end = a.K << a.logT;
+    const int64_t first = td.lo & ~static_cast<int64_t>(3);
+    auto at = [&](int i) { return placed(a.at, first + 4 * (i & (T - 1))) + static_cast<int64_t>(i >> a.logT) * a.at.stride; };
+    auto mask = [&](int i) { return cut_column(first + 4 * (i & (T - 1)), td.lo, td.n).mine; };
+    Rows<NT, Q1> rows;
+    rows.begin(a, td);
+    rows.finish(a, td, ids);
+#pragma unroll 1
+    for (int i = threadIdx.x; i < end; i += NT)
+        if (const unsigned mk = mask(i)) tile[i] = load_col(a.theta + at(i), mk);
+    __syncthreads();
+#pragma unroll 1
+    for (int i = threadIdx.x; i < end; i += NT) {
+        const unsigned mk = mask(i);
+        if (mk == 0u) continue;
+        v4f tn = average<Q1>(tile, ids + (i >> a.logT) * ids_pitch(Q1, a.q), td.q + 1, a.logT, i & (T - 1), inv);
+        if (slots_too) {
+            const v4f avg = tn, o = load_col(a.omega + at(i), mk), d = load_col(a.delta + at(i), mk);
+            v4f on, dn;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                float t1, o1, d1;
+                filter(avg[c], o[c], d[c], a.eta, a.zeta, a.mode, t1, o1, d1);
+                tn[c] = t1; on[c] = o1; dn[c] = d1;
+            }
+            store_col(a.omega + at(i), on, mk);
+            store_col(a.delta + at(i), dn, mk);
+        }
+        store_col(a.theta + at(i), tn, mk);
+    }
+}
+
 template <int NT, int SLOTS, int DEPTH, int Q1, int POL>
 __device__ __forceinline__ void any_tile(const SyncArgs &a, const TileDesc &td, v4f *tile, uint16_t *ids)
 {
@@ -509,6 +542,8 @@ __device__ __forceinline__ void any_tile(const SyncArgs &a, const TileDesc &td, 
     if (cut) {
         if constexpr (DEPTH == SLOTS) {
             do_tile<NT, SLOTS, Q1>(a, td, tile, ids);
+        } else if (is_thin(td.lo, td.n, a.at.logB)) {
+            thin_tile<NT, Q1>(a, td, tile, ids);
         } else if (a.mode == GBMUF_MODE_GOSSIP_MA) {
             WholeTile<NT, SLOTS, DEPTH, Q1, kPlain, true, true>(a, td, tile, ids).run();
             __builtin_amdgcn_endpgm();

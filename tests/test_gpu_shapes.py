@@ -14,14 +14,22 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-def check(K, q, off, layout, mode, stride=None, every=None, rounds=(0, 1), **plan):
-    """Syncs in ascending and descending order; `every`: one element of so many is compared, None: all."""
+def check(K, q, off, layout, mode, stride=None, every=None, rounds=(0, 1), narrow=False, **plan):
+    """Syncs in ascending and descending order; `every`: one element of so many is compared, None: all; `narrow`: blocks as
+    small as the plan takes."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     off = np.asarray(off, dtype=np.int64)
     P, seed, ma = int(off[-1]), 5 + K, mode == B.MODE_GOSSIP_MA
-    pl = B.Plan(off, K, q, (q + 1) // 2 if q > 2 else 0, seed=seed, **plan)
+    most = int(np.max(q))
+    pl = B.Plan(off, K, q, (most + 1) // 2 if most > 2 else 0, seed=seed, **plan)
     st = W.DeviceState(K, P, DEV, layout, stride=stride, plan=pl)
+    if narrow:
+        size = pl.info.min_block_floats
+        blocks = -(-P // size)
+        st.arena = torch.empty(blocks * 3 * K * size, device=DEV)
+        st.block_floats, st.worker_stride, st.block_stride, st.width = size, size, 3 * K * size, blocks * size
+        st.arrays = [torch.as_strided(st.arena, (K, blocks, size), (size, 3 * K * size, 1), a * K * size) for a in range(3)]
     g = torch.Generator(device=DEV)
     g.manual_seed(seed)
     for flat in [st.arena] if st.arena is not None else st.arrays:
@@ -99,3 +107,22 @@ def test_large_launches(K, q, mode, layout):
     P = 510_000_000 // K
     off = [0, P // 5 | 1, P // 5 + 70 | 1, P // 3 * 2, P]
     check(K, q, off, "separate" if layout == "odd" else layout, mode, stride_of(layout, P), every=128 if K <= 128 else 32)
+
+
+# The shapes that stream omega and Delta, in tiles that component edges cut: components of 1 to 3 floats, edges a float beside a
+# block's (also of blocks narrower than a tile, whose columns are then read float by float), rows that end inside a column; one number of neighbours for
+# all components or one each.
+@pytest.mark.parametrize("place", ["blocked", "narrow", "rows", "odd"])
+@pytest.mark.parametrize("K,values,q,mode", [
+    (40, 5_600_000, [3, 0, 2, 6, 1, 4], B.MODE_PAPER), (64, 5_200_000, [2, 7, 5], B.MODE_PAPER), (48, 5_600_000, 9, B.MODE_LITERAL),
+    (100, 2_200_000, [1, 4, 0, 6, 3], B.MODE_PAPER), (128, 2_300_000, 3, B.MODE_NO_RESTART), (300, 2_200_000, [1, 2], B.MODE_PAPER),
+    (130, 20_400_000, [2, 0, 3], B.MODE_PAPER), (200, 20_500_000, [5, 1, 7, 4], B.MODE_PAPER), (300, 20_400_000, 3, B.MODE_PAPER),
+    (300, 20_400_000, 2, B.MODE_GOSSIP_MA), (700, 21_000_000, [2, 1], B.MODE_GOSSIP_MA), (700, 64_000_000, [2, 1], B.MODE_GOSSIP_MA)])
+def test_cut_tiles_of_streamed_shapes(K, values, q, mode, place):
+    P = values // K // 8 * 8 + 3
+    at = P // 128 * 64                                       # a multiple of the narrowest blocks
+    off = [0, 1, 3, 4, 7, 61, 62, 126, 130, 8191, 8194, 8195, 12289, at + 62, at + 127, at + 193, at + 1021, P - 6, P - 5, P - 2, P]
+    off = sorted(x for x in off if x <= P)
+    q = q if np.ndim(q) == 0 else [q[i % len(q)] for i in range(len(off) - 1)]
+    layout = {"narrow": "blocked", "odd": "separate"}.get(place, place)
+    check(K, q, off, layout, mode, P | 1 if place == "odd" else None, narrow=place == "narrow")
