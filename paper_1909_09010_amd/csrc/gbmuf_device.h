@@ -149,7 +149,8 @@ __device__ __forceinline__ void store4(float *p, v4f v)
 #if defined(__HIP_DEVICE_COMPILE__)
     if constexpr (POL == kStreamed) {
         typedef unsigned v4u __attribute__((ext_vector_type(4)));
-        __builtin_amdgcn_global_store_b128((__attribute__((address_space(1))) v4u *)p, __builtin_bit_cast(v4u, v), "agent");
+        typedef unsigned v4u_any __attribute__((ext_vector_type(4), aligned(4)));      // any 4-byte address, as above
+        __builtin_amdgcn_global_store_b128((__attribute__((address_space(1))) v4u_any *)p, __builtin_bit_cast(v4u, v), "agent");
         return;
     }
 #endif

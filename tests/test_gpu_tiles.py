@@ -142,11 +142,8 @@ def test_many_workers(K, q, mode):
     pl.destroy()
 
 
-# one workgroup is 64 columns of 4 floats; groups of 8 or 32 workgroups are dealt to the XCDs, the last P % 4 floats go to
-# one thread each; rows are read 4, 8 or 16 at a time, the last ones in halves of that
-@pytest.mark.parametrize("K", [1, 2, 3, 4, 5, 6, 8, 9, 11, 14, 16, 17, 18, 21, 25, 32, 33, 35, 41, 64, 130])
-@pytest.mark.parametrize("P", [1, 4, 255, 256, 2048 * 4 + 3, 4 * 64 * 33 - 1, 262146])
-def test_final_average_at_its_edges(K, P):
+def check_average(K, P):
+    """Rows of an odd stride that start inside a line, and blocks; sums to an address that is and one that is not a multiple of 16."""
     _need_gpu()
     pl = B.Plan([0, P], K, 0, 0, seed=0)
     g = torch.Generator(device=DEV)
@@ -167,6 +164,23 @@ def test_final_average_at_its_edges(K, P):
     assert np.array_equal(out[1:1 + P].cpu().numpy(), want) and np.array_equal(out2[4:4 + P].cpu().numpy(), want)
     assert bool((out[1 + P:] == 7).all()) and bool((out2[4 + P:] == 7).all()) and float(out[0]) == 7
     pl.destroy()
+
+
+# one workgroup is 64 columns of 4 floats; groups of 8 or 32 workgroups are dealt to the XCDs, the last P % 4 floats go to
+# one thread each; rows are read 4, 8 or 16 at a time, the last ones in halves of that
+@pytest.mark.parametrize("K", [1, 2, 3, 4, 5, 6, 8, 9, 11, 14, 16, 17, 18, 21, 25, 32, 33, 35, 41, 64, 130])
+@pytest.mark.parametrize("P", [1, 4, 255, 256, 2048 * 4 + 3, 4 * 64 * 33 - 1, 262146])
+def test_final_average_at_its_edges(K, P):
+    check_average(K, P)
+
+
+# sums beyond the caches are streamed, from 60 M values on with the resident waves bounded; rows too short for that; blocked
+# state of more than 500 M values of 33 to 64 workers moves on by an XCD from block to block
+@pytest.mark.parametrize("K,P", [(1, 61_000_001), (2, 31_000_002), (3, 21_000_003), (5, 13_000_001), (8, 5_000_003), (11, 6_000_002), (16, 4_000_001),
+                                 (20, 2_000_001), (33, 1_300_001), (48, 1_500_003), (70, 1_000_002), (130, 300_001), (130, 500_003), (300, 130_001),
+                                 (300, 210_003), (300, 510_001), (1000, 70_002), (40, 13_000_003)])
+def test_final_averages_beyond_the_caches(K, P):
+    check_average(K, P)
 
 
 # Rows drawn in registers (up to 7 neighbours, at the largest degree the ring wraps) and from a table, one number of
