@@ -632,9 +632,10 @@ size_t lds_floor(const gbmuf_plan_s *pl, const LayoutCfg &cfg)
 
 // Rows in flight per thread, resident one-wave workgroups per CU (32: as many as fit), who reads what and how, for a final
 // average.  us on MI355X, in the order of the rules:
-//   sums of up to 20 M values come from the caches, which plain loads leave them in (64 x 0.16 M 7.4, streamed 8.1) and whose latency
-//     more waves hide, with enough rows per thread that few workers take one pass: 8 x 4.2 M padded 25 (16 rows x 3 waves 33),
-//     1024 x 36 K 66 (8 rows 87).
+//   sums of up to 20 M values come from the caches, which plain loads leave them in (64 x 0.16 M 7.4, streamed 8.1), and of up to 22 M
+//     (theta 88 MB, of three states in turn) rows and blocks of up to 16 workers (8 x 2.6 M padded 15.4, 16.9; 5 x 4.2 M odd rows 16.2, 17.9; 7 x 3 M
+//     blocked 15.8, 16.7; 48 x 0.44 M blocked 14.2, 13.6; from 25 M on 2 to 13 % the other way).  More waves hide their latency, with enough
+//     rows per thread that few workers take one pass: 8 x 4.2 M padded 25 (16 rows x 3 waves 33), 1024 x 36 K 66 (8 rows 87).
 //     More than 64 workers up to 35 M (300 x 83 K 22.7, streamed 24.0).
 //   beyond, streamed: 8 x 25 M blocked 127, plain 145; 64 x 15.6 M padded 607, plain 674.  Up to 60 M, and where rows are too short to fill the
 //     chip with waves, without bound and with 16 rows of more than 64 workers in flight (1024 x 195 K 122, 4 rows x 6 waves 157).
@@ -651,7 +652,8 @@ AverageShape average_shape(const gbmuf_plan_s *pl, int layout, bool shared_lines
     AverageShape s{};
     int waves = 32;
     const bool short_rows = pl->P <= 250000;                  // fewer than 1000 waves
-    if (values <= (K <= 64 ? kCompactValues : 35000000)) {
+    const int64_t cached = K > 64 ? 35000000 : K <= 2 || (layout == kBlocked && K > 16) ? kCompactValues : 22000000;
+    if (values <= cached) {
         s.rows_in_flight = K <= 4 ? 4 : K <= 16 ? 8 : 16;
         s.xcd_log = K > 1 ? 2 : 0;
     } else {
