@@ -641,8 +641,8 @@ size_t lds_floor(const gbmuf_plan_s *pl, const LayoutCfg &cfg)
 //     chip with waves, without bound and with 16 rows of more than 64 workers in flight (1024 x 195 K 122, 4 rows x 6 waves 157).
 //   one worker is a copy: 590 M 746, 16 waves 770, 8 waves 1303.
 //   larger sums take 4 rows at a time, and the fewer waves the more workers there are: blocked 4 x 50 M 142 (12 waves), 64 x 3.1 M 119 (6;
-//     8 rows x 4 125), 128 x 7.8 M 577 (6; 16 rows x 3 591); padded 16 x 62 M 630 (8), 128 x 1.6 M 122 (8; 16 rows x 6 134).  Blocked 9 to 16
-//     workers: 16 rows x 4 waves (16 x 231 M 2177, 4 x 8 2250).  4 KB per XCD where rows share lines (2 x 100 M 185, workgroup by
+//     8 rows x 4 125), 128 x 7.8 M 577 (6; 16 rows x 3 591); padded 16 x 62 M 630 (8), 128 x 1.6 M 122 (8; 16 rows x 6 134).  Blocked 14 to 16
+//     workers, who fill a batch of 16 rows: 16 x 4 (16 x 62 M 591, 4 x 8 603; 10 x 50 M 379, 4 x 8 315).  4 KB per XCD where rows share lines (2 x 100 M 185, workgroup by
 //     workgroup 191) and for 9 to 64 workers of blocked state (32 x 116 M 2092 / 2130), but 33 to 64 of more than 500 M
 //     values move on by an XCD from block to block as in the fused kernel (64 x 57.8 M 2177, 4 KB per XCD 2250; 64 x 3.1 M 121 / 119).
 AverageShape average_shape(const gbmuf_plan_s *pl, int layout, bool shared_lines)
@@ -662,8 +662,8 @@ AverageShape average_shape(const gbmuf_plan_s *pl, int layout, bool shared_lines
         s.xcd_log = (K > 1 && shared_lines) || (layout == kBlocked && K > 8 && K <= 64) ? 2 : 0;
         if (values > 60000000 && !short_rows) {
             if (layout == kBlocked) {
-                waves = K <= 3 ? 32 : K <= 7 ? 12 : K <= 8 ? 8 : K <= 16 ? 4 : K > 64 && values < 100000000 ? 12 : 6;
-                if (K > 8 && K <= 16) s.rows_in_flight = 16;
+                waves = K <= 3 ? 32 : K <= 7 ? 12 : K <= 13 ? 8 : K <= 16 ? 4 : K > 64 && values < 100000000 ? 12 : 6;
+                if (K > 13 && K <= 16) s.rows_in_flight = 16;
                 s.rotate = K > 32 && K <= 64 && values > kLargeValues;
                 if (s.rotate) s.xcd_log = 0;
             } else {
