@@ -8,6 +8,7 @@
 #include <array>
 #include <cstddef>
 #include <cstdio>
+#include <cmath>
 #include <cstring>
 #include <mutex>
 #include <new>
@@ -67,7 +68,7 @@ struct gbmuf_plan_s {
 
     bool has_device = false;
     int device = -1;
-    int32_t lds_per_cu = 0;
+    int32_t lds_per_cu = 0, cus = 0;
     CompDesc *d_comp = nullptr;
     int64_t *d_starts = nullptr;     // off, then tile_start of every set
     TileDesc *d_tiles = nullptr;     // the lists of all sets
@@ -467,6 +468,8 @@ int make_device_state(gbmuf_plan_s &pl, int32_t sampling)
     err = hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, pl.device);
     if (err != hipSuccess) return hip_failed("hipDeviceGetAttribute(MaxSharedMemoryPerBlock)", err, GBMUF_EDEVICE);
     pl.lds_per_cu = max_lds;                               // on this GPU one workgroup may take a CU's whole LDS
+    err = hipDeviceGetAttribute(&pl.cus, hipDeviceAttributeMultiprocessorCount, pl.device);
+    if (err != hipSuccess) return hip_failed("hipDeviceGetAttribute(MultiprocessorCount)", err, GBMUF_EDEVICE);
     {
         const int rc0 = resolve_scratch(pl.device);
         if (rc0 != GBMUF_OK) return rc0;
@@ -630,6 +633,24 @@ size_t lds_floor(const gbmuf_plan_s *pl, const LayoutCfg &cfg)
     return share > 0 ? static_cast<size_t>(share) : 0;
 }
 
+// How many resident one-wave workgroups per CU take `n` of them best, of which `aim` is best for very many.  The last round takes
+// as long as 0.6 of a full one however few it has: 6, 7, 8 or, up to 14, all at once are taken so that it is not nearly empty; above
+// 24 workgroups per CU it hardly counts.  128 x 0.59 M (8.9 per CU), odd rows: 8 resident 59.6 us, 6 52.1, 16 47.0; 96 x 0.94 M
+// (14.3), padded: 8 54.1, 6 59.1; 256 x 0.47 M (7.2), blocked: 6 92.3, 8 70.7; 65 x 1.2 M (17.6), padded: 8 50.4, 6 43.7; 200 x 6.5 M (99),
+// blocked: 6 747, 8 775.
+int average_waves(double n, int aim)
+{
+    if (n > 24) return aim;
+    int best = 16;
+    double least = n <= 14 ? 1.02 * n : 1e30;
+    for (int w = 6; w <= 8; ++w) {
+        const double rounds = n / w, whole = std::floor(rounds), rest = rounds - whole;
+        const double cost = (whole + (rest > 0 ? std::max(rest, 0.6) : 0)) * w * (1 + 0.005 * std::abs(w - aim));
+        if (cost < least) { least = cost; best = w; }
+    }
+    return best;
+}
+
 // Rows in flight per thread, resident one-wave workgroups per CU (32: as many as fit), who reads what and how, for a final
 // average.  us on MI355X, in the order of the rules:
 //   sums of up to 20 M values come from the caches, which plain loads leave them in (64 x 0.16 M 7.4, streamed 8.1), and of up to 22 M
@@ -637,11 +658,12 @@ size_t lds_floor(const gbmuf_plan_s *pl, const LayoutCfg &cfg)
 //     blocked 15.8, 16.7; 48 x 0.44 M blocked 14.2, 13.6; from 25 M on 2 to 13 % the other way).  More waves hide their latency, with enough
 //     rows per thread that few workers take one pass: 8 x 4.2 M padded 25 (16 rows x 3 waves 33), 1024 x 36 K 66 (8 rows 87).
 //     More than 64 workers up to 35 M (300 x 83 K 22.7, streamed 24.0).
-//   beyond, streamed: 8 x 25 M blocked 127, plain 145; 64 x 15.6 M padded 607, plain 674.  Up to 60 M, and where rows are too short to fill the
-//     chip with waves, without bound and with 16 rows of more than 64 workers in flight (1024 x 195 K 122, 4 rows x 6 waves 157).
+//   beyond, streamed: 8 x 25 M blocked 127, plain 145; 64 x 15.6 M padded 607, plain 674.  Up to 60 M, and where rows are of up
+//     to 4 workgroups per CU, without bound and with 16 rows of more than 64 workers in flight (1024 x 195 K 122, 4 rows x 6 waves 157).
 //   one worker is a copy: 590 M 746, 16 waves 770, 8 waves 1303.
-//   larger sums take 4 rows at a time, and the fewer waves the more workers there are: blocked 4 x 50 M 142 (12 waves), 64 x 3.1 M 119 (6;
-//     8 rows x 4 125), 128 x 7.8 M 577 (6; 16 rows x 3 591); padded 16 x 62 M 630 (8), 128 x 1.6 M 122 (8; 16 rows x 6 134).  Blocked 14 to 16
+//   larger sums take 4 rows at a time, and the fewer waves the more workers there are, above 16 by the workgroups too
+//     (average_waves): blocked 4 x 50 M 142 (12 waves), 64 x 3.1 M 119 (6; 8 rows x 4 125), 128 x 7.8 M 577 (6; 16 rows x 3 591); padded 16 x 62
+//     M 630 (8).  Blocked 14 to 16
 //     workers, who fill a batch of 16 rows: 16 x 4 (16 x 62 M 591, 4 x 8 603; 10 x 50 M 379, 4 x 8 315).  4 KB per XCD where rows share lines (2 x 100 M 185, workgroup by
 //     workgroup 191) and for 9 to 64 workers of blocked state (32 x 116 M 2092 / 2130), but 33 to 64 of more than 500 M
 //     values move on by an XCD from block to block as in the fused kernel (64 x 57.8 M 2177, 4 KB per XCD 2250; 64 x 3.1 M 121 / 119).
@@ -651,7 +673,8 @@ AverageShape average_shape(const gbmuf_plan_s *pl, int layout, bool shared_lines
     const int64_t values = static_cast<int64_t>(K) * pl->P;
     AverageShape s{};
     int waves = 32;
-    const bool short_rows = pl->P <= 250000;                  // fewer than 1000 waves
+    const double groups = pl->cus > 0 ? static_cast<double>(pl->P) / 256 / pl->cus : 1e6;      // workgroups per CU
+    const bool short_rows = groups <= 4;
     const int64_t cached = K > 64 ? 35000000 : K <= 2 || (layout == kBlocked && K > 16) ? kCompactValues : 22000000;
     if (values <= cached) {
         s.rows_in_flight = K <= 4 ? 4 : K <= 16 ? 8 : 16;
@@ -662,12 +685,12 @@ AverageShape average_shape(const gbmuf_plan_s *pl, int layout, bool shared_lines
         s.xcd_log = (K > 1 && shared_lines) || (layout == kBlocked && K > 8 && K <= 64) ? 2 : 0;
         if (values > 60000000 && !short_rows) {
             if (layout == kBlocked) {
-                waves = K <= 3 ? 32 : K <= 7 ? 12 : K <= 13 ? 8 : K <= 16 ? 4 : K > 64 && values < 100000000 ? 12 : 6;
+                waves = K <= 3 ? 32 : K <= 7 ? 12 : K <= 13 ? 8 : K <= 16 ? 4 : average_waves(groups, 6);
                 if (K > 13 && K <= 16) s.rows_in_flight = 16;
                 s.rotate = K > 32 && K <= 64 && values > kLargeValues;
                 if (s.rotate) s.xcd_log = 0;
             } else {
-                waves = K == 1 ? 32 : K <= 3 ? 16 : K <= 7 ? 12 : K <= 128 ? 8 : 6;
+                waves = K == 1 ? 32 : K <= 3 ? 16 : K <= 7 ? 12 : K <= 16 ? 8 : average_waves(groups, K <= 128 ? 8 : 6);
             }
         }
     }

@@ -209,6 +209,22 @@ def test_rows_in_flight_of_a_final_average_are_filled(values):
     assert seen[8][0] != seen[14][0] and seen[8][1] < seen[14][1]
 
 
+# A final average takes its workgroups in rounds of as many as are resident: the last round is not nearly empty (128 x 0.59 M, 8.9
+# workgroups per CU: 60 us in rounds of 8, 47 at once).
+@pytest.mark.gpu
+@pytest.mark.parametrize("place", ["blocked", "rows"])
+@pytest.mark.parametrize("K,per_cu,waves", [(128, 8.9, 16), (300, 7.2, 8), (300, 10.6, 6), (96, 14.3, 8), (300, 15.3, 8),
+                                            (65, 17.6, 6), (72, 19.1, 7), (60, 19.1, 7), (300, 17.9, 6), (200, 99, 6)])
+def test_no_nearly_empty_last_round_of_a_final_average(K, per_cu, waves, place):
+    need_gpu()
+    import torch
+    props = torch.cuda.get_device_properties(0)
+    pl = B.Plan([0, int(per_cu * props.multi_processor_count) * 256], K, 0, 0, seed=0)
+    (_, _, lds), = launches(lambda s: pl.final_average_state(fake_state(pl, place), 1 << 36, s))
+    assert lds == 160 * 1024 // waves - 2048
+    pl.destroy()
+
+
 # A copy launches a workgroup for every 4 KB of a row, or what rounds rows of a blocked source up to whole runs: no
 # multiple of the work where a row is shorter than a run (1024 x 1000 in runs of 32: 58 us, 13 as launched).
 @pytest.mark.gpu
