@@ -232,8 +232,9 @@ int launch_state_copy(const CopyArgs &c, int arrays, hipStream_t stream)
         for (int n = 0; n < arrays; ++n) shared = shared || reinterpret_cast<uintptr_t>(c.dst[n]) % 128 != 0;
         if (c.K <= (shared ? 48 : 16)) run = shared ? 1 : 8;
     }
-    const int64_t len = std::min(run, pieces);
-    int64_t blocks = (pieces + len - 1) / len * len * c.K;
+    // runs of equal length: the last one of a row is filled up by workgroups that have nothing to do
+    const int64_t runs = (pieces + run - 1) / run, len = (pieces + runs - 1) / runs;
+    int64_t blocks = runs * len * c.K;
     if (fold && blocks * arrays > (static_cast<int64_t>(511) << 23)) fold = false;
     args.run_len = static_cast<uint32_t>(len);
     args.fold = fold ? static_cast<uint32_t>(arrays) : 1u;

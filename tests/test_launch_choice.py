@@ -225,16 +225,19 @@ def test_no_nearly_empty_last_round_of_a_final_average(K, per_cu, waves, place):
     pl.destroy()
 
 
-# A copy launches a workgroup for every 4 KB of a row, or what rounds rows of a blocked source up to whole runs: no
-# multiple of the work where a row is shorter than a run (1024 x 1000 in runs of 32: 58 us, 13 as launched).
+# A copy launches a workgroup for every 4 KB of a row, in runs of equal length, so that less than one for a run is
+# left over, and no multiple of the work where a row is little longer than a run (512 blocks of 9 pieces in runs of 8: 26 us, 19 as
+# launched; 1024 x 1000 in runs of 32: 58 us, 13).
 @pytest.mark.gpu
 @pytest.mark.parametrize("to", ["rows", "blocked"])
 @pytest.mark.parametrize("frm", ["rows", "blocked"])
-@pytest.mark.parametrize("K,P", [(1, 5), (16, 1000), (64, 1000), (1024, 1000), (256, 3000), (1024, 40_000), (8, 200_000)])
-def test_a_copy_launches_no_more_than_its_rows(K, P, frm, to):
+@pytest.mark.parametrize("K,P", [(1, 5), (16, 1000), (64, 1000), (1024, 1000), (256, 3000), (1024, 40_000), (8, 200_000), (512, 8200), (1024, 8200),
+                                 (1024, 16_500), (1024, 40_500), (16, 270_000), (24, 1_100_000), (100, 700_000)])
+@pytest.mark.parametrize("which", [1, 7])
+def test_a_copy_launches_no_more_than_its_rows(which, K, P, frm, to):
     need_gpu()
     pl = B.Plan([0, P], K, 0, 0, seed=0)
-    (blocks, threads, _), = launches(lambda s: pl.state_copy(fake_state(pl, to), fake_state(pl, frm), 1, s))
-    pieces, run = -(-(P + 31) // 1024), 32 if K <= 32 else 4
-    assert threads == 256 and pieces * K <= blocks
-    assert blocks <= (pieces if frm == "rows" or pieces <= run else -(-pieces // run) * run) * K
+    (blocks, threads, _), = launches(lambda s: pl.state_copy(fake_state(pl, to), fake_state(pl, frm), which, s))
+    pieces, arrays = -(-(P + 31) // 1024), bin(which).count("1")
+    assert threads == 256 and pieces * K * arrays <= blocks <= (pieces + pieces // 8) * K * arrays
+    pl.destroy()
