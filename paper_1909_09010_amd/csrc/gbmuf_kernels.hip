@@ -209,9 +209,10 @@ int launch_final_average(const float *theta, const Placement &at, int K, int64_t
 // The walk of a copy.  Rows to rows are copied whole, array by array: two long streams.  A blocked side is one stretch of memory where
 // the arrays of a run follow each other.  us for three arrays, now / runs of 4 KB to 128 KB or whole rows, array by array, at their best:
 //   blocked to blocked, 32 KB, folded, 400 M values: 3 workers 1420 / 1625, 44 workers 1418 / 1751, 300 workers 1411 / 1463.
-//   rows to blocked, folded, up to 32 workers 128 KB: 3 x 133 M odd rows 1528 / 1713, 24 x 16.7 M 1602 / 1633; more workers 32 KB: 44 x 9.1 M 1610
-//     / 1678, 128 x 3.1 M 1582 / 1633; at 128 KB 1662 and more than 1690.  More than 32 workers and up to 40 M values whole rows: 64 x
-//     0.47 M 121 / folded 131.
+//   rows to blocked, folded, up to 32 workers 128 KB: 3 x 133 M odd rows 1528 / 1713, 24 x 16.7 M 1602 / 1633; up to 200 workers 64 KB: 40 x
+//     0.75 M odd rows 117 / 32 KB 120, whole rows 130; 64 x 0.94 M padded 241 / 279, 252; 64 x 6.2 M 1504 / 1581, 1703; more workers 32 KB: 256 x 1.6
+//     M 1566 / 64 KB 1689, whole rows 1717 (128 x 3.1 M 1582 / 1565, 1726).  33 to 60 workers and up to 15 M values, and more workers and up to 40 M, whole
+//     rows: 64 x 0.47 M 120 / 64 KB 127.  Single sizes differ by 5 to 10 % either way, by where the arrays lie.
 //   blocked to rows, array by array: aligned rows of up to 16 workers 32 KB, 12 x 33 M 1469 / whole rows 1505, of more whole rows, 44 x 9.1 M
 //     1513 / 1631; rows that share lines of up to 48 workers 4 KB, 24 x 16.7 M 1629 / whole rows 1710, 44 x 9.1 M 1745 / 1782, of
 //     more whole rows, 100 x 4 M 1673 / 4 KB 1860.
@@ -224,8 +225,8 @@ int launch_state_copy(const CopyArgs &c, int arrays, hipStream_t stream)
     const bool from = c.sa.logB != 62, to = c.da.logB != 62, streamed = values > 4000000;
     int64_t run = pieces;
     bool fold = false;
-    if (streamed && to && (from || c.K <= 32 || values > 40000000)) {
-        run = !from && c.K <= 32 ? 32 : 8;
+    if (streamed && to && (from || c.K <= 32 || values > (c.K <= 60 ? 15000000 : 40000000))) {
+        run = from || c.K > 200 ? 8 : c.K <= 32 ? 32 : 16;
         fold = true;
     } else if (streamed && from && !to) {
         bool shared = c.K > 1 && c.da.stride % 32 != 0;

@@ -20,8 +20,14 @@ class _KernelNodeParams(ctypes.Structure):
                 ("params", ctypes.c_void_p), ("shared", ctypes.c_uint32)]
 
 
-def launches(call, kernels=False):
-    """[(blocks, threads, LDS bytes)] of what ``call(stream)`` enqueues, or which kernels; nothing runs."""
+class _CopyArgs(ctypes.Structure):
+    """The argument of the copy kernel (CopyArgs)."""
+    _fields_ = [("arrays", ctypes.c_void_p * 6), ("placements", ctypes.c_int64 * 6), ("P", ctypes.c_int64), ("K", ctypes.c_int32),
+                ("run_len", ctypes.c_uint32), ("fold", ctypes.c_uint32)]
+
+
+def launches(call, kernels=False, args=None):
+    """[(blocks, threads, LDS bytes)] of what ``call(stream)`` enqueues, or which kernels, or their one argument; nothing runs."""
     import torch
     hip = ctypes.CDLL(B.LIB_PATH)          # the HIP runtime that the library itself is bound to
     stream = torch.cuda.Stream()
@@ -39,6 +45,10 @@ def launches(call, kernels=False):
         kind, p = ctypes.c_int(-1), _KernelNodeParams()
         assert hip.hipGraphNodeGetType(ctypes.c_void_p(node), ctypes.byref(kind)) == 0 and kind.value == 0   # a kernel
         assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)) == 0
+        if args is not None:
+            first = ctypes.cast(p.params, ctypes.POINTER(ctypes.c_void_p))[0]
+            out.append(args.from_buffer_copy(ctypes.string_at(first, ctypes.sizeof(args))))
+            continue
         out.append(p.func if kernels else (p.grid.x * p.grid.y * p.grid.z, p.block.x, p.shared))
     assert hip.hipGraphDestroy(graph) == 0
     return out
@@ -240,4 +250,21 @@ def test_a_copy_launches_no_more_than_its_rows(which, K, P, frm, to):
     (blocks, threads, _), = launches(lambda s: pl.state_copy(fake_state(pl, to), fake_state(pl, frm), which, s))
     pieces, arrays = -(-(P + 31) // 1024), bin(which).count("1")
     assert threads == 256 and pieces * K * arrays <= blocks <= (pieces + pieces // 8) * K * arrays
+    pl.destroy()
+
+
+# (run, arrays that follow each other) of copies from rows into blocks: rows of 33 to 60 workers are copied whole only where the
+# caches hold them (40 x 0.75 M 130 us, in runs of 64 KB 117); runs of 64 KB up to 200 workers (64 x 0.94 M 241 us, in runs of 32 KB 279).
+@pytest.mark.gpu
+@pytest.mark.parametrize("aligned", [True, False])
+@pytest.mark.parametrize("K,values,walk", [(32, 17_000_000, (32, 3)), (33, 14_000_000, None), (33, 17_000_000, (16, 3)), (60, 30_000_000, (16, 3)),
+                                           (61, 39_000_000, None), (64, 60_000_000, (16, 3)), (200, 400_000_000, (16, 3)), (256, 400_000_000, (8, 3))])
+def test_walks_of_rows_into_blocks(K, values, walk, aligned):
+    need_gpu()
+    P = values // K
+    pl = B.Plan([0, P], K, 0, 0, seed=0)
+    got, = launches(lambda s: pl.state_copy(fake_state(pl), fake_state(pl, "rows", aligned), 7, s), args=_CopyArgs)
+    pieces = -(-(P + 31) // 1024)
+    run, fold = walk or (pieces, 1)
+    assert (got.P, got.K, got.fold) == (P, K, fold) and got.run_len == -(-pieces // -(-pieces // run))
     pl.destroy()
