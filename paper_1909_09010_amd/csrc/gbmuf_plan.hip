@@ -297,7 +297,8 @@ Variant shared_variant(int K, int what, int size, bool few)
 //     7.5 M 1072 us, 512 x 4 1057; 64 x 4.7 M 1070, 512 x 4 1085), 65-128 kMany, 129-512 kVeryMany (200 x 1.5 M 1167, kMany 1185;
 //     256 x 1.2 M 1156, kSixtyFour 1165; 300 x 1 M 1245, kMany 1206), up to 20 M values kSixtyFour (200 x 0.1 M 84 us, kMany 88).
 //   Aligned rows are 3K address streams: 5.9 up to 8 workers, 5.1 from 64 on, whatever the shape.  Wide tiles, and 4 KB
-//     of a row per XCD from 33 workers on, from 129 above 500 M values (96 x 2.6 M 1167 us, tile by tile 1210).  2-4 256 x 1, four per CU (4 x
+//     of a row per XCD from 129 workers on, from 17 up to 20 M values; beyond that fewer take tile by tile (25 to 480 M values of 33 to 128
+//     workers within 2 % of the best of all shapes and walks, 4 KB 2 to 10 %: 64 x 4.7 M 1414 us, 1624).  2-4 256 x 1, four per CU (4 x
 //     62.5 M 987 us; unbounded 1034), 5-8 1024 x 1 (8 x 87.5 M 2852; kSixtyFour 2900, 512 x 1 2998), 9-32 kSixtyFour (32 x 7.8 M 1136; 1024 x 2
 //     1152), 33-128 512 x 4 (64 x 1.6 M 472, kVeryMany 483; 48 x 5.2 M 1158 / 1136; 96 x 2.6 M 1167, 1024 x 4 1223), above 500 M values
 //     kVeryMany (48 x 14.6 M 3204, 512 x 4 3273; 88 x 22.7 M 7895, 1024 x 4 8075), above 128 workers kVeryMany (300 x 0.8 M 1209, 4 KB per XCD
@@ -350,7 +351,7 @@ void aligned_shape(int K, int layout, int what, int size, bool few, LayoutCfg &c
         cfg.rotate = K > 32 && (K <= 128 || what == kMa || size != kCompact);
         run = cfg.rotate ? 0 : 6;
     } else {
-        run = K > (size == kCompact || what == kMa ? 16 : size == kLarge ? 128 : 32) ? 8 : 0;
+        run = K > (size == kCompact || what == kMa ? 16 : 128) ? 8 : 0;
     }
 }
 // Small plans with rows of more than 7 neighbours draw them through LDS in every workgroup (launch_bound), a thread a

@@ -26,6 +26,16 @@ class _CopyArgs(ctypes.Structure):
                 ("run_len", ctypes.c_uint32), ("fold", ctypes.c_uint32)]
 
 
+class _SyncArgs(ctypes.Structure):
+    """The beginning of the argument of the fused kernel (SyncArgs)."""
+    _fields_ = [("arrays", ctypes.c_void_p * 6), ("stride", ctypes.c_int64), ("block_extra", ctypes.c_int64), ("logB", ctypes.c_int32),
+                ("reserved", ctypes.c_int32), ("K", ctypes.c_int32), ("q", ctypes.c_int32), ("logT", ctypes.c_int32), ("xcd_log", ctypes.c_int32),
+                ("mode", ctypes.c_int32), ("eta", ctypes.c_float), ("zeta", ctypes.c_float), ("inv", ctypes.c_float), ("flags", ctypes.c_int32)]
+
+
+ROTATE = 64                                # in _SyncArgs.flags
+
+
 def launches(call, kernels=False, args=None):
     """[(blocks, threads, LDS bytes)] of what ``call(stream)`` enqueues, or which kernels, or their one argument; nothing runs."""
     import torch
@@ -52,6 +62,11 @@ def launches(call, kernels=False, args=None):
         out.append(p.func if kernels else (p.grid.x * p.grid.y * p.grid.z, p.block.x, p.shared))
     assert hip.hipGraphDestroy(graph) == 0
     return out
+
+
+def fused_args(call):
+    """The argument of the fused kernel that ``call(stream)`` launches after the sampler."""
+    return launches(call, args=_SyncArgs)[-1]
 
 
 def fake_state(plan, place="blocked", aligned=True):
@@ -119,6 +134,27 @@ def test_a_tiny_frequent_component_does_not_unbound_the_rest(often):
         assert len(step) == len(everything) == 2 and step[-1] == everything[-1]        # an empty component is not sampled
         rare = launches(lambda s: pl.sync_step_state(st, 0.9, 1.0, 1, 1, s))
         assert rare == [] if often == [0] else len(rare) == 1 and rare[0][0] <= 8
+
+
+def shape(K, values, place, aligned=True, mode=B.MODE_PAPER):
+    """(threads, columns of a tile, LDS bytes, floats of a row that one XCD takes, whether these move on) of a sync."""
+    pl = B.Plan([0, values // K], K, min(2, K - 1), 0, sampling=B.SAMPLING_SEPARATE)
+    call = lambda s: pl.sync_state(fake_state(pl, place, aligned), 0.9, 1.0, mode, 0, s)
+    _, threads, lds = launches(call)[-1]
+    node = fused_args(call)
+    pl.destroy()
+    return threads, 1 << node.logT, lds, 4 << node.logT + node.xcd_log, bool(node.flags & ROTATE)
+
+
+# Aligned rows of 33 to 128 workers beyond the caches: the XCDs take tiles one by one (4 KB of a row each: 64 x 4.7 M 15 % longer).
+@pytest.mark.gpu
+@pytest.mark.parametrize("K", [33, 48, 64, 96, 128])
+@pytest.mark.parametrize("values", [25_000_000, 150_000_000, 480_000_000])
+def test_aligned_rows_go_to_the_xcds_tile_by_tile(K, values):
+    need_gpu()
+    threads, columns, _, run, rotate = shape(K, values, "rows")
+    assert threads == 512 and run == 4 * columns and not rotate
+    assert shape(160, values, "rows")[3] == shape(K, 15_000_000, "rows")[3] == 1024
 
 
 # More than 7 neighbours are drawn through LDS, which only plans of up to 8192 tiles of about 32 columns do.
