@@ -299,7 +299,7 @@ Variant shared_variant(int K, int what, int size, bool few)
 //   Aligned rows are 3K address streams: 5.9 up to 8 workers, 5.1 from 64 on, whatever the shape.  Wide tiles, and 4 KB
 //     of a row per XCD from 129 workers on, from 17 up to 20 M values; beyond that fewer take tile by tile (25 to 480 M values of 33 to 128
 //     workers within 2 % of the best of all shapes and walks, 4 KB 2 to 10 %: 64 x 4.7 M 1414 us, 1624).  2-4 256 x 1, four per CU (4 x
-//     62.5 M 987 us; unbounded 1034), 5-8 1024 x 1 (8 x 87.5 M 2852; kSixtyFour 2900, 512 x 1 2998), 9-32 kSixtyFour (32 x 7.8 M 1136; 1024 x 2
+//     62.5 M 987 us; unbounded 1034), up to 20 M values also 5-8 (8 x 0.75 M 21.9 us, 1024 x 1 22.5; 5 x 1.6 M 30.9, 34.7), beyond 1024 x 1 (8 x 87.5 M 2852; kSixtyFour 2900, 512 x 1 2998), 9-32 kSixtyFour (32 x 7.8 M 1136; 1024 x 2
 //     1152), 33-128 512 x 4 (64 x 1.6 M 472, kVeryMany 483; 48 x 5.2 M 1158 / 1136; 96 x 2.6 M 1167, 1024 x 4 1223), above 500 M values
 //     kVeryMany (48 x 14.6 M 3204, 512 x 4 3273; 88 x 22.7 M 7895, 1024 x 4 8075), above 128 workers kVeryMany (300 x 0.8 M 1209, 4 KB per XCD
 //     not taken 1259).  5 to 20 M values of more than 32 workers: 1024 x 4.
@@ -338,13 +338,14 @@ void aligned_shape(int K, int layout, int what, int size, bool few, LayoutCfg &c
         else v = kMany;
         if (K <= 4) bound = K <= 2 ? 3 : 6;
     } else {
-        if (K <= 4) find_variant(256, 1, &v);
+        const bool small = K <= 4 || (K <= 8 && size == kCompact);
+        if (small) find_variant(256, 1, &v);
         else if (K <= 8) find_variant(1024, 1, &v);
         else if (K <= 32) v = kSixtyFour;
         else if (size == kCompact) v = Variant{1024, 4, 4};
         else if (K <= 128 && size != kLarge) find_variant(512, 4, &v);
         else if (few) v = kVeryMany;
-        if (K <= 4) bound = 4;
+        if (small) bound = 4;
     }
     if (size <= kSmall) return;
     if (blocked) {

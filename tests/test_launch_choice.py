@@ -157,6 +157,17 @@ def test_aligned_rows_go_to_the_xcds_tile_by_tile(K, values):
     assert shape(160, values, "rows")[3] == shape(K, 15_000_000, "rows")[3] == 1024
 
 
+# 5 to 8 workers' aligned rows of 5 to 20 M values take small tiles like fewer workers' (in 1024 x 1 up to 40 % longer).
+@pytest.mark.gpu
+@pytest.mark.parametrize("K", [4, 5, 6, 7, 8])
+def test_aligned_rows_of_few_workers_take_small_tiles(K):
+    need_gpu()
+    for values in (5_500_000, 12_000_000, 19_500_000):
+        threads, _, lds, _, _ = shape(K, values, "rows")
+        assert threads == 256 and lds == 160 * 1024 // 4 - 2048
+    assert (shape(K, 30_000_000, "rows")[0] == 256) == (K == 4)
+
+
 # More than 7 neighbours are drawn through LDS, which only plans of up to 8192 tiles of about 32 columns do.
 @pytest.mark.gpu
 @pytest.mark.parametrize("K,p,q,most", [(8, -1, 7, None), (9, -1, 8, 8192 * 128), (16, -1, 8, 8192 * 128), (32, -1, 20, 8192 * 128),
