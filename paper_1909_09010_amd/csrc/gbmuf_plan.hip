@@ -252,12 +252,20 @@ int32_t widest_tile(const Variant &v, int K)
     return lg;
 }
 
+// Rows that share lines: whether 3 to 16 workers take 1024 x 1, whose slots K rows fill to 7/8 up to 8 workers, above 500 M values to
+// 3/4, and to 15/16 from 9 on (6 x 133 M 1024 x 1 3639 us, 512 x 1 3720; 14 x 57 M 3857 / 3749; 14 x 7.1 M 480 / 474).
+bool shared_wide(int K, int size)
+{
+    const int rows = K << widest_tile({1024, 1, 1}, K);
+    return K == 3 || (K <= 16 && rows >= (K > 8 ? 960 : size == kLarge ? 768 : 896));
+}
+
 // Rows that share lines, beyond the caches: 3K address streams, of which each access touches one line more than it needs.  All wide
 // shapes end within 5 % of each other: 5.4 TB/s with 4 workers, 5.1 with 16 and 4.9 from 64 on.
-//   BMUF: up to 2 workers 512 x 2, one per CU (2 x 350 M 3069 us, 256 x 1 3250), up to 16 1024 x 1 where K rows fill its slots to 7/8 (8 x 75 M 2735,
+//   BMUF: up to 2 workers 512 x 2, one per CU (2 x 350 M 3069 us, 256 x 1 3250), up to 16 1024 x 1 where K rows fill its slots (8 x 75 M 2735,
 //     kSixtyFour 2870; 16 x 37.5 M 2819 / 2873), and with 3 workers (3 x 233 M 3132, 512 x 1 3179), else 512 x 1 (6 x 33 M
 //     914, kSixtyFour 931; 12 x 16.7 M 927 / 938), up to 64 kSixtyFour (32 x
-//     18.8 M 2887, 1024 x 2 2948; 48 x 12.5 M 2885 / 2965), above 1024 x 4 (200 x 3 M 2970, kVeryMany 2988), large up to 128 kMany (96 x 6.2 M 2929,
+//     18.8 M 2887, 1024 x 2 2948; 48 x 12.5 M 2885 / 2965), but 33 to 39 kMany, one per CU (33 x 24 M 3792, kSixtyFour 3954; 36 x 8.3 M 1435 / 1462), above 1024 x 4 (200 x 3 M 2970, kVeryMany 2988), large up to 128 kMany (96 x 6.2 M 2929,
 //     1024 x 4 3008; 128 x 0.5 M 366 / 356), large above 256 kVeryMany (300 x 2 M 3100), above 512 at all sizes (1024 x 4 20 to 50 % more).
 //   gossip-MA: up to 4 workers 512 x 2, large 1024 x 4 (2 x 250 M 692, 512 x 2 733), up to 16 256 x 2 (16 x 25 M 600, 256 x 4 609), up to 32 256 x 4, up to
 //     64 512 x 4 (64 x 6.2 M 629, 1024 x 4 632), up to 128 1024 x 4, above kVeryMany (200 x 2 M 657, 1024 x 4 710).
@@ -274,10 +282,10 @@ Variant shared_variant(int K, int what, int size, bool few)
     } else {
         if (few && (K > 512 || (K > 256 && large))) return kVeryMany;
         if (K <= 2) find_variant(512, 2, &v);
-        else if (K == 3 || (K <= 16 && (K << widest_tile({1024, 1, 1}, K)) >= 896)) find_variant(1024, 1, &v);
+        else if (shared_wide(K, size)) find_variant(1024, 1, &v);
         else if (K <= 16) find_variant(512, 1, &v);
-        else if (K <= 64) v = kSixtyFour;
-        else if (K <= 128 && large) v = kMany;
+        else if (K <= 32 || (K >= 40 && K <= 64)) v = kSixtyFour;
+        else if (K < 40 || (K <= 128 && large)) v = kMany;
     }
     return v;
 }
@@ -374,8 +382,8 @@ Variant lds_drawing_variant(int K, int layout)
 int shared_workgroups_per_cu(int K, int what, int size)
 {
     if (size == kCompact || what == kMa) return 0;
-    if (K <= 2 || (K > 64 && K <= 128 && size == kLarge)) return 1;
-    return K > 4 && K <= 16 && (K << widest_tile({1024, 1, 1}, K)) < 896 ? 4 : 2;
+    if (K <= 2 || (K > 32 && K < 40) || (K > 64 && K <= 128 && size == kLarge)) return 1;
+    return K > 4 && K <= 16 && !shared_wide(K, size) ? 4 : 2;
 }
 
 // What a plan that names its shape gets if it does not name a bound: no bound on rows, few on blocked state.

@@ -168,6 +168,19 @@ def test_aligned_rows_of_few_workers_take_small_tiles(K):
     assert (shape(K, 30_000_000, "rows")[0] == 256) == (K == 4)
 
 
+# Rows that share cache lines: 1024 x 1 where K rows fill it (14 workers do not: 3 % longer), 33 to 39 workers wide tiles of their
+# own (4 % longer in 1024 x 2).
+@pytest.mark.gpu
+@pytest.mark.parametrize("values", [100_000_000, 600_000_000])
+def test_shapes_of_rows_that_share_lines(values):
+    need_gpu()
+    got = {K: shape(K, values, "rows", aligned=False) for K in (3, 5, 6, 7, 8, 9, 13, 14, 15, 16, 32, 33, 36, 39, 40, 64)}
+    wide = {K for K in got if K <= 16 and got[K][0] == 1024}
+    assert wide == {3, 7, 8, 15, 16} | ({6} if values > 500_000_000 else set())
+    assert all(got[K][1] == 64 and got[K][2] > 64 * 1024 for K in (33, 36, 39)) and got[40][1] == got[64][1] == 32
+    assert all(got[K][3] == 8192 for K in got)
+
+
 # More than 7 neighbours are drawn through LDS, which only plans of up to 8192 tiles of about 32 columns do.
 @pytest.mark.gpu
 @pytest.mark.parametrize("K,p,q,most", [(8, -1, 7, None), (9, -1, 8, 8192 * 128), (16, -1, 8, 8192 * 128), (32, -1, 20, 8192 * 128),
