@@ -298,8 +298,10 @@ Variant shared_variant(int K, int what, int size, bool few)
 //     5.6 us, 1024 slots 5.9, 4096 9.5; 3 M 12.7, 13.0, 14.4).
 //   Blocked state is one stretch of memory, and every tile shape that keeps 512 bytes to 1 KB of a row together is fast: 6.7 to 6.85
 //     up to 64 workers.  An XCD takes 1 KB of each row in one run (xcd 6): 8 x 300 M / 8 1045 us, tile by tile 1065; from 33 to 128
-//     workers and beyond the caches up to 512 runs of one tile that move on from block to block (rotate), without which an
-//     XCD sees the same addresses modulo 4 KB in every block: 64 x 23.4 M 5356 us, not rotated 5425 (1 KB) and more.
+//     workers, and beyond the caches up to 256 and above 512, one tile, and these move on from block to block (rotate), without which an
+//     XCD sees the same addresses modulo 4 KB in every block: 64 x 23.4 M 5356 us, not rotated 5425 (1 KB) and more; 160 x 1.9 M 1091, 1100; but 257 to 512,
+//     whose tiles hold 256 bytes of a row (300 x 1 M 1244, one tile moving on 1314; 400 x 1.8 M 2976 / 3129),
+//     481 to 512 in tiles of 128 bytes, which they fill, and runs of 4 KB (512 x 0.6 M 1378, kVeryMany 1411).
 //     No bound of the residency helps above 4 workers; up to 2 three per CU (2 x 300 M 2165 us, six 2517).  Up to 8 workers 256 x 1, 9-16 512 x 1 where K rows fill its
 //     slots to 7/8, else 256 x 2, whose threads idle in whole slots (12 x 25 M 1051 us; 512 x 1 1080), 17-32 512 x 2, 33-64 kSixtyFour (40 x
 //     7.5 M 1072 us, 512 x 4 1057; 64 x 4.7 M 1070, 512 x 4 1085), 65-128 kMany, 129-512 kVeryMany (200 x 1.5 M 1167, kMany 1185;
@@ -342,7 +344,8 @@ void aligned_shape(int K, int layout, int what, int size, bool few, LayoutCfg &c
         else if (K <= 64) v = kSixtyFour;
         else if (K <= 128) v = kMany;
         else if (size == kCompact && K <= 256) v = kSixtyFour;
-        else if (size != kCompact && few) v = kVeryMany;
+        else if (size != kCompact && few && !(K > 480 && K <= 512)) v = kVeryMany;
+        else if (size != kCompact && few) find_variant(512, 8, &v);
         else v = kMany;
         if (K <= 4) bound = K <= 2 ? 3 : 6;
     } else {
@@ -357,8 +360,8 @@ void aligned_shape(int K, int layout, int what, int size, bool few, LayoutCfg &c
     }
     if (size <= kSmall) return;
     if (blocked) {
-        cfg.rotate = K > 32 && (K <= 128 || what == kMa || size != kCompact);
-        run = cfg.rotate ? 0 : 6;
+        cfg.rotate = K > 32 && (what == kMa || K <= 128 || (size != kCompact && (K <= 256 || K > 512)));
+        run = cfg.rotate ? 0 : K > 480 && K <= 512 && size != kCompact ? 8 : 6;
     } else {
         run = K > (size == kCompact || what == kMa ? 16 : 128) ? 8 : 0;
     }

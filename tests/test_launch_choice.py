@@ -157,6 +157,18 @@ def test_aligned_rows_go_to_the_xcds_tile_by_tile(K, values):
     assert shape(160, values, "rows")[3] == shape(K, 15_000_000, "rows")[3] == 1024
 
 
+# Blocked state beyond the caches: the XCDs' tiles move on from block to block, but for 257 to 512 workers, whose tiles hold 256 bytes of a
+# row and who take 1 KB of it in one run (one tile each, moving on, 5 % longer).
+@pytest.mark.gpu
+@pytest.mark.parametrize("values", [30_000_000, 300_000_000, 1_000_000_000])
+def test_which_xcd_takes_which_blocks(values):
+    need_gpu()
+    for K in (129, 200, 256, 257, 300, 400, 480, 481, 512, 513, 1000):
+        _, columns, _, run, rotate = shape(K, values, "blocked")
+        assert (run, rotate) == ((256 if K <= 480 else 1024, False) if 256 < K <= 512 else (4 * columns, True))
+        assert columns == (32 if K <= 256 else 16 if K <= 480 else 8)
+
+
 # 5 to 8 workers' aligned rows of 5 to 20 M values take small tiles like fewer workers' (in 1024 x 1 up to 40 % longer).
 @pytest.mark.gpu
 @pytest.mark.parametrize("K", [4, 5, 6, 7, 8])
