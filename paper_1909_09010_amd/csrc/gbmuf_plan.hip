@@ -313,8 +313,10 @@ Variant shared_variant(int K, int what, int size, bool few)
 //     1152), 33-128 512 x 4 (64 x 1.6 M 472, kVeryMany 483; 48 x 5.2 M 1158 / 1136; 96 x 2.6 M 1167, 1024 x 4 1223), above 500 M values
 //     kVeryMany (48 x 14.6 M 3204, 512 x 4 3273; 88 x 22.7 M 7895, 1024 x 4 8075), above 128 workers kVeryMany (300 x 0.8 M 1209, 4 KB per XCD
 //     not taken 1259).  5 to 20 M values of more than 32 workers: 1024 x 4.
-//   Gossip-MA has a third of the loads and takes more slots per thread.  Blocked: up to 2 workers 256 x 1, up to 16 256 x 2 where K rows
-//     fill it to 7/8 (8 x 75 M 723 us; 512 x 2 748), else 256 x 4, up to 32 256 x 4 (725; 512 x 2 735), 33-64 512 x 4, above 1024 x 4, large of
+//   Gossip-MA has a third of the loads and takes more slots per thread.  Blocked: up to 2 workers 256 x 1, but 2 of
+//     more than 500 M values 512 x 2, two per CU (2 x 650 M 1610 us, 256 x 1 1817), 4 512 x 2 (4 x 175 M 848, 256 x 2 898; two per CU 837, but 4 x 5.2 M 6 %
+//     more), up to 16 256 x 2 where K rows
+//     fill it to 7/8 (8 x 75 M 723 us; 512 x 2 748), and 5 and 6 (5 x 140 M 923, 256 x 4 1050; 6 x 50 M 362 / 402), else 256 x 4, up to 32 256 x 4 (725; 512 x 2 735), 33-64 512 x 4, above 1024 x 4, large of
 //     more than 256 workers kVeryMany (300 x 2 M 947; 956).  Rows: up to 8 256 x 2, up to 24 256 x 4, up to 64 1024 x 4, above
 //     kVeryMany (300 x 2 M 1003; 1024 x 4 1089).  5 to 20 M values: 256 x 2 up to 64 workers, up to 128 512 x 2.
 void aligned_shape(int K, int layout, int what, int size, bool few, LayoutCfg &cfg)
@@ -328,8 +330,12 @@ void aligned_shape(int K, int layout, int what, int size, bool few, LayoutCfg &c
     if (what == kMa) {
         if (size <= kSmall) v = cached_variant(K, what);
         else if (size <= kCompact) find_variant(K <= 64 ? 256 : K <= 128 ? 512 : 1024, K <= 128 ? 2 : 4, &v);
+        else if (blocked && (K == 4 || (K == 2 && size == kLarge))) {
+            find_variant(512, 2, &v);
+            if (K == 2) bound = 2;
+        }
         else if (blocked && K <= 2) find_variant(256, 1, &v);
-        else if (blocked ? K <= 16 && fills(512) : K <= 8) find_variant(256, 2, &v);
+        else if (blocked ? K == 5 || K == 6 || (K <= 16 && fills(512)) : K <= 8) find_variant(256, 2, &v);
         else if (K <= (blocked ? 32 : 24)) find_variant(256, 4, &v);
         else if (blocked && K <= 64) find_variant(512, 4, &v);
         else if (few && (blocked ? K > 512 || (K > 256 && size == kLarge) : K > 64)) v = kVeryMany;

@@ -157,6 +157,17 @@ def test_aligned_rows_go_to_the_xcds_tile_by_tile(K, values):
     assert shape(160, values, "rows")[3] == shape(K, 15_000_000, "rows")[3] == 1024
 
 
+# Gossip-MA of few blocks (5 x 140 M 18 % longer in 256 x 4, 4 x 175 M 6 % in 256 x 2).
+@pytest.mark.gpu
+@pytest.mark.parametrize("values", [30_000_000, 300_000_000, 700_000_000])
+def test_shapes_of_gossip_ma_of_few_blocks(values):
+    need_gpu()
+    got = {K: shape(K, values, "blocked", mode=B.MODE_GOSSIP_MA) for K in (2, 3, 4, 5, 6, 7, 8)}
+    assert {K for K in got if got[K][0] == 512} == ({2, 4} if values > 500_000_000 else {4})
+    assert got[4][1] == 256 and got[4][2] < 24 * 1024
+    assert [got[K][1] for K in (3, 5, 6, 7, 8)] == [256, 64, 64, 64, 64]
+
+
 # Blocked state beyond the caches: the XCDs' tiles move on from block to block, but for 257 to 512 workers, whose tiles hold 256 bytes of a
 # row and who take 1 KB of it in one run (one tile each, moving on, 5 % longer).
 @pytest.mark.gpu
