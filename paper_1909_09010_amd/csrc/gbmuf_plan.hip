@@ -630,6 +630,11 @@ gbmuf_state_t rows_state(float *theta, float *omega, float *delta, int64_t strid
     return st;
 }
 
+// Groups of 8 runs that a launch on rows that share lines has at least, its runs being halved for it: tiles beyond the last whole group go
+// to the XCDs one by one, and with 32 KB a run those are all of a row of less than 256 KB.  us, runs of 32 KB / halved: gossip-MA 128 x
+// 12 K 8.6 / 6.2, 128 x 47 K 14.8 / 11.9; BMUF 16 x 50 K 6.9 / 5.3, 128 x 47 K 29.2 / 26.5.  With 8 or 16 groups 1 and 3 % more.
+constexpr int64_t kLeastGroups = 4;
+
 // Whether rows or blocks start inside 128-byte lines, so that neighbouring tiles share lines: unless both are taken by one XCD its
 // L2 cannot join the halves, and every shared line is fetched twice and written in two pieces.  One XCD takes 32 KB of a
 // row then, and one line in 256 is shared.  16 workers x 35.0 M in plain tensors: 3944 GB/s at 512 B, 4984 at 4 KB, 5073 at
@@ -786,6 +791,7 @@ int enqueue_sync(const gbmuf_plan_s *pl, const int32_t *nbr_dev, const gbmuf_sta
     a.round0 = static_cast<uint32_t>(round); a.round1 = static_cast<uint32_t>(round >> 32);
     a.step = round;
     a.xcd_log = std::max(0, (shared ? 11 : cfg.xcd_columns_log) - cfg.logT);
+    while (shared && a.xcd_log > 0 && (end - first) >> (3 + a.xcd_log) < kLeastGroups) --a.xcd_log;
     return launch_sync(cfg.variant, shared ? kPlain : cfg.policy, a, end - first, lds_floor(pl, cfg), stream);
 }
 

@@ -45,8 +45,8 @@ def check_rows(K, q, off, stride, skew=(0, 0, 0), mode=B.MODE_PAPER, rounds=(0, 
     return info
 
 
-# Consecutive tiles that one XCD takes: 2048 columns of a row where rows share cache lines, else one tile; a group is 8
-# such runs.  The lists here end before, at and after one and two groups of the plan's own tile width.
+# Consecutive tiles that one XCD takes: 2048 columns of a row where rows share cache lines, halved until the list has 4 groups of 8
+# such runs, else one tile.  The lists here end before, at and after one and two groups of 2048 columns at the plan's own tile width.
 @pytest.mark.parametrize("K", [4, 7, 16, 33])
 @pytest.mark.parametrize("tiles", ["1", "9", "group-1", "group", "group+1", "2*group-1", "2*group+3"])
 @pytest.mark.parametrize("odd", [0, 1])

@@ -157,6 +157,20 @@ def test_aligned_rows_go_to_the_xcds_tile_by_tile(K, values):
     assert shape(160, values, "rows")[3] == shape(K, 15_000_000, "rows")[3] == 1024
 
 
+# Rows that share cache lines: an XCD takes 32 KB of a row, or so much less that 4 groups of 8 such runs are whole: tiles beyond the last
+# go to the XCDs one by one (128 x 47 K, gossip-MA: all of them, 40 % longer).
+@pytest.mark.gpu
+@pytest.mark.parametrize("mode", [B.MODE_PAPER, B.MODE_GOSSIP_MA])
+@pytest.mark.parametrize("K", [2, 8, 16, 64, 128, 300, 1024])
+def test_runs_of_tiles_are_whole_where_rows_share_lines(K, mode):
+    need_gpu()
+    for values in (200_000, 1_500_000, 6_000_000, 20_000_000, 100_000_000, 1_000_000_000):
+        _, columns, _, run, rotate = shape(K, values, "rows", False, mode)
+        groups = lambda run: -(-(values // K) // (4 * columns)) // (8 * run // (4 * columns))
+        assert not rotate and run <= 8192 and (groups(run) >= 4 or run == 4 * columns)
+        assert run == 8192 or groups(2 * run) < 4
+
+
 # Gossip-MA of few blocks (5 x 140 M 18 % longer in 256 x 4, 4 x 175 M 6 % in 256 x 2).
 @pytest.mark.gpu
 @pytest.mark.parametrize("values", [30_000_000, 300_000_000, 700_000_000])
