@@ -209,9 +209,9 @@ bool find_variant(int threads, int slots, Variant *out)
 // stay in the caches, and loads that leave them early lose (choose_policy).  From kSmallValues on there are enough tiles of
 // any shape for all CUs.  Up to kCompactValues something is left in the 256 MB memory-side cache from one sync to the next;
 // for rows that share lines that is all that counts (three arrays, or theta alone).  Above kLargeValues a launch's rows are
-// drawn in a kernel of their own (draws_itself).
+// drawn in a kernel of their own (draws_itself), but gossip-MA's from kLargeValuesMa on.
 constexpr int64_t kTinyValues = 2000000, kSmallValues = 5000000, kCompactValues = 20000000, kCompactValuesSharedMa = 60000000;
-constexpr int64_t kLargeValues = 500000000, kLargeValuesMa = 130000000;
+constexpr int64_t kLargeValues = 500000000, kLargeValuesMa = 130000000, kLargeValuesSharedMa = 149000000;
 
 int size_of_launch(int64_t values, int layout, int what)
 {
@@ -219,7 +219,7 @@ int size_of_launch(int64_t values, int layout, int what)
     if (!shared && values <= kTinyValues) return kTiny;
     if (!shared && values <= kSmallValues) return kSmall;
     if (values <= (shared && what == kMa ? kCompactValuesSharedMa : kCompactValues)) return kCompact;
-    return values <= kLargeValues ? kMiddle : kLarge;
+    return values <= (shared && what == kMa ? kLargeValuesSharedMa : kLargeValues) ? kMiddle : kLarge;
 }
 
 // Which sizes a call of this plan can have: without periods a call updates everything.
@@ -267,7 +267,8 @@ bool shared_wide(int K, int size)
 //     914, kSixtyFour 931; 12 x 16.7 M 927 / 938), up to 64 kSixtyFour (32 x
 //     18.8 M 2887, 1024 x 2 2948; 48 x 12.5 M 2885 / 2965), but 33 to 39 kMany, one per CU (33 x 24 M 3792, kSixtyFour 3954; 36 x 8.3 M 1435 / 1462), above 1024 x 4 (200 x 3 M 2970, kVeryMany 2988), large up to 128 kMany (96 x 6.2 M 2929,
 //     1024 x 4 3008; 128 x 0.5 M 366 / 356), large above 256 kVeryMany (300 x 2 M 3100), above 512 at all sizes (1024 x 4 20 to 50 % more).
-//   gossip-MA: up to 4 workers 512 x 2, large 1024 x 4 (2 x 250 M 692, 512 x 2 733), up to 16 256 x 2 (16 x 25 M 600, 256 x 4 609), up to 32 256 x 4, up to
+//   gossip-MA: 2 and 4 workers 256 x 4, three per CU (2 x 40 M 111 us, 512 x 2 114; 4 x 30 M 166 / 174), 1 and 3 512 x 2, above 149 M values 1024
+//     x 4 (4 x 75 M 428, 256 x 4 445), 2 workers 512 x 8, two per CU (2 x 150 M 415, 1024 x 4 424, 256 x 4 441), up to 16 256 x 2 (16 x 25 M 600, 256 x 4 609), up to 32 256 x 4, up to
 //     64 512 x 4 (64 x 6.2 M 629, 1024 x 4 632), up to 128 1024 x 4, above kVeryMany (200 x 2 M 657, 1024 x 4 710).
 Variant shared_variant(int K, int what, int size, bool few)
 {
@@ -276,7 +277,9 @@ Variant shared_variant(int K, int what, int size, bool few)
     if (size == kCompact) return cached_variant(K, what);
     if (what == kMa) {
         if (few && K > 128) return kVeryMany;
-        if (K <= 4 && !large) find_variant(512, 2, &v);
+        if ((K == 2 || K == 4) && !large) find_variant(256, 4, &v);
+        else if (K <= 4 && !large) find_variant(512, 2, &v);
+        else if (K == 2) find_variant(512, 8, &v);
         else if (K > 4 && K <= 32) find_variant(256, K <= 16 ? 2 : 4, &v);
         else if (K > 32 && K <= 64) find_variant(512, 4, &v);
     } else {
@@ -387,10 +390,12 @@ Variant lds_drawing_variant(int K, int layout)
 }
 
 // Rows that share lines: one workgroup per CU with up to 2 workers (2 x 350 M 3069 us, two 3200) and of kMany (96 x 6.2 M 2929, two 2976), four of 512 x
-// 1, else two.  A state that stays in the cache has nothing to gain from a bound, and gossip-MA moves too little to need one.
+// 1, else two.  A state that stays in the cache has nothing to gain from a bound, and gossip-MA moves too little to need one but
+// in the wide tiles of 2 and 4 workers (see above).
 int shared_workgroups_per_cu(int K, int what, int size)
 {
-    if (size == kCompact || what == kMa) return 0;
+    if (size == kCompact) return 0;
+    if (what == kMa) return size == kMiddle ? (K == 2 || K == 4 ? 3 : 0) : K == 2 ? 2 : 0;
     if (K <= 2 || (K > 32 && K < 40) || (K > 64 && K <= 128 && size == kLarge)) return 1;
     return K > 4 && K <= 16 && !shared_wide(K, size) ? 4 : 2;
 }

@@ -171,6 +171,19 @@ def test_runs_of_tiles_are_whole_where_rows_share_lines(K, mode):
         assert run == 8192 or groups(2 * run) < 4
 
 
+# Gossip-MA of 2 and 4 workers' rows that share cache lines: (threads, columns, workgroups per CU).  In 512 x 2 3 to 8 % longer.
+@pytest.mark.gpu
+@pytest.mark.parametrize("values,two,three,four", [(65_000_000, (256, 512, 3), (512, 256, 0), (256, 256, 3)), (145_000_000, (256, 512, 3), (512, 256, 0), (256, 256, 3)),
+                                                   (155_000_000, (512, 2048, 2), (1024, 1024, 0), (1024, 1024, 0)),
+                                                   (600_000_000, (512, 2048, 2), (1024, 1024, 0), (1024, 1024, 0))])
+def test_shapes_of_gossip_ma_of_few_odd_rows(values, two, three, four):
+    need_gpu()
+    for K, (threads, columns, bound) in ((2, two), (3, three), (4, four)):
+        got = shape(K, values, "rows", False, B.MODE_GOSSIP_MA)
+        assert got[:2] == (threads, columns)
+        assert bound == 0 or got[2] == 160 * 1024 // bound - 2048
+
+
 # Gossip-MA of few blocks (5 x 140 M 18 % longer in 256 x 4, 4 x 175 M 6 % in 256 x 2).
 @pytest.mark.gpu
 @pytest.mark.parametrize("values", [30_000_000, 300_000_000, 700_000_000])
