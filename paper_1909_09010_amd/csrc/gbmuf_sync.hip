@@ -493,31 +493,49 @@ struct WholeTile {
     }
 };
 
-// A cut tile of the streamed shapes whose columns are not loaded whole (is_thin): one column of one worker at a time.
+// A cut tile of the streamed shapes whose columns are not loaded whole (is_thin): one column of one worker at a time, only those that
+// hold floats of the tile.  One or two as a rule, of which a thread has few: its first one's loads are all issued before the barrier.
 template <int NT, int Q1>
 __device__ __forceinline__ void thin_tile(const SyncArgs &a, const TileDesc &td, v4f *tile, uint16_t *ids)
 {
     const float inv = (a.flags & kFlagMixedQ) ? a.comp[td.comp].inv : a.inv;
     const bool slots_too = a.mode != GBMUF_MODE_GOSSIP_MA;
-    const int T = 1 << a.logT, end = a.K << a.logT;
     const int64_t first = td.lo & ~static_cast<int64_t>(3);
-    auto at = [&](int i) { return placed(a.at, first + 4 * (i & (T - 1))) + static_cast<int64_t>(i >> a.logT) * a.at.stride; };
-    auto mask = [&](int i) { return cut_column(first + 4 * (i & (T - 1)), td.lo, td.n).mine; };
+    const int columns = static_cast<int>((td.lo + td.n - 1 - first) >> 2) + 1;
+    const int lg = columns == 1 ? 0 : columns == 2 ? 1 : a.logT, end = a.K << lg;
+    auto column = [&](int i) { return i & ((1 << lg) - 1); };
+    auto at = [&](int i) { return placed(a.at, first + 4 * column(i)) + static_cast<int64_t>(i >> lg) * a.at.stride; };
+    auto mask = [&](int i) { return i < end ? cut_column(first + 4 * column(i), td.lo, td.n).mine : 0u; };
     Rows<NT, Q1> rows;
     rows.begin(a, td);
-    rows.finish(a, td, ids);
+    const int i0 = threadIdx.x;
+    const unsigned mine = mask(i0);
+    v4f t, o, d;
+    if (mine) {
+        t = load_col(a.theta + at(i0), mine);
+        if (slots_too) {
+            o = load_col(a.omega + at(i0), mine);
+            d = load_col(a.delta + at(i0), mine);
+        }
+    }
+    rows.finish(a, td, ids);                                      // drawn while the loads are under way
+    if (mine) tile[((i0 >> lg) << a.logT) + column(i0)] = t;
 #pragma unroll 1
-    for (int i = threadIdx.x; i < end; i += NT)
-        if (const unsigned mk = mask(i)) tile[i] = load_col(a.theta + at(i), mk);
+    for (int i = i0 + NT; i < end; i += NT)
+        if (const unsigned mk = mask(i)) tile[((i >> lg) << a.logT) + column(i)] = load_col(a.theta + at(i), mk);
     __syncthreads();
 #pragma unroll 1
-    for (int i = threadIdx.x; i < end; i += NT) {
+    for (int i = i0; i < end; i += NT) {
         const unsigned mk = mask(i);
         if (mk == 0u) continue;
-        v4f tn = average<Q1>(tile, ids + (i >> a.logT) * ids_pitch(Q1, a.q), td.q + 1, a.logT, i & (T - 1), inv);
+        v4f tn = average<Q1>(tile, ids + (i >> lg) * ids_pitch(Q1, a.q), td.q + 1, a.logT, column(i), inv);
         if (slots_too) {
-            const v4f avg = tn, o = load_col(a.omega + at(i), mk), d = load_col(a.delta + at(i), mk);
+            const v4f avg = tn;
             v4f on, dn;
+            if (i != i0) {
+                o = load_col(a.omega + at(i), mk);
+                d = load_col(a.delta + at(i), mk);
+            }
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 float t1, o1, d1;
