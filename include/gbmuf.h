@@ -118,9 +118,11 @@ typedef struct gbmuf_plan_desc {
                                        by K and layout; a pair that is not built in -> EINVAL     */
     int32_t sampling;               /* GBMUF_SAMPLING_*                                           */
     int32_t sweep;                  /* GBMUF_SWEEP_*                                              */
-    int32_t cache_hints;            /* 0: by size and placement.  Any of bits 0 and 1: non-temporal
-                                       loads and stores through the L2 at every size (not where
-                                       rows start inside cache lines)                              */
+    int32_t cache_hints;            /* 0: by size and placement.  Either of bits 0 and 1, or both:
+                                       non-temporal loads and stores through the L2 at every size;
+                                       not where rows or blocks start inside cache lines, not by
+                                       tiles of less than 8 columns (more than 512 workers, for
+                                       most shapes), nor in tiles that a component edge cuts       */
     int32_t workgroups_per_cu;      /* upper bound on the fused kernel's resident workgroups per
                                        compute unit (enforced through its LDS request); 0 = by
                                        layout, K and what the call updates                               */
@@ -143,7 +145,8 @@ typedef struct gbmuf_info {
     int32_t in_kernel_sampling; /* 1 if a sync of everything draws the rows inside the fused kernel
                                    in every mode (no neighbour scratch is used then)         */
     int32_t tile_columns_blocked, threads_blocked;   /* the same for blocked state           */
-    int32_t workgroups_per_cu_blocked;               /* resident workgroups per CU, blocked  */
+    int32_t workgroups_per_cu_blocked;               /* upper bound on the resident workgroups per
+                                                        CU, blocked; 0 = none                */
     int32_t tile_columns_blocked_ma;  /* tile width of the gossip-MA branch on blocked state  */
     int32_t min_block_floats;         /* smallest gbmuf_state_t.block_floats this plan takes  */
 } gbmuf_info_t;
@@ -306,9 +309,8 @@ int gbmuf_final_average_state(const gbmuf_plan_t *plan, const gbmuf_state_t *sta
  *     state.theta = arena, state.omega = arena + omega_offset, state.delta = arena + delta_offset
  * GBMUF_LAYOUT_BLOCKED (recommended): blocks of block_floats floats; the blocks with one index
  *   lie together as [theta: K blocks | omega: K blocks | delta: K blocks], then the next index.
- *   The fused kernel then streams ONE moving address range instead of 3K, keeps few workgroups
- *   resident per compute unit so that this range stays short, and runs at the same speed
- *   wherever the driver placed the arena.
+ *   The fused kernel then streams ONE moving address range instead of 3K, and runs at nearly the
+ *   same speed wherever the driver placed the arena (MI355X, 16 workers x 278.6 M: 15.6 or 16.2 ms).
  * GBMUF_LAYOUT_ROWS: K groups [theta_w | omega_w | delta_w] of rows padded to 4 KB.  With rows
  *   the kernel streams 3K ranges; measured bandwidth then depends on the physical placement the
  *   allocation happens to get (about 61 % or 73 % of peak for a 53 GB state).
@@ -343,7 +345,7 @@ int gbmuf_state_copy(const gbmuf_plan_t *plan, const gbmuf_state_t *dst, const g
  * (a multiple of 4; both pointers device memory, 16-byte aligned, not overlapping) with
  * one read and one write per byte.  It gives hardware byte counters a launch of known
  * traffic (4 * n_floats bytes read, 4 * n_floats written).  Its grid strides over the words; one word per
- * thread, as gbmuf_state_copy runs, is faster (MI355X: 4.6 against 5.8 to 6.1 TB/s).  flags: bit 0 = streaming stores, bit 1 = streaming loads.
+ * thread, as gbmuf_state_copy runs, is faster (MI355X: 4.6 TB/s against 5.6 to 6.8, by the two placements).  flags: bit 0 = streaming stores, bit 1 = streaming loads.
  */
 int gbmuf_probe_copy(float *dst_dev, const float *src_dev, int64_t n_floats, int32_t flags,
                      void *stream);

@@ -261,7 +261,7 @@ bool shared_wide(int K, int size)
 }
 
 // Rows that share lines, beyond the caches: 3K address streams, of which each access touches one line more than it needs.  All wide
-// shapes end within 5 % of each other: 5.4 TB/s with 4 workers, 5.1 with 16 and 4.9 from 64 on.
+// shapes end within 5 % of each other: 5.4 TB/s with 4 workers, 5.1 to 5.8 with 16, by placement, and 4.9 from 64 on.
 //   BMUF: up to 2 workers 512 x 2, one per CU (2 x 350 M 3069 us, 256 x 1 3250), up to 16 1024 x 1 where K rows fill its slots (8 x 75 M 2735,
 //     kSixtyFour 2870; 16 x 37.5 M 2819 / 2873), and with 3 workers (3 x 233 M 3132, 512 x 1 3179), else 512 x 1 (6 x 33 M
 //     914, kSixtyFour 931; 12 x 16.7 M 927 / 938), up to 64 kSixtyFour (32 x
@@ -298,24 +298,27 @@ Variant shared_variant(int K, int what, int size, bool few)
 // of K and is what came out best or within 1 to 3 % of it in sweeps of all built-in shapes, bounds and runs on K = 2 .. 400,
 // 1 M .. 1.5 G values; TB/s of the rule, then the nearest rival.
 //   Tiny and small launches want many tiles: up to 64 workers as few slots as give tiles of 8 columns and more (64 workers, 1 M values
-//     5.6 us, 1024 slots 5.9, 4096 9.5; 3 M 12.7, 13.0, 14.4).
+//     5.6 us, 1024 slots 5.9, 4096 9.5; 3 M 12.7, 13.0, 14.4). Of more workers small ones stream omega and Delta (kMany: 128 x 20 K 10.9, 1024 x 4 12.1; 200 x 24 K 18.8, 20.2); tiny ones
+//     do not, which would be 6 to 16 % faster up to 512 workers and 8 to 15 % slower for 600 (128 x 9 K 9.7, 1024 x 4 11.3; 600 x 2.3 K 16.3, 13.9).
 //   Blocked state is one stretch of memory, and every tile shape that keeps 512 bytes to 1 KB of a row together is fast: 6.7 to 6.85
 //     up to 64 workers.  An XCD takes 1 KB of each row in one run (xcd 6): 8 x 300 M / 8 1045 us, tile by tile 1065; from 33 to 128
 //     workers, and beyond the caches up to 256 and above 512, one tile, and these move on from block to block (rotate), without which an
 //     XCD sees the same addresses modulo 4 KB in every block: 64 x 23.4 M 5356 us, not rotated 5425 (1 KB) and more; 160 x 1.9 M 1091, 1100; but 257 to 512,
 //     whose tiles hold 256 bytes of a row (300 x 1 M 1244, one tile moving on 1314; 400 x 1.8 M 2976 / 3129),
 //     481 to 512 in tiles of 128 bytes, which they fill, and runs of 4 KB (512 x 0.6 M 1378, kVeryMany 1411).
-//     No bound of the residency helps above 4 workers; up to 2 three per CU (2 x 300 M 2165 us, six 2517).  Up to 8 workers 256 x 1, 9-16 512 x 1 where K rows fill its
+//     No bound of the residency helps above 4 workers; up to 2 three per CU (2 x 300 M 2165 us, six 2517), 3 and 4 six
+//     (3 x 333 M 3511, four 3727, unbounded 3553; 4 x 250 M 3554, 3492, 3562).  Up to 8 workers 256 x 1, 9-16 512 x 1 where K rows fill its
 //     slots to 7/8, else 256 x 2, whose threads idle in whole slots (12 x 25 M 1051 us; 512 x 1 1080), 17-32 512 x 2, 33-64 kSixtyFour (40 x
-//     7.5 M 1072 us, 512 x 4 1057; 64 x 4.7 M 1070, 512 x 4 1085), 65-128 kMany, 129-512 kVeryMany (200 x 1.5 M 1167, kMany 1185;
-//     256 x 1.2 M 1156, kSixtyFour 1165; 300 x 1 M 1245, kMany 1206), up to 20 M values kSixtyFour (200 x 0.1 M 84 us, kMany 88).
+//     7.5 M 1070 us, 512 x 4 1092; 44 x 9.1 M 1422, 1459; 64 x 4.7 M 1070, 1085), 65-128 kMany, above kVeryMany (160 x 1.9 M 1092, kMany
+//     1290; 300 x 1 M 1244, 1250; 300 x 4.3 M 5467, 5737), 5 to 20 M values kSixtyFour (200 x 0.1 M 84 us, kMany 88).
 //   Aligned rows are 3K address streams: 5.9 up to 8 workers, 5.1 from 64 on, whatever the shape.  Wide tiles, and 4 KB
 //     of a row per XCD from 129 workers on, from 17 up to 20 M values; beyond that fewer take tile by tile (25 to 480 M values of 33 to 128
 //     workers within 2 % of the best of all shapes and walks, 4 KB 2 to 10 %: 64 x 4.7 M 1414 us, 1624).  2-4 256 x 1, four per CU (4 x
 //     62.5 M 987 us; unbounded 1034), up to 20 M values also 5-8 (8 x 0.75 M 21.9 us, 1024 x 1 22.5; 5 x 1.6 M 30.9, 34.7), beyond 1024 x 1 (8 x 87.5 M 2852; kSixtyFour 2900, 512 x 1 2998), 9-32 kSixtyFour (32 x 7.8 M 1136; 1024 x 2
-//     1152), 33-128 512 x 4 (64 x 1.6 M 472, kVeryMany 483; 48 x 5.2 M 1158 / 1136; 96 x 2.6 M 1167, 1024 x 4 1223), above 500 M values
+//     1152), 33-128 512 x 4 (48 x 5.2 M 1155, kVeryMany 1147; tiles of half the size within 1 % too), above 500 M values
 //     kVeryMany (48 x 14.6 M 3204, 512 x 4 3273; 88 x 22.7 M 7895, 1024 x 4 8075), above 128 workers kVeryMany (300 x 0.8 M 1209, 4 KB per XCD
-//     not taken 1259).  5 to 20 M values of more than 32 workers: 1024 x 4.
+//     not taken 1259).  5 to 20 M values of more than 32 workers: 1024 x 4; of up to 2 workers 512 x 1 as for small launches (1 x 12 M 49.9, 256 x 1 51.3; 2 x 9.5 M
+//     81.2 / 79.3).
 //   Gossip-MA has a third of the loads and takes more slots per thread.  Blocked: up to 2 workers 256 x 1, but 2 of
 //     more than 500 M values 512 x 2, two per CU (2 x 650 M 1610 us, 256 x 1 1817), 4 512 x 2 (4 x 175 M 848, 256 x 2 898; two per CU 837, but 4 x 5.2 M 6 %
 //     more), up to 16 256 x 2 where K rows
@@ -642,8 +645,8 @@ constexpr int64_t kLeastGroups = 4;
 
 // Whether rows or blocks start inside 128-byte lines, so that neighbouring tiles share lines: unless both are taken by one XCD its
 // L2 cannot join the halves, and every shared line is fetched twice and written in two pieces.  One XCD takes 32 KB of a
-// row then, and one line in 256 is shared.  16 workers x 35.0 M in plain tensors: 3944 GB/s at 512 B, 4984 at 4 KB, 5073 at
-// 16 KB (aligned rows: 5161); 64 workers x 26.9 M: 3880 at 1 KB, 4405 at 4 KB, 5163 at 32 KB.  (The stride of a single
+// row then, and one line in 256 is shared.  16 workers x 35.0 M in plain tensors, an earlier kernel: 3944 GB/s at 512 B, 4984 at 4 KB, 5073 at
+// 16 KB; 64 workers x 26.9 M: 3880 at 1 KB, 4405 at 4 KB, 5163 at 32 KB.  (The stride of a single
 // worker is no distance between rows: 1 x 600 M, odd stride, 2497 us; by 32 KB 2694.)
 bool shares_lines(const Placement &at, const gbmuf_state_t *st, int32_t mode, int K)
 {
@@ -687,7 +690,8 @@ int average_waves(double n, int aim)
 //     blocked 15.8, 16.7; 48 x 0.44 M blocked 14.2, 13.6; from 25 M on 2 to 13 % the other way).  More waves hide their latency, with enough
 //     rows per thread that few workers take one pass: 8 x 4.2 M padded 25 (16 rows x 3 waves 33), 1024 x 36 K 66 (8 rows 87).
 //     More than 64 workers up to 35 M (300 x 83 K 22.7, streamed 24.0).
-//   beyond, streamed: 8 x 25 M blocked 127, plain 145; 64 x 15.6 M padded 607, plain 674.  Up to 60 M, and where rows are of up
+//   beyond, streamed: 8 x 25 M blocked 127, plain 145; 64 x 15.6 M padded 607, plain 674; also rows that share lines, of which nothing is written (8 x
+//     5 M odd rows 30.4, plain 32.5; 200 x 1.5 M 179, 191).  Up to 60 M, and where rows are of up
 //     to 4 workgroups per CU, without bound and with 16 rows of more than 64 workers in flight (1024 x 195 K 122, 4 rows x 6 waves 157).
 //   one worker is a copy: 590 M 746, 16 waves 770, 8 waves 1303.
 //   larger sums take 4 rows at a time, and the fewer waves the more workers there are, above 16 by the workgroups too

@@ -468,7 +468,7 @@ struct WholeTile {
         for (int n = 0; n < SLOTS; ++n)
             if (used(n)) th[n] = load4<POL>(a.theta + at(n));
         // kSixtyFour: omega and Delta on top of theta would be more in flight per CU than HBM takes best.  64 workers x 57.8 M
-        // in components of 1 M, blocked: 13350 us, all at once 13515; 16 x 35.0 M odd rows 2330 / 2436.  With more than 4 neighbours the
+        // in components of 1 M, blocked: 13350 us, all at once 13515.  With more than 4 neighbours the
         // registers leave one workgroup per CU, which needs all of them in flight.
         if (DEPTH == 1 && SLOTS == 2 && Q1 >= 1 && Q1 <= 5) __builtin_amdgcn_s_waitcnt(0x0F70);     // vmcnt(0)
         if constexpr (DEPTH == SLOTS) {
