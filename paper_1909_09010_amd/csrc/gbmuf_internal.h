@@ -10,14 +10,18 @@ namespace gbmuf {
 
 // One workgroup's share of a sync: elements [lo, lo + n) of component `comp`, for all K
 // workers.  The range never crosses a component boundary and lies inside one run of
-// tile_columns 16-byte columns (a column is 4 elements whose first index is a multiple of 4).  q is the number of
-// neighbours this component draws.
+// tile_columns 16-byte columns (a column is 4 elements whose first index is a multiple of 4).  The low bits of q are the number
+// of neighbours this component draws, the two above (kTileKind) say whether the tile's n = 4 * tile_columns elements lie side by side
+// or in stretches of 2^kLogStretch columns, pairs of which are 2^kLogApart columns from each other (tile_kernel).
 struct TileDesc {
     int64_t lo;
     uint16_t n;
     uint16_t q;
     int32_t comp;
 };
+constexpr int kTileKind = 14;            // the bit of q where the kind begins
+enum : int { kOneStretch = 0, kApartWide = 1, kApartNarrow = 2 };
+constexpr int kLogStretch = 5, kLogApart = 11;     // 512 bytes, 32 KB
 static_assert(sizeof(TileDesc) == 16, "one 16-byte load per workgroup");
 
 // Per-component constants on the device.
@@ -147,6 +151,7 @@ struct TileArgs {
     TileDesc *out;
     int64_t n;               // tiles
     int32_t m, logT;
+    int32_t apart;           // whole tiles lie in stretches
 };
 
 // gbmuf_kernels.hip

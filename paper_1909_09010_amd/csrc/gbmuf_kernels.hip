@@ -59,6 +59,14 @@ __global__ void sample_kernel(SampleArgs a)
 // start, not from the component start: with rows aligned to T*16 bytes every interior tile then covers whole
 // cache lines (a component that starts mid-line only gets a short first tile), and no tile
 // crosses a block of a blocked state.  Tiles that straddle lines cost a quarter of the bandwidth on MI355X.
+//
+// With `apart` (aligned rows, see tiles_apart on the host) the whole tiles of a component are dealt anew among as many: 64 tiles, or the 64 KB
+// worth of tiles that are left, share the columns they cover in stretches of 512 bytes.  A tile's stretches lie in pairs
+// 32 KB apart, so that each instruction of a wave, 1 KB, accesses both of a pair; the pairs follow each other every 64 KB (64 tiles), or are spread
+// evenly over 32 KB (64 KB of tiles).  HBM takes such writes better, it seems because a memory page holds the same 512 bytes of
+// neighbouring 32 KB.  16 or 32 rows in turns of 4 KB, in-place: 5.8, 5.7 TB/s, with 4 stretches 32 KB apart 6.5, 6.1, with whole runs of 64 KB in one row 6.3, 6.4;
+// reads alone 7.5 whatever the order.  Stretches of 256 bytes or 1 KB and distances of 8, 16, 64 or 128 KB gain nothing in the fused kernel, nor do pairs of
+// different waves.
 // ---------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void tile_kernel(TileArgs a)
 {
@@ -72,8 +80,22 @@ __global__ __launch_bounds__(256) void tile_kernel(TileArgs a)
     }
     const int64_t begin = a.off[lo], end = a.off[lo + 1], T = static_cast<int64_t>(1) << a.logT;
     const int64_t g = ((begin >> 2) >> a.logT) + (i - a.start[lo]);
-    const int64_t first = max(g * T * 4, begin), last = min((g + 1) * T * 4, end);
-    a.out[i] = TileDesc{first, static_cast<uint16_t>(last - first), static_cast<uint16_t>(a.comp[lo].q), lo};
+    int64_t first = max(g * T * 4, begin);
+    const int64_t last = min((g + 1) * T * 4, end), n = last - first;
+    int kind = kOneStretch;
+    if (a.apart) {
+        const int64_t whole = (begin + 4 * T - 1) >> (a.logT + 2), wholes = max((end >> (a.logT + 2)) - whole, int64_t{0}), j = g - whole;
+        const int64_t wide = wholes >> 6 << 6, narrow = 1 << (kLogApart + 1 - a.logT), left = (wholes - wide) / narrow * narrow;
+        if (j >= 0 && j < wide) {
+            first = ((whole + (j >> 6 << 6)) * T + ((j & 63) << kLogStretch)) * 4;
+            kind = kApartWide;
+        } else if (j >= wide && j < wide + left) {
+            const int64_t in = (j - wide) % narrow;
+            first = ((g - in) * T + (in << kLogStretch)) * 4;
+            kind = kApartNarrow;
+        }
+    }
+    a.out[i] = TileDesc{first, static_cast<uint16_t>(n), static_cast<uint16_t>(a.comp[lo].q | kind << kTileKind), lo};
 }
 
 // ---------------------------------------------------------------------------------------

@@ -21,6 +21,7 @@ namespace {
 // Work list of the fused kernel for one tile width, in component order.
 struct TileSet {
     int32_t logT = 0;
+    bool apart = false;                // see tile_kernel
     std::vector<int64_t> tile_start;   // m+1: first tile of every component, and how many there are
     TileDesc *d_tiles = nullptr;       // in gbmuf_plan_s::d_tiles
 };
@@ -34,6 +35,7 @@ struct LayoutCfg {
     int32_t workgroups_per_cu = 0;     // 0 = no bound
     int32_t xcd_columns_log = 0;       // log2 of the columns of a row that one XCD takes in one run (if more than a tile)
     bool rotate = false;               // see tile_of_block
+    bool apart = false;                // see tile_kernel
 };
 
 // kShared: rows of which some start inside a 128-byte line, so that neighbouring tiles share lines.
@@ -311,20 +313,20 @@ Variant shared_variant(int K, int what, int size, bool few)
 //     slots to 7/8, else 256 x 2, whose threads idle in whole slots (12 x 25 M 1051 us; 512 x 1 1080), 17-32 512 x 2, 33-64 kSixtyFour (40 x
 //     7.5 M 1070 us, 512 x 4 1092; 44 x 9.1 M 1422, 1459; 64 x 4.7 M 1070, 1085), 65-128 kMany, above kVeryMany (160 x 1.9 M 1092, kMany
 //     1290; 300 x 1 M 1244, 1250; 300 x 4.3 M 5467, 5737), 5 to 20 M values kSixtyFour (200 x 0.1 M 84 us, kMany 88).
-//   Aligned rows are 3K address streams: 5.9 up to 8 workers, 5.1 from 64 on, whatever the shape.  Wide tiles, and 4 KB
-//     of a row per XCD from 129 workers on, from 17 up to 20 M values; beyond that fewer take tile by tile (25 to 480 M values of 33 to 128
-//     workers within 2 % of the best of all shapes and walks, 4 KB 2 to 10 %: 64 x 4.7 M 1414 us, 1624).  2-4 256 x 1, four per CU (4 x
-//     62.5 M 987 us; unbounded 1034), up to 20 M values also 5-8 (8 x 0.75 M 21.9 us, 1024 x 1 22.5; 5 x 1.6 M 30.9, 34.7), beyond 1024 x 1 (8 x 87.5 M 2852; kSixtyFour 2900, 512 x 1 2998), 9-32 kSixtyFour (32 x 7.8 M 1136; 1024 x 2
-//     1152), 33-128 512 x 4 (48 x 5.2 M 1155, kVeryMany 1147; tiles of half the size within 1 % too), above 500 M values
-//     kVeryMany (48 x 14.6 M 3204, 512 x 4 3273; 88 x 22.7 M 7895, 1024 x 4 8075), above 128 workers kVeryMany (300 x 0.8 M 1209, 4 KB per XCD
-//     not taken 1259).  5 to 20 M values of more than 32 workers: 1024 x 4; of up to 2 workers 512 x 1 as for small launches (1 x 12 M 49.9, 256 x 1 51.3; 2 x 9.5 M
-//     81.2 / 79.3).
+//   Aligned rows are 3K address streams: 6.4 with 4 workers, 5.8 with 32, 5.5 with 128, in tiles whose stretches lie 32 KB apart (tiles_apart), the more of them
+//     the better until one tile is all that a CU holds.  1, 2 and 4 256 x 2, two per CU (4 x 112 M 1670 us; 1024 x 1 1670, 256 x 1 1720), 3 512 x 1 (3 x 8.3 M 94.6;
+//     256 x 1 98.3; kSixtyFour 94.8, but 96.9 in 87 components, whose ends cut its wide tiles, 512 x 1 94), 5-8 kSixtyFour (8 x 56 M 1693, 1024 x 2 1706), 9-32 kMany (24 x 42 M 4014, 1024 x 4 4039, kSixtyFour 4536; 16 x 28 M 1779,
+//     kSixtyFour 1744), 33-128 kVeryMany (48 x 21 M 4240, 1024 x 4 4252; 64 x 15.6 M 4206, kMany 4298), tile by tile (64 x 15.6 M 4206, 4 KB
+//     per XCD 4288), above 128 too, where a stretch is all of a tile and 4 KB of a row go to one XCD (300 x 0.8 M 1209, tile by tile 1259).
+//     5 to 20 M values: up to 8 256 x 1, four per CU (2 x 6 M 46.8 us, 512 x 1 47.1; 8 x 0.75 M 21.9, 1024 x 1 22.5; 5 x 1.6 M 30.9, 34.7), up to 32 kSixtyFour (16 x 0.75 M 50.7,
+//     256 x 4 52.3), above 1024 x 4 (40 x 0.3 M 55.2, kMany 55.9), 4 KB per XCD from 17 on.
 //   Gossip-MA has a third of the loads and takes more slots per thread.  Blocked: up to 2 workers 256 x 1, but 2 of
 //     more than 500 M values 512 x 2, two per CU (2 x 650 M 1610 us, 256 x 1 1817), 4 512 x 2 (4 x 175 M 848, 256 x 2 898; two per CU 837, but 4 x 5.2 M 6 %
 //     more), up to 16 256 x 2 where K rows
 //     fill it to 7/8 (8 x 75 M 723 us; 512 x 2 748), and 5 and 6 (5 x 140 M 923, 256 x 4 1050; 6 x 50 M 362 / 402), else 256 x 4, up to 32 256 x 4 (725; 512 x 2 735), 33-64 512 x 4, above 1024 x 4, large of
-//     more than 256 workers kVeryMany (300 x 2 M 947; 956).  Rows: up to 8 256 x 2, up to 24 256 x 4, up to 64 1024 x 4, above
-//     kVeryMany (300 x 2 M 1003; 1024 x 4 1089).  5 to 20 M values: 256 x 2 up to 64 workers, up to 128 512 x 2.
+//     more than 256 workers kVeryMany (300 x 2 M 947; 956).  Rows, in stretches: up to 8 512 x 2 where K rows fill 1024 slots to 7/8 (4 x 100 M 481, 512 x 4 488), 3 256 x 4
+//     (3 x 133 M 480), up to 24 512 x 4 (12 x 33 M 499, 512 x 2 513; 6 x 17 M 124, 512 x 2 129), up to 32 kMany (32 x 12.5 M 528, 512 x 4 545), above kVeryMany (64 x 15.6 M 1340, kMany 1379; 300 x 2 M 1003,
+//     1024 x 4 1089).  5 to 20 M values: 256 x 2 up to 64 workers, up to 128 512 x 2.
 void aligned_shape(int K, int layout, int what, int size, bool few, LayoutCfg &cfg)
 {
     Variant &v = cfg.variant;
@@ -341,11 +343,17 @@ void aligned_shape(int K, int layout, int what, int size, bool few, LayoutCfg &c
             if (K == 2) bound = 2;
         }
         else if (blocked && K <= 2) find_variant(256, 1, &v);
-        else if (blocked ? K == 5 || K == 6 || (K <= 16 && fills(512)) : K <= 8) find_variant(256, 2, &v);
-        else if (K <= (blocked ? 32 : 24)) find_variant(256, 4, &v);
-        else if (blocked && K <= 64) find_variant(512, 4, &v);
-        else if (few && (blocked ? K > 512 || (K > 256 && size == kLarge) : K > 64)) v = kVeryMany;
-    } else if (size <= kSmall || (!blocked && K <= 2 && size == kCompact)) {
+        else if (!blocked) {
+            if (K == 3) find_variant(256, 4, &v);
+            else if (K <= 24) find_variant(512, K <= 8 && fills(1024) ? 2 : 4, &v);
+            else if (K <= 32) v = kMany;
+            else if (few) v = kVeryMany;
+        }
+        else if (K == 5 || K == 6 || (K <= 16 && fills(512))) find_variant(256, 2, &v);
+        else if (K <= 32) find_variant(256, 4, &v);
+        else if (K <= 64) find_variant(512, 4, &v);
+        else if (few && (K > 512 || (K > 256 && size == kLarge))) v = kVeryMany;
+    } else if (size <= kSmall) {
         if (K <= 64) find_variant(K <= 16 && (blocked || K > 2) ? 256 : 512, 1, &v);
         else if (size == kSmall) v = kMany;
     } else if (blocked) {
@@ -361,21 +369,25 @@ void aligned_shape(int K, int layout, int what, int size, bool few, LayoutCfg &c
         else v = kMany;
         if (K <= 4) bound = K <= 2 ? 3 : 6;
     } else {
-        const bool small = K <= 4 || (K <= 8 && size == kCompact);
-        if (small) find_variant(256, 1, &v);
-        else if (K <= 8) find_variant(1024, 1, &v);
-        else if (K <= 32) v = kSixtyFour;
-        else if (size == kCompact) v = Variant{1024, 4, 4};
-        else if (K <= 128 && size != kLarge) find_variant(512, 4, &v);
-        else if (few) v = kVeryMany;
-        if (small) bound = 4;
+        if (size == kCompact) {
+            if (K <= 8) find_variant(256, 1, &v);
+            else if (K <= 32) v = kSixtyFour;
+            if (K <= 8) bound = 4;
+        } else {
+            if (K <= 2 || K == 4) find_variant(256, 2, &v);
+            else if (K == 3) find_variant(512, 1, &v);
+            else if (K <= 8) v = kSixtyFour;
+            else if (K <= 32) v = kMany;
+            else if (few) v = kVeryMany;
+            if (K <= 2 || K == 4) bound = 2;
+        }
     }
     if (size <= kSmall) return;
     if (blocked) {
         cfg.rotate = K > 32 && (what == kMa || K <= 128 || (size != kCompact && (K <= 256 || K > 512)));
         run = cfg.rotate ? 0 : K > 480 && K <= 512 && size != kCompact ? 8 : 6;
     } else {
-        run = K > (size == kCompact || what == kMa ? 16 : 128) ? 8 : 0;
+        run = K > (size == kCompact ? 16 : 128) ? 8 : 0;
     }
 }
 // Small plans with rows of more than 7 neighbours draw them through LDS in every workgroup (launch_bound), a thread a
@@ -419,6 +431,15 @@ int32_t named_workgroups_per_cu(int K, int layout, int what)
 int choose_policy(int layout, int size, int logT, int hints)
 {
     return layout != kShared && logT >= 3 && (size != kTiny || hints != 0) ? kStreamed : kPlain;
+}
+
+// Whether a launch's tiles lie in stretches 32 KB apart (tile_kernel): aligned rows whose tiles hold 64 columns and more.  us on rows padded to 4 KB, the
+// shapes of aligned_shape, stretches / side by side: 8 x 25 M 750 / 794 (the best shape of those side by side), 16 x 12.5 M 804 / 851, 32 x 6.2 M 828 / 905,
+// 64 x 15.6 M 4206 / 4652, 128 x 7.8 M 4384 / 4771; gossip-MA 16 x 62 M 1270 / 1276, 64 x 15.6 M 1340 / 1455.  Up to 5 M values all comes from the caches (2 x 3 M 21.2
+// / 21.9, 32 x 0.19 M 21.3 / 21.4).  Blocks of 32 KB have the pairs by themselves: a wave takes neighbouring workers' blocks.
+bool tiles_apart(int layout, int size, int logT, bool named)
+{
+    return layout == kRows && !named && size >= kCompact && logT > kLogStretch && logT <= kLogApart;
 }
 
 // Tiles of a component [a, b) at T columns each.
@@ -544,7 +565,7 @@ int make_device_state(gbmuf_plan_s &pl, int32_t sampling)
         ts.d_tiles = next;
         next += ts.tile_start.back();
         rc = launch_tiles(TileArgs{pl.d_starts, pl.d_starts + static_cast<int64_t>(s + 1) * (pl.m + 1), pl.d_comp, ts.d_tiles,
-                                   ts.tile_start.back(), pl.m, ts.logT}, nullptr);
+                                   ts.tile_start.back(), pl.m, ts.logT, ts.apart ? 1 : 0}, nullptr);
         if (rc != GBMUF_OK) return rc;
     }
     err = hipStreamSynchronize(nullptr);                   // calls may come on any stream
@@ -934,6 +955,7 @@ int gbmuf_plan_create(gbmuf_plan_t **out, const gbmuf_plan_desc_t *desc)
                 }
                 cfg.logT = widest_tile(cfg.variant, K);
                 cfg.policy = choose_policy(layout, size, cfg.logT, desc->cache_hints);
+                cfg.apart = tiles_apart(layout, size, cfg.logT, pl->named_shape);
                 if (desc->workgroups_per_cu != 0) cfg.workgroups_per_cu = desc->workgroups_per_cu;
             }
             if (rc == GBMUF_OK) {
@@ -944,10 +966,11 @@ int gbmuf_plan_create(gbmuf_plan_t **out, const gbmuf_plan_desc_t *desc)
                     LayoutCfg &cfg = pl->cfg[layout][what][size];
                     int found = -1;
                     for (int s2 = 0; s2 < pl->n_sets; ++s2)
-                        if (pl->sets[s2].logT == cfg.logT) found = s2;
+                        if (pl->sets[s2].logT == cfg.logT && pl->sets[s2].apart == cfg.apart) found = s2;
                     if (found < 0) {
                         found = pl->n_sets++;
                         pl->sets[found].logT = cfg.logT;
+                        pl->sets[found].apart = cfg.apart;
                         build_tiles(*pl, pl->sets[found]);
                     }
                     cfg.set = found;

@@ -78,15 +78,21 @@ __device__ __forceinline__ unsigned tile_of_block(const SyncArgs &a)
     return b - rest < whole ? in_group : alone;                   // backwards b < rest wraps to beyond whole
 }
 
-__device__ __forceinline__ TileDesc load_tile(const TileDesc *p)
+struct Tile {
+    int64_t lo;
+    int32_t n, q, comp, kind;
+};
+
+__device__ __forceinline__ Tile load_tile(const TileDesc *p)
 {
     typedef uint32_t v4u __attribute__((ext_vector_type(4)));
     const v4u v = *reinterpret_cast<const v4u *>(p);
     uint32_t w[4] = {v[0], v[1], v[2], v[3]};
 #pragma unroll
     for (int i = 0; i < 4; ++i) hold(w[i]);                       // else it is taken apart into loads of each field
-    return TileDesc{static_cast<int64_t>(w[0] | (static_cast<uint64_t>(w[1]) << 32)), static_cast<uint16_t>(w[2] & 0xFFFFu),
-                    static_cast<uint16_t>(w[2] >> 16), static_cast<int32_t>(w[3])};
+    return Tile{static_cast<int64_t>(w[0] | (static_cast<uint64_t>(w[1]) << 32)), static_cast<int32_t>(w[2] & 0xFFFFu),
+                static_cast<int32_t>((w[2] >> 16) & ((1u << kTileKind) - 1u)), static_cast<int32_t>(w[3]),
+                static_cast<int32_t>(w[2] >> (16 + kTileKind))};
 }
 
 // ---------------------------------------------------------------------------------------
@@ -143,12 +149,12 @@ struct LdsRow {
 template <int NT, int Q1>
 struct Rows {
     int32_t v[Q1];
-    __device__ __forceinline__ void begin(const SyncArgs &a, const TileDesc &td)
+    __device__ __forceinline__ void begin(const SyncArgs &a, const Tile &td)
     {
         const int q = Q1 == kUpTo8 ? td.q : Q1 - 1;
         if (a.nbr != nullptr && static_cast<int>(threadIdx.x) < a.K) load_row<Q1>(v, a, td.comp, threadIdx.x, q);
     }
-    __device__ __forceinline__ void put(const SyncArgs &a, const TileDesc &td, uint16_t *ids, int w, int q)
+    __device__ __forceinline__ void put(const SyncArgs &a, const Tile &td, uint16_t *ids, int w, int q)
     {
         if (a.nbr != nullptr) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -167,7 +173,7 @@ struct Rows {
         }
         put_row<Q1>(ids + w * ids_pitch(Q1, 0), v, w, q);
     }
-    __device__ __forceinline__ void finish(const SyncArgs &a, const TileDesc &td, uint16_t *ids)
+    __device__ __forceinline__ void finish(const SyncArgs &a, const Tile &td, uint16_t *ids)
     {
         const int K = a.K, q = Q1 == kUpTo8 ? td.q : Q1 - 1, first = threadIdx.x;
         if (first < K) put(a, td, ids, first, q);
@@ -185,8 +191,8 @@ struct Rows {
 // registers: 232), gossip-MA 10 x 6 M 110 / 182 (91); 20 neighbours, 24 x 2.5 M 287 / 412.
 template <int NT>
 struct Rows<NT, kAnyQ> {
-    __device__ __forceinline__ void begin(const SyncArgs &, const TileDesc &) {}
-    __device__ __forceinline__ void finish(const SyncArgs &a, const TileDesc &td, uint16_t *ids)
+    __device__ __forceinline__ void begin(const SyncArgs &, const Tile &) {}
+    __device__ __forceinline__ void finish(const SyncArgs &a, const Tile &td, uint16_t *ids)
     {
         const int K = a.K, q = td.q, pitch = ids_pitch(kAnyQ, a.q);
         const int32_t *table = a.nbr + static_cast<int64_t>(td.comp) * K * a.q;
@@ -297,7 +303,7 @@ __device__ __forceinline__ v4f average(const v4f *tile, const uint16_t *row, int
 // the same wn, cn for all threads: with T <= NT a thread keeps its column and visits every (NT/T)-th worker, with T > NT (few
 // workers in a wide shape) slot n is one stretch of one worker's row.
 template <int NT, int SLOTS, int Q1>
-__device__ __forceinline__ void do_tile(const SyncArgs &a, const TileDesc &td, v4f *tile, uint16_t *ids)
+__device__ __forceinline__ void do_tile(const SyncArgs &a, const Tile &td, v4f *tile, uint16_t *ids)
 {
     const int tid = threadIdx.x, K = a.K, logT = a.logT, T = 1 << logT, mode = a.mode;
     const float inv = (a.flags & kFlagMixedQ) ? a.comp[td.comp].inv : a.inv;
@@ -366,22 +372,25 @@ __device__ __forceinline__ void do_tile(const SyncArgs &a, const TileDesc &td, v
 // Where all arrays are in flight at once the slots beyond the N that hold rows are left out; where omega and Delta are
 // streamed, blocks of DEPTH slots are left out in front, so that the stream ends in the same slots for any K.  A thread
 // that has no row in a slot loads the tile's first column of row K - 1, one line for the whole wave, and stores nothing.
+// Bits 5 and up of a column's number say where its stretch lies in the row if the tile has several (tile_kernel).
 // CUT (T <= NT): component edges cut the tile, which is not thin.  A column that is not the tile's at all is treated like a missing row.
 // Of a cut column the four floats nearest to it that are the tile's are loaded and moved, and its own are stored one by one (cut_column).
 template <int NT, int SLOTS, int DEPTH, int Q1, int POL, bool MA, bool CUT>
 struct WholeTile {
+    static constexpr bool APART = POL == kStreamed && !CUT;       // only streamed launches have such tiles
     const SyncArgs &a;
-    const TileDesc &td;
+    const Tile &td;
     v4f *tile;
     uint16_t *ids;
     int N, skipped, w0, col0;                                     // slots with rows; DEPTH < SLOTS: the first slot that is used
+    int apart, beyond;                                            // where in a row bit 5 of a column's number goes, and those above it
     int64_t col_at, spare;                                        // where the thread's first column lies in row 0; what is loaded without a row
     float inv;
     unsigned mine;                                                // CUT: which floats of the thread's column are the tile's
     int from;                                                     // CUT: where its load starts, counted from it
     v4f om[DEPTH], de[DEPTH];
 
-    __device__ __forceinline__ WholeTile(const SyncArgs &args, const TileDesc &desc, v4f *lds, uint16_t *rows)
+    __device__ __forceinline__ WholeTile(const SyncArgs &args, const Tile &desc, v4f *lds, uint16_t *rows)
         : a(args), td(desc), tile(lds), ids(rows) {}
     __device__ __forceinline__ int worker(int n) const { return w0 + (((n - skipped) * NT) >> a.logT); }
     __device__ __forceinline__ int column(int n) const { return ((n - skipped) * NT) & ((1 << a.logT) - 1); }
@@ -393,7 +402,7 @@ struct WholeTile {
     }
     __device__ __forceinline__ int64_t at(int n) const
     {
-        const int64_t p = col_at + static_cast<int64_t>(worker(n)) * a.at.stride + 4 * column(n);
+        const int64_t p = col_at + static_cast<int64_t>(worker(n)) * a.at.stride + (APART ? column(n) >> 6 << (beyond + 2) : 4 * column(n));
         return (!may_lack(n) || worker(n) < a.K) && (!CUT || mine) ? p : spare;
     }
     // The floats of a column as they were loaded, in their places.
@@ -455,7 +464,13 @@ struct WholeTile {
         col0 = tid & (T - 1);
         w0 = tid >> a.logT;
         inv = (a.flags & kFlagMixedQ) ? a.comp[td.comp].inv : a.inv;
-        const int64_t first = td.lo & ~static_cast<int64_t>(3), e = first + 4 * col0;
+        int in_row = col0;
+        if (APART) {
+            apart = td.kind == kOneStretch ? kLogStretch : kLogApart;
+            beyond = td.kind == kOneStretch ? kLogStretch + 1 : td.kind == kApartWide ? kLogApart + 1 : kLogApart + 6 - a.logT;
+            in_row = (col0 & 31) | (((col0 >> 5) & 1) << apart) | (col0 >> 6 << beyond);
+        }
+        const int64_t first = td.lo & ~static_cast<int64_t>(3), e = first + 4 * in_row;
         const CutColumn cut = CUT ? cut_column(e, td.lo, td.n) : CutColumn{0xFu, 0};
         mine = cut.mine;
         from = cut.from;
@@ -496,7 +511,7 @@ struct WholeTile {
 // A cut tile of the streamed shapes whose columns are not loaded whole (is_thin): one column of one worker at a time, only those that
 // hold floats of the tile.  One or two as a rule, of which a thread has few: its first one's loads are all issued before the barrier.
 template <int NT, int Q1>
-__device__ __forceinline__ void thin_tile(const SyncArgs &a, const TileDesc &td, v4f *tile, uint16_t *ids)
+__device__ __forceinline__ void thin_tile(const SyncArgs &a, const Tile &td, v4f *tile, uint16_t *ids)
 {
     const float inv = (a.flags & kFlagMixedQ) ? a.comp[td.comp].inv : a.inv;
     const bool slots_too = a.mode != GBMUF_MODE_GOSSIP_MA;
@@ -550,7 +565,7 @@ __device__ __forceinline__ void thin_tile(const SyncArgs &a, const TileDesc &td,
 }
 
 template <int NT, int SLOTS, int DEPTH, int Q1, int POL>
-__device__ __forceinline__ void any_tile(const SyncArgs &a, const TileDesc &td, v4f *tile, uint16_t *ids)
+__device__ __forceinline__ void any_tile(const SyncArgs &a, const Tile &td, v4f *tile, uint16_t *ids)
 {
     // Cut tiles take plain accesses: they share lines, and a store that goes through the L2 is counted as under way until memory has
     // it, for which loads issued behind it wait (128 workers x 54 K in 9 components 50 us, with plain ones below 29).
@@ -593,7 +608,7 @@ __global__ __launch_bounds__(NT) void sync_kernel(SyncArgs a)
     uint32_t logB = static_cast<uint32_t>(a.at.logB);
     hold(logB);                                                   // fetched with the other arguments, not after the descriptor
     a.at.logB = static_cast<int32_t>(logB);
-    const TileDesc td = load_tile(a.tiles + tile_of_block(a));
+    const Tile td = load_tile(a.tiles + tile_of_block(a));
     if ((a.flags & kFlagCheckPeriods) && a.step % static_cast<uint64_t>(a.comp[td.comp].period) != 0)
         return;                                                   // not due: the whole workgroup leaves
     if constexpr (Q1 == kMixed) {

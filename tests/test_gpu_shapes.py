@@ -126,3 +126,21 @@ def test_cut_tiles_of_streamed_shapes(K, values, q, mode, place):
     q = q if np.ndim(q) == 0 else [q[i % len(q)] for i in range(len(off) - 1)]
     layout = {"narrow": "blocked", "odd": "separate"}.get(place, place)
     check(K, q, off, layout, mode, P | 1 if place == "odd" else None, narrow=place == "narrow")
+
+
+# Aligned rows, whose whole tiles are dealt in stretches 32 KB apart: 64 tiles of T columns (256 * T floats) at a time, then 64 KB (16384 floats) at a
+# time.  Components around both sizes, that begin on a tile, a float after and beside one; rows that begin on 4 KB and on a line; in both walks every float.
+@pytest.mark.parametrize("place", ["rows", "lines"])
+@pytest.mark.parametrize("values,mode", [(5_300_000, B.MODE_PAPER), (20_500_000, B.MODE_PAPER), (20_500_000, B.MODE_GOSSIP_MA)])
+@pytest.mark.parametrize("K,q", [(1, 0), (2, 1), (3, 2), (4, 1), (5, 2), (8, 3), (12, 5), (16, 4), (24, 9), (32, 2), (33, 3), (48, 8), (64, 5), (100, 1), (128, 3)])
+def test_tiles_in_stretches(K, q, values, mode, place):
+    P = values // K
+    pl = B.Plan([0, P], K, q, (q + 1) // 2 if q > 2 else 0)
+    wide, narrow, tile = 256 * pl.info.tile_columns, 16384, 4 * pl.info.tile_columns
+    pl.destroy()
+    off, at = [0, 5], 5
+    for n in (narrow - 1, narrow + tile, wide, wide + narrow + tile + 3, -1, wide, narrow - tile, -1, 1, wide + tile, 2 * wide - 1):
+        at = at + n if n > 0 else -(-at // tile) * tile       # -1: the next begins on a tile
+        off.append(at)
+    off = sorted({x for x in off if x < P} | {P})
+    check(K, q, off, "separate" if place == "lines" else place, mode, -(-P // 32) * 32 + 32 if place == "lines" else None)
