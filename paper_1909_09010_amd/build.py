@@ -9,8 +9,8 @@ import tempfile
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "libgbmuf.so")
-# (source, defines): the fused kernel's shapes are compiled in five parts, each with plain and with streamed accesses
-UNITS = [("gbmuf_sync.hip", [f"-DGBMUF_PART={i}", f"-DGBMUF_POLICY={j}"]) for i in (4, 3, 2, 0, 1) for j in (0, 1)] + [
+# (source, defines): the fused kernel's shapes are compiled in five parts, each with plain and streamed accesses and for tiles in stretches
+UNITS = [("gbmuf_sync.hip", [f"-DGBMUF_PART={i}", f"-DGBMUF_POLICY={j}"]) for i in (4, 3, 2, 0, 1) for j in (0, 1, 2)] + [
     ("gbmuf_plan.hip", []), ("gbmuf_kernels.hip", [])]
 
 # -ffp-contract=off: the method's fp32 arithmetic rounds every multiply and add separately.

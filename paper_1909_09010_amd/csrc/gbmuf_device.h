@@ -139,7 +139,7 @@ template <int POL>
 __device__ __forceinline__ v4f load4(const float *p)
 {
     const v4f_any *q = reinterpret_cast<const v4f_any *>(p);
-    if constexpr (POL == kStreamed) return __builtin_nontemporal_load(q);
+    if constexpr (POL != kPlain) return __builtin_nontemporal_load(q);
     else return *q;
 }
 
@@ -147,7 +147,7 @@ template <int POL>
 __device__ __forceinline__ void store4(float *p, v4f v)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
-    if constexpr (POL == kStreamed) {
+    if constexpr (POL != kPlain) {
         typedef unsigned v4u __attribute__((ext_vector_type(4)));
         typedef unsigned v4u_any __attribute__((ext_vector_type(4), aligned(4)));      // any 4-byte address, as above
         __builtin_amdgcn_global_store_b128((__attribute__((address_space(1))) v4u_any *)p, __builtin_bit_cast(v4u, v), "agent");

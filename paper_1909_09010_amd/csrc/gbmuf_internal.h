@@ -129,8 +129,11 @@ __host__ __device__ constexpr size_t ids_words(int K, int pitch)
 using KernelFn = void (*)(SyncArgs);
 
 // How the accesses of state use the caches (load4, store4): plainly, or loads that leave the L2 first and stores that go
-// through it at once.
-enum : int { kPlain = 0, kStreamed = 1 };
+// through it at once.  kApart: streamed, and whole tiles may lie in stretches (tile_kernel).  Kernels of their own, because what these take
+// is paid where no tile does: with the code for them in the streamed kernels those of gossip-MA waited for their neighbour table before
+// the first load of theta, and of what is then in flight some shapes have too little (blocked, us, apart / together: 5 x 380 M 2492 / 2685, 6 x 150 M
+// 1066 / 1127, 40 x 22 M 1068 / 1102).
+enum : int { kPlain = 0, kStreamed = 1, kApart = 2 };
 
 // The shapes of gbmuf_sync.hip in each part and policy, or nullptr.
 #define GBMUF_PICK_NAME2(part, policy) pick_kernel_##part##_##policy
@@ -138,6 +141,7 @@ enum : int { kPlain = 0, kStreamed = 1 };
 using PickFn = KernelFn(const Variant &v, int q, bool mixed);
 PickFn GBMUF_PICK_NAME(0, 0), GBMUF_PICK_NAME(1, 0), GBMUF_PICK_NAME(2, 0), GBMUF_PICK_NAME(3, 0), GBMUF_PICK_NAME(4, 0);
 PickFn GBMUF_PICK_NAME(0, 1), GBMUF_PICK_NAME(1, 1), GBMUF_PICK_NAME(2, 1), GBMUF_PICK_NAME(3, 1), GBMUF_PICK_NAME(4, 1);
+PickFn GBMUF_PICK_NAME(0, 2), GBMUF_PICK_NAME(1, 2), GBMUF_PICK_NAME(2, 2), GBMUF_PICK_NAME(3, 2), GBMUF_PICK_NAME(4, 2);
 
 // Remembers the most recent failing HIP call of this thread (what gbmuf_last_error_detail
 // returns) and maps it to a status.

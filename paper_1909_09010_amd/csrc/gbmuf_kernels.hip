@@ -297,9 +297,10 @@ constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 
 KernelFn pick_kernel(const Variant &v, int policy, int q, bool mixed)
 {
-    static constexpr PickFn *parts[2][5] = {
+    static constexpr PickFn *parts[3][5] = {
         {GBMUF_PICK_NAME(0, 0), GBMUF_PICK_NAME(1, 0), GBMUF_PICK_NAME(2, 0), GBMUF_PICK_NAME(3, 0), GBMUF_PICK_NAME(4, 0)},
-        {GBMUF_PICK_NAME(0, 1), GBMUF_PICK_NAME(1, 1), GBMUF_PICK_NAME(2, 1), GBMUF_PICK_NAME(3, 1), GBMUF_PICK_NAME(4, 1)}};
+        {GBMUF_PICK_NAME(0, 1), GBMUF_PICK_NAME(1, 1), GBMUF_PICK_NAME(2, 1), GBMUF_PICK_NAME(3, 1), GBMUF_PICK_NAME(4, 1)},
+        {GBMUF_PICK_NAME(0, 2), GBMUF_PICK_NAME(1, 2), GBMUF_PICK_NAME(2, 2), GBMUF_PICK_NAME(3, 2), GBMUF_PICK_NAME(4, 2)}};
     for (PickFn *pick : parts[policy])
         if (KernelFn k = pick(v, q, mixed)) return k;
     return nullptr;

@@ -956,6 +956,7 @@ int gbmuf_plan_create(gbmuf_plan_t **out, const gbmuf_plan_desc_t *desc)
                 cfg.logT = widest_tile(cfg.variant, K);
                 cfg.policy = choose_policy(layout, size, cfg.logT, desc->cache_hints);
                 cfg.apart = tiles_apart(layout, size, cfg.logT, pl->named_shape);
+                if (cfg.apart) cfg.policy = kApart;
                 if (desc->workgroups_per_cu != 0) cfg.workgroups_per_cu = desc->workgroups_per_cu;
             }
             if (rc == GBMUF_OK) {

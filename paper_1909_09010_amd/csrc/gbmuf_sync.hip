@@ -78,21 +78,18 @@ __device__ __forceinline__ unsigned tile_of_block(const SyncArgs &a)
     return b - rest < whole ? in_group : alone;                   // backwards b < rest wraps to beyond whole
 }
 
-struct Tile {
-    int64_t lo;
-    int32_t n, q, comp, kind;
-};
-
-__device__ __forceinline__ Tile load_tile(const TileDesc *p)
+// kApart: the tile's kind besides; other lists have none.
+template <int POL>
+__device__ __forceinline__ TileDesc load_tile(const TileDesc *p, int &kind)
 {
     typedef uint32_t v4u __attribute__((ext_vector_type(4)));
     const v4u v = *reinterpret_cast<const v4u *>(p);
     uint32_t w[4] = {v[0], v[1], v[2], v[3]};
 #pragma unroll
     for (int i = 0; i < 4; ++i) hold(w[i]);                       // else it is taken apart into loads of each field
-    return Tile{static_cast<int64_t>(w[0] | (static_cast<uint64_t>(w[1]) << 32)), static_cast<int32_t>(w[2] & 0xFFFFu),
-                static_cast<int32_t>((w[2] >> 16) & ((1u << kTileKind) - 1u)), static_cast<int32_t>(w[3]),
-                static_cast<int32_t>(w[2] >> (16 + kTileKind))};
+    kind = POL == kApart ? static_cast<int>(w[2] >> (16 + kTileKind)) : kOneStretch;
+    return TileDesc{static_cast<int64_t>(w[0] | (static_cast<uint64_t>(w[1]) << 32)), static_cast<uint16_t>(w[2] & 0xFFFFu),
+                    static_cast<uint16_t>(POL == kApart ? (w[2] >> 16) & ((1u << kTileKind) - 1u) : w[2] >> 16), static_cast<int32_t>(w[3])};
 }
 
 // ---------------------------------------------------------------------------------------
@@ -149,12 +146,12 @@ struct LdsRow {
 template <int NT, int Q1>
 struct Rows {
     int32_t v[Q1];
-    __device__ __forceinline__ void begin(const SyncArgs &a, const Tile &td)
+    __device__ __forceinline__ void begin(const SyncArgs &a, const TileDesc &td)
     {
         const int q = Q1 == kUpTo8 ? td.q : Q1 - 1;
         if (a.nbr != nullptr && static_cast<int>(threadIdx.x) < a.K) load_row<Q1>(v, a, td.comp, threadIdx.x, q);
     }
-    __device__ __forceinline__ void put(const SyncArgs &a, const Tile &td, uint16_t *ids, int w, int q)
+    __device__ __forceinline__ void put(const SyncArgs &a, const TileDesc &td, uint16_t *ids, int w, int q)
     {
         if (a.nbr != nullptr) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -173,7 +170,7 @@ struct Rows {
         }
         put_row<Q1>(ids + w * ids_pitch(Q1, 0), v, w, q);
     }
-    __device__ __forceinline__ void finish(const SyncArgs &a, const Tile &td, uint16_t *ids)
+    __device__ __forceinline__ void finish(const SyncArgs &a, const TileDesc &td, uint16_t *ids)
     {
         const int K = a.K, q = Q1 == kUpTo8 ? td.q : Q1 - 1, first = threadIdx.x;
         if (first < K) put(a, td, ids, first, q);
@@ -191,8 +188,8 @@ struct Rows {
 // registers: 232), gossip-MA 10 x 6 M 110 / 182 (91); 20 neighbours, 24 x 2.5 M 287 / 412.
 template <int NT>
 struct Rows<NT, kAnyQ> {
-    __device__ __forceinline__ void begin(const SyncArgs &, const Tile &) {}
-    __device__ __forceinline__ void finish(const SyncArgs &a, const Tile &td, uint16_t *ids)
+    __device__ __forceinline__ void begin(const SyncArgs &, const TileDesc &) {}
+    __device__ __forceinline__ void finish(const SyncArgs &a, const TileDesc &td, uint16_t *ids)
     {
         const int K = a.K, q = td.q, pitch = ids_pitch(kAnyQ, a.q);
         const int32_t *table = a.nbr + static_cast<int64_t>(td.comp) * K * a.q;
@@ -303,7 +300,7 @@ __device__ __forceinline__ v4f average(const v4f *tile, const uint16_t *row, int
 // the same wn, cn for all threads: with T <= NT a thread keeps its column and visits every (NT/T)-th worker, with T > NT (few
 // workers in a wide shape) slot n is one stretch of one worker's row.
 template <int NT, int SLOTS, int Q1>
-__device__ __forceinline__ void do_tile(const SyncArgs &a, const Tile &td, v4f *tile, uint16_t *ids)
+__device__ __forceinline__ void do_tile(const SyncArgs &a, const TileDesc &td, v4f *tile, uint16_t *ids)
 {
     const int tid = threadIdx.x, K = a.K, logT = a.logT, T = 1 << logT, mode = a.mode;
     const float inv = (a.flags & kFlagMixedQ) ? a.comp[td.comp].inv : a.inv;
@@ -372,25 +369,25 @@ __device__ __forceinline__ void do_tile(const SyncArgs &a, const Tile &td, v4f *
 // Where all arrays are in flight at once the slots beyond the N that hold rows are left out; where omega and Delta are
 // streamed, blocks of DEPTH slots are left out in front, so that the stream ends in the same slots for any K.  A thread
 // that has no row in a slot loads the tile's first column of row K - 1, one line for the whole wave, and stores nothing.
-// Bits 5 and up of a column's number say where its stretch lies in the row if the tile has several (tile_kernel).
+// kApart: bits 5 and up of a column's number say where its stretch lies in the row if the tile has several (tile_kernel).
 // CUT (T <= NT): component edges cut the tile, which is not thin.  A column that is not the tile's at all is treated like a missing row.
 // Of a cut column the four floats nearest to it that are the tile's are loaded and moved, and its own are stored one by one (cut_column).
 template <int NT, int SLOTS, int DEPTH, int Q1, int POL, bool MA, bool CUT>
 struct WholeTile {
-    static constexpr bool APART = POL == kStreamed && !CUT;       // only streamed launches have such tiles
+    static constexpr bool APART = POL == kApart && !CUT;
     const SyncArgs &a;
-    const Tile &td;
+    const TileDesc &td;
     v4f *tile;
     uint16_t *ids;
     int N, skipped, w0, col0;                                     // slots with rows; DEPTH < SLOTS: the first slot that is used
-    int apart, beyond;                                            // where in a row bit 5 of a column's number goes, and those above it
+    int beyond;                                                   // APART: where in a row bits 6 and up of a column's number go
     int64_t col_at, spare;                                        // where the thread's first column lies in row 0; what is loaded without a row
     float inv;
     unsigned mine;                                                // CUT: which floats of the thread's column are the tile's
     int from;                                                     // CUT: where its load starts, counted from it
     v4f om[DEPTH], de[DEPTH];
 
-    __device__ __forceinline__ WholeTile(const SyncArgs &args, const Tile &desc, v4f *lds, uint16_t *rows)
+    __device__ __forceinline__ WholeTile(const SyncArgs &args, const TileDesc &desc, v4f *lds, uint16_t *rows)
         : a(args), td(desc), tile(lds), ids(rows) {}
     __device__ __forceinline__ int worker(int n) const { return w0 + (((n - skipped) * NT) >> a.logT); }
     __device__ __forceinline__ int column(int n) const { return ((n - skipped) * NT) & ((1 << a.logT) - 1); }
@@ -402,7 +399,9 @@ struct WholeTile {
     }
     __device__ __forceinline__ int64_t at(int n) const
     {
-        const int64_t p = col_at + static_cast<int64_t>(worker(n)) * a.at.stride + (APART ? column(n) >> 6 << (beyond + 2) : 4 * column(n));
+        int64_t p = col_at + static_cast<int64_t>(worker(n)) * a.at.stride;
+        if constexpr (APART) p += column(n) >> 6 << (beyond + 2);
+        else p += 4 * column(n);
         return (!may_lack(n) || worker(n) < a.K) && (!CUT || mine) ? p : spare;
     }
     // The floats of a column as they were loaded, in their places.
@@ -456,7 +455,7 @@ struct WholeTile {
             store(a.theta + p, tn);
         }
     }
-    __device__ __forceinline__ void run()
+    __device__ __forceinline__ void run(int kind)
     {
         const int tid = threadIdx.x, T = 1 << a.logT;
         N = ((a.K << a.logT) + NT - 1) / NT;
@@ -465,9 +464,9 @@ struct WholeTile {
         w0 = tid >> a.logT;
         inv = (a.flags & kFlagMixedQ) ? a.comp[td.comp].inv : a.inv;
         int in_row = col0;
-        if (APART) {
-            apart = td.kind == kOneStretch ? kLogStretch : kLogApart;
-            beyond = td.kind == kOneStretch ? kLogStretch + 1 : td.kind == kApartWide ? kLogApart + 1 : kLogApart + 6 - a.logT;
+        if constexpr (APART) {
+            const int apart = kind == kOneStretch ? kLogStretch : kLogApart;
+            beyond = kind == kOneStretch ? kLogStretch + 1 : kind == kApartWide ? kLogApart + 1 : kLogApart + 6 - a.logT;
             in_row = (col0 & 31) | (((col0 >> 5) & 1) << apart) | (col0 >> 6 << beyond);
         }
         const int64_t first = td.lo & ~static_cast<int64_t>(3), e = first + 4 * in_row;
@@ -511,7 +510,7 @@ struct WholeTile {
 // A cut tile of the streamed shapes whose columns are not loaded whole (is_thin): one column of one worker at a time, only those that
 // hold floats of the tile.  One or two as a rule, of which a thread has few: its first one's loads are all issued before the barrier.
 template <int NT, int Q1>
-__device__ __forceinline__ void thin_tile(const SyncArgs &a, const Tile &td, v4f *tile, uint16_t *ids)
+__device__ __forceinline__ void thin_tile(const SyncArgs &a, const TileDesc &td, v4f *tile, uint16_t *ids)
 {
     const float inv = (a.flags & kFlagMixedQ) ? a.comp[td.comp].inv : a.inv;
     const bool slots_too = a.mode != GBMUF_MODE_GOSSIP_MA;
@@ -565,7 +564,7 @@ __device__ __forceinline__ void thin_tile(const SyncArgs &a, const Tile &td, v4f
 }
 
 template <int NT, int SLOTS, int DEPTH, int Q1, int POL>
-__device__ __forceinline__ void any_tile(const SyncArgs &a, const Tile &td, v4f *tile, uint16_t *ids)
+__device__ __forceinline__ void any_tile(const SyncArgs &a, const TileDesc &td, int kind, v4f *tile, uint16_t *ids)
 {
     // Cut tiles take plain accesses: they share lines, and a store that goes through the L2 is counted as under way until memory has
     // it, for which loads issued behind it wait (128 workers x 54 K in 9 components 50 us, with plain ones below 29).
@@ -578,18 +577,18 @@ __device__ __forceinline__ void any_tile(const SyncArgs &a, const Tile &td, v4f 
         } else if (is_thin(td.lo, td.n, a.at.logB)) {
             thin_tile<NT, Q1>(a, td, tile, ids);
         } else if (a.mode == GBMUF_MODE_GOSSIP_MA) {
-            WholeTile<NT, SLOTS, DEPTH, Q1, kPlain, true, true>(a, td, tile, ids).run();
+            WholeTile<NT, SLOTS, DEPTH, Q1, kPlain, true, true>(a, td, tile, ids).run(kOneStretch);
             __builtin_amdgcn_endpgm();
         } else {
-            WholeTile<NT, SLOTS, DEPTH, Q1, kPlain, false, true>(a, td, tile, ids).run();
+            WholeTile<NT, SLOTS, DEPTH, Q1, kPlain, false, true>(a, td, tile, ids).run(kOneStretch);
         }
         __builtin_amdgcn_endpgm();
     }
     if (a.mode == GBMUF_MODE_GOSSIP_MA) {
-        WholeTile<NT, SLOTS, DEPTH, Q1, POL, true, false>(a, td, tile, ids).run();
+        WholeTile<NT, SLOTS, DEPTH, Q1, POL, true, false>(a, td, tile, ids).run(kind);
         __builtin_amdgcn_endpgm();
     }
-    WholeTile<NT, SLOTS, DEPTH, Q1, POL, false, false>(a, td, tile, ids).run();
+    WholeTile<NT, SLOTS, DEPTH, Q1, POL, false, false>(a, td, tile, ids).run(kind);
     __builtin_amdgcn_endpgm();
 }
 
@@ -608,20 +607,21 @@ __global__ __launch_bounds__(NT) void sync_kernel(SyncArgs a)
     uint32_t logB = static_cast<uint32_t>(a.at.logB);
     hold(logB);                                                   // fetched with the other arguments, not after the descriptor
     a.at.logB = static_cast<int32_t>(logB);
-    const Tile td = load_tile(a.tiles + tile_of_block(a));
+    int kind;
+    const TileDesc td = load_tile<POL>(a.tiles + tile_of_block(a), kind);
     if ((a.flags & kFlagCheckPeriods) && a.step % static_cast<uint64_t>(a.comp[td.comp].period) != 0)
         return;                                                   // not due: the whole workgroup leaves
     if constexpr (Q1 == kMixed) {
         switch (td.q) {
-            case 0: return any_tile<NT, SLOTS, DEPTH, 1, POL>(a, td, tile, ids);
-            case 1: return any_tile<NT, SLOTS, DEPTH, 2, POL>(a, td, tile, ids);
-            case 2: return any_tile<NT, SLOTS, DEPTH, 3, POL>(a, td, tile, ids);
-            case 3: return any_tile<NT, SLOTS, DEPTH, 4, POL>(a, td, tile, ids);
-            case 4: return any_tile<NT, SLOTS, DEPTH, 5, POL>(a, td, tile, ids);
-            default: return any_tile<NT, SLOTS, DEPTH, kUpTo8, POL>(a, td, tile, ids);
+            case 0: return any_tile<NT, SLOTS, DEPTH, 1, POL>(a, td, kind, tile, ids);
+            case 1: return any_tile<NT, SLOTS, DEPTH, 2, POL>(a, td, kind, tile, ids);
+            case 2: return any_tile<NT, SLOTS, DEPTH, 3, POL>(a, td, kind, tile, ids);
+            case 3: return any_tile<NT, SLOTS, DEPTH, 4, POL>(a, td, kind, tile, ids);
+            case 4: return any_tile<NT, SLOTS, DEPTH, 5, POL>(a, td, kind, tile, ids);
+            default: return any_tile<NT, SLOTS, DEPTH, kUpTo8, POL>(a, td, kind, tile, ids);
         }
     } else {
-        any_tile<NT, SLOTS, DEPTH, Q1, POL>(a, td, tile, ids);
+        any_tile<NT, SLOTS, DEPTH, Q1, POL>(a, td, kind, tile, ids);
     }
 }
 
@@ -644,11 +644,17 @@ KernelFn pick_q(int Q1)
 
 #define GBMUF_CASE(NT, SL, D) \
     if (v.threads == NT && v.slots == SL && v.depth == D) return pick_q<NT, SL, D>(kernel_q1(q, mixed));
+// shapes that tiles in stretches never take
+#if GBMUF_POLICY == 2
+#define GBMUF_CASE_SIDE_BY_SIDE(NT, SL, D)
+#else
+#define GBMUF_CASE_SIDE_BY_SIDE(NT, SL, D) GBMUF_CASE(NT, SL, D)
+#endif
 
 #if GBMUF_PART == 0
 KernelFn GBMUF_PICK_NAME(0, GBMUF_POLICY)(const Variant &v, int q, bool mixed)
 {
-    GBMUF_CASE(256, 16, 16)
+    GBMUF_CASE_SIDE_BY_SIDE(256, 16, 16)
     GBMUF_CASE(256, 2, 2)
     GBMUF_CASE(256, 1, 1)
     return nullptr;
@@ -664,17 +670,17 @@ KernelFn GBMUF_PICK_NAME(1, GBMUF_POLICY)(const Variant &v, int q, bool mixed)
 #elif GBMUF_PART == 2
 KernelFn GBMUF_PICK_NAME(2, GBMUF_POLICY)(const Variant &v, int q, bool mixed)
 {
-    GBMUF_CASE(256, 8, 8)
+    GBMUF_CASE_SIDE_BY_SIDE(256, 8, 8)
     GBMUF_CASE(256, 4, 4)
-    GBMUF_CASE(1024, 1, 1)
+    GBMUF_CASE_SIDE_BY_SIDE(1024, 1, 1)
     GBMUF_CASE(1024, 2, 1)
     return nullptr;
 }
 #elif GBMUF_PART == 3
 KernelFn GBMUF_PICK_NAME(3, GBMUF_POLICY)(const Variant &v, int q, bool mixed)
 {
-    GBMUF_CASE(512, 8, 8)
-    GBMUF_CASE(1024, 2, 2)
+    GBMUF_CASE_SIDE_BY_SIDE(512, 8, 8)
+    GBMUF_CASE_SIDE_BY_SIDE(1024, 2, 2)
     GBMUF_CASE(512, 4, 4)
     return nullptr;
 }

@@ -86,6 +86,21 @@ def need_gpu():
         pytest.skip("no GPU")
 
 
+# Kernels for tiles in stretches are theirs alone: 40 workers' blocks and 12 workers' aligned rows both take 512 x 4 in gossip-MA, and
+# blocks waited for their neighbour table before the first load of theta while the kernel was one (40 x 22 M 1102 us, 1068).
+@pytest.mark.gpu
+@pytest.mark.parametrize("values", [150_000_000, 600_000_000])
+def test_blocks_take_no_kernel_of_tiles_in_stretches(values):
+    need_gpu()
+    seen = []
+    for K, place in ((40, "blocked"), (12, "rows")):
+        pl = B.Plan([0, values // K], K, 2, 0)
+        call = lambda s: pl.sync_state(fake_state(pl, place), 0.9, 1.0, B.MODE_GOSSIP_MA, 0, s)
+        seen.append((launches(call)[-1][1], launches(call, kernels=True)[-1]))
+        pl.destroy()
+    assert seen[0][0] == seen[1][0] == 512 and seen[0][1] != seen[1][1]
+
+
 # The component that syncs most often is a bias, or empty; all the others sync every 16th time.  A sync of everything
 # has to run like that of a plan without periods.
 RARE = [83_070_000 // 8] * 8
