@@ -475,6 +475,9 @@ struct WholeTile {
         from = cut.from;
         col_at = placed(a.at, e + from);
         spare = placed(a.at, td.lo) + static_cast<int64_t>(a.K - 1) * a.at.stride;
+        // Nothing is under way here, but the compiler, to which the paths join where the program ends, cannot know: it waited for one slot's
+        // theta before the next one's load (gossip-MA 25 x 16 M 519 us, 577).  Two kinds of wait, or it would move one in front of both paths.
+        if constexpr (APART) __builtin_amdgcn_s_waitcnt(MA ? 0x0070 : 0x0F70);          // vmcnt(0) and, MA, lgkmcnt(0)
         Rows<NT, Q1> rows;
         rows.begin(a, td);
         v4f th[SLOTS];
