@@ -309,7 +309,8 @@ Variant shared_variant(int K, int what, int size, bool few)
 //     whose tiles hold 256 bytes of a row (300 x 1 M 1244, one tile moving on 1314; 400 x 1.8 M 2976 / 3129),
 //     481 to 512 in tiles of 128 bytes, which they fill, and runs of 4 KB (512 x 0.6 M 1378, kVeryMany 1411).
 //     No bound of the residency helps above 4 workers; up to 2 three per CU (2 x 300 M 2165 us, six 2517), 3 and 4 six
-//     (3 x 333 M 3511, four 3727, unbounded 3553; 4 x 250 M 3554, 3492, 3562).  Up to 8 workers 256 x 1, 9-16 512 x 1 where K rows fill its
+//     (3 x 333 M 3511, four 3727, unbounded 3553; 4 x 250 M 3554, 3492, 3562), but five where components draw different numbers of neighbours, whose
+//     tiles load sooner (4 x 225 M 3153, six 3187), and then two with 17 to 32 workers (24 x 4.2 M 356, unbounded 359).  Up to 8 workers 256 x 1, 9-16 512 x 1 where K rows fill its
 //     slots to 7/8, else 256 x 2, whose threads idle in whole slots (12 x 25 M 1051 us; 512 x 1 1080), 17-32 512 x 2, 33-64 kSixtyFour (40 x
 //     7.5 M 1070 us, 512 x 4 1092; 44 x 9.1 M 1422, 1459; 64 x 4.7 M 1070, 1085), 65-128 kMany, above kVeryMany (160 x 1.9 M 1092, kMany
 //     1290; 300 x 1 M 1244, 1250; 300 x 4.3 M 5467, 5737), 5 to 20 M values kSixtyFour (200 x 0.1 M 84 us, kMany 88).
@@ -327,7 +328,7 @@ Variant shared_variant(int K, int what, int size, bool few)
 //     more than 256 workers kVeryMany (300 x 2 M 947; 956).  Rows, in stretches: up to 8 512 x 2 where K rows fill 1024 slots to 7/8 (4 x 100 M 481, 512 x 4 488), 3 256 x 4
 //     (3 x 133 M 480), up to 24 512 x 4 (12 x 33 M 499, 512 x 2 513; 6 x 17 M 124, 512 x 2 129), up to 32 kMany (32 x 12.5 M 528, 512 x 4 545), above kVeryMany (64 x 15.6 M 1340, kMany 1379; 300 x 2 M 1003,
 //     1024 x 4 1089).  5 to 20 M values: 256 x 2 up to 64 workers, up to 128 512 x 2.
-void aligned_shape(int K, int layout, int what, int size, bool few, LayoutCfg &cfg)
+void aligned_shape(int K, int layout, int what, int size, bool few, bool mixed, LayoutCfg &cfg)
 {
     Variant &v = cfg.variant;
     int &bound = cfg.workgroups_per_cu, &run = cfg.xcd_columns_log;
@@ -367,7 +368,8 @@ void aligned_shape(int K, int layout, int what, int size, bool few, LayoutCfg &c
         else if (size != kCompact && few && !(K > 480 && K <= 512)) v = kVeryMany;
         else if (size != kCompact && few) find_variant(512, 8, &v);
         else v = kMany;
-        if (K <= 4) bound = K <= 2 ? 3 : 6;
+        if (K <= 4) bound = K <= 2 ? 3 : mixed ? 5 : 6;
+        else if (mixed && K > 16 && K <= 32) bound = 2;
     } else {
         if (size == kCompact) {
             if (K <= 8) find_variant(256, 1, &v);
@@ -940,7 +942,7 @@ int gbmuf_plan_create(gbmuf_plan_t **out, const gbmuf_plan_desc_t *desc)
                         cfg.variant = shared_variant(K, what, size, few);
                         cfg.workgroups_per_cu = shared_workgroups_per_cu(K, what, size);
                     } else {
-                        aligned_shape(K, layout, what, size, few, cfg);
+                        aligned_shape(K, layout, what, size, few, pl->mixed_q, cfg);
                     }
                     if (through_lds) {
                         cfg.variant = lds_drawing_variant(K, layout);

@@ -296,14 +296,23 @@ __device__ __forceinline__ v4f average(const v4f *tile, const uint16_t *row, int
     return s * inv;
 }
 
+// MIXED (up to 7 neighbours, whose path the workgroup has taken): 1/(q+1) of the tile's component is a constant, because a load of it
+// is waited for before the tile's own are issued.  us, loaded / constant: gossip-MA on blocks 24 x 8 M 240 / 232, 48 x 19 M 1127 / 1073, 12 x 0.46 M
+// 8.6 / 8.1; BMUF 16 x 29 M 1649 / 1636, 128 x 14 K 14.2 / 13.6 (up to 7 neighbours), but 4 x 50 M 700 / 702.
+template <int Q1>
+__device__ __forceinline__ constexpr float inverse_of(int q)
+{
+    return Q1 != kUpTo8 ? 1.0f / Q1 : q == 5 ? 1.0f / 6 : q == 6 ? 1.0f / 7 : 1.0f / 8;
+}
+
 // A tile that a component edge cuts, all arrays in flight at once.  Slot n of a thread is worker w0 + wn(n), column col0 + cn(n) with
 // the same wn, cn for all threads: with T <= NT a thread keeps its column and visits every (NT/T)-th worker, with T > NT (few
 // workers in a wide shape) slot n is one stretch of one worker's row.
-template <int NT, int SLOTS, int Q1>
+template <int NT, int SLOTS, int Q1, bool MIXED>
 __device__ __forceinline__ void do_tile(const SyncArgs &a, const TileDesc &td, v4f *tile, uint16_t *ids)
 {
     const int tid = threadIdx.x, K = a.K, logT = a.logT, T = 1 << logT, mode = a.mode;
-    const float inv = (a.flags & kFlagMixedQ) ? a.comp[td.comp].inv : a.inv;
+    const float inv = MIXED ? inverse_of<Q1>(td.q) : (a.flags & kFlagMixedQ) ? a.comp[td.comp].inv : a.inv;
     const bool slots_too = mode != GBMUF_MODE_GOSSIP_MA;
     const int col0 = tid & (T - 1), w0 = tid >> logT;
     auto wn = [&](int n) { return (n * NT) >> logT; };
@@ -372,7 +381,7 @@ __device__ __forceinline__ void do_tile(const SyncArgs &a, const TileDesc &td, v
 // kApart: bits 5 and up of a column's number say where its stretch lies in the row if the tile has several (tile_kernel).
 // CUT (T <= NT): component edges cut the tile, which is not thin.  A column that is not the tile's at all is treated like a missing row.
 // Of a cut column the four floats nearest to it that are the tile's are loaded and moved, and its own are stored one by one (cut_column).
-template <int NT, int SLOTS, int DEPTH, int Q1, int POL, bool MA, bool CUT>
+template <int NT, int SLOTS, int DEPTH, int Q1, bool MIXED, int POL, bool MA, bool CUT>
 struct WholeTile {
     static constexpr bool APART = POL == kApart && !CUT;
     const SyncArgs &a;
@@ -462,7 +471,7 @@ struct WholeTile {
         skipped = DEPTH == SLOTS ? 0 : (SLOTS - N) / DEPTH * DEPTH;
         col0 = tid & (T - 1);
         w0 = tid >> a.logT;
-        inv = (a.flags & kFlagMixedQ) ? a.comp[td.comp].inv : a.inv;
+        inv = MIXED ? inverse_of<Q1>(td.q) : (a.flags & kFlagMixedQ) ? a.comp[td.comp].inv : a.inv;
         int in_row = col0;
         if constexpr (APART) {
             const int apart = kind == kOneStretch ? kLogStretch : kLogApart;
@@ -512,10 +521,10 @@ struct WholeTile {
 
 // A cut tile of the streamed shapes whose columns are not loaded whole (is_thin): one column of one worker at a time, only those that
 // hold floats of the tile.  One or two as a rule, of which a thread has few: its first one's loads are all issued before the barrier.
-template <int NT, int Q1>
+template <int NT, int Q1, bool MIXED>
 __device__ __forceinline__ void thin_tile(const SyncArgs &a, const TileDesc &td, v4f *tile, uint16_t *ids)
 {
-    const float inv = (a.flags & kFlagMixedQ) ? a.comp[td.comp].inv : a.inv;
+    const float inv = MIXED ? inverse_of<Q1>(td.q) : (a.flags & kFlagMixedQ) ? a.comp[td.comp].inv : a.inv;
     const bool slots_too = a.mode != GBMUF_MODE_GOSSIP_MA;
     const int64_t first = td.lo & ~static_cast<int64_t>(3);
     const int columns = static_cast<int>((td.lo + td.n - 1 - first) >> 2) + 1;
@@ -566,7 +575,7 @@ __device__ __forceinline__ void thin_tile(const SyncArgs &a, const TileDesc &td,
     }
 }
 
-template <int NT, int SLOTS, int DEPTH, int Q1, int POL>
+template <int NT, int SLOTS, int DEPTH, int Q1, bool MIXED, int POL>
 __device__ __forceinline__ void any_tile(const SyncArgs &a, const TileDesc &td, int kind, v4f *tile, uint16_t *ids)
 {
     // Cut tiles take plain accesses: they share lines, and a store that goes through the L2 is counted as under way until memory has
@@ -576,22 +585,22 @@ __device__ __forceinline__ void any_tile(const SyncArgs &a, const TileDesc &td, 
     const bool cut = ((td.lo & 3) | (td.n & ~(4 << a.logT))) != 0;      // n is less than T columns
     if (cut) {
         if constexpr (DEPTH == SLOTS) {
-            do_tile<NT, SLOTS, Q1>(a, td, tile, ids);
+            do_tile<NT, SLOTS, Q1, MIXED>(a, td, tile, ids);
         } else if (is_thin(td.lo, td.n, a.at.logB)) {
-            thin_tile<NT, Q1>(a, td, tile, ids);
+            thin_tile<NT, Q1, MIXED>(a, td, tile, ids);
         } else if (a.mode == GBMUF_MODE_GOSSIP_MA) {
-            WholeTile<NT, SLOTS, DEPTH, Q1, kPlain, true, true>(a, td, tile, ids).run(kOneStretch);
+            WholeTile<NT, SLOTS, DEPTH, Q1, MIXED, kPlain, true, true>(a, td, tile, ids).run(kOneStretch);
             __builtin_amdgcn_endpgm();
         } else {
-            WholeTile<NT, SLOTS, DEPTH, Q1, kPlain, false, true>(a, td, tile, ids).run(kOneStretch);
+            WholeTile<NT, SLOTS, DEPTH, Q1, MIXED, kPlain, false, true>(a, td, tile, ids).run(kOneStretch);
         }
         __builtin_amdgcn_endpgm();
     }
     if (a.mode == GBMUF_MODE_GOSSIP_MA) {
-        WholeTile<NT, SLOTS, DEPTH, Q1, POL, true, false>(a, td, tile, ids).run(kind);
+        WholeTile<NT, SLOTS, DEPTH, Q1, MIXED, POL, true, false>(a, td, tile, ids).run(kind);
         __builtin_amdgcn_endpgm();
     }
-    WholeTile<NT, SLOTS, DEPTH, Q1, POL, false, false>(a, td, tile, ids).run(kind);
+    WholeTile<NT, SLOTS, DEPTH, Q1, MIXED, POL, false, false>(a, td, tile, ids).run(kind);
     __builtin_amdgcn_endpgm();
 }
 
@@ -616,15 +625,15 @@ __global__ __launch_bounds__(NT) void sync_kernel(SyncArgs a)
         return;                                                   // not due: the whole workgroup leaves
     if constexpr (Q1 == kMixed) {
         switch (td.q) {
-            case 0: return any_tile<NT, SLOTS, DEPTH, 1, POL>(a, td, kind, tile, ids);
-            case 1: return any_tile<NT, SLOTS, DEPTH, 2, POL>(a, td, kind, tile, ids);
-            case 2: return any_tile<NT, SLOTS, DEPTH, 3, POL>(a, td, kind, tile, ids);
-            case 3: return any_tile<NT, SLOTS, DEPTH, 4, POL>(a, td, kind, tile, ids);
-            case 4: return any_tile<NT, SLOTS, DEPTH, 5, POL>(a, td, kind, tile, ids);
-            default: return any_tile<NT, SLOTS, DEPTH, kUpTo8, POL>(a, td, kind, tile, ids);
+            case 0: return any_tile<NT, SLOTS, DEPTH, 1, true, POL>(a, td, kind, tile, ids);
+            case 1: return any_tile<NT, SLOTS, DEPTH, 2, true, POL>(a, td, kind, tile, ids);
+            case 2: return any_tile<NT, SLOTS, DEPTH, 3, true, POL>(a, td, kind, tile, ids);
+            case 3: return any_tile<NT, SLOTS, DEPTH, 4, true, POL>(a, td, kind, tile, ids);
+            case 4: return any_tile<NT, SLOTS, DEPTH, 5, true, POL>(a, td, kind, tile, ids);
+            default: return any_tile<NT, SLOTS, DEPTH, kUpTo8, true, POL>(a, td, kind, tile, ids);
         }
     } else {
-        any_tile<NT, SLOTS, DEPTH, Q1, POL>(a, td, kind, tile, ids);
+        any_tile<NT, SLOTS, DEPTH, Q1, false, POL>(a, td, kind, tile, ids);
     }
 }
 

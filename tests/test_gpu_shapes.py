@@ -144,3 +144,14 @@ def test_tiles_in_stretches(K, q, values, mode, place):
         off.append(at)
     off = sorted({x for x in off if x < P} | {P})
     check(K, q, off, "separate" if place == "lines" else place, mode, -(-P // 32) * 32 + 32 if place == "lines" else None)
+
+
+# Every number of neighbours that a workgroup of a plan of several takes a path of its own for, in tiles that are whole, cut and thin.
+@pytest.mark.parametrize("layout", ["blocked", "rows", "odd"])
+@pytest.mark.parametrize("mode", [B.MODE_PAPER, B.MODE_GOSSIP_MA])
+@pytest.mark.parametrize("K,values", [(8, 200_000), (9, 5_300_000), (16, 200_000), (24, 20_400_000), (40, 20_400_000), (100, 5_300_000)])
+def test_every_number_of_neighbours(K, values, mode, layout):
+    P = values // K
+    off = sorted({0, 2, P // 8 | 1, P // 7 & ~3, P // 6 | 3, P // 5, P // 4 | 1, P // 3, P // 2 | 1, P - 1, P})
+    q = [(3 * i + 5) % 8 for i in range(len(off) - 1)]
+    check(K, q, off, "separate" if layout == "odd" else layout, mode, stride_of(layout, P), every=64)

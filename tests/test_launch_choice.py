@@ -210,6 +210,15 @@ def test_shapes_of_gossip_ma_of_few_blocks(values):
     assert [got[K][1] for K in (3, 5, 6, 7, 8)] == [256, 64, 64, 64, 64]
 
 
+# Components that draw different numbers of neighbours, whose 1/(q+1) no tile waits for: fewer workgroups per CU for 3 and 4 blocks and for 17 to 32.
+@pytest.mark.parametrize("values", [6_000_000, 100_000_000, 900_000_000])
+def test_bounds_of_mixed_neighbours_on_blocks(values):
+    def bounds(K):
+        P = values // K
+        return [B.Plan([0, P // 2, P], K, q, 0).info.workgroups_per_cu_blocked for q in (1, [1, 2])]
+    assert [bounds(K) for K in (3, 4, 5, 16, 17, 32, 33)] == [[6, 5], [6, 5], [0, 0], [0, 0], [0, 2], [0, 2], [0, 0]]
+
+
 # Blocked state beyond the caches: the XCDs' tiles move on from block to block, but for 257 to 512 workers, whose tiles hold 256 bytes of a
 # row and who take 1 KB of it in one run (one tile each, moving on, 5 % longer).
 @pytest.mark.gpu
