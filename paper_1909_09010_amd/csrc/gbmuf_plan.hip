@@ -39,7 +39,8 @@ struct LayoutCfg {
 };
 
 // kShared: rows of which some start inside a 128-byte line, so that neighbouring tiles share lines.
-enum { kRows = 0, kBlocked = 1, kShared = 2, kLayouts = 3 };
+// kFine: aligned rows, most of whose floats are in short components (rows_layout).
+enum { kRows = 0, kBlocked = 1, kShared = 2, kFine = 3, kLayouts = 4 };
 enum { kBmuf = 0, kMa = 1, kBranches = 2 };   // the three-array update, or the gossip-MA branch (theta only)
 // How much one launch updates.  With sync periods that differs from call to call by orders of magnitude, so
 // everything that depends on it is chosen per launch, from the components that are due.
@@ -58,6 +59,7 @@ struct gbmuf_plan_s {
     std::vector<int32_t> periods;    // m: sync period H_i (all 1 without periods)
     std::vector<int32_t> cand;       // [K][C] ring candidates, order of Definition 1
     std::vector<CompDesc> comp;      // m: per-component constants of the kernels
+    int64_t long_values = 0;         // K times the elements of components that are not short (rows_layout)
     LayoutCfg cfg[kLayouts][kBranches][kSizes];
     int32_t min_block_logT = 0;      // blocks hold at least 4 << min_block_logT floats
     TileSet sets[kMaxTileSets];      // one per distinct tile width among the configurations that calls can take
@@ -224,10 +226,34 @@ int size_of_launch(int64_t values, int layout, int what)
     return values <= (shared && what == kMa ? kLargeValuesSharedMa : kLargeValues) ? kMiddle : kLarge;
 }
 
+// The floats that a component of aligned rows has at least for tiles in stretches 32 KB apart (tile_kernel) to pay: shorter ones have few of
+// them and, in the wide shapes that go with stretches, more tiles that their ends cut.  us in components of one size, as if they were short / stretches:
+// 12 x 58 M of 16 K floats 2790 / 3194, of 140 K 2811 / 2886, of 160 K 2805 / 2760; gossip-MA 6 x 117 M of 140 K 863 / 910, of 200 K 865 / 851; 2 x 150 M of
+// 16 K 1120 / 1276, of 100 K 1113 / 1091; 13 x 23 M of 23 K 1196 / 1268, of 50 K 1202 / 1181; 32 x 9.4 M of 32 K 1325 / 1340, of 50 K 1333 / 1234; 48 x 0.6 M of 5 K
+// 103 / 107, of 50 K 103 / 102.
+int64_t long_component(int K) { return K <= 2 ? 1 << 17 : K <= 12 ? 10 << 14 : 1 << 15; }
+
+// Whether most of what a launch on aligned rows updates is in short components.  Above 64 workers stretches pay whatever the components (128 x 2.3 M
+// of 15 K floats 1456 / 1463, of 23 K 1467 / 1389), as they do with 3 above 500 M values (3 x 200 M of 16 K 2530 / 2358, 3 x 233 M of 32 K 2930 / 2997), and 33 to 39 leave
+// kMany's slots empty (33 x 0.9 M of 16 K 113, in stretches 111).  Up to 20 M values, much of which comes from the caches, it is the pages that a state has got that decide
+// (side by side / in stretches, 4 x 3.8 M gossip-MA 25.2 / 18.2 or 17.2 / 18.1, 32 x 0.25 M 30.7 / 24.6 or 28.2 / 29.8).
+int rows_layout(int K, int size, int64_t values, int64_t long_values)
+{
+    if (size <= kCompact || (K == 3 && size == kLarge) || (K > 32 && K < 40) || K > 64) return kRows;
+    return 2 * long_values < values ? kFine : kRows;
+}
+
 // Which sizes a call of this plan can have: without periods a call updates everything.
 bool size_occurs(const gbmuf_plan_s &pl, int layout, int what, int size)
 {
-    const int all = size_of_launch(pl.K * pl.P, layout, what), least = size_of_launch(0, layout, what);
+    const int64_t values = pl.K * pl.P;
+    const int all = size_of_launch(values, layout, what), least = size_of_launch(0, layout, what);
+    if (layout == kRows || layout == kFine) {
+        // with periods parts that are all short or all long may be due
+        const bool part = pl.has_periods && rows_layout(pl.K, size, values, layout == kFine ? 0 : values) == layout &&
+                          (layout == kFine ? pl.long_values < values : pl.long_values > 0);
+        if (rows_layout(pl.K, size, values, pl.long_values) != layout && !part) return false;
+    }
     return size == all || (pl.has_periods && size < all && size >= least);
 }
 
@@ -316,18 +342,22 @@ Variant shared_variant(int K, int what, int size, bool few)
 //     1290; 300 x 1 M 1244, 1250; 300 x 4.3 M 5467, 5737), 5 to 20 M values kSixtyFour (200 x 0.1 M 84 us, kMany 88).
 //   Aligned rows are 3K address streams: 6.4 with 4 workers, 5.8 with 32, 5.5 with 128, in tiles whose stretches lie 32 KB apart (tiles_apart), the more of them
 //     the better until one tile is all that a CU holds.  1, 2 and 4 256 x 2, two per CU (4 x 112 M 1670 us; 1024 x 1 1670, 256 x 1 1720), 3 512 x 1 (3 x 8.3 M 94.6;
-//     256 x 1 98.3; kSixtyFour 94.8, but 96.9 in 87 components, whose ends cut its wide tiles, 512 x 1 94), 5-8 kSixtyFour (8 x 56 M 1693, 1024 x 2 1706), 9-32 kMany (24 x 42 M 4014, 1024 x 4 4039, kSixtyFour 4536; 16 x 28 M 1779,
-//     kSixtyFour 1744), 33-128 kVeryMany (48 x 21 M 4240, 1024 x 4 4252; 64 x 15.6 M 4206, kMany 4298), tile by tile (64 x 15.6 M 4206, 4 KB
+//     256 x 1 98.3; kSixtyFour 94.8, but 96.9 in 87 components, whose ends cut its wide tiles, 512 x 1 94), 5-8 kSixtyFour (8 x 56 M 1693, 1024 x 2 1706), 9-32 kMany (24 x 42 M 4014, 1024 x 4 4039, kSixtyFour 4536; 12 x 58 M 2676,
+//     kSixtyFour 2738), but 13-16 kSixtyFour (16 x 28 M 1744, kMany 1779; 14 x 50 M in components of 300 K floats 2726, kMany 2777), 33-128 kVeryMany (48 x 21 M 4240, 1024 x 4 4252; 64 x 15.6 M 4206, kMany 4298), tile by tile (64 x 15.6 M 4206, 4 KB
 //     per XCD 4288), above 128 too, where a stretch is all of a tile and 4 KB of a row go to one XCD (300 x 0.8 M 1209, tile by tile 1259).
+//     In short components (rows_layout) tiles lie side by side and are smaller: up to 4 256 x 1, four per CU (4 x 75 M 1127, 256 x 2 in stretches 1273), 5 and 6 512 x 1 (6 x 117 M 2710, 256 x 2
+//     2785, kSixtyFour in stretches 2915), 7 and 8 256 x 2, two per CU (8 x 87 M 2774, 512 x 1 2955, kSixtyFour in stretches 3063), 9-32 kSixtyFour (12 x 58 M 2790, kMany in stretches 3194); 40-64 in stretches still, kMany (48 x 0.6 M 103.3 us,
+//     kVeryMany 107.5), large kVeryMany (48 x 14.6 M 3184, kMany 3289).
 //     5 to 20 M values: up to 8 256 x 1, four per CU (2 x 6 M 46.8 us, 512 x 1 47.1; 8 x 0.75 M 21.9, 1024 x 1 22.5; 5 x 1.6 M 30.9, 34.7), up to 32 kSixtyFour (16 x 0.75 M 50.7,
 //     256 x 4 52.3), above 1024 x 4 (40 x 0.3 M 55.2, kMany 55.9), 4 KB per XCD from 17 on.
 //   Gossip-MA has a third of the loads and takes more slots per thread.  Blocked: up to 2 workers 256 x 1, but 2 of
 //     more than 500 M values 512 x 2, two per CU (2 x 650 M 1610 us, 256 x 1 1817), 4 512 x 2 (4 x 175 M 848, 256 x 2 898; two per CU 837, but 4 x 5.2 M 6 %
 //     more), up to 16 256 x 2 where K rows
 //     fill it to 7/8 (8 x 75 M 723 us; 512 x 2 748), and 5 and 6 (5 x 140 M 923, 256 x 4 1050; 6 x 50 M 362 / 402), else 256 x 4, up to 32 256 x 4 (725; 512 x 2 735), 33-64 512 x 4, above 1024 x 4, large of
-//     more than 256 workers kVeryMany (300 x 2 M 947; 956).  Rows, in stretches: up to 8 512 x 2 where K rows fill 1024 slots to 7/8 (4 x 100 M 481, 512 x 4 488), 3 256 x 4
-//     (3 x 133 M 480), up to 24 512 x 4 (12 x 33 M 499, 512 x 2 513; 6 x 17 M 124, 512 x 2 129), up to 32 kMany (32 x 12.5 M 528, 512 x 4 545), above kVeryMany (64 x 15.6 M 1340, kMany 1379; 300 x 2 M 1003,
-//     1024 x 4 1089).  5 to 20 M values: 256 x 2 up to 64 workers, up to 128 512 x 2.
+//     more than 256 workers kVeryMany (300 x 2 M 947; 956).  Rows, in stretches: up to 8 512 x 2 where K rows fill 1024 slots to 7/8 (4 x 100 M 481, 512 x 4 488), up to
+//     24 512 x 4 (12 x 33 M 499, 512 x 2 513; 6 x 17 M 124, 512 x 2 129), up to 32 kMany (32 x 12.5 M 528, 512 x 4 545), above kVeryMany (64 x 15.6 M 1340, kMany 1379; 300 x 2 M 1003,
+//     1024 x 4 1089); 3 side by side, 256 x 2 (3 x 20 M 64.1; 256 x 4 in stretches 67.1; but 3 x 100 M 368 / 358), short components up to 8 256 x 2 (6 x 50 M 364; 512 x 4 in stretches 439), up to
+//     24 256 x 4 (12 x 25 M 380; 512 x 4 413).  5 to 20 M values: 256 x 2 up to 64 workers, up to 128 512 x 2.
 void aligned_shape(int K, int layout, int what, int size, bool few, bool mixed, LayoutCfg &cfg)
 {
     Variant &v = cfg.variant;
@@ -344,8 +374,11 @@ void aligned_shape(int K, int layout, int what, int size, bool few, bool mixed, 
             if (K == 2) bound = 2;
         }
         else if (blocked && K <= 2) find_variant(256, 1, &v);
+        else if (layout == kFine && K <= 32) {
+            if (K <= 24) find_variant(256, K <= 8 ? 2 : 4, &v);
+        }
         else if (!blocked) {
-            if (K == 3) find_variant(256, 4, &v);
+            if (K == 3) find_variant(256, 2, &v);
             else if (K <= 24) find_variant(512, K <= 8 && fills(1024) ? 2 : 4, &v);
             else if (K <= 32) v = kMany;
             else if (few) v = kVeryMany;
@@ -375,10 +408,17 @@ void aligned_shape(int K, int layout, int what, int size, bool few, bool mixed, 
             if (K <= 8) find_variant(256, 1, &v);
             else if (K <= 32) v = kSixtyFour;
             if (K <= 8) bound = 4;
+        } else if (layout == kFine && (K <= 32 || size != kLarge)) {
+            if (K <= 4) find_variant(256, 1, &v);
+            else if (K <= 6) find_variant(512, 1, &v);
+            else if (K <= 8) find_variant(256, 2, &v);
+            else v = K <= 32 ? kSixtyFour : kMany;
+            if (K <= 4) bound = 4;
+            else if (K == 7 || K == 8) bound = 2;
         } else {
             if (K <= 2 || K == 4) find_variant(256, 2, &v);
             else if (K == 3) find_variant(512, 1, &v);
-            else if (K <= 8) v = kSixtyFour;
+            else if (K <= 8 || (K > 12 && K <= 16)) v = kSixtyFour;
             else if (K <= 32) v = kMany;
             else if (few) v = kVeryMany;
             if (K <= 2 || K == 4) bound = 2;
@@ -389,7 +429,7 @@ void aligned_shape(int K, int layout, int what, int size, bool few, bool mixed, 
         cfg.rotate = K > 32 && (what == kMa || K <= 128 || (size != kCompact && (K <= 256 || K > 512)));
         run = cfg.rotate ? 0 : K > 480 && K <= 512 && size != kCompact ? 8 : 6;
     } else {
-        run = K > (size == kCompact ? 16 : 128) ? 8 : 0;
+        run = K > (size == kCompact || (layout == kFine && K <= 32 && what == kMa) ? 16 : 128) ? 8 : 0;
     }
 }
 // Small plans with rows of more than 7 neighbours draw them through LDS in every workgroup (launch_bound), a thread a
@@ -420,7 +460,7 @@ int shared_workgroups_per_cu(int K, int what, int size)
 // What a plan that names its shape gets if it does not name a bound: no bound on rows, few on blocked state.
 int32_t named_workgroups_per_cu(int K, int layout, int what)
 {
-    if (layout == kRows) return 0;
+    if (layout == kRows || layout == kFine) return 0;
     if (what == kMa) return K <= 16 ? 4 : 2;
     return K <= 4 ? 4 : K <= 32 ? 2 : 1;
 }
@@ -435,13 +475,16 @@ int choose_policy(int layout, int size, int logT, int hints)
     return layout != kShared && logT >= 3 && (size != kTiny || hints != 0) ? kStreamed : kPlain;
 }
 
-// Whether a launch's tiles lie in stretches 32 KB apart (tile_kernel): aligned rows whose tiles hold 64 columns and more.  us on rows padded to 4 KB, the
-// shapes of aligned_shape, stretches / side by side: 8 x 25 M 750 / 794 (the best shape of those side by side), 16 x 12.5 M 804 / 851, 32 x 6.2 M 828 / 905,
-// 64 x 15.6 M 4206 / 4652, 128 x 7.8 M 4384 / 4771; gossip-MA 16 x 62 M 1270 / 1276, 64 x 15.6 M 1340 / 1455.  Up to 5 M values all comes from the caches (2 x 3 M 21.2
-// / 21.9, 32 x 0.19 M 21.3 / 21.4).  Blocks of 32 KB have the pairs by themselves: a wave takes neighbouring workers' blocks.
-bool tiles_apart(int layout, int size, int logT, bool named)
+// Whether a launch's tiles lie in stretches 32 KB apart (tile_kernel): aligned rows whose tiles hold 64 columns and more, but for short components of
+// up to 32 workers and gossip-MA of 3.  us on rows padded to 4 KB, each in the better of its shapes, stretches / side by side: 8 x 37 M 1107 / 1226, 16 x 18 M 1151 / 1286,
+// 32 x 9.4 M 1221 / 1342, 64 x 4.7 M 1262 / 1400, 128 x 2.3 M 1350 / 1463; gossip-MA 8 x 37 M 360 / 374, 24 x 12 M 356 / 426, 64 x 4.7 M 388 / 425.  Up to 5 M
+// values all comes from the caches (2 x 3 M 21.2 / 21.9, 32 x 0.19 M 21.3 / 21.4), up to 20 M much: 16 x 0.75 M 38.1 / 41.6, but 24 x 0.25 M 24.1 / 22.3 and 64 x 0.28 M 65.7 / 60.8.
+// Blocks of 32 KB have the pairs by themselves: a wave takes neighbouring workers' blocks.
+bool tiles_apart(int K, int layout, int what, int size, int logT, bool named)
 {
-    return layout == kRows && !named && size >= kCompact && logT > kLogStretch && logT <= kLogApart;
+    if (named || logT <= kLogStretch || logT > kLogApart) return false;
+    if (layout == kFine ? K <= 32 : layout != kRows) return false;
+    return size == kCompact || (size > kCompact && (what != kMa || K != 3));
 }
 
 // Tiles of a component [a, b) at T columns each.
@@ -533,7 +576,7 @@ int make_device_state(gbmuf_plan_s &pl, int32_t sampling)
         for (int policy : {static_cast<int>(kPlain), pl.cfg[layout][what][size].policy}) {       // blocks may share lines: plain
             LayoutCfg c = pl.cfg[layout][what][size];
             c.policy = policy;
-            if (layout == kRows && policy != pl.cfg[layout][what][size].policy) continue;
+            if ((layout == kRows || layout == kFine) && policy != pl.cfg[layout][what][size].policy) continue;
             bool seen = false;
             for (const LayoutCfg &d : done)
                 seen = seen || (d.policy == c.policy && d.variant.threads == c.variant.threads && d.variant.slots == c.variant.slots &&
@@ -757,11 +800,12 @@ AverageShape average_shape(const gbmuf_plan_s *pl, int layout, bool shared_lines
 // What one call updates.
 struct Due {
     int64_t values = 0;                                       // K times the elements of the components that are due
+    int64_t long_values = 0;                                  // those of components that are not short (rows_layout)
     int32_t first = 0, last = -1;                             // the first and the last component with elements among them
     bool one_run = true;                                      // they lie side by side, with none in between that is not due
 };
 
-Due due_all(const gbmuf_plan_s *pl) { return Due{pl->K * pl->P, 0, pl->m - 1, true}; }
+Due due_all(const gbmuf_plan_s *pl) { return Due{pl->K * pl->P, pl->long_values, 0, pl->m - 1, true}; }
 
 // The components that are due at this step, on the host: empty ones do not matter.
 Due due_at(const gbmuf_plan_s *pl, uint64_t step)
@@ -776,6 +820,7 @@ Due due_at(const gbmuf_plan_s *pl, uint64_t step)
         d.last = i;
         end = b;
         d.values += pl->K * (b - a);
+        if (b - a >= long_component(pl->K)) d.long_values += pl->K * (b - a);
     }
     return d;
 }
@@ -799,7 +844,8 @@ int enqueue_sync(const gbmuf_plan_s *pl, const int32_t *nbr_dev, const gbmuf_sta
 {
     const int what = mode == GBMUF_MODE_GOSSIP_MA ? kMa : kBmuf;
     const bool shared = shares_lines(at, st, mode, pl->K);
-    if (shared && layout == kRows) layout = kShared;
+    if (layout == kRows)
+        layout = shared ? kShared : rows_layout(pl->K, size_of_launch(due.values, kRows, what), due.values, due.long_values);
     const LayoutCfg &cfg = pl->cfg[layout][what][size_of_launch(due.values, layout, what)];
     const TileSet &ts = pl->sets[cfg.set];
     // One run of components is launched as exactly its tiles (the list is in component order); for several
@@ -910,6 +956,10 @@ int gbmuf_plan_create(gbmuf_plan_t **out, const gbmuf_plan_desc_t *desc)
             pl->comp[static_cast<size_t>(i)] = CompDesc{1.0f / static_cast<float>(pl->qv[static_cast<size_t>(i)] + 1),
                                                        pl->periods[static_cast<size_t>(i)],
                                                        pl->qv[static_cast<size_t>(i)], 0};
+        for (int32_t i = 0; i < m; ++i) {
+            const int64_t n = comp_offsets[i + 1] - comp_offsets[i];
+            if (n >= long_component(K)) pl->long_values += K * n;
+        }
 
         std::vector<int32_t> ring;
         ring_of(0, K, pl->p, ring);
@@ -957,7 +1007,7 @@ int gbmuf_plan_create(gbmuf_plan_t **out, const gbmuf_plan_desc_t *desc)
                 }
                 cfg.logT = widest_tile(cfg.variant, K);
                 cfg.policy = choose_policy(layout, size, cfg.logT, desc->cache_hints);
-                cfg.apart = tiles_apart(layout, size, cfg.logT, pl->named_shape);
+                cfg.apart = tiles_apart(K, layout, what, size, cfg.logT, pl->named_shape);
                 if (cfg.apart) cfg.policy = kApart;
                 if (desc->workgroups_per_cu != 0) cfg.workgroups_per_cu = desc->workgroups_per_cu;
             }
@@ -1023,16 +1073,17 @@ int gbmuf_plan_info(const gbmuf_plan_t *plan, gbmuf_info_t *info)
     info->m = plan->m; info->K = plan->K; info->q = plan->q; info->p = plan->p; info->C = plan->C;
     info->has_device = plan->has_device ? 1 : 0;
     info->P = plan->P;
-    const LayoutCfg &rows = cfg_of_all(*plan, kRows, kBmuf), &blocked = cfg_of_all(*plan, kBlocked, kBmuf);
+    const int64_t values = plan->K * plan->P;
+    const int layout = rows_layout(plan->K, size_of_launch(values, kRows, kBmuf), values, plan->long_values);
+    const LayoutCfg &rows = cfg_of_all(*plan, layout, kBmuf), &blocked = cfg_of_all(*plan, kBlocked, kBmuf);
     info->n_tiles = plan->sets[rows.set].tile_start.back();
     info->tile_columns = 1 << rows.logT;
     info->threads = rows.variant.threads;
     info->seed = plan->seed;
     info->mixed_q = plan->mixed_q ? 1 : 0;
     info->has_periods = plan->has_periods ? 1 : 0;
-    const int64_t all = plan->K * plan->P;                  // what is drawn in the kernel for all is so for any part
-    info->in_kernel_sampling = plan->has_device && draws_itself(plan, GBMUF_MODE_PAPER, all) &&
-                                       draws_itself(plan, GBMUF_MODE_GOSSIP_MA, all) ? 1 : 0;
+    info->in_kernel_sampling = plan->has_device && draws_itself(plan, GBMUF_MODE_PAPER, values) &&      // then any part is, too
+                                       draws_itself(plan, GBMUF_MODE_GOSSIP_MA, values) ? 1 : 0;
     info->tile_columns_blocked = 1 << blocked.logT;
     info->threads_blocked = blocked.variant.threads;
     info->workgroups_per_cu_blocked = blocked.workgroups_per_cu;

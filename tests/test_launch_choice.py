@@ -69,6 +69,15 @@ def fused_args(call):
     return launches(call, args=_SyncArgs)[-1]
 
 
+def tile_kinds(call):
+    """How many tiles of the launch lie side by side, in stretches spread over 64 tiles' worth of a row, over 64 KB (TileDesc)."""
+    (blocks, _, _), node = launches(call)[-1], fused_args(call)
+    tiles = np.zeros((blocks, 8), dtype=np.uint16)
+    hip = ctypes.CDLL(B.LIB_PATH)
+    assert hip.hipMemcpy(tiles.ctypes.data_as(ctypes.c_void_p), ctypes.c_void_p(node.arrays[0]), ctypes.c_size_t(tiles.nbytes), 2) == 0      # device to host
+    return np.bincount(tiles[:, 5] >> 14, minlength=3).tolist()
+
+
 def fake_state(plan, place="blocked", aligned=True):
     """A state of the plan's size at addresses that nothing may touch."""
     K, P, base = plan.info.K, plan.info.P, 1 << 40
@@ -99,6 +108,67 @@ def test_blocks_take_no_kernel_of_tiles_in_stretches(values):
         seen.append((launches(call)[-1][1], launches(call, kernels=True)[-1]))
         pl.destroy()
     assert seen[0][0] == seen[1][0] == 512 and seen[0][1] != seen[1][1]
+
+
+def cut(values, K, size):
+    """Components of `size` floats, the last one what is left; 0: one component."""
+    P = values // K
+    return [*range(0, P, size or P), P]
+
+
+# Aligned rows in short components: shapes of their own, (threads, columns), next to those of the same rows in long ones.  In the latter
+# 2 x 150 M 14 % longer, 4 x 175 M 14, 6 x 117 M 7, 8 x 87 M 11, 12 x 58 M 14, 32 x 0.9 M 5.
+@pytest.mark.parametrize("values", [30_000_000, 300_000_000])
+def test_rows_in_short_components_take_shapes_of_their_own(values):
+    wide = {1: (256, 512), 2: (256, 256), 3: (512, 128), 4: (256, 128), 5: (1024, 256), 6: (1024, 256), 7: (1024, 256), 8: (1024, 256), 9: (1024, 256), 12: (1024, 256),
+            13: (1024, 128), 16: (1024, 128), 17: (1024, 128), 32: (1024, 128), 33: (512, 128), 39: (512, 128), 48: (512, 128), 64: (512, 128), 65: (512, 64)}
+    fine = {1: (256, 256), 2: (256, 128), 3: (256, 64), 4: (256, 64), 5: (512, 64), 6: (512, 64), 7: (256, 64), 8: (256, 64), 9: (1024, 128), 12: (1024, 128),
+            13: (1024, 128), 16: (1024, 128), 17: (1024, 64), 32: (1024, 64), 33: (512, 128), 39: (512, 128), 48: (1024, 64), 64: (1024, 64), 65: (512, 64)}
+    for K in wide:
+        for size, expect in ((0, wide), (5120, fine), (32512, fine), (320_000, wide)):
+            pl = B.Plan(cut(values, K, size), K, min(K - 1, 2), 0)
+            assert (pl.info.threads, pl.info.tile_columns) == expect[K], (K, size)
+            pl.destroy()
+
+
+# Which of them have tiles in stretches 32 KB apart: none of 32 columns, and components of less than 64 KB no group of them.
+@pytest.mark.gpu
+@pytest.mark.parametrize("mode", [B.MODE_PAPER, B.MODE_GOSSIP_MA])
+@pytest.mark.parametrize("K", [1, 2, 3, 4, 5, 8, 10, 16, 24, 32, 33, 48, 64, 65, 128, 200])
+def test_which_rows_have_tiles_in_stretches(K, mode):
+    need_gpu()
+    ma = mode == B.MODE_GOSSIP_MA
+    for values in (4_000_000, 10_000_000, 30_000_000, 600_000_000):
+        for size in (0, 5120, 20_480):
+            pl = B.Plan(cut(values, K, size), K, min(K - 1, 2), 0)
+            call = lambda s: pl.sync_state(fake_state(pl, "rows"), 0.9, 1.0, mode, 0, s)
+            kinds, log = tile_kinds(call), fused_args(call).logT
+            if values < 20_000_000:
+                expect = values > 5_000_000 and log > 5 and size != 5120
+            else:
+                expect = K <= 128 and size != 5120 and not (ma and K == 3) and not (size and K <= 32 and (K != 3 or values < 500_000_000))
+            assert sum(kinds[1:]) >= sum(kinds) * (0.6 if size else 0.9) if expect else kinds[1:] == [0, 0], (values, size, kinds)
+            assert kinds[2] == 0 or log > 6                      # else 64 tiles are 64 KB
+            pl.destroy()
+
+
+# With sync periods it depends on what is due.
+@pytest.mark.gpu
+@pytest.mark.parametrize("mode", [B.MODE_PAPER, B.MODE_GOSSIP_MA])
+@pytest.mark.parametrize("K", [2, 8, 13, 16, 32])
+def test_a_step_of_short_components_runs_like_a_sync_of_them(K, mode):
+    need_gpu()
+    short = cut(150_000_000, K, 15_872)
+    n, long = len(short) - 1, 200_000_000 // K
+    off = [0, *(long + np.asarray(short))]
+    pl, whole, part = B.Plan(off, K, 1, 0, periods=[2] + [1] * n), B.Plan(off, K, 1, 0), B.Plan(short, K, 1, 0)
+    look = lambda p, call, r: (lambda c: (launches(c)[-1], launches(c, kernels=True)[-1], tile_kinds(c)))(lambda s: call(fake_state(p, "rows"), 0.9, 1.0, mode, r, s))
+    everything, shorts = look(whole, whole.sync_state, 0), look(part, part.sync_state, 0)
+    assert everything[2][1] > 0 and shorts[2][1:] == [0, 0]
+    assert look(pl, pl.sync_state, 0) == look(pl, pl.sync_step_state, 2) == everything
+    step = look(pl, pl.sync_step_state, 1)
+    assert step[0][1:] == shorts[0][1:] and step[1] == shorts[1] and step[2][1:] == [0, 0]
+    assert abs(step[0][0] - shorts[0][0]) <= n               # the components begin elsewhere in the row
 
 
 # The component that syncs most often is a bias, or empty; all the others sync every 16th time.  A sync of everything
