@@ -353,7 +353,9 @@ Variant shared_variant(int K, int what, int size, bool few)
 //   Gossip-MA has a third of the loads and takes more slots per thread.  Blocked: up to 2 workers 256 x 1, but 2 of
 //     more than 500 M values 512 x 2, two per CU (2 x 650 M 1610 us, 256 x 1 1817), 4 512 x 2 (4 x 175 M 848, 256 x 2 898; two per CU 837, but 4 x 5.2 M 6 %
 //     more), up to 16 256 x 2 where K rows
-//     fill it to 7/8 (8 x 75 M 723 us; 512 x 2 748), and 5 and 6 (5 x 140 M 923, 256 x 4 1050; 6 x 50 M 362 / 402), else 256 x 4, up to 32 256 x 4 (725; 512 x 2 735), 33-64 512 x 4, above 1024 x 4, large of
+//     fill it to 7/8 (8 x 75 M 723 us; 512 x 2 748), and 5 and 6 (5 x 140 M 923, 256 x 4 1050; 6 x 50 M 362 / 402), of 7 and more
+//     workers six per CU (16 x 119 M, three states in turn, 2224 us, unbounded 2246, five 2244, four 2404; 7 x 271 M 2495 / 2580; 14 x 136 M 2277 / 2338; 5 x 380 M 2580 / 2496; with 5 neighbours
+//     16 x 119 M 2311 / 2314, five 2446), else 256 x 4, up to 32 256 x 4 (725; 512 x 2 735), 33-64 512 x 4, above 1024 x 4, large of
 //     more than 256 workers kVeryMany (300 x 2 M 947; 956).  Rows, in stretches: up to 8 512 x 2 where K rows fill 1024 slots to 7/8 (4 x 100 M 481, 512 x 4 488), up to
 //     24 512 x 4 (12 x 33 M 499, 512 x 2 513; 6 x 17 M 124, 512 x 2 129), up to 32 kMany (32 x 12.5 M 528, 512 x 4 545), above kVeryMany (64 x 15.6 M 1340, kMany 1379; 300 x 2 M 1003,
 //     1024 x 4 1089); 3 side by side, 256 x 2 (3 x 20 M 64.1; 256 x 4 in stretches 67.1; but 3 x 100 M 368 / 358), short components up to 8 256 x 2 (6 x 50 M 364; 512 x 4 in stretches 439), up to
@@ -383,7 +385,10 @@ void aligned_shape(int K, int layout, int what, int size, bool few, bool mixed, 
             else if (K <= 32) v = kMany;
             else if (few) v = kVeryMany;
         }
-        else if (K == 5 || K == 6 || (K <= 16 && fills(512))) find_variant(256, 2, &v);
+        else if (K == 5 || K == 6 || (K <= 16 && fills(512))) {
+            find_variant(256, 2, &v);
+            if (K > 6) bound = 6;
+        }
         else if (K <= 32) find_variant(256, 4, &v);
         else if (K <= 64) find_variant(512, 4, &v);
         else if (few && (K > 512 || (K > 256 && size == kLarge))) v = kVeryMany;

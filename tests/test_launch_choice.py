@@ -280,6 +280,19 @@ def test_shapes_of_gossip_ma_of_few_blocks(values):
     assert [got[K][1] for K in (3, 5, 6, 7, 8)] == [256, 64, 64, 64, 64]
 
 
+# Gossip-MA of 7 and more blocks in 256 x 2: six workgroups per CU (7 x 271 M unbounded 3 % longer), of 5 and 6 all that fit (5 x 380 M six 3 % longer).
+@pytest.mark.gpu
+@pytest.mark.parametrize("values", [30_000_000, 1_900_000_000])
+def test_bounds_of_gossip_ma_of_blocks(values):
+    need_gpu()
+    for K, bound in ((5, 0), (6, 0), (7, 6), (8, 6), (12, 0), (14, 6), (15, 6), (16, 6), (24, 0)):
+        for q in (1, 4, [2, 1]):
+            pl = B.Plan([0, values // K // 2, values // K] if np.ndim(q) else [0, values // K], K, q, 3)
+            lds = launches(lambda s: pl.sync_state(fake_state(pl), 0.9, 1.0, B.MODE_GOSSIP_MA, 0, s))[-1][2]
+            assert lds == 160 * 1024 // bound - 2048 if bound else lds < 20 * 1024, (K, q)
+            pl.destroy()
+
+
 # Components that draw different numbers of neighbours, whose 1/(q+1) no tile waits for: fewer workgroups per CU for 3 and 4 blocks and for 17 to 32.
 @pytest.mark.parametrize("values", [6_000_000, 100_000_000, 900_000_000])
 def test_bounds_of_mixed_neighbours_on_blocks(values):
