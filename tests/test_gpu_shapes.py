@@ -8,15 +8,16 @@ import pytest
 import oracle
 from paper_1909_09010_amd import binding as B
 from paper_1909_09010_amd import workloads as W
+from test_launch_choice import fake_state, fused_args, tile_kinds
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-def check(K, q, off, layout, mode, stride=None, every=None, rounds=(0, 1), narrow=False, **plan):
-    """Syncs in ascending and descending order; `every`: one element of so many is compared, None: all; `narrow`: blocks as
-    small as the plan takes."""
+def check(K, q, off, layout, mode, stride=None, every=None, rounds=(0, 1), narrow=False, stretches=False, **plan):
+    """Syncs in ascending and descending order, steps if the plan has periods; `every`: one element of so many is compared, None: all;
+    `narrow`: blocks as small as the plan takes; `stretches`: a sync of everything has tiles in stretches of every kind."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     off = np.asarray(off, dtype=np.int64)
@@ -38,13 +39,19 @@ def check(K, q, off, layout, mode, stride=None, every=None, rounds=(0, 1), narro
     idx = torch.from_numpy(cols).to(DEV)
     host = [np.ascontiguousarray(st.gather(a, idx).cpu().numpy()) for a in range(3)]
     pads = [st.padding(a).clone() for a in range(3)]
+    if stretches:
+        call = lambda s: pl.sync_state(st.desc(gossip_ma=ma), 0.9, 1.0, mode, 0, s)
+        side_by_side, wide, narrow_kind = tile_kinds(call)
+        assert side_by_side > 0 and wide > 0 and (narrow_kind > 0) == (fused_args(call).logT > 6)      # 64 tiles of 64 columns are 64 KB
     for r in rounds:
-        if layout == "separate":
+        if "periods" in plan:
+            pl.sync_step_state(st.desc(gossip_ma=ma), 0.9, 1.0, mode, r, None)
+        elif layout == "separate":
             pl.sync(st.arrays[0], *([None, None] if ma else st.arrays[1:]), st.worker_stride, 0.9, 1.0, mode, r, None)
         else:
             pl.sync_state(st.desc(gossip_ma=ma), 0.9, 1.0, mode, r, None)
         oracle.sync(red, K, pl.info.p, q, seed, r, host[0], *([None, None] if ma else host[1:]), np.float32(0.9),
-                    np.float32(1.0), mode)
+                    np.float32(1.0), mode, active=(r % np.asarray(plan["periods"]) == 0).astype(np.uint8) if "periods" in plan else None)
     torch.cuda.synchronize()
     for a, name in enumerate(("theta", "omega", "delta")):
         assert np.array_equal(st.gather(a, idx).cpu().numpy(), host[a]), (name, pl.info.tile_columns, pl.info.threads)
@@ -129,21 +136,50 @@ def test_cut_tiles_of_streamed_shapes(K, values, q, mode, place):
 
 
 # Aligned rows, whose whole tiles are dealt in stretches 32 KB apart: 64 tiles of T columns (256 * T floats) at a time, then 64 KB (16384 floats) at a
-# time.  Components around both sizes, that begin on a tile, a float after and beside one; rows that begin on 4 KB and on a line; in both walks every float.
-@pytest.mark.parametrize("place", ["rows", "lines"])
-@pytest.mark.parametrize("values,mode", [(5_300_000, B.MODE_PAPER), (20_500_000, B.MODE_PAPER), (20_500_000, B.MODE_GOSSIP_MA)])
-@pytest.mark.parametrize("K,q", [(1, 0), (2, 1), (3, 2), (4, 1), (5, 2), (8, 3), (12, 5), (16, 4), (24, 9), (32, 2), (33, 3), (48, 8), (64, 5), (100, 1), (128, 3)])
-def test_tiles_in_stretches(K, q, values, mode, place):
-    P = values // K
-    pl = B.Plan([0, P], K, q, (q + 1) // 2 if q > 2 else 0)
-    wide, narrow, tile = 256 * pl.info.tile_columns, 16384, 4 * pl.info.tile_columns
+# time.  Components around both sizes, that begin on a tile, a float after and beside one, and a long one.
+def stretched(K, q, values, mode, **plan):
+    P, most = values // K, int(np.max(q))
+    pl = B.Plan([0, P], K, most, (most + 1) // 2 if most > 2 else 0, **plan)
+    T = 1 << fused_args(lambda s: pl.sync_state(fake_state(pl, "rows"), 0.9, 1.0, mode, 0, s)).logT
     pl.destroy()
+    wide, narrow, tile = 256 * T, 16384, 4 * T
     off, at = [0, 5], 5
     for n in (narrow - 1, narrow + tile, wide, wide + narrow + tile + 3, -1, wide, narrow - tile, -1, 1, wide + tile, 2 * wide - 1):
         at = at + n if n > 0 else -(-at // tile) * tile       # -1: the next begins on a tile
         off.append(at)
-    off = sorted({x for x in off if x < P} | {P})
-    check(K, q, off, "separate" if place == "lines" else place, mode, -(-P // 32) * 32 + 32 if place == "lines" else None)
+    return sorted({x for x in off if x < P} | {P})
+
+
+# Rows that begin on 4 KB and on a line; in both walks every float.  More than 7 neighbours have a sampler launch, or tiles would be too narrow.
+@pytest.mark.parametrize("place", ["rows", "lines"])
+@pytest.mark.parametrize("values,mode,K,q", [
+    (values, mode, K, q) for values, mode, most in ((5_300_000, B.MODE_PAPER, 64), (20_500_000, B.MODE_PAPER, 128), (5_300_000, B.MODE_GOSSIP_MA, 8),
+                                                    (20_500_000, B.MODE_GOSSIP_MA, 128))
+    for K, q in ((1, 0), (2, 1), (3, 2), (4, 1), (5, 2), (8, 3), (12, 5), (16, 4), (24, 9), (32, 2), (33, 3), (48, 8), (64, 5), (100, 1), (128, 3),
+                 (2, [1, 0]), (4, [2, 3]), (8, [3, 1]), (12, [6, 7, 1]), (16, [3, 2, 1, 0]), (32, [5, 2, 7]), (48, [4, 1, 6]), (100, [1, 3]))
+    if K <= most and not (values < 6_000_000 and mode == B.MODE_PAPER and 5 <= K <= 8) and not (values > 6_000_000 and mode == B.MODE_GOSSIP_MA and K == 3)])
+def test_tiles_in_stretches(values, mode, K, q, place):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    P = values // K
+    plan = {"sampling": B.SAMPLING_SEPARATE} if int(np.max(q)) > 7 else {}
+    off = stretched(K, q, values, mode, **plan)
+    q = q if np.ndim(q) == 0 else [q[i % len(q)] for i in range(len(off) - 1)]
+    check(K, q, off, "separate" if place == "lines" else place, mode, -(-P // 32) * 32 + 32 if place == "lines" else None, stretches=True, **plan)
+
+
+# Under sync periods: what is due is not one run of components (odd steps), or the first or second half; every third step all.
+@pytest.mark.parametrize("mode", [B.MODE_PAPER, B.MODE_GOSSIP_MA])
+@pytest.mark.parametrize("due", ["others", "first", "second"])
+@pytest.mark.parametrize("K,q", [(2, 1), (4, [1, 2]), (8, 2), (16, [3, 1]), (32, 4), (64, 2), (100, 3)])
+def test_steps_of_tiles_in_stretches(K, q, due, mode):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    off = np.asarray(stretched(K, q, 21_000_000, mode))
+    off = [*off, *(off[1:] + off[-1])]                       # the same twice: either half is enough for stretches
+    m = len(off) - 1
+    periods = [1 + 2 * {"others": i % 2, "first": int(i >= m // 2), "second": int(i < m // 2)}[due] for i in range(m)]
+    check(K, q if np.ndim(q) == 0 else [q[i % len(q)] for i in range(m)], off, "rows", mode, rounds=(1, 2, 3), stretches=True, periods=periods)
 
 
 # Every number of neighbours that a workgroup of a plan of several takes a path of its own for, in tiles that are whole, cut and thin.
