@@ -321,6 +321,11 @@ Variant shared_variant(int K, int what, int size, bool few)
     return v;
 }
 
+// Gossip-MA on aligned rows beyond the caches: whether components that draw more than 4 neighbours, whose averages take longer, need more workgroups per CU
+// than the wide shapes leave (33 to 64 workers: one), or tiles side by side.  us, shapes for few neighbours / smaller ones: 6 neighbours, 64 x 0.9 M 91.3 / 78.0, 40 x 0.55 M
+// 42.7 / 35.9, 20 x 30 M 926 / 858, 12 x 50 M 840 / 772; 5, 2 and 7 in turn, 48 x 0.9 M 78.5 / 62.7, 8 x 7.5 M 75.9 / 69.7; 9, 28 x 5.4 M 272.5 / 257; but 6, 28 x 5.4 M 204.5 / 214.8, and 5, 6 x 10 M 71.9 / 76.7.
+bool long_averages(int K, int q) { return q > 4 && K > 6 && (K <= 24 || (K > 32 && K <= 64) || !draws_in_registers(q)); }
+
 // How the fused kernel runs where no line is shared, by K, layout, branch and size of the launch: the shape, the resident
 // workgroups per CU (0: as many as fit) and which XCD takes which tiles (tile_of_block).  Each rule holds over a whole range
 // of K and is what came out best or within 1 to 3 % of it in sweeps of all built-in shapes, bounds and runs on K = 2 .. 400,
@@ -358,15 +363,15 @@ Variant shared_variant(int K, int what, int size, bool few)
 //     16 x 119 M 2311 / 2314, five 2446), else 256 x 4, up to 32 256 x 4 (725; 512 x 2 735), 33-64 512 x 4, above 1024 x 4, large of
 //     more than 256 workers kVeryMany (300 x 2 M 947; 956).  Rows, in stretches: up to 8 512 x 2 where K rows fill 1024 slots to 7/8 (4 x 100 M 481, 512 x 4 488), up to
 //     24 512 x 4 (12 x 33 M 499, 512 x 2 513; 6 x 17 M 124, 512 x 2 129), up to 32 kMany (32 x 12.5 M 528, 512 x 4 545), above kVeryMany (64 x 15.6 M 1340, kMany 1379; 300 x 2 M 1003,
-//     1024 x 4 1089); 3 side by side, 256 x 2 (3 x 20 M 64.1; 256 x 4 in stretches 67.1; but 3 x 100 M 368 / 358), short components up to 8 256 x 2 (6 x 50 M 364; 512 x 4 in stretches 439), up to
+//     1024 x 4 1089); smaller ones where averages are long (long_averages); 3 side by side, 256 x 2 (3 x 20 M 64.1; 256 x 4 in stretches 67.1; but 3 x 100 M 368 / 358), short components up to 8 256 x 2 (6 x 50 M 364; 512 x 4 in stretches 439), up to
 //     24 256 x 4 (12 x 25 M 380; 512 x 4 413).  5 to 20 M values: 256 x 2 up to 64 workers, up to 128 512 x 2.
-void aligned_shape(int K, int layout, int what, int size, bool few, bool mixed, LayoutCfg &cfg)
+void aligned_shape(int K, int layout, int what, int size, int q, bool mixed, LayoutCfg &cfg)
 {
     Variant &v = cfg.variant;
     int &bound = cfg.workgroups_per_cu, &run = cfg.xcd_columns_log;
     v = Variant{1024, 4, 4};
     bound = 0; run = 0; cfg.rotate = false;
-    const bool blocked = layout == kBlocked;
+    const bool blocked = layout == kBlocked, few = draws_in_registers(q), smaller = (layout == kFine && K <= 32) || (!blocked && long_averages(K, q));
     const auto fills = [K](int slots) { return (K << widest_tile({slots, 1, 1}, K)) * 8 >= slots * 7; };
     if (what == kMa) {
         if (size <= kSmall) v = cached_variant(K, what);
@@ -376,7 +381,7 @@ void aligned_shape(int K, int layout, int what, int size, bool few, bool mixed, 
             if (K == 2) bound = 2;
         }
         else if (blocked && K <= 2) find_variant(256, 1, &v);
-        else if (layout == kFine && K <= 32) {
+        else if (smaller) {
             if (K <= 24) find_variant(256, K <= 8 ? 2 : 4, &v);
         }
         else if (!blocked) {
@@ -434,7 +439,7 @@ void aligned_shape(int K, int layout, int what, int size, bool few, bool mixed, 
         cfg.rotate = K > 32 && (what == kMa || K <= 128 || (size != kCompact && (K <= 256 || K > 512)));
         run = cfg.rotate ? 0 : K > 480 && K <= 512 && size != kCompact ? 8 : 6;
     } else {
-        run = K > (size == kCompact || (layout == kFine && K <= 32 && what == kMa) ? 16 : 128) ? 8 : 0;
+        run = K > (size == kCompact || (what == kMa && smaller) ? 16 : 128) ? 8 : 0;
     }
 }
 // Small plans with rows of more than 7 neighbours draw them through LDS in every workgroup (launch_bound), a thread a
@@ -481,15 +486,17 @@ int choose_policy(int layout, int size, int logT, int hints)
 }
 
 // Whether a launch's tiles lie in stretches 32 KB apart (tile_kernel): aligned rows whose tiles hold 64 columns and more, but for short components of
-// up to 32 workers and gossip-MA of 3.  us on rows padded to 4 KB, each in the better of its shapes, stretches / side by side: 8 x 37 M 1107 / 1226, 16 x 18 M 1151 / 1286,
+// up to 32 workers, gossip-MA of 3 and some of its long averages.  us on rows padded to 4 KB, each in the better of its shapes, stretches / side by side: 8 x 37 M 1107 / 1226, 16 x 18 M 1151 / 1286,
 // 32 x 9.4 M 1221 / 1342, 64 x 4.7 M 1262 / 1400, 128 x 2.3 M 1350 / 1463; gossip-MA 8 x 37 M 360 / 374, 24 x 12 M 356 / 426, 64 x 4.7 M 388 / 425.  Up to 5 M
-// values all comes from the caches (2 x 3 M 21.2 / 21.9, 32 x 0.19 M 21.3 / 21.4), up to 20 M much: 16 x 0.75 M 38.1 / 41.6, but 24 x 0.25 M 24.1 / 22.3 and 64 x 0.28 M 65.7 / 60.8.
+// values all comes from the caches (2 x 3 M 21.2 / 21.9, 32 x 0.19 M 21.3 / 21.4), up to 20 M much: as much is
+// lost as gained (16 x 0.75 M 38.1 / 41.6, 24 x 0.58 M 42.6 / 47.7, 48 x 0.29 M 44.1 / 48.2, 24 x 0.25 M 24.1 / 22.3, 36 x 0.22 M 27.8 / 26.7, 64 x 0.28 M 65.7 / 60.8).
 // Blocks of 32 KB have the pairs by themselves: a wave takes neighbouring workers' blocks.
-bool tiles_apart(int K, int layout, int what, int size, int logT, bool named)
+bool tiles_apart(int K, int q, int layout, int what, int size, int logT, bool named)
 {
     if (named || logT <= kLogStretch || logT > kLogApart) return false;
     if (layout == kFine ? K <= 32 : layout != kRows) return false;
-    return size == kCompact || (size > kCompact && (what != kMa || K != 3));
+    if (size <= kCompact) return size == kCompact;
+    return what != kMa || (K != 3 && !(long_averages(K, q) && (K > 24 || !draws_in_registers(q))));
 }
 
 // Tiles of a component [a, b) at T columns each.
@@ -997,7 +1004,7 @@ int gbmuf_plan_create(gbmuf_plan_t **out, const gbmuf_plan_desc_t *desc)
                         cfg.variant = shared_variant(K, what, size, few);
                         cfg.workgroups_per_cu = shared_workgroups_per_cu(K, what, size);
                     } else {
-                        aligned_shape(K, layout, what, size, few, pl->mixed_q, cfg);
+                        aligned_shape(K, layout, what, size, pl->q, pl->mixed_q, cfg);
                     }
                     if (through_lds) {
                         cfg.variant = lds_drawing_variant(K, layout);
@@ -1012,7 +1019,7 @@ int gbmuf_plan_create(gbmuf_plan_t **out, const gbmuf_plan_desc_t *desc)
                 }
                 cfg.logT = widest_tile(cfg.variant, K);
                 cfg.policy = choose_policy(layout, size, cfg.logT, desc->cache_hints);
-                cfg.apart = tiles_apart(K, layout, what, size, cfg.logT, pl->named_shape);
+                cfg.apart = tiles_apart(K, pl->q, layout, what, size, cfg.logT, pl->named_shape);
                 if (cfg.apart) cfg.policy = kApart;
                 if (desc->workgroups_per_cu != 0) cfg.workgroups_per_cu = desc->workgroups_per_cu;
             }

@@ -157,7 +157,7 @@ def stretched(K, q, values, mode, **plan):
                                                     (20_500_000, B.MODE_GOSSIP_MA, 128))
     for K, q in ((1, 0), (2, 1), (3, 2), (4, 1), (5, 2), (8, 3), (12, 5), (16, 4), (24, 9), (32, 2), (33, 3), (48, 8), (64, 5), (100, 1), (128, 3),
                  (2, [1, 0]), (4, [2, 3]), (8, [3, 1]), (12, [6, 7, 1]), (16, [3, 2, 1, 0]), (32, [5, 2, 7]), (48, [4, 1, 6]), (100, [1, 3]))
-    if K <= most and not (values < 6_000_000 and mode == B.MODE_PAPER and 5 <= K <= 8) and not (values > 6_000_000 and mode == B.MODE_GOSSIP_MA and K == 3)])
+    if K <= most and not (values < 6_000_000 and mode == B.MODE_PAPER and 5 <= K <= 8) and not (values > 6_000_000 and mode == B.MODE_GOSSIP_MA and (K == 3 or (np.max(q) > 4 and K in (24, 48, 64))))])
 def test_tiles_in_stretches(values, mode, K, q, place):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")

@@ -152,6 +152,25 @@ def test_which_rows_have_tiles_in_stretches(K, mode):
             pl.destroy()
 
 
+# Gossip-MA of more than 4 neighbours: (threads, columns, stretches).  In the shapes of few neighbours 64 x 0.9 M 17 % longer, 48 x 0.9 M 24, 20 x 30 M 8.
+@pytest.mark.gpu
+@pytest.mark.parametrize("values", [30_000_000, 600_000_000])
+def test_gossip_ma_of_long_averages_takes_smaller_tiles(values):
+    need_gpu()
+    wide = {6: (512, 256, 1), 8: (512, 128, 1), 12: (512, 128, 1), 16: (512, 128, 1), 20: (512, 64, 1), 24: (512, 64, 1), 28: (1024, 128, 1), 32: (1024, 128, 1),
+            33: (512, 128, 1), 64: (512, 128, 1), 65: (512, 64, 1)}
+    small = {8: (256, 64, 1), 12: (256, 64, 1), 16: (256, 64, 1), 20: (256, 32, 0), 24: (256, 32, 0), 33: (1024, 64, 0), 64: (1024, 64, 0)}
+    many = {**small, 12: (256, 64, 0), 16: (256, 64, 0), 28: (1024, 128, 0), 32: (1024, 128, 0), 65: (1024, 32, 0)}
+    for K in wide:
+        for q, expect in ((4, wide), ([2, 4], wide), (5, small), ([1, 5], small), (9, many), ([9, 1], many)):
+            if np.max(q) >= K:
+                continue
+            pl = B.Plan([0, values // K // 2, values // K] if np.ndim(q) else [0, values // K], K, q, 5, sampling=B.SAMPLING_SEPARATE)
+            call = lambda s: pl.sync_state(fake_state(pl, "rows"), 0.9, 1.0, B.MODE_GOSSIP_MA, 0, s)
+            assert (launches(call)[-1][1], 1 << fused_args(call).logT, int(sum(tile_kinds(call)[1:]) > 0)) == expect.get(K, wide[K]), (K, q)
+            pl.destroy()
+
+
 # With sync periods it depends on what is due.
 @pytest.mark.gpu
 @pytest.mark.parametrize("mode", [B.MODE_PAPER, B.MODE_GOSSIP_MA])
