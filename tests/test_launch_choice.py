@@ -190,6 +190,38 @@ def test_a_step_of_short_components_runs_like_a_sync_of_them(K, mode):
     assert abs(step[0][0] - shorts[0][0]) <= n               # the components begin elsewhere in the row
 
 
+# Whatever is due, the tiles of a launch are those of its own width: lists of components of all lengths, some of them empty, under periods.
+@pytest.mark.gpu
+@pytest.mark.parametrize("seed", range(40))
+def test_a_launch_takes_the_tile_list_of_its_width(seed):
+    need_gpu()
+    rng = np.random.default_rng(seed)
+    K = int(rng.choice([1, 2, 3, 4, 6, 8, 12, 16, 20, 32, 36, 48, 64, 100, 200]))
+    values = 10 ** rng.uniform(6, 9)
+    sizes = [rng.integers(0, 3, n) * rng.integers(1, 2 * m, n) for n, m in ((30, 300), (200, 15_000), (50, 60_000), (10, 400_000), (3, 5_000_000)) if rng.random() < 0.6]
+    sizes = np.concatenate([*sizes, [1 + int(values) // K // 2]])
+    rng.shuffle(sizes)
+    off = np.concatenate([[0], np.cumsum(sizes[: 1 + int(np.searchsorted(np.cumsum(sizes), values / K))])]).astype(np.int64)
+    m = len(off) - 1
+    periods = rng.choice([1, 2, 3], m) if rng.random() < 0.5 else np.where(np.diff(off) < 40_000, 2, 3)
+    pl = B.Plan(off, K, [int(x) for x in rng.integers(0, min(K, 4), m)], 3, periods=[int(h) for h in periods], sampling=B.SAMPLING_SEPARATE)
+    for place, aligned in (("rows", True), ("rows", False), ("blocked", True)):
+        for mode in (B.MODE_PAPER, B.MODE_GOSSIP_MA):
+            for step in (1, 2, 3, 6):
+                call = lambda s: pl.sync_step_state(fake_state(pl, place, aligned), 0.9, 1.0, mode, step, s)
+                due = np.flatnonzero((step % periods == 0) & (np.diff(off) > 0))
+                got = launches(call)
+                if due.size == 0:
+                    assert got == []
+                    continue
+                T = 4 << fused_args(call).logT
+                tiles = np.where(np.diff(off) > 0, -(-off[1:] // T) - off[:-1] // T, 0)
+                between = np.diff(off)[due[0]:due[-1] + 1] > 0
+                one_run = not np.any(between & (step % periods[due[0]:due[-1] + 1] != 0))
+                assert got[-1][0] == (tiles[due[0]:due[-1] + 1].sum() if one_run else tiles.sum()), (K, place, mode, step)
+    pl.destroy()
+
+
 # The component that syncs most often is a bias, or empty; all the others sync every 16th time.  A sync of everything
 # has to run like that of a plan without periods.
 RARE = [83_070_000 // 8] * 8
