@@ -8,11 +8,11 @@
 
 namespace gbmuf {
 
-// One workgroup's share of a sync: elements [lo, lo + n) of component `comp`, for all K
-// workers.  The range never crosses a component boundary and lies inside one run of
-// tile_columns 16-byte columns (a column is 4 elements whose first index is a multiple of 4).  The low bits of q are the number
-// of neighbours this component draws, the two above (kTileKind) say whether the tile's n = 4 * tile_columns elements lie side by side
-// or in stretches of 2^kLogStretch columns, pairs of which are 2^kLogApart columns from each other (tile_kernel).
+// One workgroup's share of a sync: n elements of component `comp`, for all K workers, the first of them `lo`.  A tile of kind kOneStretch holds the
+// elements [lo, lo + n), which never cross a component boundary and lie inside one run of tile_columns 16-byte columns (a column is 4 elements whose first
+// index is a multiple of 4).  The n = 4 * tile_columns elements of the other kinds lie in stretches of 2^kLogStretch columns, the first of which begins at lo;
+// the two of a pair begin 2^kLogApart columns from each other, and the last ends up to 64 tiles' worth of columns, or 64 KB, behind lo (tile_kernel).  The low bits
+// of q are the number of neighbours this component draws, the two above (from kTileKind on) the tile's kind.
 struct TileDesc {
     int64_t lo;
     uint16_t n;

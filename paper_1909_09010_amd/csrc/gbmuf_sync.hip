@@ -493,9 +493,10 @@ struct WholeTile {
 #pragma unroll
         for (int n = 0; n < SLOTS; ++n)
             if (used(n)) th[n] = load4<POL>(a.theta + at(n));
-        // kSixtyFour: omega and Delta on top of theta would be more in flight per CU than HBM takes best.  64 workers x 57.8 M
-        // in components of 1 M, blocked: 13350 us, all at once 13515.  With more than 4 neighbours the
-        // registers leave one workgroup per CU, which needs all of them in flight.
+        // kSixtyFour: omega and Delta on top of theta would be more in flight per CU than HBM takes best, although from 2 neighbours on the scalar registers
+        // leave one workgroup per CU.  With / without the wait, us, blocked 40 x 62 M 2 neighbours 8850 / 9142, 4 8834 / 8994, 64 x 39 M none;
+        // aligned rows 16 x 44 M 3 neighbours 2741 / 2774.  With 5 to 7 it gains as much on rows and 3 % of 40 x 62 M, but costs 1 to 2 % of 40 x 7.5 M and 0.5 % of 64 x 39 M;
+        // with more it costs 1 to 4 % (40 x 7.5 M 1268 / 1215).
         if (DEPTH == 1 && SLOTS == 2 && Q1 >= 1 && Q1 <= 5) __builtin_amdgcn_s_waitcnt(0x0F70);     // vmcnt(0)
         if constexpr (DEPTH == SLOTS) {
 #pragma unroll
