@@ -236,7 +236,7 @@ int64_t long_component(int K) { return K <= 2 ? 1 << 17 : K <= 12 ? 10 << 14 : 1
 // Whether most of what a launch on aligned rows updates is in short components.  Above 64 workers stretches pay whatever the components (128 x 2.3 M
 // of 15 K floats 1456 / 1463, of 23 K 1467 / 1389), as they do with 3 above 500 M values (3 x 200 M of 16 K 2530 / 2358, 3 x 233 M of 32 K 2930 / 2997), and 33 to 39 leave
 // kMany's slots empty (33 x 0.9 M of 16 K 113, in stretches 111).  Up to 20 M values, much of which comes from the caches, it is the pages that a state has got that decide
-// (side by side / in stretches, 4 x 3.8 M gossip-MA 25.2 / 18.2 or 17.2 / 18.1, 32 x 0.25 M 30.7 / 24.6 or 28.2 / 29.8).
+// (side by side / in stretches, 4 x 3.8 M gossip-MA 25.2 / 18.2 or 17.2 / 18.1, 12 x 0.67 M 26.2 / 27.8 or 28.0 / 26.1).
 int rows_layout(int K, int size, int64_t values, int64_t long_values)
 {
     if (size <= kCompact || (K == 3 && size == kLarge) || (K > 32 && K < 40) || K > 64) return kRows;
@@ -326,6 +326,11 @@ Variant shared_variant(int K, int what, int size, bool few)
 // 42.7 / 35.9, 20 x 30 M 926 / 858, 12 x 50 M 840 / 772; 5, 2 and 7 in turn, 48 x 0.9 M 78.5 / 62.7, 8 x 7.5 M 75.9 / 69.7; 9, 28 x 5.4 M 272.5 / 257; but 6, 28 x 5.4 M 204.5 / 214.8, and 5, 6 x 10 M 71.9 / 76.7.
 bool long_averages(int K, int q) { return q > 4 && K > 6 && (K <= 24 || (K > 32 && K <= 64) || !draws_in_registers(q)); }
 
+// Rows that are so long that tiles of 64 columns in stretches lose where there are more than 16 of them: each then lies in address ranges of its own that have to be
+// translated.  us, side by side / in stretches, by the floats of a row, 50 M values of them due: 66 workers 20 M 197.5 / 202.8, 28 M 200 / 220, 42 M 198 / 238; 128 workers 20 M 198.7 / 199.9, 28 M
+// 198 / 212, 42 M 199 / 227; all of 96 workers' 8 M 2971 / 2983, 12 M 5181 / 4860, 34 M 12567 / 14402; gossip-MA of all of 66 workers' 16 M 1557 / 1588, 24 M 2228 / 2529, 42 M 4065 / 5280.
+bool far_rows(int64_t P) { return P > 20000000; }
+
 // How the fused kernel runs where no line is shared, by K, layout, branch and size of the launch: the shape, the resident
 // workgroups per CU (0: as many as fit) and which XCD takes which tiles (tile_of_block).  Each rule holds over a whole range
 // of K and is what came out best or within 1 to 3 % of it in sweeps of all built-in shapes, bounds and runs on K = 2 .. 400,
@@ -352,7 +357,8 @@ bool long_averages(int K, int q) { return q > 4 && K > 6 && (K <= 24 || (K > 32 
 //     per XCD 4288), above 128 too, where a stretch is all of a tile and 4 KB of a row go to one XCD (300 x 0.8 M 1209, tile by tile 1259).
 //     In short components (rows_layout) tiles lie side by side and are smaller: up to 4 256 x 1, four per CU (4 x 75 M 1127, 256 x 2 in stretches 1273), 5 and 6 512 x 1 (6 x 117 M 2710, 256 x 2
 //     2785, kSixtyFour in stretches 2915), 7 and 8 256 x 2, two per CU (8 x 87 M 2774, 512 x 1 2955, kSixtyFour in stretches 3063), 9-32 kSixtyFour (12 x 58 M 2790, kMany in stretches 3194); 40-64 in stretches still, kMany (48 x 0.6 M 103.3 us,
-//     kVeryMany 107.5), large kVeryMany (48 x 14.6 M 3184, kMany 3289).
+//     kVeryMany 107.5), of rows far from each other (far_rows) 512 x 4 side by side
+//     (64 x 0.5 M of rows of 60 M 112.2, kMany 117.6), large kVeryMany (48 x 14.6 M 3184, kMany 3289); 65-128 workers' rows far from each other side by side too, 512 x 4, large kVeryMany.
 //     5 to 20 M values: up to 8 256 x 1, four per CU (2 x 6 M 46.8 us, 512 x 1 47.1; 8 x 0.75 M 21.9, 1024 x 1 22.5; 5 x 1.6 M 30.9, 34.7), up to 32 kSixtyFour (16 x 0.75 M 50.7,
 //     256 x 4 52.3), above 1024 x 4 (40 x 0.3 M 55.2, kMany 55.9), 4 KB per XCD from 17 on.
 //   Gossip-MA has a third of the loads and takes more slots per thread.  Blocked: up to 2 workers 256 x 1, but 2 of
@@ -365,7 +371,7 @@ bool long_averages(int K, int q) { return q > 4 && K > 6 && (K <= 24 || (K > 32 
 //     24 512 x 4 (12 x 33 M 499, 512 x 2 513; 6 x 17 M 124, 512 x 2 129), up to 32 kMany (32 x 12.5 M 528, 512 x 4 545), above kVeryMany (64 x 15.6 M 1340, kMany 1379; 300 x 2 M 1003,
 //     1024 x 4 1089); smaller ones where averages are long (long_averages); 3 side by side, 256 x 2 (3 x 20 M 64.1; 256 x 4 in stretches 67.1; but 3 x 100 M 368 / 358), short components up to 8 256 x 2 (6 x 50 M 364; 512 x 4 in stretches 439), up to
 //     24 256 x 4 (12 x 25 M 380; 512 x 4 413).  5 to 20 M values: 256 x 2 up to 64 workers, up to 128 512 x 2.
-void aligned_shape(int K, int layout, int what, int size, int q, bool mixed, LayoutCfg &cfg)
+void aligned_shape(int K, int64_t P, int layout, int what, int size, int q, bool mixed, LayoutCfg &cfg)
 {
     Variant &v = cfg.variant;
     int &bound = cfg.workgroups_per_cu, &run = cfg.xcd_columns_log;
@@ -422,6 +428,7 @@ void aligned_shape(int K, int layout, int what, int size, int q, bool mixed, Lay
             if (K <= 4) find_variant(256, 1, &v);
             else if (K <= 6) find_variant(512, 1, &v);
             else if (K <= 8) find_variant(256, 2, &v);
+            else if (K > 32 && far_rows(P)) find_variant(512, 4, &v);
             else v = K <= 32 ? kSixtyFour : kMany;
             if (K <= 4) bound = 4;
             else if (K == 7 || K == 8) bound = 2;
@@ -430,6 +437,7 @@ void aligned_shape(int K, int layout, int what, int size, int q, bool mixed, Lay
             else if (K == 3) find_variant(512, 1, &v);
             else if (K <= 8 || (K > 12 && K <= 16)) v = kSixtyFour;
             else if (K <= 32) v = kMany;
+            else if (K > 64 && K <= 128 && size != kLarge && far_rows(P)) find_variant(512, 4, &v);
             else if (few) v = kVeryMany;
             if (K <= 2 || K == 4) bound = 2;
         }
@@ -439,7 +447,7 @@ void aligned_shape(int K, int layout, int what, int size, int q, bool mixed, Lay
         cfg.rotate = K > 32 && (what == kMa || K <= 128 || (size != kCompact && (K <= 256 || K > 512)));
         run = cfg.rotate ? 0 : K > 480 && K <= 512 && size != kCompact ? 8 : 6;
     } else {
-        run = K > (size == kCompact || (what == kMa && smaller) ? 16 : 128) ? 8 : 0;
+        run = K > (size == kCompact || (what == kMa && (smaller || (K > 64 && far_rows(P)))) ? 16 : 128) ? 8 : 0;
     }
 }
 // Small plans with rows of more than 7 neighbours draw them through LDS in every workgroup (launch_bound), a thread a
@@ -486,16 +494,17 @@ int choose_policy(int layout, int size, int logT, int hints)
 }
 
 // Whether a launch's tiles lie in stretches 32 KB apart (tile_kernel): aligned rows whose tiles hold 64 columns and more, but for short components of
-// up to 32 workers, gossip-MA of 3 and some of its long averages.  us on rows padded to 4 KB, each in the better of its shapes, stretches / side by side: 8 x 37 M 1107 / 1226, 16 x 18 M 1151 / 1286,
-// 32 x 9.4 M 1221 / 1342, 64 x 4.7 M 1262 / 1400, 128 x 2.3 M 1350 / 1463; gossip-MA 8 x 37 M 360 / 374, 24 x 12 M 356 / 426, 64 x 4.7 M 388 / 425.  Up to 5 M
-// values all comes from the caches (2 x 3 M 21.2 / 21.9, 32 x 0.19 M 21.3 / 21.4), up to 20 M much: as much is
-// lost as gained (16 x 0.75 M 38.1 / 41.6, 24 x 0.58 M 42.6 / 47.7, 48 x 0.29 M 44.1 / 48.2, 24 x 0.25 M 24.1 / 22.3, 36 x 0.22 M 27.8 / 26.7, 64 x 0.28 M 65.7 / 60.8).
-// Blocks of 32 KB have the pairs by themselves: a wave takes neighbouring workers' blocks.
-bool tiles_apart(int K, int q, int layout, int what, int size, int logT, bool named)
+// up to 32 workers, gossip-MA of 3, some of its long averages, and more than 64 rows that are far from each other.  us on rows padded to 4 KB, each in the better of its shapes,
+// stretches / side by side: 8 x 37 M 1107 / 1226, 16 x 18 M 1151 / 1286, 32 x 9.4 M 1221 / 1342, 64 x 4.7 M 1262 / 1400, 64 x 119 M 32121 / 35654, 128 x 2.3 M 1350 / 1463; gossip-MA 8 x 37 M 360 / 374,
+// 24 x 12 M 356 / 426, 64 x 4.7 M 388 / 425.  Up to 5 M values all comes from the caches (2 x 3 M 21.2 / 21.9, 32 x 0.19 M 21.3 / 21.4), up to 20 M much: 16 x 0.75 M 38.1 / 41.6, of rows of 100 M 38.9 / 45.2,
+// but above 16 workers, whose tiles hold 64 columns, as much is lost as gained (24 x 0.58 M 42.6 / 47.7, 24 x 0.25 M 24.1 / 22.3, 64 x 0.28 M 65.7 / 60.8) and a third of rows that are far from each other
+// (32 x 0.33 M of rows of 53 M 51.0 / 39.3, 64 x 0.22 M of rows of 34 M 70.1 / 54.1).  Blocks of 32 KB have the pairs by themselves: a wave takes neighbouring workers' blocks.
+bool tiles_apart(int K, int64_t P, int q, int layout, int what, int size, int logT, bool named)
 {
     if (named || logT <= kLogStretch || logT > kLogApart) return false;
     if (layout == kFine ? K <= 32 : layout != kRows) return false;
-    if (size <= kCompact) return size == kCompact;
+    if (size <= kCompact) return size == kCompact && (what == kMa || K <= 16);
+    if (K > 64 && far_rows(P)) return false;
     return what != kMa || (K != 3 && !(long_averages(K, q) && (K > 24 || !draws_in_registers(q))));
 }
 
@@ -1004,7 +1013,7 @@ int gbmuf_plan_create(gbmuf_plan_t **out, const gbmuf_plan_desc_t *desc)
                         cfg.variant = shared_variant(K, what, size, few);
                         cfg.workgroups_per_cu = shared_workgroups_per_cu(K, what, size);
                     } else {
-                        aligned_shape(K, layout, what, size, pl->q, pl->mixed_q, cfg);
+                        aligned_shape(K, pl->P, layout, what, size, pl->q, pl->mixed_q, cfg);
                     }
                     if (through_lds) {
                         cfg.variant = lds_drawing_variant(K, layout);
@@ -1019,7 +1028,7 @@ int gbmuf_plan_create(gbmuf_plan_t **out, const gbmuf_plan_desc_t *desc)
                 }
                 cfg.logT = widest_tile(cfg.variant, K);
                 cfg.policy = choose_policy(layout, size, cfg.logT, desc->cache_hints);
-                cfg.apart = tiles_apart(K, pl->q, layout, what, size, cfg.logT, pl->named_shape);
+                cfg.apart = tiles_apart(K, pl->P, pl->q, layout, what, size, cfg.logT, pl->named_shape);
                 if (cfg.apart) cfg.policy = kApart;
                 if (desc->workgroups_per_cu != 0) cfg.workgroups_per_cu = desc->workgroups_per_cu;
             }

@@ -153,7 +153,7 @@ def stretched(K, q, values, mode, **plan):
 # Rows that begin on 4 KB and on a line; in both walks every float.  More than 7 neighbours have a sampler launch, or tiles would be too narrow.
 @pytest.mark.parametrize("place", ["rows", "lines"])
 @pytest.mark.parametrize("values,mode,K,q", [
-    (values, mode, K, q) for values, mode, most in ((5_300_000, B.MODE_PAPER, 64), (20_500_000, B.MODE_PAPER, 128), (5_300_000, B.MODE_GOSSIP_MA, 8),
+    (values, mode, K, q) for values, mode, most in ((5_300_000, B.MODE_PAPER, 16), (20_500_000, B.MODE_PAPER, 128), (5_300_000, B.MODE_GOSSIP_MA, 8),
                                                     (20_500_000, B.MODE_GOSSIP_MA, 128))
     for K, q in ((1, 0), (2, 1), (3, 2), (4, 1), (5, 2), (8, 3), (12, 5), (16, 4), (24, 9), (32, 2), (33, 3), (48, 8), (64, 5), (100, 1), (128, 3),
                  (2, [1, 0]), (4, [2, 3]), (8, [3, 1]), (12, [6, 7, 1]), (16, [3, 2, 1, 0]), (32, [5, 2, 7]), (48, [4, 1, 6]), (100, [1, 3]))

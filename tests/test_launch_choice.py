@@ -144,7 +144,7 @@ def test_which_rows_have_tiles_in_stretches(K, mode):
             call = lambda s: pl.sync_state(fake_state(pl, "rows"), 0.9, 1.0, mode, 0, s)
             kinds, log = tile_kinds(call), fused_args(call).logT
             if values < 20_000_000:
-                expect = values > 5_000_000 and log > 5 and size != 5120
+                expect = values > 5_000_000 and log > 5 and size != 5120 and (ma or K <= 16)
             else:
                 expect = K <= 128 and size != 5120 and not (ma and K == 3) and not (size and K <= 32 and (K != 3 or values < 500_000_000))
             assert sum(kinds[1:]) >= sum(kinds) * (0.6 if size else 0.9) if expect else kinds[1:] == [0, 0], (values, size, kinds)
@@ -168,6 +168,35 @@ def test_gossip_ma_of_long_averages_takes_smaller_tiles(values):
             pl = B.Plan([0, values // K // 2, values // K] if np.ndim(q) else [0, values // K], K, q, 5, sampling=B.SAMPLING_SEPARATE)
             call = lambda s: pl.sync_state(fake_state(pl, "rows"), 0.9, 1.0, B.MODE_GOSSIP_MA, 0, s)
             assert (launches(call)[-1][1], 1 << fused_args(call).logT, int(sum(tile_kinds(call)[1:]) > 0)) == expect.get(K, wide[K]), (K, q)
+            pl.destroy()
+
+
+# Rows far from each other, in tiles of 64 columns: side by side (65 x 77 M in stretches 17 % longer, 32 x 0.33 M of rows of 53 M 30 %).
+@pytest.mark.gpu
+@pytest.mark.parametrize("mode", [B.MODE_PAPER, B.MODE_GOSSIP_MA])
+def test_rows_far_from_each_other_have_no_narrow_tiles_in_stretches(mode):
+    need_gpu()
+    ma = mode == B.MODE_GOSSIP_MA
+    def look(K, P, due):                                     # `due` values of rows of P floats
+        n = min(due // K, P)
+        pl = B.Plan([0, n, P], K, 2, 0, periods=[1, 2])
+        call = lambda s: pl.sync_step_state(fake_state(pl, "rows"), 0.9, 1.0, mode, 1, s)
+        got = launches(call)[-1][1], 1 << fused_args(call).logT, sum(tile_kinds(call)[1:]) > 0
+        pl.destroy()
+        return got
+    for K in (17, 32, 33, 48, 64, 65, 100, 128):
+        for P in (19_000_000, 21_000_000, 60_000_000):
+            for due in (12_000_000, 50_000_000, K * P):
+                threads, columns, apart = look(K, P, due)
+                assert not (apart and columns == 64 and P > 20_000_000) or (ma and K <= 24)
+                assert apart == (due > 20_000_000 and (K <= 64 or P < 20_000_000))
+                if K > 64 and due == 50_000_000 and not ma:
+                    assert (threads, columns) == ((512, 64) if P < 20_000_000 else (512, 16))
+    for K in (40, 64):                                       # short components
+        for P, expect in ((4_000_000, (1024, 64, True)), (30_000_000, (512, 32, False))):
+            pl = B.Plan([*cut(100_000_000, K, 20_480), P], K, 2, 0, periods=[1] * (len(cut(100_000_000, K, 20_480)) - 1) + [2])
+            call = lambda s: pl.sync_step_state(fake_state(pl, "rows"), 0.9, 1.0, B.MODE_PAPER, 1, s)
+            assert (launches(call)[-1][1], 1 << fused_args(call).logT, sum(tile_kinds(call)[1:]) > 0) == expect
             pl.destroy()
 
 
