@@ -226,12 +226,16 @@ int size_of_launch(int64_t values, int layout, int what)
     return values <= (shared && what == kMa ? kLargeValuesSharedMa : kLargeValues) ? kMiddle : kLarge;
 }
 
-// The floats that a component of aligned rows has at least for tiles in stretches 32 KB apart (tile_kernel) to pay: shorter ones have few of
-// them and, in the wide shapes that go with stretches, more tiles that their ends cut.  us in components of one size, as if they were short / stretches:
-// 12 x 58 M of 16 K floats 2790 / 3194, of 140 K 2811 / 2886, of 160 K 2805 / 2760; gossip-MA 6 x 117 M of 140 K 863 / 910, of 200 K 865 / 851; 2 x 150 M of
-// 16 K 1120 / 1276, of 100 K 1113 / 1091; 13 x 23 M of 23 K 1196 / 1268, of 50 K 1202 / 1181; 32 x 9.4 M of 32 K 1325 / 1340, of 50 K 1333 / 1234; 48 x 0.6 M of 5 K
-// 103 / 107, of 50 K 103 / 102.
-int64_t long_component(int K) { return K <= 2 ? 1 << 17 : K <= 12 ? 10 << 14 : 1 << 15; }
+// Whether tiles in stretches 32 KB apart (tile_kernel) pay in the component [a, b) of aligned rows: shorter ones have few of them and, in the wide shapes that
+// go with stretches, more tiles that their ends cut.  us in components of one size, as if they were short / stretches: 12 x 58 M of 16 K floats (15872) 2790 / 3194, of 140 K 2811 / 2886, of
+// 160 K 2805 / 2760; gossip-MA 6 x 117 M of 140 K 863 / 910, of 200 K 865 / 851; 2 x 150 M of 16 K 1120 / 1276, of 100 K 1113 / 1091; 13 x 23 M of 23 K 1196 / 1268, of 50 K 1202 / 1181; 32 x 9.4 M of 32 K
+// 1325 / 1340, of 50 K 1333 / 1234; 48 x 0.6 M of 5 K 103 / 107, of 50 K 103 / 102.  Short ones that begin on a tile and are, but for a twentieth, 64 KB or a multiple long have
+// nothing else: 12 x 12.5 M of 16384 606 / 530, 8 x 19 M of 65536 610 / 550, 2 x 350 M of 49152 gossip-MA 890 / 822, 32 x 22 M of 16384 3152 / 2881, at worst 4 x 175 M of 102400 2687 / 2784.
+bool long_component(int K, int64_t a, int64_t b)
+{
+    const int64_t n = b - a, tile = K <= 2 ? 4096 : 1024;
+    return n >= (K <= 2 ? 1 << 17 : K <= 12 ? 10 << 14 : 1 << 15) || (n >= 1 << 14 && a % tile == 0 && n % (1 << 14) <= n / 20);
+}
 
 // Whether most of what a launch on aligned rows updates is in short components.  Above 64 workers stretches pay whatever the components (128 x 2.3 M
 // of 15 K floats 1456 / 1463, of 23 K 1467 / 1389), as they do with 3 above 500 M values (3 x 200 M of 16 K 2530 / 2358, 3 x 233 M of 32 K 2930 / 2997), and 33 to 39 leave
@@ -328,8 +332,8 @@ bool long_averages(int K, int q) { return q > 4 && K > 6 && (K <= 24 || (K > 32 
 
 // Rows that are so long that tiles of 64 columns in stretches lose where there are more than 16 of them: each then lies in address ranges of its own that have to be
 // translated.  us, side by side / in stretches, by the floats of a row, 50 M values of them due: 66 workers 20 M 197.5 / 202.8, 28 M 200 / 220, 42 M 198 / 238; 128 workers 20 M 198.7 / 199.9, 28 M
-// 198 / 212, 42 M 199 / 227; all of 96 workers' 8 M 2971 / 2983, 12 M 5181 / 4860, 34 M 12567 / 14402; gossip-MA of all of 66 workers' 16 M 1557 / 1588, 24 M 2228 / 2529, 42 M 4065 / 5280.
-bool far_rows(int64_t P) { return P > 20000000; }
+// 198 / 212, 42 M 199 / 227; all of 96 workers' 12 M 5181 / 4860, 20 M 9275 / 8539 or 7407 / 7555, 34 M 12567 / 14402; gossip-MA of all of 66 workers' 16 M 1557 / 1588, 24 M 2228 / 2529, 42 M 4065 / 5280.
+bool far_rows(int64_t P) { return P > 22000000; }
 
 // How the fused kernel runs where no line is shared, by K, layout, branch and size of the launch: the shape, the resident
 // workgroups per CU (0: as many as fit) and which XCD takes which tiles (tile_of_block).  Each rule holds over a whole range
@@ -841,7 +845,7 @@ Due due_at(const gbmuf_plan_s *pl, uint64_t step)
         d.last = i;
         end = b;
         d.values += pl->K * (b - a);
-        if (b - a >= long_component(pl->K)) d.long_values += pl->K * (b - a);
+        if (long_component(pl->K, a, b)) d.long_values += pl->K * (b - a);
     }
     return d;
 }
@@ -978,8 +982,8 @@ int gbmuf_plan_create(gbmuf_plan_t **out, const gbmuf_plan_desc_t *desc)
                                                        pl->periods[static_cast<size_t>(i)],
                                                        pl->qv[static_cast<size_t>(i)], 0};
         for (int32_t i = 0; i < m; ++i) {
-            const int64_t n = comp_offsets[i + 1] - comp_offsets[i];
-            if (n >= long_component(K)) pl->long_values += K * n;
+            const int64_t a = comp_offsets[i], b = comp_offsets[i + 1];
+            if (long_component(K, a, b)) pl->long_values += K * (b - a);
         }
 
         std::vector<int32_t> ring;

@@ -125,7 +125,7 @@ def test_rows_in_short_components_take_shapes_of_their_own(values):
     fine = {1: (256, 256), 2: (256, 128), 3: (256, 64), 4: (256, 64), 5: (512, 64), 6: (512, 64), 7: (256, 64), 8: (256, 64), 9: (1024, 128), 12: (1024, 128),
             13: (1024, 128), 16: (1024, 128), 17: (1024, 64), 32: (1024, 64), 33: (512, 128), 39: (512, 128), 48: (1024, 64), 64: (1024, 64), 65: (512, 64)}
     for K in wide:
-        for size, expect in ((0, wide), (5120, fine), (32512, fine), (320_000, wide)):
+        for size, expect in ((0, wide), (5120, fine), (32512, fine), (320_000, wide), (16384, wide), (49152, wide), (16385, fine)):
             pl = B.Plan(cut(values, K, size), K, min(K - 1, 2), 0)
             assert (pl.info.threads, pl.info.tile_columns) == expect[K], (K, size)
             pl.destroy()
@@ -185,13 +185,13 @@ def test_rows_far_from_each_other_have_no_narrow_tiles_in_stretches(mode):
         pl.destroy()
         return got
     for K in (17, 32, 33, 48, 64, 65, 100, 128):
-        for P in (19_000_000, 21_000_000, 60_000_000):
+        for P in (21_000_000, 23_000_000, 60_000_000):
             for due in (12_000_000, 50_000_000, K * P):
                 threads, columns, apart = look(K, P, due)
-                assert not (apart and columns == 64 and P > 20_000_000) or (ma and K <= 24)
-                assert apart == (due > 20_000_000 and (K <= 64 or P < 20_000_000))
+                assert not (apart and columns == 64 and P > 22_000_000) or (ma and K <= 24)
+                assert apart == (due > 20_000_000 and (K <= 64 or P < 22_000_000))
                 if K > 64 and due == 50_000_000 and not ma:
-                    assert (threads, columns) == ((512, 64) if P < 20_000_000 else (512, 16))
+                    assert (threads, columns) == ((512, 64) if P < 22_000_000 else (512, 16))
     for K in (40, 64):                                       # short components
         for P, expect in ((4_000_000, (1024, 64, True)), (30_000_000, (512, 32, False))):
             pl = B.Plan([*cut(100_000_000, K, 20_480), P], K, 2, 0, periods=[1] * (len(cut(100_000_000, K, 20_480)) - 1) + [2])
