@@ -47,6 +47,31 @@ enum { kBmuf = 0, kMa = 1, kBranches = 2 };   // the three-array update, or the 
 enum { kTiny = 0, kSmall = 1, kCompact = 2, kMiddle = 3, kLarge = 4, kSizes = 5 };
 constexpr int kMaxTileSets = kLayouts * kBranches * kSizes;
 
+// Whether tiles in stretches 32 KB apart (tile_kernel) pay in the component [a, b) of aligned rows: shorter ones have few of them and, in the wide shapes that
+// go with stretches, more tiles that their ends cut.  us in components of one size, as if they were short / stretches: 12 x 58 M of 16 K floats (15872) 2790 / 3194, of 140 K 2811 / 2886, of
+// 160 K 2805 / 2760; gossip-MA 6 x 117 M of 140 K 863 / 910, of 200 K 865 / 851; 2 x 150 M of 16 K 1120 / 1276, of 100 K 1113 / 1091; 13 x 23 M of 23 K 1196 / 1268, of 50 K 1202 / 1181; 32 x 9.4 M of 32 K
+// 1325 / 1340, of 50 K 1333 / 1234; 48 x 0.6 M of 5 K 103 / 107, of 50 K 103 / 102; 8 x 19 M of 102400 610 / 560, 8 x 87 M of 76800 2754 / 2891; 3 x 10 M of 51200 97.4 / 95.4, gossip-MA 6 x 50 M of
+// 51200 361 / 373.  Short ones that begin on a tile and are, but for a twentieth, 64 KB or a multiple long have
+// nothing else: 12 x 12.5 M of 16384 606 / 530, 8 x 19 M of 65536 610 / 550, 2 x 350 M of 49152 gossip-MA 890 / 822, 32 x 22 M of 16384 3152 / 2881, at worst 4 x 175 M of 102400 2687 / 2784.
+bool long_component(int K, int what, bool large, int64_t a, int64_t b)
+{
+    const int64_t n = b - a, tile = K <= 2 ? 4096 : 1024;
+    int64_t least = K <= 2 ? 1 << 17 : K <= 12 ? 10 << 14 : 1 << 15;
+    if (K == 3 || K == 4 || K == 8 || (K > 4 && K < 8 && what == kBmuf)) least = large && K > 4 ? 10 << 14 : 3 << 14;
+    return n >= least || (n >= 1 << 14 && a % tile == 0 && n % (1 << 14) <= n / 20);
+}
+
+// What launches on aligned rows update in long components, by branch and in launches of up to and of more than kLargeValues.
+struct LongValues {
+    int64_t of[kBranches][2] = {};
+    void add(int K, int64_t a, int64_t b)
+    {
+        for (int what = 0; what < kBranches; ++what)
+            for (int large = 0; large < 2; ++large)
+                if (long_component(K, what, large != 0, a, b)) of[what][large] += K * (b - a);
+    }
+};
+
 }  // namespace
 
 struct gbmuf_plan_s {
@@ -59,7 +84,7 @@ struct gbmuf_plan_s {
     std::vector<int32_t> periods;    // m: sync period H_i (all 1 without periods)
     std::vector<int32_t> cand;       // [K][C] ring candidates, order of Definition 1
     std::vector<CompDesc> comp;      // m: per-component constants of the kernels
-    int64_t long_values = 0;         // K times the elements of components that are not short (rows_layout)
+    LongValues long_values;
     LayoutCfg cfg[kLayouts][kBranches][kSizes];
     int32_t min_block_logT = 0;      // blocks hold at least 4 << min_block_logT floats
     TileSet sets[kMaxTileSets];      // one per distinct tile width among the configurations that calls can take
@@ -226,25 +251,14 @@ int size_of_launch(int64_t values, int layout, int what)
     return values <= (shared && what == kMa ? kLargeValuesSharedMa : kLargeValues) ? kMiddle : kLarge;
 }
 
-// Whether tiles in stretches 32 KB apart (tile_kernel) pay in the component [a, b) of aligned rows: shorter ones have few of them and, in the wide shapes that
-// go with stretches, more tiles that their ends cut.  us in components of one size, as if they were short / stretches: 12 x 58 M of 16 K floats (15872) 2790 / 3194, of 140 K 2811 / 2886, of
-// 160 K 2805 / 2760; gossip-MA 6 x 117 M of 140 K 863 / 910, of 200 K 865 / 851; 2 x 150 M of 16 K 1120 / 1276, of 100 K 1113 / 1091; 13 x 23 M of 23 K 1196 / 1268, of 50 K 1202 / 1181; 32 x 9.4 M of 32 K
-// 1325 / 1340, of 50 K 1333 / 1234; 48 x 0.6 M of 5 K 103 / 107, of 50 K 103 / 102.  Short ones that begin on a tile and are, but for a twentieth, 64 KB or a multiple long have
-// nothing else: 12 x 12.5 M of 16384 606 / 530, 8 x 19 M of 65536 610 / 550, 2 x 350 M of 49152 gossip-MA 890 / 822, 32 x 22 M of 16384 3152 / 2881, at worst 4 x 175 M of 102400 2687 / 2784.
-bool long_component(int K, int64_t a, int64_t b)
-{
-    const int64_t n = b - a, tile = K <= 2 ? 4096 : 1024;
-    return n >= (K <= 2 ? 1 << 17 : K <= 12 ? 10 << 14 : 1 << 15) || (n >= 1 << 14 && a % tile == 0 && n % (1 << 14) <= n / 20);
-}
-
 // Whether most of what a launch on aligned rows updates is in short components.  Above 64 workers stretches pay whatever the components (128 x 2.3 M
 // of 15 K floats 1456 / 1463, of 23 K 1467 / 1389), as they do with 3 above 500 M values (3 x 200 M of 16 K 2530 / 2358, 3 x 233 M of 32 K 2930 / 2997), and 33 to 39 leave
 // kMany's slots empty (33 x 0.9 M of 16 K 113, in stretches 111).  Up to 20 M values, much of which comes from the caches, it is the pages that a state has got that decide
 // (side by side / in stretches, 4 x 3.8 M gossip-MA 25.2 / 18.2 or 17.2 / 18.1, 12 x 0.67 M 26.2 / 27.8 or 28.0 / 26.1).
-int rows_layout(int K, int size, int64_t values, int64_t long_values)
+int rows_layout(int K, int what, int size, int64_t values, const LongValues &in)
 {
     if (size <= kCompact || (K == 3 && size == kLarge) || (K > 32 && K < 40) || K > 64) return kRows;
-    return 2 * long_values < values ? kFine : kRows;
+    return 2 * in.of[what][size == kLarge] < values ? kFine : kRows;
 }
 
 // Which sizes a call of this plan can have: without periods a call updates everything.
@@ -254,9 +268,9 @@ bool size_occurs(const gbmuf_plan_s &pl, int layout, int what, int size)
     const int all = size_of_launch(values, layout, what), least = size_of_launch(0, layout, what);
     if (layout == kRows || layout == kFine) {
         // with periods parts that are all short or all long may be due
-        const bool part = pl.has_periods && rows_layout(pl.K, size, values, layout == kFine ? 0 : values) == layout &&
-                          (layout == kFine ? pl.long_values < values : pl.long_values > 0);
-        if (rows_layout(pl.K, size, values, pl.long_values) != layout && !part) return false;
+        const int64_t in_long = pl.long_values.of[what][size == kLarge];
+        const bool part = pl.has_periods && (layout == kFine ? rows_layout(pl.K, what, size, 1, LongValues{}) == kFine && in_long < values : in_long > 0);
+        if (rows_layout(pl.K, what, size, values, pl.long_values) != layout && !part) return false;
     }
     return size == all || (pl.has_periods && size < all && size >= least);
 }
@@ -825,7 +839,7 @@ AverageShape average_shape(const gbmuf_plan_s *pl, int layout, bool shared_lines
 // What one call updates.
 struct Due {
     int64_t values = 0;                                       // K times the elements of the components that are due
-    int64_t long_values = 0;                                  // those of components that are not short (rows_layout)
+    LongValues long_values;
     int32_t first = 0, last = -1;                             // the first and the last component with elements among them
     bool one_run = true;                                      // they lie side by side, with none in between that is not due
 };
@@ -845,7 +859,7 @@ Due due_at(const gbmuf_plan_s *pl, uint64_t step)
         d.last = i;
         end = b;
         d.values += pl->K * (b - a);
-        if (long_component(pl->K, a, b)) d.long_values += pl->K * (b - a);
+        d.long_values.add(pl->K, a, b);
     }
     return d;
 }
@@ -870,7 +884,7 @@ int enqueue_sync(const gbmuf_plan_s *pl, const int32_t *nbr_dev, const gbmuf_sta
     const int what = mode == GBMUF_MODE_GOSSIP_MA ? kMa : kBmuf;
     const bool shared = shares_lines(at, st, mode, pl->K);
     if (layout == kRows)
-        layout = shared ? kShared : rows_layout(pl->K, size_of_launch(due.values, kRows, what), due.values, due.long_values);
+        layout = shared ? kShared : rows_layout(pl->K, what, size_of_launch(due.values, kRows, what), due.values, due.long_values);
     const LayoutCfg &cfg = pl->cfg[layout][what][size_of_launch(due.values, layout, what)];
     const TileSet &ts = pl->sets[cfg.set];
     // One run of components is launched as exactly its tiles (the list is in component order); for several
@@ -981,10 +995,7 @@ int gbmuf_plan_create(gbmuf_plan_t **out, const gbmuf_plan_desc_t *desc)
             pl->comp[static_cast<size_t>(i)] = CompDesc{1.0f / static_cast<float>(pl->qv[static_cast<size_t>(i)] + 1),
                                                        pl->periods[static_cast<size_t>(i)],
                                                        pl->qv[static_cast<size_t>(i)], 0};
-        for (int32_t i = 0; i < m; ++i) {
-            const int64_t a = comp_offsets[i], b = comp_offsets[i + 1];
-            if (long_component(K, a, b)) pl->long_values += K * (b - a);
-        }
+        for (int32_t i = 0; i < m; ++i) pl->long_values.add(K, comp_offsets[i], comp_offsets[i + 1]);
 
         std::vector<int32_t> ring;
         ring_of(0, K, pl->p, ring);
@@ -1099,7 +1110,7 @@ int gbmuf_plan_info(const gbmuf_plan_t *plan, gbmuf_info_t *info)
     info->has_device = plan->has_device ? 1 : 0;
     info->P = plan->P;
     const int64_t values = plan->K * plan->P;
-    const int layout = rows_layout(plan->K, size_of_launch(values, kRows, kBmuf), values, plan->long_values);
+    const int layout = rows_layout(plan->K, kBmuf, size_of_launch(values, kRows, kBmuf), values, plan->long_values);
     const LayoutCfg &rows = cfg_of_all(*plan, layout, kBmuf), &blocked = cfg_of_all(*plan, kBlocked, kBmuf);
     info->n_tiles = plan->sets[rows.set].tile_start.back();
     info->tile_columns = 1 << rows.logT;

@@ -131,6 +131,19 @@ def test_rows_in_short_components_take_shapes_of_their_own(values):
             pl.destroy()
 
 
+# How long a component has to be: 8 x 19 M of 75 K floats 3 % longer as if it were short, 8 x 87 M 5 % less.
+@pytest.mark.parametrize("K,values,size,wide", [(3, 300_000_000, 48_000, False), (3, 300_000_000, 50_001, True), (4, 600_000_000, 50_001, True), (8, 150_000_000, 48_000, False),
+                                                (8, 150_000_000, 75_001, True), (8, 600_000_000, 75_001, False), (8, 600_000_000, 164_001, True), (10, 150_000_000, 75_001, False),
+                                                (10, 150_000_000, 164_001, True), (2, 150_000_000, 75_001, False), (2, 150_000_000, 132_001, True), (32, 150_000_000, 33_001, True)])
+def test_how_long_a_long_component_is(K, values, size, wide):
+    shapes = []
+    for n in (size, 0):
+        pl = B.Plan(cut(values, K, n), K, 1, 0)
+        shapes.append((pl.info.threads, pl.info.tile_columns))
+        pl.destroy()
+    assert (shapes[0] == shapes[1]) == wide
+
+
 # Which of them have tiles in stretches 32 KB apart: none of 32 columns, and components of less than 64 KB no group of them.
 @pytest.mark.gpu
 @pytest.mark.parametrize("mode", [B.MODE_PAPER, B.MODE_GOSSIP_MA])
