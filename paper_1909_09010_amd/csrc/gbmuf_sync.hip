@@ -489,6 +489,11 @@ struct WholeTile {
         if constexpr (APART) __builtin_amdgcn_s_waitcnt(MA ? 0x0070 : 0x0F70);          // vmcnt(0) and, MA, lgkmcnt(0)
         Rows<NT, Q1> rows;
         rows.begin(a, td);
+        // Gossip-MA, more than 4 neighbours, drawn here: behind a full set of theta's loads drawing takes longest, and it goes first (blocked, us, after / before them, 6 neighbours:
+        // 64 x 1.2 M 104.2 / 91.3, 32 x 3.8 M 167.0 / 144.8; but with a slot less 48 x 0.6 M 39.8 / 41.6, 24 x 5 M 150.6 / 158.6, and in 1024 x 4 100 x 0.3 M 44.9 / 46.8).
+        constexpr bool MAY_DRAW_FIRST = MA && POL == kStreamed && !CUT && Q1 == kUpTo8 && SLOTS == 4 && DEPTH == SLOTS && NT <= 512;
+        const bool drawn = MAY_DRAW_FIRST && a.nbr == nullptr && N == SLOTS;
+        if (MAY_DRAW_FIRST && drawn) rows.finish(a, td, ids);
         v4f th[SLOTS];
 #pragma unroll
         for (int n = 0; n < SLOTS; ++n)
@@ -506,7 +511,7 @@ struct WholeTile {
 #pragma unroll
             for (int n = 0; n < DEPTH; ++n) load_slots(skipped + n, n);
         }
-        rows.finish(a, td, ids);
+        if (!MAY_DRAW_FIRST || !drawn) rows.finish(a, td, ids);
 #pragma unroll
         for (int n = 0; n < SLOTS; ++n)
             if (used(n)) tile[tid + (n - skipped) * NT] = moved(th[n]);

@@ -191,3 +191,12 @@ def test_every_number_of_neighbours(K, values, mode, layout):
     off = sorted({0, 2, P // 8 | 1, P // 7 & ~3, P // 6 | 3, P // 5, P // 4 | 1, P // 3, P // 2 | 1, P - 1, P})
     q = [(3 * i + 5) % 8 for i in range(len(off) - 1)]
     check(K, q, off, "separate" if layout == "odd" else layout, mode, stride_of(layout, P), every=64)
+
+
+# Gossip-MA of blocks that draws 5 to 7 neighbours in the kernel: before theta's loads where these fill all four slots of a thread (32, 49 and 64 workers), else behind them.
+@pytest.mark.parametrize("sampling", [B.SAMPLING_AUTO, B.SAMPLING_SEPARATE])
+@pytest.mark.parametrize("K,q", [(24, 6), (25, 5), (32, 6), (32, [5, 2, 7]), (48, 7), (49, 5), (64, 6), (64, [7, 1]), (100, 5)])
+def test_drawing_before_and_behind_the_loads(K, q, sampling):
+    P = 22_000_000 // K
+    off = [0, P // 3 | 1, P // 3 + 70 | 1, P // 3 * 2, P]
+    check(K, q if np.ndim(q) == 0 else [q[i % len(q)] for i in range(4)], off, "blocked", B.MODE_GOSSIP_MA, every=128, sampling=sampling)
